@@ -55,8 +55,8 @@
  *     max_iter, see results); < 0 = error.  Inputs are validated before any
  *     device work; on error nothing is launched and wri_last_error() gives a
  *     message (thread-local).  No C++ exception crosses this ABI.
- *   - Tiling: the batched solver times candidate slab tiles on the first call
- *     of each batch shape and caches the fastest.  As systems stop, a tuned
+ *   - Tiling: the batched solver times candidate tiles on the first call of
+ *     each batch shape of at least 64^3 cells and caches the fastest.  As systems stop, a tuned
  *     recomputed-t tile changes its z-slab (the tuned one, halved down to 16
  *     planes) to the one with the least modelled time for the systems still
  *     iterating: rounds of workgroups on the chip times planes per slab
@@ -149,7 +149,7 @@ enum {
                                scalars (the straightforward transcription of the
                                iterative solver; the baseline of the batched form) */
   WRI_FLAG_NO_GRAPH = 2,    /* launch the batched iterations eagerly (no hipGraph) */
-  WRI_FLAG_NO_AUTOTUNE = 4, /* use the default slab tile instead of the tuned one */
+  WRI_FLAG_NO_AUTOTUNE = 4, /* use the default tile instead of the tuned one */
   WRI_FLAG_UNSCALED_ALPHA = 8, /* ESTIMATE: use the source column -e exactly as printed
                                (default: -c e with c = sqrt(42)/h^2, same minimiser,
                                better-conditioned iteration) */
@@ -205,15 +205,15 @@ int wri_solve(const wri_grid* grids, int32_t n_grids, const float* const* m,
 /* wri_solve for callers that cannot allocate device memory: code under HIP
  * graph capture, allocation-free serving loops, harnesses that forbid
  * hipMalloc.  Arguments and results as in wri_solve, without ws / ws_bytes.
- *   Workspace: a fixed scratch array of WRI_NOALLOC_SCRATCH_BYTES (64 MiB) in
- *   the library's device code, one copy per device, held from the library's
+ *   Workspace: a fixed scratch array of WRI_NOALLOC_SCRATCH_BYTES (64 MiB; and 4
+ *   MiB for partial sums, outside the limit below) in the library's device code, one copy per device, held from the library's
  *   first use on that device until the process ends.  The call allocates
  *   nothing (no hipMalloc/hipFree, no graph, no events): the iterations are
- *   launched eagerly on `stream` with the default slab tile (WRI_FLAG_NO_GRAPH
+ *   launched eagerly on `stream` with the untuned tile (WRI_FLAG_NO_GRAPH
  *   and WRI_FLAG_NO_AUTOTUNE are implied; the WRI_TILE environment variable
  *   still forces a tile).
- *   Limit: systems whose wri_workspace_bytes() exceeds the scratch are
- *   rejected with WRI_ENOWS before any device work (e.g. up to about 8
+ *   Limit: systems whose wri_workspace_bytes() (without the window march's
+ *   partial sums) exceeds WRI_NOALLOC_SCRATCH_BYTES are rejected with WRI_ENOWS before any device work (e.g. up to about 8
  *   systems of 64^3 cells fit).  WRI_FLAG_TIMING is rejected (WRI_EINVAL).
  *   Sharing: every call on a device uses that device's one scratch and leaves
  *   its contents behind (the solver initialises everything it reads).  Calls
@@ -470,8 +470,10 @@ typedef struct {
                                                            march: 0 plain, 1 pipelined,
                                                            2 pipelined with t recomputed
                                                            in the adjoint pass, 3 as 2 with
-                                                           two planes of prefetch; block
-                                                           order)                        */
+                                                           two planes of prefetch, 4 window
+                                                           (64 x waves x rows consecutive
+                                                           cells of the x-y plane, z-slab
+                                                           planes at once); block order)  */
   int32_t tail_switches;                 /* changes of the tiling during the solve (the
                                             convergence tail, see Tiling above)          */
 } wri_timing;

@@ -30,12 +30,12 @@ thread_local std::string g_last_error;
 //   forward k: reads s, p_{k-1}, m; writes p_k, t                       36 B
 //              + at even k >= 2 reads x, p_{k-2} and writes x           24 B
 //   adjoint k: reads r_k, t, m; writes r_{k+1}, s                       36 B
-// With t recomputed in the adjoint pass (tile pf >= 2) the forward pass does
+// With t recomputed in the adjoint pass (tile pf = 2, 3) the forward pass does
 // not write t (28 B) and the adjoint pass reads p_k in its place (36 B).
 // Halo re-reads and the receiver rows are not counted.
 constexpr int kFwdBytesPerCell = 36, kFwdXBytesPerCell = 24, kAdjBytesPerCell = 36, kTBytesPerCell = 8;
 inline int fwd_bytes_per_cell(int64_t k, int pf) {
-  return kFwdBytesPerCell - (pf >= 2 ? kTBytesPerCell : 0) + ((k >= 2 && (k & 1) == 0) ? kFwdXBytesPerCell : 0);
+  return kFwdBytesPerCell - (pf == 2 || pf == 3 ? kTBytesPerCell : 0) + ((k >= 2 && (k & 1) == 0) ? kFwdXBytesPerCell : 0);
 }
 
 struct KernelTimes {
@@ -65,7 +65,8 @@ int fail(int code, const char* fmt, ...) {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-// Slab-tile candidates explored by the autotuner; the first is the default.
+// Tile candidates explored by the autotuner; the first is the default where the
+// window march does not fit.
 const TileCfg kCands[] = {
     {4, 4, 32, 0, 0}, {4, 2, 32, 1, 0}, {4, 2, 32, 1, 1}, {4, 2, 16, 1, 1}, {4, 2, 64, 1, 1},
     {8, 1, 32, 1, 0}, {8, 1, 32, 1, 1}, {8, 1, 16, 1, 1}, {8, 2, 32, 1, 0}, {8, 2, 32, 1, 1},
@@ -76,6 +77,7 @@ const TileCfg kCands[] = {
     {8, 1, 32, 3, 4}, {4, 2, 32, 3, 4}, {4, 2, 64, 2, 4}, {4, 2, 16, 2, 4}, {8, 1, 64, 3, 4},
     {4, 4, 32, 1, 4}, {8, 4, 64, 2, 4}, {8, 4, 32, 2, 4}, {4, 4, 64, 2, 4}, {8, 4, 32, 1, 4},
     {8, 4, 64, 2, 8}, {8, 4, 64, 2, 2},
+    {4, 1, 2, 4, 0}, {4, 1, 4, 4, 0}, {4, 2, 4, 4, 0}, {8, 2, 4, 4, 0},
 };
 constexpr int kNumCands = sizeof(kCands) / sizeof(kCands[0]);
 
@@ -88,15 +90,35 @@ struct Tiling {
 Tiling make_tiling(const TileCfg& c, const wri_grid& g) {
   Tiling t;
   t.cfg = c;
-  t.tx = (g.nx + kTX - 1) / kTX;
-  t.ty = (g.ny + c.ty() - 1) / c.ty();
+  if (c.pf == kWindow) {
+    t.tx = (int)(((int64_t)g.nx * g.ny + c.win_cells() - 1) / c.win_cells());
+    t.ty = 1;
+  } else {
+    t.tx = (g.nx + kTX - 1) / kTX;
+    t.ty = (g.ny + c.ty() - 1) / c.ty();
+  }
   t.tz = (g.nz + c.tz - 1) / c.tz;
   return t;
 }
 
-int max_tiles(const wri_grid& g) {
+// The window march runs on grids whose rows fit its LDS (at least four
+// workgroups per compute unit beside the receiver map) and whose tile count
+// keeps the sum of the partials in every workgroup short (2048: 32 loads a
+// lane; a grid with more cells than 2048 tiles of 1024 x 4 fills the slab
+// marches anyway).
+constexpr size_t kWinMaxLds = 40 * 1024;
+constexpr int kWinMaxTiles = 2048;
+bool win_fits(const TileCfg& c, const wri_grid& g) {
+  return win_lds_bytes(c, g.nx) <= kWinMaxLds && make_tiling(c, g).ntiles() <= kWinMaxTiles;
+}
+
+// Partial-sum slots of one system: the largest tile count of the slab
+// candidates, or, with the window march, of every candidate that fits the grid.
+int max_tiles(const wri_grid& g, bool window) {
   int m = 1;
-  for (int i = 0; i < kNumCands; ++i) m = std::max(m, make_tiling(kCands[i], g).ntiles());
+  for (int i = 0; i < kNumCands; ++i)
+    if (kCands[i].pf != kWindow || (window && win_fits(kCands[i], g)))
+      m = std::max(m, make_tiling(kCands[i], g).ntiles());
   return m;
 }
 
@@ -165,6 +187,7 @@ struct RecSet {       // one distinct receiver list on one grid
 
 struct Layout {
   bool plain = false;
+  bool window = false;              // slots for the window march (batched path)
   std::vector<int> order;           // processing order -> original system index (grouped by grid)
   std::vector<int> set_of;          // original system -> receiver-set id
   std::vector<RecSet> sets;
@@ -177,6 +200,7 @@ struct Layout {
   int part_j_stride = 1;
   int dot_nparts = 1;
   size_t vec_bytes_plain = 0, rvec_bytes_plain = 0;
+  size_t total_slab = 0;            // total without the window march's slots
   size_t total = 0;
 };
 
@@ -185,9 +209,11 @@ struct Group {
   int rhs0, nrhs;  // processing slots
 };
 
-Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, int flags) {
+Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, int flags,
+                   bool window = true) {
   Layout L;
   L.plain = (flags & WRI_FLAG_PLAIN) != 0;
+  L.window = window && !L.plain;
   L.order.resize(n_sys);
   for (int i = 0; i < n_sys; ++i) L.order[i] = i;
   std::stable_sort(L.order.begin(), L.order.end(), [&](int a, int b) { return sys[a].grid < sys[b].grid; });
@@ -217,7 +243,7 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   L.slot_base.resize(n_sys);
   for (int p = 0; p < n_sys; ++p) {
     L.slot_base[p] = slots;
-    slots += max_tiles(grids[sys[L.order[p]].grid]);
+    slots += max_tiles(grids[sys[L.order[p]].grid], false);
   }
   L.off_part_d = take(sizeof(double) * std::max(slots, 1));
   L.off_part_s = take(sizeof(double) * std::max(slots, 1));
@@ -256,7 +282,17 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
     L.rvec_bytes_plain = align_up(sizeof(float2) * (size_t)rmax);
     L.off_rvec.assign(1, take(2 * L.rvec_bytes_plain));
   }
-  L.total = o + kAlign;  // slack for aligning the caller's base pointer
+  L.total_slab = o + kAlign;  // slack for aligning the caller's base pointer
+  if (L.window) {  // the window march has more tiles: partial sums of their own, at the end
+    slots = 0;
+    for (int p = 0; p < n_sys; ++p) {
+      L.slot_base[p] = slots;
+      slots += max_tiles(grids[sys[L.order[p]].grid], true);
+    }
+    L.off_part_d = take(sizeof(double) * std::max(slots, 1));
+    L.off_part_s = take(sizeof(double) * std::max(slots, 1));
+  }
+  L.total = o + kAlign;
   return L;
 }
 
@@ -328,6 +364,7 @@ struct Ctx {
   std::vector<Tiling> tiling;        // per group (one tile shape for all groups)
   std::vector<GroupDesc> hgd;        // host copy of the device group table
   int nblocks = 0;                   // blocks of one fused launch over all groups
+  int nx_max = 1;                    // widest row of the groups' grids
   GroupDesc* dgd = nullptr;
   SysDev* dsys = nullptr;
   SysState* dstate = nullptr;
@@ -423,19 +460,40 @@ struct EventPool {
   }
 };
 
+// tile t runs on grid g: its tile count fits the layout's partial-sum slots, and a window its LDS
+bool tile_fits(const Ctx& C, const TileCfg& t, const wri_grid& g) {
+  if (t.pf == kWindow && !(C.L.window && win_fits(t, g))) return false;
+  return make_tiling(t, g).ntiles() <= max_tiles(g, C.L.window);
+}
+
+bool tiles_fit(const Ctx& C, const TileCfg& t) {
+  for (const auto& G : C.groups)
+    if (!tile_fits(C, t, C.grids[G.grid])) return false;
+  return true;
+}
+
+// The tile of batches that are not tuned (too small for the timing to tell, or
+// WRI_FLAG_NO_AUTOTUNE): the window march with the shortest chain of work per
+// workgroup, 13.8 us per iteration on 4 systems of 70x37x19 cells against 164 us
+// with the slab tile 4,4,32,0,0.  It depends on the grids only, so a system gives
+// the same bits alone and in a batch.
+constexpr TileCfg kUntunedWindow{4, 1, 2, kWindow, 0};
+TileCfg untuned_tile(const Ctx& C) { return tiles_fit(C, kUntunedWindow) ? kUntunedWindow : kCands[0]; }
+
 // One tile shape for every group: per-group tile counts and the device table
 // that maps a block of a fused launch to (group, system, tile).
 int set_config(Ctx& C, const TileCfg& cfg) {
   C.tiling.resize(C.groups.size());
   C.hgd.resize(C.groups.size());
   int b0 = 0;
+  C.nx_max = 1;
   for (size_t gi = 0; gi < C.groups.size(); ++gi) {
     const wri_grid& g = C.grids[C.groups[gi].grid];
     const Tiling t = make_tiling(cfg, g);
-    // each system has max_tiles(g) partial-sum slots (the layout's count)
-    if (!cfg_supported(cfg) || t.ntiles() > max_tiles(g))
+    C.nx_max = std::max(C.nx_max, (int)g.nx);
+    if (!cfg_supported(cfg) || !tile_fits(C, cfg, g))
       return fail(WRI_EINVAL, "tile w=%d ry=%d tz=%d pf=%d: %d tiles per system, %d partial slots", cfg.w, cfg.ry,
-                  cfg.tz, cfg.pf, t.ntiles(), max_tiles(g));
+                  cfg.tz, cfg.pf, t.ntiles(), max_tiles(g, C.L.window));
     C.tiling[gi] = t;
     GroupDesc& d = C.hgd[gi];
     d.rhs0 = C.groups[gi].rhs0;
@@ -469,12 +527,6 @@ int set_config(Ctx& C, const TileCfg& cfg) {
 
 const TileCfg& cur_cfg(const Ctx& C) { return C.tiling.front().cfg; }
 
-// the tile counts of t fit every group's partial-sum slots
-bool tiles_fit(const Ctx& C, const TileCfg& t) {
-  for (const auto& G : C.groups)
-    if (make_tiling(t, C.grids[G.grid]).ntiles() > max_tiles(C.grids[G.grid])) return false;
-  return true;
-}
 
 // Convergence tail.  Once few systems still iterate, the tiling tuned for the
 // full batch leaves compute units idle, or ends every launch with a partly
@@ -550,7 +602,7 @@ TailPlan tail_plan(const Ctx& C, const TileCfg& main, bool forced_main) {
   }
   const char* u = getenv("WRI_TAIL_UNITS");
   const bool u_set = u != nullptr && *u;
-  if ((forced_main && !u_set) || main.pf < 2 || main.tz <= kTailTZ) return P;
+  if ((forced_main && !u_set) || main.pf < 2 || main.pf == kWindow || main.tz <= kTailTZ) return P;
   int64_t units = 0;
   if (u_set) {
     units = atoll(u);
@@ -600,10 +652,10 @@ int launch_iteration_timed(Ctx& C, int k, EventPool& pool, std::vector<std::pair
     if (!a || !b) return fail(WRI_EHIP, "hipEventCreate failed");
     WRI_HIP(hipEventRecord(a, C.st));
     if (phase == 0)
-      WRI_HIP(launch_fwd(cur_cfg(C), C.dsys, C.dstate, C.part_s, C.part_d, C.dgd, (int)C.hgd.size(), C.nblocks, k,
+      WRI_HIP(launch_fwd(cur_cfg(C), C.dsys, C.dstate, C.part_s, C.part_d, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, k,
                          C.st));
     else
-      WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, (int)C.hgd.size(), C.nblocks, C.st));
+      WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, C.st));
     WRI_HIP(hipEventRecord(b, C.st));
     (phase == 0 ? fwd : adj).emplace_back(a, b);
   }
@@ -612,14 +664,14 @@ int launch_iteration_timed(Ctx& C, int k, EventPool& pool, std::vector<std::pair
 
 // CGLS iteration k: the forward launch then the adjoint launch, each over all groups
 int launch_iteration(Ctx& C, int k, hipStream_t s) {
-  WRI_HIP(launch_fwd(cur_cfg(C), C.dsys, C.dstate, C.part_s, C.part_d, C.dgd, (int)C.hgd.size(), C.nblocks, k, s));
-  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, (int)C.hgd.size(), C.nblocks, s));
+  WRI_HIP(launch_fwd(cur_cfg(C), C.dsys, C.dstate, C.part_s, C.part_d, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, k, s));
+  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, s));
   return WRI_OK;
 }
 
 int launch_setup(Ctx& C) {
   WRI_HIP(launch_init(C.dsys, C.dstate, C.n_sys, C.st, 0, (C.flags & WRI_FLAG_ADJOINT_SOURCE) ? 1 : 0));
-  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, (int)C.hgd.size(), C.nblocks, C.st));
+  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, C.st));
   return WRI_OK;
 }
 
@@ -627,14 +679,14 @@ int launch_setup(Ctx& C) {
 // ||S^H b||^2, then r = b - S x0 and s0 = S^H r.
 int launch_setup_warm(Ctx& C) {
   WRI_HIP(launch_init(C.dsys, C.dstate, C.n_sys, C.st, 1));
-  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, (int)C.hgd.size(), C.nblocks, C.st));
+  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, C.st));
   std::vector<int32_t> np(C.n_sys);
   for (size_t gi = 0; gi < C.hgd.size(); ++gi)
     for (int r = 0; r < C.hgd[gi].nrhs; ++r) np[C.hgd[gi].rhs0 + r] = C.hgd[gi].ntiles;
   int32_t* dnp = at<int32_t>(C.ws, C.L.off_nparts);
   WRI_HIP(hipMemcpyAsync(dnp, np.data(), sizeof(int32_t) * np.size(), hipMemcpyHostToDevice, C.st));
   WRI_HIP(launch_warm_residual(C.dsys, C.dstate, C.part_s, dnp, C.n_sys, C.st));
-  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, (int)C.hgd.size(), C.nblocks, C.st));
+  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, C.st));
   WRI_HIP(hipStreamSynchronize(C.st));  // np is host memory
   return WRI_OK;
 }
@@ -677,8 +729,8 @@ int autotune(Ctx& C) {
   auto it = g_tuned.find(key);
   if (it != g_tuned.end()) return set_config(C, it->second);
   if (total < (int64_t)64 * 64 * 64) {  // too small for the choice to matter
-    g_tuned[key] = kCands[0];
-    return set_config(C, kCands[0]);
+    g_tuned[key] = untuned_tile(C);
+    return set_config(C, g_tuned[key]);
   }
   hipEvent_t e0, e1;
   WRI_HIP(hipEventCreate(&e0));
@@ -686,6 +738,7 @@ int autotune(Ctx& C) {
   float best = 1e30f;
   TileCfg best_cfg = kCands[0];
   for (int c = 0; c < kNumCands; ++c) {
+    if (!tiles_fit(C, kCands[c])) continue;
     int rc = set_config(C, kCands[c]);
     if (rc == WRI_OK) rc = launch_setup(C);
     if (rc == WRI_OK) rc = launch_iteration(C, 0, C.st);  // warm
@@ -724,10 +777,11 @@ std::string graph_key(const Ctx& C, int64_t k0, int chunk) {
            (const void*)C.part_s, (const void*)C.part_d, (const void*)C.dgd, (int)C.hgd.size());
   k += buf;
   const TileCfg& c = cur_cfg(C);
-  snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d,%d;", c.w, c.ry, c.tz, c.pf, c.order, C.nblocks);
+  snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d,%d,%d;", c.w, c.ry, c.tz, c.pf, c.order, C.nblocks, C.nx_max);
   k += buf;
   for (const auto& d : C.hgd) {
-    snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d,%d;", d.rhs0, d.nrhs, d.tiles_x, d.tiles_y, d.tz, d.block0);
+    snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d,%d,%d,%d;", d.rhs0, d.nrhs, d.tiles_x, d.tiles_y, d.tz, d.ntiles,
+             d.block0, d.xchunk);
     k += buf;
   }
   return k;
@@ -803,7 +857,7 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
     const bool is_forced = forced_tile(C, &forced);
     if (is_forced) rc = set_config(C, forced);
     else if (!(C.flags & WRI_FLAG_NO_AUTOTUNE)) rc = autotune(C);
-    else rc = set_config(C, kCands[0]);
+    else rc = set_config(C, untuned_tile(C));
     if (rc != WRI_OK) return rc;
     if (warm) {  // the tuned tile is known; now point x at the caller's initial guess
       fill_tables(true);
@@ -1076,7 +1130,7 @@ int run_plain(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
 int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, const wri_system* sys,
                  int32_t n_sys, int32_t mode, int32_t max_iter, int32_t flags, wri_c32* const* u_out,
                  wri_result* res, void* ws, size_t ws_bytes, void* stream, float* const* grad, double* J_out,
-                 wri_c64* alpha_out) {
+                 wri_c64* alpha_out, bool window = true) {
   int rc = validate(grids, n_grids, sys, n_sys, mode, max_iter);
   if (rc != WRI_OK) return rc;
   if (n_sys > 0 && res == nullptr) return fail(WRI_EINVAL, "res is NULL");
@@ -1102,7 +1156,7 @@ int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, 
   C.grids = grids; C.n_grids = n_grids; C.m = m; C.sys = sys; C.n_sys = n_sys;
   C.mode = mode; C.max_iter = max_iter; C.flags = flags; C.u_out = u_out;
   C.st = reinterpret_cast<hipStream_t>(stream);
-  C.L = make_layout(grids, n_grids, sys, n_sys, flags);
+  C.L = make_layout(grids, n_grids, sys, n_sys, flags, window);
   if (ws == nullptr || ws_bytes < C.L.total)
     return fail(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, C.L.total);
   C.ws = reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(ws)));
@@ -1158,8 +1212,12 @@ int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, 
 // device, held by the loaded code object until the process ends.  On the host
 // the name `scratch` is only a stand-in symbol: every kernel argument and copy
 // uses the per-device address that hipGetSymbolAddress returns.
+// Beyond the documented size it has room for the window march's partial sums,
+// which do not count against the limit; a batch whose sums exceed that room runs
+// the slab tile.
 constexpr size_t kNoAllocBytes = WRI_NOALLOC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
+constexpr size_t kScratchBytes = kNoAllocBytes + ((size_t)4 << 20);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 std::mutex g_scratch_mutex;
 std::map<int, char*> g_scratch_addr;  // device -> address of its copy of `scratch`
@@ -1229,7 +1287,8 @@ int wri_solve_noalloc(const wri_grid* grids, int32_t n_grids, const float* const
     if (flags & WRI_FLAG_TIMING) return fail(WRI_EINVAL, "wri_solve_noalloc: WRI_FLAG_TIMING creates events");
     int rc = validate(grids, n_grids, sys, n_sys, mode, max_iter);
     if (rc != WRI_OK) return rc;
-    const size_t need = make_layout(grids, n_grids, sys, n_sys, flags).total;
+    const Layout L = make_layout(grids, n_grids, sys, n_sys, flags);
+    const size_t need = L.total_slab;
     if (need > kNoAllocBytes)
       return fail(WRI_ENOWS,
                   "wri_solve_noalloc: these systems need %zu bytes of workspace; the fixed scratch holds %zu "
@@ -1242,8 +1301,8 @@ int wri_solve_noalloc(const wri_grid* grids, int32_t n_grids, const float* const
     // eager launches on the caller's stream (graph instantiation and the
     // autotuner's events would allocate); the default tile unless WRI_TILE forces one
     return solve_common(grids, n_grids, m, sys, n_sys, mode, max_iter,
-                        flags | WRI_FLAG_NO_GRAPH | WRI_FLAG_NO_AUTOTUNE, u_out, res, ws, kNoAllocBytes, stream,
-                        nullptr, nullptr, nullptr);
+                        flags | WRI_FLAG_NO_GRAPH | WRI_FLAG_NO_AUTOTUNE, u_out, res, ws, kScratchBytes, stream,
+                        nullptr, nullptr, nullptr, L.total <= kScratchBytes);
   } catch (const std::exception& e) {
     return fail(WRI_EINVAL, "exception: %s", e.what());
   }

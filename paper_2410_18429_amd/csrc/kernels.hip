@@ -29,6 +29,7 @@
 #include "wri_impl.hpp"
 #include "stencil.hpp"
 
+#include <algorithm>
 #include <cfloat>
 #include <climits>
 
@@ -1742,12 +1743,572 @@ k_adj_rc(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const doub
 }
 
 // ---------------------------------------------------------------------------
+// Window march (tile pf = 4): batches whose vectors stay in the caches
+//
+// The slab marches above are built for HBM bandwidth: a wavefront per 64-cell
+// row and 16 to 64 planes per workgroup, one barrier and one wait per plane.  A
+// batch of a few million cells gives them at most about one workgroup per
+// compute unit, so a launch takes the serial latency of its march, whatever the
+// size.  Here a workgroup owns B = 64 W CX consecutive cells of the x-y plane
+// (whole rows and parts of rows: the neighbours in y are nx cells away in the
+// same linear order, so the halo of a plane is the nx cells before and the nx
+// cells after the tile, and a ragged or narrow nx idles no lane) and TZ planes.
+// All loads of the TZ + 2 planes are issued at once, one barrier separates them
+// from the stencils, and nothing is serial in z.  The price is (TZ + 2) / TZ of
+// the own cells and 2 nx / B of halo re-read, which the L2s serve (8 systems of
+// 64^3: 38 MB fetched past L2 per launch, 34.6 MB of inputs).  t is stored:
+// recomputing it would double the halo.
+//
+// Measured, us per iteration (both launches), best slab tile -> best window:
+// 4 systems of 70x37x19 42.2 -> 13.8 (164 with the untuned default 4,4,32,0,0),
+// 48 of 32^3 71.2 -> 32.2, 8 of 64^3 70.7 -> 37.8, 8 each of 48^3, 64^3 and 96^3
+// 231 -> 184.  The smallest is bound by the chain launch - tables - loads -
+// stores (7 us per launch), the others by the 72 MB per launch between the L2s
+// and memory (5.5 TB/s for 8 systems of 64^3).
+//
+// Same stencil routine, same operands in the same order and the same rounding
+// points as the slab marches: iterates differ only through the summation order
+// of the float64 partials.
+// ---------------------------------------------------------------------------
+
+// Sum of a system's partials by every wave for itself: the order and bits of
+// block_sum_slots without its barriers.  The first kAhead loads are issued where
+// it is constructed (slots past n read zero).
+struct SlotSum {
+  static constexpr int kAhead = 4;
+  double v[kAhead];
+  __device__ __forceinline__ SlotSum(const double* p, int n) {
+    const BufRes r = mkbuf(p, 0, n, 8);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+      v[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, ((threadIdx.x & 63) + 64 * i) * 8, 0, 0));
+  }
+  __device__ __forceinline__ double sum(const double* __restrict__ p, int n) const {
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) s += v[i];
+    for (int i = (threadIdx.x & 63) + 64 * kAhead; i < n; i += 64) s += p[i];
+    return wave_sum(s);
+  }
+};
+
+// Stores of the window march go through L2 (system scope: sc0 and sc1).  Its
+// outputs fit the L2s (4 MB per XCD), where ordinary stores would stay dirty
+// until the end of the launch and be written back then, after the last
+// workgroup: 8 systems of 64^3 took 42.8 us per iteration with ordinary or
+// non-temporal stores and 37.6 us with these.
+constexpr int kStoreThrough = 17;
+
+// The group of a block, from the launch arguments (up to kWinGroups groups; a
+// load from the device table would be one more memory latency in every launch).
+__device__ __forceinline__ GroupDesc win_group(const WinGroups& G, int logical) {
+  GroupDesc d = G.g[0];
+  if (G.n <= kWinGroups) {
+#pragma unroll
+    for (int i = 1; i < kWinGroups; ++i)
+      if (i < G.n && logical >= G.g[i].block0) d = G.g[i];
+  } else {
+    int g = 0;
+    while (g + 1 < G.n && logical >= G.table[g + 1].block0) ++g;
+    d = G.table[g];
+  }
+  return d;
+}
+
+// Loads above this point are issued before anything below it: without it the
+// compiler moves them down to their uses (behind the scalars and the stop
+// test), one latency after the other.  It waits for nothing.
+__device__ __forceinline__ void issue_point() { asm volatile("" ::: "memory"); }
+
+template <int W, int CX, int TZ>
+struct Win {
+  static constexpr int NT = 64 * W;
+  static constexpr int B = NT * CX;   // own cells per plane
+  int nx, ny, nz, plane, c0, z0, wl, zlo, zhi;
+  int cell[CX];                       // linear cell in the plane (may lie past its end)
+  bool in[CX];
+  unsigned obit[CX];                  // out-of-range bit of cells past the end of the plane
+
+  __device__ __forceinline__ void setup(const SysDev& S, int tile, int tiles_x) {
+    nx = S.nx; ny = S.ny; nz = S.nz;
+    plane = nx * ny;
+    const int tz = tile / tiles_x;
+    c0 = (tile - tz * tiles_x) * B;
+    z0 = tz * TZ;
+    zlo = max(z0 - 1, 0);
+    zhi = min(z0 + TZ + 1, nz);
+    wl = B + 2 * nx;
+#pragma unroll
+    for (int j = 0; j < CX; ++j) {
+      cell[j] = c0 + j * NT + (int)threadIdx.x;
+      in[j] = cell[j] < plane;
+      obit[j] = in[j] ? 0u : kOOB;
+    }
+  }
+  // Buffer accesses: plane i (z0 - 1 + i, i = 0 .. TZ + 1) of a stencil input and
+  // plane i (z0 + i, i = 0 .. TZ - 1) of a vector of own cells.  The plane is a
+  // scalar offset; a plane outside the grid gets a resource without records and
+  // a cell outside it the out-of-range bit, so reads there give zero and stores
+  // are dropped.
+  __device__ __forceinline__ BufRes in_res(const void* v, int i, int elem) const {
+    const int z = z0 - 1 + i;
+    const bool ok = z >= 0 && z < nz;
+    return __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(static_cast<const char*>(v) + (int64_t)zlo * plane * elem), (short)0,
+        ok ? (zhi - zlo) * plane * elem : 0, kBufFlags);
+  }
+  __device__ __forceinline__ unsigned in_off(int i, int elem) const {
+    const int z = min(max(z0 - 1 + i, zlo), zhi - 1);
+    return (unsigned)((z - zlo) * plane * elem);
+  }
+  __device__ __forceinline__ float2 load2(const void* v, int i, unsigned voff) const {
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(in_res(v, i, 8), voff, in_off(i, 8), 0));
+  }
+  __device__ __forceinline__ float load1(const void* v, int i, unsigned voff) const {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(in_res(v, i, 4), voff, in_off(i, 4), 0));
+  }
+  __device__ __forceinline__ void store2(void* v, int i, unsigned voff, float2 x) const {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), in_res(v, i, 8), voff, in_off(i, 8), kStoreThrough);
+  }
+  __device__ __forceinline__ unsigned own2(int j) const { return (unsigned)(cell[j] * 8) | obit[j]; }
+  __device__ __forceinline__ unsigned own1(int j) const { return (unsigned)(cell[j] * 4) | obit[j]; }
+  __device__ __forceinline__ int first_receiver(const SysDev& S) const {
+    return (int)threadIdx.x < S.n_rec ? gptr(S.rec)[threadIdx.x] : -1;
+  }
+  __device__ __forceinline__ bool live(int j, int i) const { return in[j] && z0 + i < nz; }
+  // halo cell h (0 .. 2 nx - 1): byte offset in a plane and window index
+  __device__ __forceinline__ unsigned halo_off(int h) const {
+    const int c = h < nx ? c0 - nx + h : c0 + B + (h - nx);
+    return (unsigned)(c * 8) | ((c >= 0 && c < plane) ? 0u : kOOB);
+  }
+  __device__ __forceinline__ int halo_slot(int h) const { return h < nx ? h : B + h; }
+
+  // Row of a cell of the tile: the offset from the first cell's row start is
+  // below B + nx, where the float quotient (with half a cell's margin) is exact.
+  __device__ __forceinline__ void row_of(int c, int* x, int* y) const {
+    const int y0 = c0 / nx, d = c - y0 * nx;
+    const int r = (int)(((float)d + 0.5f) * (1.0f / (float)nx));
+    *y = y0 + r;
+    *x = d - r * nx;
+  }
+  // Receivers of the tile: recq[] takes the receiver index of each own cell (-1:
+  // none; a receiver cell occurs once in a system's list).  Returns whether the
+  // tile holds any; only then is recq written, and the caller's next barrier
+  // publishes it.
+  // rec0: the receiver cell tid of the list, loaded ahead (-1 past its end).
+  __device__ __forceinline__ bool find_receivers(const SysDev& S, int rec0, int* recq) const {
+    const GLOBAL int* rec = gptr(S.rec);
+    const int first = z0 * plane, span = (min(z0 + TZ, nz) - z0) * plane;
+    auto slot = [&](int q) -> int {   // own-cell slot of receiver q, or -1
+      const int d = (q == (int)threadIdx.x ? rec0 : rec[q]) - first;
+      if (d < 0 || d >= span) return -1;
+      int z = 0;
+#pragma unroll
+      for (int i = 1; i < TZ; ++i) z += d >= i * plane ? 1 : 0;
+      const int o = d - z * plane - c0;
+      return o >= 0 && o < B ? z * B + o : -1;
+    };
+    bool any = false;
+    for (int q = threadIdx.x; q < S.n_rec; q += NT) any = any || slot(q) >= 0;
+    if (!__syncthreads_or(any)) return false;
+#pragma unroll
+    for (int i = 0; i < CX * TZ; ++i) recq[i * NT + (int)threadIdx.x] = -1;
+    __syncthreads();
+    for (int q = threadIdx.x; q < S.n_rec; q += NT) {
+      const int o = slot(q);
+      if (o >= 0) recq[o] = q;
+    }
+    return true;
+  }
+  // whether the tile's planes and cells hold the source
+  __device__ __forceinline__ bool src_plane(const SysDev& S) const {
+    const int sz = S.src / plane, sc = S.src - sz * plane;
+    return sz >= z0 && sz < z0 + TZ && sc >= c0 && sc < c0 + B;
+  }
+  // the own cell that holds the source, as j * TZ + i; -1: none
+  __device__ __forceinline__ int source(const SysDev& S) const {
+    int ji = -1;
+    if (S.mode == 1) {
+      const int sz = S.src / plane, sc = S.src - sz * plane;
+      if (sz >= z0 && sz < z0 + TZ) {
+#pragma unroll
+        for (int j = 0; j < CX; ++j)
+          if (cell[j] == sc) ji = j * TZ + (sz - z0);
+      }
+    }
+    return ji;
+  }
+};
+
+template <int W, int CX, int TZ, int XS>
+__global__ void __launch_bounds__(64 * W)
+k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const double* __restrict__ part_s,
+          double* __restrict__ part_d, WinGroups G) {
+  using Tile = Win<W, CX, TZ>;
+  constexpr int NT = Tile::NT, B = Tile::B;
+  __shared__ int recq[B * TZ];
+  __shared__ double red[W + 1];
+  extern __shared__ float2 win[];   // [TZ][B + 2 nx]
+
+  const int tid = threadIdx.x;
+  const int logical = xcd_remap(blockIdx.x, gridDim.x, G.g[0].xchunk);
+  const GroupDesc gd = win_group(G, logical);
+  const int ntiles = gd.ntiles, tiles_x = gd.tiles_x;
+  int rl, tile;
+  block_map(gd, logical - gd.block0, &rl, &tile);
+  const int rhs = gd.rhs0 + rl;
+  const SysDev& S = sysv[rhs];
+  SysState* T = stv + rhs;
+  if (T->status != kActive) return;
+  const int k = T->iterA;
+
+  Tile Q;
+  Q.setup(S, tile, tiles_x);
+  const int nx = Q.nx, wl = Q.wl;
+  const float2* sv = S.s;
+  const float2* po = S.p[k & 1];
+  float2* pn = S.p[(k + 1) & 1];
+  float2* xv = S.x;
+  float2* tout = S.t;
+  // every load of the tile, before the scalars they are combined with
+  const SlotSum slots(part_s + S.slot_base, ntiles);
+  const int rec0 = Q.first_receiver(S);
+  float2 rs[CX][TZ + 2], rp[CX][TZ + 2], rx[CX][TZ], rq[CX][TZ];
+  float mm[CX][TZ];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < TZ + 2; ++i) {
+      rs[j][i] = Q.load2(sv, i, Q.own2(j));
+      rp[j][i] = Q.load2(po, i, Q.own2(j));
+    }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < TZ; ++i) {
+      mm[j][i] = Q.load1(S.m, i + 1, Q.own1(j));
+      if constexpr (XS != 0) {
+        rx[j][i] = Q.load2(xv, i + 1, Q.own2(j));
+        rq[j][i] = Q.load2(pn, i + 1, Q.own2(j));
+      }
+    }
+  float2 hs[TZ], hp[TZ];   // the thread's first halo cell (most rows need no second)
+  const unsigned ho = tid < 2 * nx ? Q.halo_off(tid) : kOOB;
+#pragma unroll
+  for (int i = 0; i < TZ; ++i) {
+    hs[i] = Q.load2(sv, i + 1, ho);
+    hp[i] = Q.load2(po, i + 1, ho);
+  }
+  issue_point();
+  const bool has_rec = S.n_rec > 0 && Q.find_receivers(S, rec0, recq);
+
+  const double gk = slots.sum(part_s + S.slot_base, ntiles);
+  const bool warm = T->warm != 0;
+  const double g0 = (k == 0 && !warm) ? gk : T->gamma0;
+  const double gmin = (k == 0) ? gk : T->gmin[(k - 1) & 1];
+  const bool brk = T->brk != 0;
+  const bool stop = brk || (g0 == 0.0) || (gk <= S.rtol2 * g0) || (k >= S.max_iter) || (gk > kDivergeRatio * gmin);
+  const double beta = (k == 0) ? 0.0 : gk / T->gamma[(k - 1) & 1];
+  const double aprev = (k == 0) ? 0.0 : T->a[(k - 1) & 1];
+  // the pending x steps, as in the slab marches
+  const bool xstep = brk ? (k & 1) == 1 : stop ? (k >= 1) : (k >= 2 && (k & 1) == 0);
+  const double c1 = xstep ? aprev : 0.0;
+  const double c2 = (xstep && !brk && k >= 2 && (k & 1) == 0) ? T->a[k & 1] : 0.0;
+  if (tile == 0 && tid == 0) {
+    T->gamma[k & 1] = gk;
+    T->gmin[k & 1] = fmin(gmin, gk);
+    if (k == 0 && !warm) T->gamma0 = gk;
+    T->iterB = k;
+  }
+  const int srcji = Q.source(S);
+  const bool src_tile = S.mode == 1 && Q.src_plane(S);   // uniform: most tiles skip the source's cell
+
+  if (stop || (!XS && xstep)) {
+    if (xstep) {
+#pragma unroll
+      for (int j = 0; j < CX; ++j)
+#pragma unroll
+        for (int i = 0; i < TZ; ++i) {
+          const float2 p2 = (c2 != 0.0) ? Q.load2(pn, i + 1, Q.own2(j)) : f2(0.f, 0.f);
+          const float2 x = Q.load2(xv, i + 1, Q.own2(j));
+          Q.store2(xv, i + 1, Q.own2(j), xupd2(x, c2, p2, c1, rp[j][i + 1]));
+        }
+      if (srcji >= 0 && stop && !brk) {
+        const double2 pa = T->pa;
+        T->xa = make_double2(T->xa.x + aprev * pa.x, T->xa.y + aprev * pa.y);
+      }
+    }
+    if (stop) return;
+  }
+  double2 pa_new = make_double2(0.0, 0.0);
+  if (srcji >= 0) {
+    const double2 pa = T->pa, sa = T->sa;
+    pa_new = make_double2(sa.x + beta * pa.x, sa.y + beta * pa.y);
+    T->xa = make_double2(T->xa.x + aprev * pa.x, T->xa.y + aprev * pa.y);
+  }
+
+  // p_k of the own cells and the halo; x of the own cells
+  float2 pv[CX][TZ + 2];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < TZ + 2; ++i) {
+      pv[j][i] = axpy2(rs[j][i], beta, rp[j][i]);
+      if (i >= 1 && i <= TZ) win[(i - 1) * wl + nx + j * NT + tid] = pv[j][i];
+    }
+  for (int h = tid; h < 2 * nx; h += NT) {
+    const int sl = Q.halo_slot(h);
+    if (h >= NT) {
+      const unsigned o = Q.halo_off(h);
+#pragma unroll
+      for (int i = 0; i < TZ; ++i) {
+        hs[i] = Q.load2(sv, i + 1, o);
+        hp[i] = Q.load2(po, i + 1, o);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < TZ; ++i) win[i * wl + sl] = axpy2(hs[i], beta, hp[i]);
+  }
+  if constexpr (XS != 0) {
+#pragma unroll
+    for (int j = 0; j < CX; ++j)
+#pragma unroll
+      for (int i = 0; i < TZ; ++i)
+        Q.store2(xv, i + 1, Q.own2(j), xstep ? xupd2(rx[j][i], c2, rq[j][i], c1, rp[j][i + 1]) : rx[j][i]);
+  }
+  __syncthreads();
+
+  const double w2 = S.omega_d * S.omega_d;
+  const double sp_scale = S.sp_scale_d, h2inv = S.h2inv_d, om = S.omega_d, inv_nb = S.inv_nb_d, lam = S.lam_d;
+  const double acol = S.alpha_c;
+  const int nb = S.nb;
+  GLOBAL float2* t2v = gptr(S.t2);
+  double acc = 0.0;
+#pragma unroll
+  for (int j = 0; j < CX; ++j) {
+    int x, y;
+    Q.row_of(Q.cell[j], &x, &y);
+    const double sxy2 = sponge_axis_d(x, nx, nb, inv_nb) + sponge_axis_d(y, Q.ny, nb, inv_nb);
+#pragma unroll
+    for (int i = 0; i < TZ; ++i) {
+      const float2* row = win + i * wl + nx + j * NT + tid;
+      const float2 xm = x > 0 ? row[-1] : f2(0.f, 0.f);
+      const float2 xp = x < nx - 1 ? row[1] : f2(0.f, 0.f);
+      const float2 ym = row[-nx], yp = row[nx];
+      const double b = sp_scale * (sxy2 + sponge_axis_d(Q.z0 + i, Q.nz, nb, inv_nb));
+      double2 td = helm(pv[j][i + 1], xm, xp, ym, yp, pv[j][i], pv[j][i + 2], h2inv, w2 * (double)mm[j][i], -(om * b));
+      if (src_tile && srcji == j * TZ + i) {
+        td.x -= acol * pa_new.x;
+        td.y -= acol * pa_new.y;
+      }
+      const float2 tv = round2(td);
+      Q.store2(tout, i + 1, Q.own2(j), tv);
+      Q.store2(pn, i + 1, Q.own2(j), pv[j][i + 1]);
+      if (Q.live(j, i)) acc = fma((double)tv.x, (double)tv.x, fma((double)tv.y, (double)tv.y, acc));
+    }
+  }
+  if (has_rec) {  // receiver rows of S p
+#pragma unroll
+    for (int j = 0; j < CX; ++j)
+#pragma unroll
+      for (int i = 0; i < TZ; ++i) {
+        const int q = recq[i * B + j * NT + tid];
+        if (q >= 0) {
+          const float2 tq = f2((float)(lam * pv[j][i + 1].x), (float)(lam * pv[j][i + 1].y));
+          st2(t2v, q, tq);
+          acc += norm2d(tq);
+        }
+      }
+  }
+  const double tot = block_reduce<W>(acc, red);
+  if (tid == 0) part_d[S.slot_base + tile] = tot;
+  if (srcji >= 0) T->pa = pa_new;
+}
+
+template <int W, int CX, int TZ>
+__global__ void __launch_bounds__(64 * W)
+k_adj_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const double* __restrict__ part_d,
+          double* __restrict__ part_s, WinGroups G, int setup_only) {
+  using Tile = Win<W, CX, TZ>;
+  constexpr int NT = Tile::NT, B = Tile::B;
+  __shared__ int recq[B * TZ];
+  __shared__ double red[W + 1];
+  extern __shared__ float2 win[];   // [TZ][B + 2 nx]
+
+  const int tid = threadIdx.x;
+  const int logical = xcd_remap(blockIdx.x, gridDim.x, G.g[0].xchunk);
+  const GroupDesc gd = win_group(G, logical);
+  const int ntiles = gd.ntiles, tiles_x = gd.tiles_x;
+  int rl, tile;
+  block_map(gd, logical - gd.block0, &rl, &tile);
+  const int rhs = gd.rhs0 + rl;
+  const SysDev& S = sysv[rhs];
+  SysState* T = stv + rhs;
+  if (T->status != kActive) return;
+  const int k = T->iterB;
+  const bool setup = k < 0;
+  if (setup_only && !setup) return;
+
+  Tile Q;
+  Q.setup(S, tile, tiles_x);
+  const int nx = Q.nx, wl = Q.wl;
+  const float2* ro = S.r[setup ? 1 : (k & 1)];
+  float2* rn = S.r[setup ? 0 : ((k + 1) & 1)];
+  const float2* tv = S.t;
+  float2* sout = S.s;
+  // the set-up pass (s_0 = S^H b) reads no t
+  const unsigned tbit = setup ? kOOB : 0u;
+
+  const SlotSum slots(part_d + S.slot_base, setup ? 0 : ntiles);
+  const int rec0 = Q.first_receiver(S);
+  float2 rr[CX][TZ + 2], rt[CX][TZ + 2];
+  float mm[CX][TZ];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < TZ + 2; ++i) {
+      rr[j][i] = Q.load2(ro, i, Q.own2(j));
+      rt[j][i] = Q.load2(tv, i, Q.own2(j) | tbit);
+    }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < TZ; ++i) mm[j][i] = Q.load1(S.m, i + 1, Q.own1(j));
+  float2 hr[TZ], ht[TZ];   // the thread's first halo cell
+  const unsigned ho = tid < 2 * nx ? Q.halo_off(tid) : kOOB;
+#pragma unroll
+  for (int i = 0; i < TZ; ++i) {
+    hr[i] = Q.load2(ro, i + 1, ho);
+    ht[i] = Q.load2(tv, i + 1, ho | tbit);
+  }
+  issue_point();
+  const bool has_rec = S.n_rec > 0 && Q.find_receivers(S, rec0, recq);
+
+  double a = 0.0;
+  if (!setup) {
+    const double gk = T->gamma[k & 1];
+    const double g0 = T->gamma0;
+    const double gmin = (k == 0) ? gk : T->gmin[(k - 1) & 1];
+    const bool brk = T->brk != 0;
+    const bool stop = brk || (g0 == 0.0) || (gk <= S.rtol2 * g0) || (k >= S.max_iter) || (gk > kDivergeRatio * gmin);
+    if (stop) {
+      if (tile == 0 && tid == 0) {
+        T->status = brk ? kBreakdown
+                  : (g0 == 0.0) ? kZeroRhs
+                  : (gk <= S.rtol2 * g0) ? kConverged
+                  : (gk > kDivergeRatio * gmin) ? kDiverged : kMaxIter;
+        T->iters = k;
+      }
+      return;
+    }
+    const double dk = slots.sum(part_d + S.slot_base, ntiles);
+    if (!(dk > 0.0) || !(dk <= DBL_MAX) || !(gk <= DBL_MAX)) {
+      if (tile == 0 && tid == 0) T->brk = 1;   // see k_adj
+      return;
+    }
+    a = gk / dk;
+    if (tile == 0 && tid == 0) T->a[k & 1] = a;
+  }
+  const int srcji = Q.source(S);
+  const bool src_tile = S.mode == 1 && Q.src_plane(S);   // uniform: most tiles skip the source's cell
+
+  float2 rv[CX][TZ + 2];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < TZ + 2; ++i) {
+      rv[j][i] = setup ? rr[j][i] : axpy2(rr[j][i], -a, rt[j][i]);
+      if (i >= 1 && i <= TZ) win[(i - 1) * wl + nx + j * NT + tid] = rv[j][i];
+    }
+  for (int h = tid; h < 2 * nx; h += NT) {
+    const int sl = Q.halo_slot(h);
+    if (h >= NT) {
+      const unsigned o = Q.halo_off(h);
+#pragma unroll
+      for (int i = 0; i < TZ; ++i) {
+        hr[i] = Q.load2(ro, i + 1, o);
+        ht[i] = Q.load2(tv, i + 1, o | tbit);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < TZ; ++i) win[i * wl + sl] = setup ? hr[i] : axpy2(hr[i], -a, ht[i]);
+  }
+  __syncthreads();
+
+  const double w2 = S.omega_d * S.omega_d;
+  const double sp_scale = S.sp_scale_d, h2inv = S.h2inv_d, om = S.omega_d, inv_nb = S.inv_nb_d, lam = S.lam_d;
+  const double acol = S.alpha_c;
+  const int nb = S.nb;
+  GLOBAL float2* r2v = gptr(S.r2);
+  const GLOBAL float2* t2v = gptr((const float2*)S.t2);
+  double acc = 0.0;
+  double2 sa = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int j = 0; j < CX; ++j) {
+    int x, y;
+    Q.row_of(Q.cell[j], &x, &y);
+    const double sxy2 = sponge_axis_d(x, nx, nb, inv_nb) + sponge_axis_d(y, Q.ny, nb, inv_nb);
+#pragma unroll
+    for (int i = 0; i < TZ; ++i) {
+      const float2* row = win + i * wl + nx + j * NT + tid;
+      const float2 xm = x > 0 ? row[-1] : f2(0.f, 0.f);
+      const float2 xp = x < nx - 1 ? row[1] : f2(0.f, 0.f);
+      const float2 ym = row[-nx], yp = row[nx];
+      const double b = sp_scale * (sxy2 + sponge_axis_d(Q.z0 + i, Q.nz, nb, inv_nb));
+      double2 sd = helm(rv[j][i + 1], xm, xp, ym, yp, rv[j][i], rv[j][i + 2], h2inv, w2 * (double)mm[j][i], om * b);
+      if (has_rec) {
+        const int q = recq[i * B + j * NT + tid];
+        if (q >= 0) {  // receiver column of S^H
+          float2 r2 = ld2(r2v, q);
+          if (!setup) {
+            r2 = axpy2(r2, -a, ld2(t2v, q));
+            st2(r2v, q, r2);
+          }
+          sd.x += lam * r2.x;
+          sd.y += lam * r2.y;
+        }
+      }
+      const float2 s = round2(sd);
+      if (src_tile && srcji == j * TZ + i) {
+        sa = make_double2(-acol * (double)rv[j][i + 1].x, -acol * (double)rv[j][i + 1].y);
+        acc += sa.x * sa.x + sa.y * sa.y;
+      }
+      Q.store2(sout, i + 1, Q.own2(j), s);
+      Q.store2(rn, i + 1, Q.own2(j), rv[j][i + 1]);
+      if (Q.live(j, i)) acc = fma((double)s.x, (double)s.x, fma((double)s.y, (double)s.y, acc));
+    }
+  }
+  const double tot = block_reduce<W>(acc, red);
+  if (tid == 0) part_s[S.slot_base + tile] = tot;
+  if (tile == 0 && tid == 0) T->iterA = k + 1;
+  if (srcji >= 0) T->sa = sa;
+}
+
+// ---------------------------------------------------------------------------
 // dispatch over the supported tile shapes
 // ---------------------------------------------------------------------------
 
 #define WRI_TILE_LIST(X) X(4, 1) X(4, 2) X(4, 4) X(8, 1) X(8, 2) X(2, 8) X(8, 4)
 
+#define WRI_WIN_LIST(X) X(4, 1, 2) X(4, 1, 4) X(4, 2, 4) X(8, 2, 4)
+
+static WinGroups win_groups(const GroupDesc* host_gd, const GroupDesc* gd, int n) {
+  WinGroups G{};
+  G.n = n;
+  G.table = gd;
+  for (int i = 0; i < std::min(n, kWinGroups); ++i) G.g[i] = host_gd[i];
+  return G;
+}
+
+size_t win_lds_bytes(const TileCfg& c, int nx) { return sizeof(float2) * (size_t)c.tz * (64 * c.w * c.ry + 2 * nx); }
+
 bool cfg_supported(const TileCfg& c) {
+  if (c.pf == kWindow) {
+#define X(W_, C_, Z_) if (c.w == W_ && c.ry == C_ && c.tz == Z_) return true;
+    WRI_WIN_LIST(X)
+#undef X
+    return false;
+  }
 #define X(W_, R_) if (c.w == W_ && c.ry == R_) return c.tz >= 1 && c.tz <= 64 && c.pf >= 0 && c.pf <= 3;
   WRI_TILE_LIST(X)
 #undef X
@@ -1755,9 +2316,26 @@ bool cfg_supported(const TileCfg& c) {
 }
 
 hipError_t launch_fwd(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_s, double* part_d,
-                      const GroupDesc* gd, int ngroups, int nblocks, int k, hipStream_t s) {
+                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max, int k, hipStream_t s) {
   if (nblocks <= 0 || ngroups <= 0) return hipSuccess;
   const unsigned nb = (unsigned)nblocks;
+  if (c.pf == kWindow) {
+    const unsigned lds = (unsigned)win_lds_bytes(c, nx_max);
+    const WinGroups G = win_groups(host_gd, gd, ngroups);
+#define X(W_, C_, Z_)                                                                                    \
+    if (c.w == W_ && c.ry == C_ && c.tz == Z_) {                                                         \
+      if (fwd_x_step(k))                                                                                 \
+        hipLaunchKernelGGL((k_fwd_win<W_, C_, Z_, 1>), dim3(nb), dim3(64 * W_), lds, s, sys, st, part_s,   \
+                           part_d, G);                                                                   \
+      else                                                                                               \
+        hipLaunchKernelGGL((k_fwd_win<W_, C_, Z_, 0>), dim3(nb), dim3(64 * W_), lds, s, sys, st, part_s,   \
+                           part_d, G);                                                                   \
+      return hipGetLastError();                                                                          \
+    }
+    WRI_WIN_LIST(X)
+#undef X
+    return hipErrorInvalidValue;
+  }
 #define X(W_, R_)                                                                                   \
   if (c.w == W_ && c.ry == R_) {                                                                    \
     if (c.pf == 1 && fwd_x_step(k))                                                                 \
@@ -1798,9 +2376,22 @@ int adj_blocks_per_cu(const TileCfg& c) {
 }
 
 hipError_t launch_adj(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_d, double* part_s,
-                      const GroupDesc* gd, int ngroups, int nblocks, hipStream_t s, int setup_only) {
+                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max, hipStream_t s, int setup_only) {
   if (nblocks <= 0 || ngroups <= 0) return hipSuccess;
   const unsigned nb = (unsigned)nblocks;
+  if (c.pf == kWindow) {
+    const unsigned lds = (unsigned)win_lds_bytes(c, nx_max);
+    const WinGroups G = win_groups(host_gd, gd, ngroups);
+#define X(W_, C_, Z_)                                                                                  \
+    if (c.w == W_ && c.ry == C_ && c.tz == Z_) {                                                       \
+      hipLaunchKernelGGL((k_adj_win<W_, C_, Z_>), dim3(nb), dim3(64 * W_), lds, s, sys, st, part_d,      \
+                         part_s, G, setup_only);                                                       \
+      return hipGetLastError();                                                                        \
+    }
+    WRI_WIN_LIST(X)
+#undef X
+    return hipErrorInvalidValue;
+  }
 #define X(W_, R_)                                                                                   \
   if (c.w == W_ && c.ry == R_) {                                                                    \
     if (c.pf == 1)                                                                                  \

@@ -73,15 +73,20 @@ struct SysState {
   int pad_[2];
 };
 
+// TileCfg::pf of the window march (tiles of consecutive cells of the x-y plane)
+constexpr int kWindow = 4;
+
 struct TileCfg {
   int w;       // wavefronts per workgroup
-  int ry;      // rows per wavefront  (tile height TY = w*ry)
+  int ry;      // rows per wavefront  (tile height TY = w*ry); pf = 4: cells per thread and plane
   int tz;      // z-slab length
   int pf = 0;  // 1: software-pipelined z march (loads of plane z+2 in flight during plane z);
                // 2: pipelined, and the adjoint pass recomputes t = S p instead of reading it;
-               // 3: as 2, with the adjoint pass's loads two planes ahead
+               // 3: as 2, with the adjoint pass's loads two planes ahead;
+               // 4: window march (64 w ry consecutive cells of the x-y plane, tz planes at once)
   int order = 0;  // 1: tile-major block order (see GroupDesc::tile_major)
   int ty() const { return w * ry; }
+  int win_cells() const { return 64 * w * ry; }
 };
 
 // One group = the systems of one grid.  A fused launch covers every group:
@@ -95,6 +100,15 @@ struct GroupDesc {
   int tile_major;  // 1: consecutive blocks take the same tile of successive systems
                    //    (the tile of m is then read once per XCD for the whole group)
   int xchunk;      // tiles per XCD chunk (same value in every entry of a table)
+};
+
+// Launch arguments of the window march: the first groups by value (the table
+// when there are more).
+constexpr int kWinGroups = 4;
+struct WinGroups {
+  int n;
+  const GroupDesc* table;
+  GroupDesc g[kWinGroups];
 };
 
 // Records a failure for wri_last_error (thread-local) and returns code.
@@ -116,12 +130,14 @@ hipError_t launch_fold_partials(const SysDev* sys, double* part_s, int rhs0, int
 // Fused CGLS launches over all groups (same tile shape c for all of them).
 // k: the iteration every active system of the launch is at (systems of one
 // call iterate in lockstep); selects the variant of the forward kernel that
-// updates x (even k >= 2) or leaves it alone (odd k, k = 0).
+// updates x (even k >= 2) or leaves it alone (odd k, k = 0).  nx_max: the
+// widest row of the launch's grids (sizes the window march's LDS).  host_gd:
+// host copy of gd.
 inline bool fwd_x_step(int64_t k) { return k >= 2 && (k & 1) == 0; }
 hipError_t launch_fwd(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_s, double* part_d,
-                      const GroupDesc* gd, int ngroups, int nblocks, int k, hipStream_t s);
+                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max, int k, hipStream_t s);
 hipError_t launch_adj(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_d, double* part_s,
-                      const GroupDesc* gd, int ngroups, int nblocks, hipStream_t s, int setup_only = 0);
+                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max, hipStream_t s, int setup_only = 0);
 hipError_t launch_grad(const SysDev* sys, SysState* st, int rhs0, int nrhs, int n, float* grad,
                        double* part_j, int stride, int accumulate, hipStream_t s);
 hipError_t launch_finalize(const SysDev* sys, SysState* st, const double* part_j, int nparts,
@@ -129,6 +145,8 @@ hipError_t launch_finalize(const SysDev* sys, SysState* st, const double* part_j
 hipError_t launch_zero_f32(float* p, size_t n, hipStream_t s);
 int grad_blocks(int n);
 bool cfg_supported(const TileCfg& c);
+// LDS bytes of the window march's tile c on rows of nx cells
+size_t win_lds_bytes(const TileCfg& c, int nx);
 // workgroups of the adjoint kernel of tile c resident on one compute unit (0 on error)
 int adj_blocks_per_cu(const TileCfg& c);
 
