@@ -55,41 +55,116 @@ __device__ __forceinline__ float block_max(float v, float* red) {
 
 // ---- total variation --------------------------------------------------------
 // phi_c = sqrt(|D m|_c^2 + eps^2) with forward differences (zero in the last
-// cell of each axis); q_a = (D_a m) / phi.  Partials of sum phi per block.
-__global__ void __launch_bounds__(kRedThreads)
-k_tv_q(int nx, int ny, int nz, double inv_h, double eps2, const float* __restrict__ m,
-       double* __restrict__ qx, double* __restrict__ qy, double* __restrict__ qz, double* __restrict__ part) {
-  __shared__ double red[kRedThreads / 64];
-  const int64_t n = (int64_t)nx * ny * nz, plane = (int64_t)nx * ny;
-  double acc = 0.0;
-  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n; c += (int64_t)gridDim.x * blockDim.x) {
-    const int x = (int)(c % nx), y = (int)((c / nx) % ny), z = (int)(c / plane);
-    const double mc = m[c];
-    const double dx = (x + 1 < nx) ? ((double)m[c + 1] - mc) * inv_h : 0.0;
-    const double dy = (y + 1 < ny) ? ((double)m[c + nx] - mc) * inv_h : 0.0;
-    const double dz = (z + 1 < nz) ? ((double)m[c + plane] - mc) * inv_h : 0.0;
-    const double phi = sqrt(dx * dx + dy * dy + dz * dz + eps2);
-    qx[c] = dx / phi;
-    qy[c] = dy / phi;
-    qz[c] = dz / phi;
-    acc += phi;
-  }
-  const double t = block_sum(acc, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = t;
+// cell of each axis); q_a = (D_a m) / phi;
+// grad_c += gamma / h * sum_a (q_a[c - e_a] - q_a[c]).
+//
+// One pass: a workgroup owns kTvB consecutive cells of the x-y plane (the
+// neighbours c - nx are nx cells back in the same order), a thread each, and
+// marches kTvZ planes at a time.  It forms q once per cell, with qx and qy in LDS
+// for the cells after in x and y (plus the nx cells before the tile) and qz in
+// registers, and updates grad: 12 bytes per cell (m, grad in and out), where a
+// pass that stored the three q in float64 and one that read them back moved 60.
+// Bound by the float64 square root and divisions (one and three per cell, nx / kTvB
+// more for the rows before the tile).  Rows too wide for the LDS (ROWS = false)
+// form q of the cell c - nx again instead.  Value and gradient, whole call
+// (25 us of it the launches and the copy of the value): 128^3 70 -> 43 us,
+// 256x256x192 299 -> 107 us.
+constexpr int kTvB = 1024, kTvZ = 2;
+constexpr int kTvMaxRow = 1024;    // (kTvB + row) * kTvZ * 16 B of LDS: 64 KB
+
+// I: the index type (int while the grid has fewer than 2^31 cells).
+template <class I>
+struct TvGeom {
+  I nx, ny, nz, plane;
+  double inv_h, eps2;
+};
+
+struct TvQ { double x, y, z, phi; };
+
+// q of the cell c = z * plane + y * nx + x
+template <class I>
+__device__ __forceinline__ TvQ tv_q(const TvGeom<I>& G, const float* __restrict__ m, I c, I x, I y, I z) {
+  const double mc = m[c];
+  TvQ q;
+  const double dx = (x + 1 < G.nx) ? ((double)m[c + 1] - mc) * G.inv_h : 0.0;
+  const double dy = (y + 1 < G.ny) ? ((double)m[c + G.nx] - mc) * G.inv_h : 0.0;
+  const double dz = (z + 1 < G.nz) ? ((double)m[c + G.plane] - mc) * G.inv_h : 0.0;
+  q.phi = sqrt(dx * dx + dy * dy + dz * dz + G.eps2);
+  q.x = dx / q.phi;
+  q.y = dy / q.phi;
+  q.z = dz / q.phi;
+  return q;
 }
 
-// grad_c += gamma / h * sum_a (q_a[c - e_a] - q_a[c])
-__global__ void __launch_bounds__(kRedThreads)
-k_tv_grad(int nx, int ny, int nz, double scale, const double* __restrict__ qx, const double* __restrict__ qy,
-          const double* __restrict__ qz, float* __restrict__ grad) {
-  const int64_t n = (int64_t)nx * ny * nz, plane = (int64_t)nx * ny;
-  for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n; c += (int64_t)gridDim.x * blockDim.x) {
-    const int x = (int)(c % nx), y = (int)((c / nx) % ny), z = (int)(c / plane);
-    double v = -(qx[c] + qy[c] + qz[c]);
-    if (x > 0) v += qx[c - 1];
-    if (y > 0) v += qy[c - nx];
-    if (z > 0) v += qz[c - plane];
-    grad[c] = (float)((double)grad[c] + scale * v);
+// tiles of zc planes; per-block partials of sum phi; GRAD = false: the value only
+template <class I, bool ROWS, bool GRAD>
+__global__ void __launch_bounds__(kTvB)
+k_tv(TvGeom<I> G, I tiles_p, I tiles, int zc, double scale, const float* __restrict__ m, float* __restrict__ grad,
+     double* __restrict__ part) {
+  __shared__ double red[kTvB / 64];
+  extern __shared__ double tvs[];   // qx then qy: [kTvZ][halo + kTvB] each (ROWS: halo = nx, else 1 and no qy)
+  const int halo = ROWS ? (int)G.nx : 1, wl = halo + kTvB, tid = threadIdx.x;
+  double* sx = tvs;
+  double* sy = tvs + kTvZ * wl;
+  double acc = 0.0;
+  for (I t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const I tz = t / tiles_p, c0 = (t - tz * tiles_p) * kTvB, zb = tz * zc, ze = zb + zc < G.nz ? zb + zc : G.nz;
+    const I c = c0 + tid, y = c / G.nx, x = c - y * G.nx;
+    const bool in = c < G.plane;
+    double qzm = 0.0;   // qz of plane z - 1
+    if (GRAD && in && zb > 0) qzm = tv_q<I>(G, m, (zb - 1) * G.plane + c, x, y, zb - 1).z;
+    for (I z0 = zb; z0 < ze; z0 += kTvZ) {
+      const I o = z0 * G.plane + c;
+      TvQ q[kTvZ];
+      float g[kTvZ];
+#pragma unroll
+      for (int i = 0; i < kTvZ; ++i)
+        if (in && z0 + i < ze) {
+          if constexpr (GRAD) g[i] = grad[o + i * G.plane];
+          q[i] = tv_q<I>(G, m, o + i * G.plane, x, y, z0 + i);
+          acc += q[i].phi;
+          if constexpr (GRAD) {
+            sx[i * wl + halo + tid] = q[i].x;
+            if constexpr (ROWS) sy[i * wl + halo + tid] = q[i].y;
+          }
+        }
+      if constexpr (GRAD) {
+        if (tid < halo && c0 - halo + tid >= 0) {   // halo <= kTvB
+          const I hc = c0 - halo + tid, hy = hc / G.nx, hx = hc - hy * G.nx;
+#pragma unroll
+          for (int i = 0; i < kTvZ; ++i)
+            if (z0 + i < ze) {
+              const TvQ v = tv_q<I>(G, m, (z0 + i) * G.plane + hc, hx, hy, z0 + i);
+              sx[i * wl + tid] = v.x;
+              if constexpr (ROWS) sy[i * wl + tid] = v.y;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kTvZ; ++i)
+          if (in && z0 + i < ze) {
+            double v = -(q[i].x + q[i].y + q[i].z);
+            if (x > 0) v += sx[i * wl + halo + tid - 1];
+            if (y > 0) {
+              if constexpr (ROWS) v += sy[i * wl + tid];
+              else v += tv_q<I>(G, m, o + i * G.plane - G.nx, x, y - 1, z0 + i).y;
+            }
+            if (z0 + i > 0) v += qzm;
+            qzm = q[i].z;
+            grad[o + i * G.plane] = (float)((double)g[i] + scale * v);
+          }
+        __syncthreads();
+      }
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if ((tid & 63) == 0) red[tid >> 6] = acc;
+  __syncthreads();
+  if (tid == 0) {
+    double s = 0.0;
+    for (int i = 0; i < kTvB / 64; ++i) s += red[i];
+    part[blockIdx.x] = s;
   }
 }
 
@@ -145,6 +220,195 @@ __global__ void k_scale_sc(float* __restrict__ y, int64_t n, const double* __res
     y[i] = (float)(a * (double)y[i]);
 }
 
+// ---- l-BFGS direction from inner products --------------------------------------
+// The two-loop recursion touches g, s_j and y_j only through inner products: with
+// s_i.g, y_i.g, s_i.y_j and y_i.y_j (i <= j) its coefficients follow in scalar
+// arithmetic, and dir = -(H0 (g - sum alpha_j y_j) + sum c_j s_j) is one pass.  Two
+// passes over the 2 M + 1 vectors and one small launch replace 3 M + 2 dot
+// products and 2 M + 3 updates, each a launch with dir read and written (M = 5,
+// 128^3: 36 launches and 219 us -> 3 launches and 47 us; 256x256x192 847 -> 215
+// us, 290 -> 92 bytes per cell at 5.4 TB/s).  Inner products and
+// coefficients are float64; dir is rounded once instead of after every update.
+// Up to kLbFused pairs (the accumulators live in registers: 88 for 8 pairs);
+// longer memories take the recursion below.
+constexpr int kLbFused = 8;
+constexpr int kLbBlocks = 512;   // partial sums per inner product
+
+struct LbPairs {   // the pairs in use, oldest first
+  const float *s[kLbFused], *y[kLbFused];
+};
+
+// accumulator of an inner product: s_i.g, y_i.g, then s_i.y_j and y_i.y_j for i <= j
+template <int M>
+struct LbIndex {
+  static constexpr int kTri = M * (M + 1) / 2;
+  static constexpr int kCount = 2 * M + 2 * kTri;
+  static constexpr __host__ __device__ int sg(int i) { return i; }
+  static constexpr __host__ __device__ int yg(int i) { return M + i; }
+  static constexpr __host__ __device__ int tri(int i, int j) { return i * M - i * (i - 1) / 2 + (j - i); }
+  static constexpr __host__ __device__ int sy(int i, int j) { return 2 * M + tri(i, j); }
+  static constexpr __host__ __device__ int yy(int i, int j) { return 2 * M + kTri + tri(i, j); }
+};
+
+// Wave sums of the N accumulators, exchanged by halves: the lanes of one half
+// take over half of the accumulators, so N sums take about N shuffles instead of
+// 6 N.  A lane ends with the sum of accumulator `id`, of `left` > 0 real ones
+// (0: padding of an odd count); lanes may share one.
+template <int N>
+__device__ __forceinline__ double wave_sums(double (&a)[N], int off, int* id, int* left) {
+  if constexpr (N == 1) {
+    double v = a[0];
+    for (; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+  } else {
+    constexpr int H = (N + 1) / 2;
+    const bool up = (threadIdx.x & off) != 0;
+    double b[H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const double hi = (i + H < N) ? a[i + H < N ? i + H : 0] : 0.0;
+      const double send = up ? a[i] : hi, keep = up ? hi : a[i];
+      b[i] = keep + __shfl_xor(send, off, 64);
+    }
+    if (up) *id += H;
+    *left = up ? max(*left - H, 0) : min(*left, H);
+    return wave_sums<H>(b, off >> 1, id, left);
+  }
+}
+
+template <int M>
+__global__ void __launch_bounds__(kRedThreads)
+k_lb_gram(LbPairs P, const float* __restrict__ g, int64_t n, double* __restrict__ part) {
+  using I = LbIndex<M>;
+  static_assert(I::kCount <= 128, "");
+  __shared__ double red[kRedThreads / 64][128];
+  double a[I::kCount];
+#pragma unroll
+  for (int i = 0; i < I::kCount; ++i) a[i] = 0.0;
+  for (int64_t c = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; c < n; c += (int64_t)gridDim.x * kRedThreads) {
+    double s[M], y[M];
+    const double gv = g[c];
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      s[i] = P.s[i][c];
+      y[i] = P.y[i][c];
+    }
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      a[I::sg(i)] = fma(s[i], gv, a[I::sg(i)]);
+      a[I::yg(i)] = fma(y[i], gv, a[I::yg(i)]);
+#pragma unroll
+      for (int j = i; j < M; ++j) {
+        a[I::sy(i, j)] = fma(s[i], y[j], a[I::sy(i, j)]);
+        a[I::yy(i, j)] = fma(y[i], y[j], a[I::yy(i, j)]);
+      }
+    }
+  }
+  // 64-lane exchange holds up to 64 accumulators at a time
+  const int w = threadIdx.x >> 6;
+  constexpr int N0 = I::kCount < 64 ? I::kCount : 64, N1 = I::kCount - N0;
+  {
+    double b[N0];
+#pragma unroll
+    for (int i = 0; i < N0; ++i) b[i] = a[i];
+    int id = 0, left = N0;
+    const double v = wave_sums<N0>(b, 32, &id, &left);
+    if (left > 0) red[w][id] = v;
+  }
+  if constexpr (N1 > 0) {
+    double b[N1];
+#pragma unroll
+    for (int i = 0; i < N1; ++i) b[i] = a[N0 + i];
+    int id = 0, left = N1;
+    const double v = wave_sums<N1>(b, 32, &id, &left);
+    if (left > 0) red[w][N0 + id] = v;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < I::kCount; i += kRedThreads) {
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < kRedThreads / 64; ++k) v += red[k][i];
+    part[(int64_t)i * kLbBlocks + blockIdx.x] = v;
+  }
+}
+
+// One block: the inner products from their partials (fixed order), then the
+// recursion's coefficients: coef[0] = H0, coef[1 + j] = H0 alpha_j (of y_j),
+// coef[1 + M + j] = c_j (of s_j).
+template <int M>
+__global__ void __launch_bounds__(1024) k_lb_coef(const double* __restrict__ part, int nparts, double h0,
+                                                  double* __restrict__ coef) {
+  using I = LbIndex<M>;
+  __shared__ double d[I::kCount];
+  const int lane = threadIdx.x & 63;
+  for (int i = threadIdx.x >> 6; i < I::kCount; i += 16) {
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < kLbBlocks / 64; ++k) {
+      const int b = lane + 64 * k;
+      v += b < nparts ? part[(int64_t)i * kLbBlocks + b] : 0.0;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (lane == 0) d[i] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  double rho[M], alpha[M], c[M];
+#pragma unroll
+  for (int i = M - 1; i >= 0; --i) {
+    rho[i] = 1.0 / d[I::sy(i, i)];
+    double sq = d[I::sg(i)];
+#pragma unroll
+    for (int j = i + 1; j < M; ++j) sq -= alpha[j] * d[I::sy(i, j)];
+    alpha[i] = rho[i] * sq;
+  }
+  const double H0 = h0 > 0.0 ? h0 : d[I::sy(M - 1, M - 1)] / d[I::yy(M - 1, M - 1)];
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    double yq = d[I::yg(i)];   // y_i . q after the first loop
+#pragma unroll
+    for (int j = 0; j < M; ++j) yq -= alpha[j] * d[j < i ? I::yy(j, i) : I::yy(i, j)];
+    double yr = H0 * yq;
+#pragma unroll
+    for (int j = 0; j < i; ++j) yr += c[j] * d[I::sy(j, i)];
+    c[i] = alpha[i] - rho[i] * yr;
+  }
+  coef[0] = H0;
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    coef[1 + i] = H0 * alpha[i];
+    coef[1 + M + i] = c[i];
+  }
+}
+
+// dir = -(H0 g - sum (H0 alpha_j) y_j + sum c_j s_j)
+template <int M>
+__global__ void __launch_bounds__(kRedThreads)
+k_lb_combine(LbPairs P, const float* __restrict__ g, int64_t n, const double* __restrict__ coef,
+             float* __restrict__ dir) {
+  const double H0 = coef[0];
+  double cy[M], cs[M];
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    cy[i] = coef[1 + i];
+    cs[i] = coef[1 + M + i];
+  }
+  for (int64_t c = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; c < n; c += (int64_t)gridDim.x * kRedThreads) {
+    double r = H0 * (double)g[c];
+#pragma unroll
+    for (int i = 0; i < M; ++i) r = fma(cs[i], (double)P.s[i][c], fma(-cy[i], (double)P.y[i][c], r));
+    dir[c] = (float)-r;
+  }
+}
+
+// dir = -h0 g (no curvature pair)
+__global__ void __launch_bounds__(kRedThreads) k_lb_steepest(const float* __restrict__ g, int64_t n, double h0,
+                                                             float* __restrict__ dir) {
+  for (int64_t c = blockIdx.x * (int64_t)kRedThreads + threadIdx.x; c < n; c += (int64_t)gridDim.x * kRedThreads)
+    dir[c] = (float)-(h0 * (double)g[c]);
+}
+
 __global__ void k_copy32(float* __restrict__ d, const float* __restrict__ s, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     d[i] = s[i];
@@ -193,45 +457,65 @@ int grid_blocks(int64_t n) { return (int)std::min<int64_t>(kRedBlocks, std::max<
 // ---- host helpers ----------------------------------------------------------------
 size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
-struct TvWs { double *qx, *qy, *qz, *part, *sum; };
-size_t tv_ws_bytes(int64_t n) { return 3 * al(sizeof(double) * n) + al(sizeof(double) * (kRedBlocks + 1)); }
-TvWs tv_ws(char* ws, int64_t n) {
-  TvWs w;
-  w.qx = reinterpret_cast<double*>(ws);
-  w.qy = reinterpret_cast<double*>(ws + al(sizeof(double) * n));
-  w.qz = reinterpret_cast<double*>(ws + 2 * al(sizeof(double) * n));
-  w.part = reinterpret_cast<double*>(ws + 3 * al(sizeof(double) * n));
-  w.sum = w.part + kRedBlocks;
-  return w;
+// per-block partials of the value and their sum
+constexpr int kTvBlocks = 2048;
+size_t tv_ws_bytes() { return al(sizeof(double) * (kTvBlocks + 1)); }
+
+// sum of n partials in one fixed order (one block)
+__global__ void __launch_bounds__(kRedThreads) k_sum_parts(const double* __restrict__ part, int n, double* __restrict__ out) {
+  __shared__ double red[kRedThreads / 64];
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += kRedThreads) v += part[i];
+  const double t = block_sum(v, red);
+  if (threadIdx.x == 0) *out = t;
+}
+
+// returns the number of partials
+template <class I>
+int tv_launch(const wri_grid& g, const float* m, double eps, double scale, float* grad, double* part, hipStream_t st) {
+  TvGeom<I> G;
+  G.nx = g.nx; G.ny = g.ny; G.nz = g.nz; G.plane = (I)g.nx * g.ny;
+  G.inv_h = 1.0 / g.h; G.eps2 = eps * eps;
+  const I tiles_p = (G.plane - 1) / kTvB + 1;
+  // planes per tile: 16 (one in 17 q is formed twice) while that leaves two
+  // workgroups per compute unit
+  int zc = 16;
+  while (zc > kTvZ && tiles_p * ((G.nz - 1) / zc + 1) < 512) zc /= 2;
+  const I tiles = tiles_p * ((G.nz - 1) / zc + 1);
+  const int nb = (int)std::min<I>(kTvBlocks, tiles);
+  const size_t rows = 2 * sizeof(double) * kTvZ * (kTvB + (size_t)g.nx), cell = sizeof(double) * kTvZ * (kTvB + 1);
+  if (grad == nullptr)
+    hipLaunchKernelGGL((k_tv<I, false, false>), dim3(nb), dim3(kTvB), 0, st, G, tiles_p, tiles, zc, scale, m, grad, part);
+  else if (g.nx <= kTvMaxRow)
+    hipLaunchKernelGGL((k_tv<I, true, true>), dim3(nb), dim3(kTvB), rows, st, G, tiles_p, tiles, zc, scale, m, grad, part);
+  else
+    hipLaunchKernelGGL((k_tv<I, false, true>), dim3(nb), dim3(kTvB), cell, st, G, tiles_p, tiles, zc, scale, m, grad, part);
+  return nb;
 }
 
 // TV(m) (host value) and, if grad != null, grad += gamma * grad TV
 int tv_run(const wri_grid& g, const float* m, double eps, double gamma, double* value, float* grad, char* ws,
            hipStream_t st) {
-  const int64_t n = (int64_t)g.nx * g.ny * g.nz;
-  TvWs w = tv_ws(ws, n);
-  const int nbk = kRedBlocks;
-  hipLaunchKernelGGL(k_tv_q, dim3(nbk), dim3(kRedThreads), 0, st, g.nx, g.ny, g.nz, 1.0 / g.h, eps * eps, m, w.qx,
-                     w.qy, w.qz, w.part);
+  double* part = reinterpret_cast<double*>(ws);
+  float* gr = gamma != 0.0 ? grad : nullptr;
+  const int nb = (int64_t)g.nx * g.ny * g.nz < (int64_t(1) << 31)
+                     ? tv_launch<int>(g, m, eps, gamma / g.h, gr, part, st)
+                     : tv_launch<int64_t>(g, m, eps, gamma / g.h, gr, part, st);
   OUTER_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_coef, dim3(1), dim3(64), 0, st, w.part, nbk, w.sum, (int)kOpSum, 0, 0, 0);
+  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(kRedThreads), 0, st, part, nb, part + kTvBlocks);
   OUTER_HIP(hipGetLastError());
-  if (grad != nullptr && gamma != 0.0) {
-    hipLaunchKernelGGL(k_tv_grad, dim3(grid_blocks(n)), dim3(kRedThreads), 0, st, g.nx, g.ny, g.nz, gamma / g.h, w.qx,
-                       w.qy, w.qz, grad);
-    OUTER_HIP(hipGetLastError());
-  }
-  OUTER_HIP(hipMemcpyAsync(value, w.sum, sizeof(double), hipMemcpyDeviceToHost, st));
+  OUTER_HIP(hipMemcpyAsync(value, part + kTvBlocks, sizeof(double), hipMemcpyDeviceToHost, st));
   OUTER_HIP(hipStreamSynchronize(st));
   return WRI_OK;
 }
 
 struct LbWs { double* part; double* sc; };
-size_t lb_ws_bytes(int cap) { return al(sizeof(double) * kRedBlocks) + al(sizeof(double) * (2 * cap + 4)); }
+constexpr int kLbParts = std::max(kRedBlocks, kLbBlocks * LbIndex<kLbFused>::kCount);
+size_t lb_ws_bytes(int cap) { return al(sizeof(double) * kLbParts) + al(sizeof(double) * (2 * cap + 4)); }
 LbWs lb_ws(char* ws) {
   LbWs w;
   w.part = reinterpret_cast<double*>(ws);
-  w.sc = reinterpret_cast<double*>(ws + al(sizeof(double) * kRedBlocks));
+  w.sc = reinterpret_cast<double*>(ws + al(sizeof(double) * kLbParts));
   return w;
 }
 
@@ -239,6 +523,19 @@ int dot_to(const float* a, const float* b, int64_t n, const LbWs& w, int op, int
   hipLaunchKernelGGL(k_dot32, dim3(kRedBlocks), dim3(kRedThreads), 0, st, a, b, n, w.part);
   OUTER_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_coef, dim3(1), dim3(64), 0, st, w.part, kRedBlocks, w.sc, op, dst, ia, ib);
+  OUTER_HIP(hipGetLastError());
+  return WRI_OK;
+}
+
+template <int M>
+int lbfgs_fused(const LbPairs& P, int64_t n, const float* g, double h0, float* dir, const LbWs& w, hipStream_t st) {
+  const int nb = (int)std::min<int64_t>(kLbBlocks, (n + kRedThreads - 1) / kRedThreads);
+  hipLaunchKernelGGL((k_lb_gram<M>), dim3(nb), dim3(kRedThreads), 0, st, P, g, n, w.part);
+  OUTER_HIP(hipGetLastError());
+  hipLaunchKernelGGL((k_lb_coef<M>), dim3(1), dim3(1024), 0, st, w.part, nb, h0, w.sc);
+  OUTER_HIP(hipGetLastError());
+  const int nc = (int)std::min<int64_t>(4096, (n + kRedThreads - 1) / kRedThreads);
+  hipLaunchKernelGGL((k_lb_combine<M>), dim3(nc), dim3(kRedThreads), 0, st, P, g, n, w.sc, dir);
   OUTER_HIP(hipGetLastError());
   return WRI_OK;
 }
@@ -251,6 +548,28 @@ int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int cap
   const int rho0 = 0, alp0 = cap, ih0 = 2 * cap, it0 = 2 * cap + 1, it1 = 2 * cap + 2;
   const int nbk = grid_blocks(n);
   auto slot = [&](int j) { return ((newest - (count - 1) + j) % cap + cap) % cap; };  // j = 0 oldest
+  if (count == 0) {
+    hipLaunchKernelGGL(k_lb_steepest, dim3(nbk), dim3(kRedThreads), 0, st, g, n, h0, dir);
+    OUTER_HIP(hipGetLastError());
+    return WRI_OK;
+  }
+  if (count <= kLbFused) {
+    LbPairs P{};
+    for (int j = 0; j < count; ++j) {
+      P.s[j] = S + (int64_t)slot(j) * n;
+      P.y[j] = Y + (int64_t)slot(j) * n;
+    }
+    switch (count) {
+      case 1: return lbfgs_fused<1>(P, n, g, h0, dir, w, st);
+      case 2: return lbfgs_fused<2>(P, n, g, h0, dir, w, st);
+      case 3: return lbfgs_fused<3>(P, n, g, h0, dir, w, st);
+      case 4: return lbfgs_fused<4>(P, n, g, h0, dir, w, st);
+      case 5: return lbfgs_fused<5>(P, n, g, h0, dir, w, st);
+      case 6: return lbfgs_fused<6>(P, n, g, h0, dir, w, st);
+      case 7: return lbfgs_fused<7>(P, n, g, h0, dir, w, st);
+      default: return lbfgs_fused<8>(P, n, g, h0, dir, w, st);
+    }
+  }
   hipLaunchKernelGGL(k_copy32, dim3(nbk), dim3(kRedThreads), 0, st, dir, g, n);
   OUTER_HIP(hipGetLastError());
   int rc;
@@ -302,7 +621,7 @@ AwriLayout awri_layout(int64_t n, size_t solver_bytes, int memory, int n_sys, bo
   const size_t vb = al(sizeof(float) * n);
   size_t off = L.off_vec + vb * (size_t)(5 + 2 * std::max(memory, 0));  // g, g_try, m_try, dir, tmp, S, Y
   L.off_tv = off;
-  off += tv_ws_bytes(n);
+  off += tv_ws_bytes();
   L.off_lb = off;
   off += lb_ws_bytes(std::max(memory, 1));
   L.off_red = off;
@@ -346,7 +665,7 @@ extern "C" {
 
 size_t wri_tv_workspace_bytes(const wri_grid* grid) {
   if (grid == nullptr || grid->nx < 1 || grid->ny < 1 || grid->nz < 1) return 0;
-  return tv_ws_bytes((int64_t)grid->nx * grid->ny * grid->nz) + 256;
+  return tv_ws_bytes() + 256;
 }
 
 int wri_tv(const wri_grid* grid, const float* m, double eps, double gamma, double* value, float* grad, void* ws,
