@@ -175,6 +175,11 @@ int validate(const wri_grid* grids, int32_t n_grids, const wri_system* sys, int3
   return WRI_OK;
 }
 
+// Cells per thread of the gradient pass: one on grids of up to 2^20 cells (4096
+// workgroups, 16 per compute unit), where the layout has the partial sums for it.
+constexpr int64_t kFineGradCells = 1 << 20;
+int grad_cpt(const wri_grid& g, bool fine) { return fine && cells(g) <= kFineGradCells ? 1 : 4; }
+
 // ---------------------------------------------------------------------------
 // planner: workspace layout (deterministic in the arguments)
 // ---------------------------------------------------------------------------
@@ -198,6 +203,7 @@ struct Layout {
   std::vector<size_t> off_rvec;     // per processing slot: r2, t2
   std::vector<int> slot_base;       // per processing slot
   int part_j_stride = 1;
+  bool fine_grad = false;           // part_j has room for the gradient pass with one cell per thread
   int dot_nparts = 1;
   size_t vec_bytes_plain = 0, rvec_bytes_plain = 0;
   size_t total_slab = 0;            // total without the window march's slots
@@ -248,7 +254,7 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   L.off_part_d = take(sizeof(double) * std::max(slots, 1));
   L.off_part_s = take(sizeof(double) * std::max(slots, 1));
   int gb = 1;
-  for (int g = 0; g < n_grids; ++g) gb = std::max(gb, grad_blocks((int)cells(grids[g])));
+  for (int g = 0; g < n_grids; ++g) gb = std::max(gb, grad_blocks((int)cells(grids[g]), 4));
   L.part_j_stride = gb;
   L.off_part_j = take(sizeof(double) * (size_t)gb * std::max(n_sys, 1));
   int64_t nmax = 1, rmax = 1;
@@ -291,6 +297,11 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
     }
     L.off_part_d = take(sizeof(double) * std::max(slots, 1));
     L.off_part_s = take(sizeof(double) * std::max(slots, 1));
+    // the gradient pass with one cell per thread, too
+    for (int g = 0; g < n_grids; ++g) gb = std::max(gb, grad_blocks((int)cells(grids[g]), grad_cpt(grids[g], true)));
+    L.part_j_stride = gb;
+    L.fine_grad = true;
+    L.off_part_j = take(sizeof(double) * (size_t)gb * std::max(n_sys, 1));
   }
   L.total = o + kAlign;
   return L;
@@ -1003,8 +1014,9 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
       if (gp) WRI_HIP(launch_zero_f32(gp, (size_t)n, C.st));
       continue;
     }
-    WRI_HIP(launch_grad(C.dsys, C.dstate, G->rhs0, G->nrhs, n, gp, C.part_j, L.part_j_stride, 0, C.st));
-    WRI_HIP(launch_finalize(C.dsys, C.dstate, C.part_j, grad_blocks(n), L.part_j_stride, G->rhs0, G->nrhs, C.st));
+    const int cpt = grad_cpt(C.grids[g], L.fine_grad);
+    WRI_HIP(launch_grad(C.dsys, C.dstate, G->rhs0, G->nrhs, n, gp, C.part_j, L.part_j_stride, cpt, 0, C.st));
+    WRI_HIP(launch_finalize(C.dsys, C.dstate, C.part_j, grad_blocks(n, cpt), L.part_j_stride, G->rhs0, G->nrhs, C.st));
   }
   return read_states(C, hs);
 }
@@ -1116,8 +1128,8 @@ int run_plain(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
     const int g = C.sys[i].grid;
     float* gp = (grad != nullptr) ? grad[g] : nullptr;
     if (status != kBreakdown) {
-      WRI_HIP(launch_grad(C.dsys, C.dstate, i, 1, n, gp, C.part_j, L.part_j_stride, 1, C.st));
-      WRI_HIP(launch_finalize(C.dsys, C.dstate, C.part_j, grad_blocks(n), L.part_j_stride, i, 1, C.st));
+      WRI_HIP(launch_grad(C.dsys, C.dstate, i, 1, n, gp, C.part_j, L.part_j_stride, 4, 1, C.st));
+      WRI_HIP(launch_finalize(C.dsys, C.dstate, C.part_j, grad_blocks(n, 4), L.part_j_stride, i, 1, C.st));
     }
   }
   return read_states(C, hs);

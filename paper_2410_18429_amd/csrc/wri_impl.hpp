@@ -139,11 +139,13 @@ hipError_t launch_fwd(const TileCfg& c, const SysDev* sys, SysState* st, const d
 hipError_t launch_adj(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_d, double* part_s,
                       const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max, hipStream_t s, int setup_only = 0);
 hipError_t launch_grad(const SysDev* sys, SysState* st, int rhs0, int nrhs, int n, float* grad,
-                       double* part_j, int stride, int accumulate, hipStream_t s);
+                       double* part_j, int stride, int cpt, int accumulate, hipStream_t s);
 hipError_t launch_finalize(const SysDev* sys, SysState* st, const double* part_j, int nparts,
                            int stride, int rhs0, int nrhs, hipStream_t s);
 hipError_t launch_zero_f32(float* p, size_t n, hipStream_t s);
-int grad_blocks(int n);
+// Workgroups (and partial sums of ||r1||^2 per system) of the gradient pass with
+// cpt (1 or 4) cells per thread.
+int grad_blocks(int n, int cpt);
 bool cfg_supported(const TileCfg& c);
 // LDS bytes of the window march's tile c on rows of nx cells
 size_t win_lds_bytes(const TileCfg& c, int nx);
