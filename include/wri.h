@@ -492,12 +492,14 @@ int wri_kernel_times(wri_timing* out);
  * minimiser is the one of eq. SimpObj; S has the printed source column -e
  * (weight 1); a system stops when ||S^H r|| <= rtol ||S^H b|| (the true
  * normal residual, as in wri_solve).  All systems of a grid iterate in
- * lockstep, chunks of iterations replay from a hipGraph.
+ * lockstep; the step scalars stay in device memory and the statuses are read
+ * every few iterations.
  *   Arguments and results as in wri_objective_grad, except:
  *   J_out, grad  may be NULL (a solve only); grad[g] DEVICE float32 n(g)
- *   flags        0 or WRI_FLAG_NO_GRAPH (anything else: WRI_EINVAL)
+ *   flags        0 or WRI_FLAG_NO_GRAPH (no effect: launches are eager; anything
+ *                else: WRI_EINVAL)
  *   ws           DEVICE workspace of ws_bytes >= wri_precond_workspace_bytes()
- *                (about 9 complex vectors per system plus 4/7 of one for the
+ *                (9 or 10 complex vectors per system plus 4/7 of one for the
  *                coarse levels)
  *   res[k].relres is sqrt(||S^H r||^2 / ||S^H b||^2), res[k].alpha the CGLS
  *   unknown and res[k].alpha_ls = (A u)[src] in float64 (ESTIMATE).

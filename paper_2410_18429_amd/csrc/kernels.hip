@@ -29,6 +29,7 @@
 #include "wri_impl.hpp"
 #include "stencil.hpp"
 #include "wave.hpp"
+#include "window.hpp"
 
 #include <algorithm>
 #include <cfloat>
@@ -93,20 +94,6 @@ __device__ __forceinline__ void block_map(const GroupDesc& d, int local, int* rl
     *tile = w / bt;
     *rl = full * bsz + (w - *tile * bt);
   }
-}
-
-__device__ __forceinline__ int xcd_remap(int b, int nb, int q) {
-  // Blocks go round-robin to the XCDs (b % 8).  The logical sequence of
-  // (group, system, tile) is cut into chunks of q consecutive tiles, dealt to the
-  // XCDs round-robin as well: the tiles of a chunk are spatial neighbours on
-  // one XCD (halo re-reads hit its L2), and every XCD holds a share of every
-  // system, so no XCD idles while others still work when some systems of the
-  // batch have converged.  Blocks past the last complete round keep their index.
-  const int xcd = b % kXCD, local = b / kXCD;
-  const int full = nb / (kXCD * q) * (kXCD * q);
-  if (b >= full) return b;
-  const int round = local / q, off = local - round * q;
-  return (round * kXCD + xcd) * q + off;
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -793,27 +780,6 @@ k_adj(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const double*
 // located with a per-column bit mask of the slab's planes, so the per-plane
 // test touches no memory.
 // ---------------------------------------------------------------------------
-
-typedef __amdgpu_buffer_rsrc_t BufRes;
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-constexpr unsigned kOOB = 0x80000000u;   // beyond any resource (records < 2^31)
-constexpr int kBufFlags = 0x00020000;    // raw 32-bit buffer, gfx9 family
-constexpr int kStoreNT = 2;              // non-temporal store
-
-// Resource over elements [first, first + count) of v (elem bytes each).
-__device__ __forceinline__ BufRes mkbuf(const void* v, int64_t first, int64_t count, int elem) {
-  const char* b = static_cast<const char*>(v) + first * elem;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(b), (short)0, (int)(count * elem), kBufFlags);
-}
-__device__ __forceinline__ float2 bld2(BufRes r, unsigned off) {
-  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-}
-__device__ __forceinline__ float bld1(BufRes r, unsigned off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
-__device__ __forceinline__ void bst2(BufRes r, unsigned off, float2 v) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, kStoreNT);
-}
 
 // Receivers of a thread's RY columns inside the slab [z0, z1): bit (z - z0) of
 // mask[j] is set where a receiver sits (at most one per cell, duplicates are
@@ -1793,13 +1759,6 @@ struct SlotSum {
   }
 };
 
-// Stores of the window march go through L2 (system scope: sc0 and sc1).  Its
-// outputs fit the L2s (4 MB per XCD), where ordinary stores would stay dirty
-// until the end of the launch and be written back then, after the last
-// workgroup: 8 systems of 64^3 took 42.8 us per iteration with ordinary or
-// non-temporal stores and 37.6 us with these.
-constexpr int kStoreThrough = 17;
-
 // The group of a block, from the launch arguments (up to kWinGroups groups; a
 // load from the device table would be one more memory latency in every launch).
 __device__ __forceinline__ GroupDesc win_group(const WinGroups& G, int logical) {
@@ -1816,133 +1775,55 @@ __device__ __forceinline__ GroupDesc win_group(const WinGroups& G, int logical) 
   return d;
 }
 
-// Loads above this point are issued before anything below it: without it the
-// compiler moves them down to their uses (behind the scalars and the stop
-// test), one latency after the other.  It waits for nothing.
-__device__ __forceinline__ void issue_point() { asm volatile("" ::: "memory"); }
+// Receiver cell tid of the system's list (-1 past its end).
+__device__ __forceinline__ int first_receiver(const SysDev& S) {
+  return (int)threadIdx.x < S.n_rec ? gptr(S.rec)[threadIdx.x] : -1;
+}
 
+// Receivers of the tile: recq[] takes the receiver index of each own cell (-1:
+// none; a receiver cell occurs once in a system's list).  Returns whether the
+// tile holds any; only then is recq written, and the caller's next barrier
+// publishes it.  rec0: first_receiver().
 template <int W, int CX, int TZ>
-struct Win {
-  static constexpr int NT = 64 * W;
-  static constexpr int B = NT * CX;   // own cells per plane
-  int nx, ny, nz, plane, c0, z0, wl, zlo, zhi;
-  int cell[CX];                       // linear cell in the plane (may lie past its end)
-  bool in[CX];
-  unsigned obit[CX];                  // out-of-range bit of cells past the end of the plane
+__device__ __forceinline__ bool find_receivers(const Win<W, CX, TZ>& Q, const SysDev& S, int rec0, int* recq) {
+  constexpr int NT = Win<W, CX, TZ>::NT, B = Win<W, CX, TZ>::B;
+  const GLOBAL int* rec = gptr(S.rec);
+  const int first = Q.z0 * Q.plane, span = (min(Q.z0 + TZ, Q.nz) - Q.z0) * Q.plane;
+  auto slot = [&](int q) -> int {   // own-cell slot of receiver q, or -1
+    const int d = (q == (int)threadIdx.x ? rec0 : rec[q]) - first;
+    if (d < 0 || d >= span) return -1;
+    int z = 0;
+#pragma unroll
+    for (int i = 1; i < TZ; ++i) z += d >= i * Q.plane ? 1 : 0;
+    const int o = d - z * Q.plane - Q.c0;
+    return o >= 0 && o < B ? z * B + o : -1;
+  };
+  bool any = false;
+  for (int q = threadIdx.x; q < S.n_rec; q += NT) any = any || slot(q) >= 0;
+  if (!__syncthreads_or(any)) return false;
+#pragma unroll
+  for (int i = 0; i < CX * TZ; ++i) recq[i * NT + (int)threadIdx.x] = -1;
+  __syncthreads();
+  for (int q = threadIdx.x; q < S.n_rec; q += NT) {
+    const int o = slot(q);
+    if (o >= 0) recq[o] = q;
+  }
+  return true;
+}
 
-  __device__ __forceinline__ void setup(int nx_, int ny_, int nz_, int tile, int tiles_x) {
-    nx = nx_; ny = ny_; nz = nz_;
-    plane = nx * ny;
-    const int tz = tile / tiles_x;
-    c0 = (tile - tz * tiles_x) * B;
-    z0 = tz * TZ;
-    zlo = max(z0 - 1, 0);
-    zhi = min(z0 + TZ + 1, nz);
-    wl = B + 2 * nx;
+// Whether the tile's planes and cells hold the source, and the thread's own cell
+// that does, as j * TZ + i (-1: none).
+template <int W, int CX, int TZ>
+__device__ __forceinline__ bool source_tile(const Win<W, CX, TZ>& Q, const SysDev& S, int* ji) {
+  *ji = -1;
+  if (S.mode != 1) return false;
+  const int sz = S.src / Q.plane, sc = S.src - sz * Q.plane;
+  if (sz < Q.z0 || sz >= Q.z0 + TZ || sc < Q.c0 || sc >= Q.c0 + Win<W, CX, TZ>::B) return false;
 #pragma unroll
-    for (int j = 0; j < CX; ++j) {
-      cell[j] = c0 + j * NT + (int)threadIdx.x;
-      in[j] = cell[j] < plane;
-      obit[j] = in[j] ? 0u : kOOB;
-    }
-  }
-  // Buffer accesses: plane i (z0 - 1 + i, i = 0 .. TZ + 1) of a stencil input and
-  // plane i (z0 + i, i = 0 .. TZ - 1) of a vector of own cells.  The plane is a
-  // scalar offset; a plane outside the grid gets a resource without records and
-  // a cell outside it the out-of-range bit, so reads there give zero and stores
-  // are dropped.
-  __device__ __forceinline__ BufRes in_res(const void* v, int i, int elem) const {
-    const int z = z0 - 1 + i;
-    const bool ok = z >= 0 && z < nz;
-    return __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(static_cast<const char*>(v) + (int64_t)zlo * plane * elem), (short)0,
-        ok ? (zhi - zlo) * plane * elem : 0, kBufFlags);
-  }
-  __device__ __forceinline__ unsigned in_off(int i, int elem) const {
-    const int z = min(max(z0 - 1 + i, zlo), zhi - 1);
-    return (unsigned)((z - zlo) * plane * elem);
-  }
-  __device__ __forceinline__ float2 load2(const void* v, int i, unsigned voff) const {
-    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(in_res(v, i, 8), voff, in_off(i, 8), 0));
-  }
-  __device__ __forceinline__ float load1(const void* v, int i, unsigned voff) const {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(in_res(v, i, 4), voff, in_off(i, 4), 0));
-  }
-  __device__ __forceinline__ void store2(void* v, int i, unsigned voff, float2 x) const {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), in_res(v, i, 8), voff, in_off(i, 8), kStoreThrough);
-  }
-  __device__ __forceinline__ void store2nt(void* v, int i, unsigned voff, float2 x) const {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), in_res(v, i, 8), voff, in_off(i, 8), kStoreNT);
-  }
-  __device__ __forceinline__ unsigned own2(int j) const { return (unsigned)(cell[j] * 8) | obit[j]; }
-  __device__ __forceinline__ unsigned own1(int j) const { return (unsigned)(cell[j] * 4) | obit[j]; }
-  __device__ __forceinline__ int first_receiver(const SysDev& S) const {
-    return (int)threadIdx.x < S.n_rec ? gptr(S.rec)[threadIdx.x] : -1;
-  }
-  __device__ __forceinline__ bool live(int j, int i) const { return in[j] && z0 + i < nz; }
-  // halo cell h (0 .. 2 nx - 1): byte offset in a plane and window index
-  __device__ __forceinline__ unsigned halo_off(int h) const {
-    const int c = h < nx ? c0 - nx + h : c0 + B + (h - nx);
-    return (unsigned)(c * 8) | ((c >= 0 && c < plane) ? 0u : kOOB);
-  }
-  __device__ __forceinline__ int halo_slot(int h) const { return h < nx ? h : B + h; }
-
-  // Row of a cell of the tile: the offset from the first cell's row start is
-  // below B + nx, where the float quotient (with half a cell's margin) is exact.
-  __device__ __forceinline__ void row_of(int c, int* x, int* y) const {
-    const int y0 = c0 / nx, d = c - y0 * nx;
-    const int r = (int)(((float)d + 0.5f) * (1.0f / (float)nx));
-    *y = y0 + r;
-    *x = d - r * nx;
-  }
-  // Receivers of the tile: recq[] takes the receiver index of each own cell (-1:
-  // none; a receiver cell occurs once in a system's list).  Returns whether the
-  // tile holds any; only then is recq written, and the caller's next barrier
-  // publishes it.
-  // rec0: the receiver cell tid of the list, loaded ahead (-1 past its end).
-  __device__ __forceinline__ bool find_receivers(const SysDev& S, int rec0, int* recq) const {
-    const GLOBAL int* rec = gptr(S.rec);
-    const int first = z0 * plane, span = (min(z0 + TZ, nz) - z0) * plane;
-    auto slot = [&](int q) -> int {   // own-cell slot of receiver q, or -1
-      const int d = (q == (int)threadIdx.x ? rec0 : rec[q]) - first;
-      if (d < 0 || d >= span) return -1;
-      int z = 0;
-#pragma unroll
-      for (int i = 1; i < TZ; ++i) z += d >= i * plane ? 1 : 0;
-      const int o = d - z * plane - c0;
-      return o >= 0 && o < B ? z * B + o : -1;
-    };
-    bool any = false;
-    for (int q = threadIdx.x; q < S.n_rec; q += NT) any = any || slot(q) >= 0;
-    if (!__syncthreads_or(any)) return false;
-#pragma unroll
-    for (int i = 0; i < CX * TZ; ++i) recq[i * NT + (int)threadIdx.x] = -1;
-    __syncthreads();
-    for (int q = threadIdx.x; q < S.n_rec; q += NT) {
-      const int o = slot(q);
-      if (o >= 0) recq[o] = q;
-    }
-    return true;
-  }
-  // whether the tile's planes and cells hold the source
-  __device__ __forceinline__ bool src_plane(const SysDev& S) const {
-    const int sz = S.src / plane, sc = S.src - sz * plane;
-    return sz >= z0 && sz < z0 + TZ && sc >= c0 && sc < c0 + B;
-  }
-  // the own cell that holds the source, as j * TZ + i; -1: none
-  __device__ __forceinline__ int source(const SysDev& S) const {
-    int ji = -1;
-    if (S.mode == 1) {
-      const int sz = S.src / plane, sc = S.src - sz * plane;
-      if (sz >= z0 && sz < z0 + TZ) {
-#pragma unroll
-        for (int j = 0; j < CX; ++j)
-          if (cell[j] == sc) ji = j * TZ + (sz - z0);
-      }
-    }
-    return ji;
-  }
-};
+  for (int j = 0; j < CX; ++j)
+    if (Q.cell[j] == sc) *ji = j * TZ + (sz - Q.z0);
+  return true;
+}
 
 template <int W, int CX, int TZ, int XS>
 __global__ void __launch_bounds__(64 * W)
@@ -1976,7 +1857,7 @@ k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
   float2* tout = S.t;
   // every load of the tile, before the scalars they are combined with
   const SlotSum slots(part_s + S.slot_base, ntiles);
-  const int rec0 = Q.first_receiver(S);
+  const int rec0 = first_receiver(S);
   float2 rs[CX][TZ + 2], rp[CX][TZ + 2], rx[CX][TZ], rq[CX][TZ];
   float mm[CX][TZ];
 #pragma unroll
@@ -2004,7 +1885,7 @@ k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
     hp[i] = Q.load2(po, i + 1, ho);
   }
   issue_point();
-  const bool has_rec = S.n_rec > 0 && Q.find_receivers(S, rec0, recq);
+  const bool has_rec = S.n_rec > 0 && find_receivers(Q, S, rec0, recq);
 
   const double gk = slots.sum(part_s + S.slot_base, ntiles);
   const bool warm = T->warm != 0;
@@ -2024,8 +1905,8 @@ k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
     if (k == 0 && !warm) T->gamma0 = gk;
     T->iterB = k;
   }
-  const int srcji = Q.source(S);
-  const bool src_tile = S.mode == 1 && Q.src_plane(S);   // uniform: most tiles skip the source's cell
+  int srcji;
+  const bool src_tile = source_tile(Q, S, &srcji);   // uniform: most tiles skip the source's cell
 
   if (stop || (!XS && xstep)) {
     if (xstep) {
@@ -2164,7 +2045,7 @@ k_adj_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
   const unsigned tbit = setup ? kOOB : 0u;
 
   const SlotSum slots(part_d + S.slot_base, setup ? 0 : ntiles);
-  const int rec0 = Q.first_receiver(S);
+  const int rec0 = first_receiver(S);
   float2 rr[CX][TZ + 2], rt[CX][TZ + 2];
   float mm[CX][TZ];
 #pragma unroll
@@ -2186,7 +2067,7 @@ k_adj_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
     ht[i] = Q.load2(tv, i + 1, ho | tbit);
   }
   issue_point();
-  const bool has_rec = S.n_rec > 0 && Q.find_receivers(S, rec0, recq);
+  const bool has_rec = S.n_rec > 0 && find_receivers(Q, S, rec0, recq);
 
   double a = 0.0;
   if (!setup) {
@@ -2213,8 +2094,8 @@ k_adj_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
     a = gk / dk;
     if (tile == 0 && tid == 0) T->a[k & 1] = a;
   }
-  const int srcji = Q.source(S);
-  const bool src_tile = S.mode == 1 && Q.src_plane(S);   // uniform: most tiles skip the source's cell
+  int srcji;
+  const bool src_tile = source_tile(Q, S, &srcji);   // uniform: most tiles skip the source's cell
 
   float2 rv[CX][TZ + 2];
 #pragma unroll

@@ -9,8 +9,8 @@
 // ||S^H r|| <= rtol ||S^H b||.
 //
 // Per iteration, over all systems of a grid in lockstep (finished systems skip
-// inside the kernels; step scalars live in device memory; chunks of iterations
-// replay from a hipGraph between host checks of the statuses):
+// inside the kernels; step scalars live in device memory; the host checks the
+// statuses between chunks of iterations):
 //   p = z + beta p;  q = M p (V-cycle);  t = S q;  a = gamma / ||t||^2;
 //   x += a q;  r -= a t;  s = S^H r (stopping test);  z = M^H s (V-cycle on
 //   conj(A_beta), M being complex symmetric);  beta = ||z||^2 / gamma.
@@ -23,6 +23,7 @@
 #include "../../include/wri.h"
 #include "wri_impl.hpp"
 #include "stencil.hpp"
+#include "window.hpp"
 
 #include <algorithm>
 #include <cfloat>
@@ -62,11 +63,13 @@ struct PcLevel {
 };
 
 struct PcSys {
-  float2 *x, *r, *p, *q, *t, *s, *z, *r2, *t2;
+  float2 *x, *r[2], *p[2], *q, *t, *s, *z, *r2, *t2;   // r, p: current vector by iteration parity (tiled passes)
   const float2* d;
   const int* rec;
   const float* m;
-  int n, nx, ny, nz, nb, nr, est, max_iter, nlev, src, pad_[2];
+  int n, nx, ny, nz, nb, nr, est, max_iter, nlev, src;
+  int tiled;    // 1: the passes by window tiles; 0: one thread per cell, r and p updated in place
+  int nparts;   // partial sums of a level-0 pass
   double lam, rtol2, omega, omega2, h2inv, sp_scale, inv_nb;
   double2 alpha;  // KNOWN-mode weight
   PcLevel lev[kMaxLev];
@@ -91,13 +94,17 @@ __device__ __forceinline__ double bsum(double v, double* red) {  // block total,
   return r;
 }
 
+// residual after `iters` iterations, and the direction p that iteration's forward cycle reads
+__device__ __forceinline__ float2* pc_r(const PcSys& S, int iters) { return S.r[S.tiled & iters & 1]; }
+__device__ __forceinline__ float2* pc_p(const PcSys& S, int iters) { return S.p[S.tiled & (iters + 1) & 1]; }
+
 __device__ __forceinline__ double nrm(float2 v) { return (double)v.x * v.x + (double)v.y * v.y; }
 __device__ __forceinline__ float2 fd(double a, double b) { return make_float2((float)a, (float)b); }
 
-// partials of one system's level-0 pass: kParts values, summed in index order
-__device__ double sum_parts(const double* __restrict__ part, double* red) {
+// partials of one system's level-0 pass, summed in one fixed order
+__device__ double sum_parts(const double* __restrict__ part, int n, double* red) {
   double v = 0.0;
-  for (int i = threadIdx.x; i < kParts; i += kThr) v += part[i];
+  for (int i = threadIdx.x; i < n; i += kThr) v += part[i];
   return bsum(v, red);
 }
 
@@ -113,8 +120,8 @@ __global__ void __launch_bounds__(kThr) k_pc_zero(const PcSys* __restrict__ sy, 
   const float2 z = make_float2(0.f, 0.f);
   for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
     S.x[c] = z;
-    S.r[c] = z;
-    S.p[c] = z;
+    S.r[0][c] = z;
+    S.p[0][c] = z;
   }
 }
 
@@ -127,7 +134,7 @@ __global__ void __launch_bounds__(kThr) k_pc_init(const PcSys* __restrict__ sy, 
     S.r2[q] = fd(S.lam * dv.x, S.lam * dv.y);
   }
   if (threadIdx.x == 0) {
-    if (!S.est) S.r[S.src] = fd(S.alpha.x, S.alpha.y);
+    if (!S.est) S.r[0][S.src] = fd(S.alpha.x, S.alpha.y);
     PcState& T = stv[k];
     T = PcState{};
     T.status = kActive;
@@ -142,8 +149,8 @@ __global__ void __launch_bounds__(kThr) k_pc_pupd(const PcSys* __restrict__ sy, 
   const PcSys& S = sy[k];
   const double be = stv[k].beta;
   for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
-    const float2 zv = S.z[c], pv = S.p[c];
-    S.p[c] = fd((double)zv.x + be * pv.x, (double)zv.y + be * pv.y);
+    const float2 zv = S.z[c], pv = S.p[0][c];
+    S.p[0][c] = fd((double)zv.x + be * pv.x, (double)zv.y + be * pv.y);
   }
 }
 
@@ -166,7 +173,7 @@ __device__ __forceinline__ double2 apply_cell(const PcSys& S, const float2* __re
 
 // t = A q - p_alpha e_src (ESTIMATE; q_alpha = p_alpha); partials of ||t||^2
 __global__ void __launch_bounds__(kThr) k_pc_fwd(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                 double* __restrict__ part, int g0) {
+                                                 double* __restrict__ part, int stride, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
@@ -181,13 +188,13 @@ __global__ void __launch_bounds__(kThr) k_pc_fwd(const PcSys* __restrict__ sy, c
     acc += nrm(t);
   }
   const double tot = bsum(acc, red);
-  if (threadIdx.x == 0) part[(size_t)k * kParts + blockIdx.x] = tot;
+  if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
 }
 
 // receiver rows t2 = lam q[rec]; delta, a; x_alpha += a p_alpha; r2 -= a t2
 // (one block per system)
 __global__ void __launch_bounds__(kThr) k_pc_step(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                  const double* __restrict__ part, int g0) {
+                                                  const double* __restrict__ part, int stride, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   if (!active(stv, k)) return;
@@ -200,7 +207,7 @@ __global__ void __launch_bounds__(kThr) k_pc_step(const PcSys* __restrict__ sy, 
     S.t2[q] = t2;
     acc += nrm(t2);
   }
-  const double delta = sum_parts(part + (size_t)k * kParts, red) + bsum(acc, red);
+  const double delta = sum_parts(part + (size_t)k * stride, S.nparts, red) + bsum(acc, red);
   const bool bad = !(delta > 0.0) || !(delta <= DBL_MAX) || !(T.gamma <= DBL_MAX);
   const double a = bad ? 0.0 : T.gamma / delta;
   for (int q = threadIdx.x; q < S.nr; q += kThr) {
@@ -226,33 +233,33 @@ __global__ void __launch_bounds__(kThr) k_pc_rupd(const PcSys* __restrict__ sy, 
   const PcSys& S = sy[k];
   const double a = stv[k].a;
   for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
-    const float2 r = S.r[c], t = S.t[c], x = S.x[c], q = S.q[c];
-    S.r[c] = fd((double)r.x - a * t.x, (double)r.y - a * t.y);
+    const float2 r = S.r[0][c], t = S.t[c], x = S.x[c], q = S.q[c];
+    S.r[0][c] = fd((double)r.x - a * t.x, (double)r.y - a * t.y);
     S.x[c] = fd((double)x.x + a * q.x, (double)x.y + a * q.y);
   }
 }
 
 // s = A^H r (the receiver and source-row terms are added per system); partials of ||s||^2
 __global__ void __launch_bounds__(kThr) k_pc_adj(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                 double* __restrict__ part, int g0) {
+                                                 double* __restrict__ part, int stride, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   double acc = 0.0;
   for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
-    const float2 s = round2(apply_cell(S, S.r, c, true));
+    const float2 s = round2(apply_cell(S, S.r[0], c, true));
     S.s[c] = s;
     acc += nrm(s);
   }
   const double tot = bsum(acc, red);
-  if (threadIdx.x == 0) part[(size_t)k * kParts + blockIdx.x] = tot;
+  if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
 }
 
 // s += lam P^H r2 (distinct receiver cells), s_alpha = -r1[src] (ESTIMATE);
 // ||s||^2, the stopping test (one block per system).  setup = 1: ||s_0||^2.
 __global__ void __launch_bounds__(kThr) k_pc_check(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                   const double* __restrict__ part, int g0, int setup) {
+                                                   const double* __restrict__ part, int stride, int g0, int setup) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   if (!active(stv, k)) return;
@@ -266,11 +273,11 @@ __global__ void __launch_bounds__(kThr) k_pc_check(const PcSys* __restrict__ sy,
     S.s[c] = s1;
     corr += nrm(s1) - nrm(s0);
   }
-  const double ss_u = sum_parts(part + (size_t)k * kParts, red) + bsum(corr, red);
+  const double ss_u = sum_parts(part + (size_t)k * stride, S.nparts, red) + bsum(corr, red);
   if (threadIdx.x == 0) {
     double2 sa = make_double2(0.0, 0.0);
     if (S.est) {
-      const float2 r1 = S.r[S.src];
+      const float2 r1 = pc_r(S, setup ? 0 : T.iters + 1)[S.src];
       sa = make_double2(-(double)r1.x, -(double)r1.y);
     }
     const double ss = ss_u + sa.x * sa.x + sa.y * sa.y;
@@ -300,12 +307,13 @@ __global__ void __launch_bounds__(kThr) k_pc_check(const PcSys* __restrict__ sy,
 // gamma' = ||z||^2, beta = gamma'/gamma, p_alpha = z_alpha + beta p_alpha
 // (one block per system).  setup = 1: gamma = ||z_0||^2, beta = 0.
 __global__ void __launch_bounds__(kThr) k_pc_beta(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                  const double* __restrict__ part, int g0, int setup) {
+                                                  const double* __restrict__ part, int stride, int g0, int setup) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   if (!active(stv, k)) return;
+  const PcSys& S = sy[k];
   PcState& T = stv[k];
-  const double zz = sum_parts(part + (size_t)k * kParts, red) + (T.za.x * T.za.x + T.za.y * T.za.y);
+  const double zz = sum_parts(part + (size_t)k * stride, S.nparts, red) + (T.za.x * T.za.x + T.za.y * T.za.y);
   if (threadIdx.x == 0) {
     const double be = setup ? 0.0 : zz / T.gamma;
     T.beta = be;
@@ -341,8 +349,8 @@ __device__ __forceinline__ void coords(const PcLevel& L, int c, int& x, int& y, 
   x = rem - y * L.nx;
 }
 
-__device__ __forceinline__ const float2* level_in(const PcSys& S, int l, int which) {
-  return l > 0 ? S.lev[l].f : (which ? S.s : S.p);
+__device__ __forceinline__ const float2* level_in(const PcSys& S, int iters, int l, int which) {
+  return l > 0 ? S.lev[l].f : (which ? S.s : pc_p(S, iters));
 }
 
 // res = f - A_beta (w D^-1 f) on level l (w D^-1 f recomputed at each neighbour)
@@ -353,7 +361,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vdown(const PcSys* __restrict__ sy,
   const PcSys& S = sy[k];
   if (l >= S.nlev - 1) return;
   const PcLevel& L = S.lev[l];
-  const float2* __restrict__ f = level_in(S, l, which);
+  const float2* __restrict__ f = level_in(S, stv[k].iters, l, which);
   for (int c = blockIdx.x * kThr + threadIdx.x; c < L.n; c += gridDim.x * kThr) {
     int x, y, z;
     coords(L, c, x, y, z);
@@ -419,7 +427,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vcoarse(const PcSys* __restrict__ s
   const PcSys& S = sy[k];
   const int l = S.nlev - 1;
   const PcLevel& L = S.lev[l];
-  const float2* __restrict__ f = level_in(S, l, which);
+  const float2* __restrict__ f = level_in(S, stv[k].iters, l, which);
   const float2* __restrict__ in = (sweep & 1) ? L.o : L.y;
   float2* __restrict__ out = (sweep & 1) ? L.y : L.o;
   for (int c = blockIdx.x * kThr + threadIdx.x; c < L.n; c += gridDim.x * kThr) {
@@ -464,7 +472,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vprolong(const PcSys* __restrict__ 
   const PcLevel& F = S.lev[l];
   const PcLevel& C = S.lev[l + 1];
   const float2* __restrict__ e = coarse_out(S, l + 1);
-  const float2* __restrict__ f = level_in(S, l, which);
+  const float2* __restrict__ f = level_in(S, stv[k].iters, l, which);
   for (int c = blockIdx.x * kThr + threadIdx.x; c < F.n; c += gridDim.x * kThr) {
     int x, y, z;
     coords(F, c, x, y, z);
@@ -504,14 +512,14 @@ __global__ void __launch_bounds__(kThr) k_pc_vprolong(const PcSys* __restrict__ 
 // o_l = y + w D^-1 (f - A_beta y); level 0 writes `out0` (q: which = 0, z:
 // which = 1) and, for z, the partials of ||z||^2
 __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                     double* __restrict__ part, int g0, int l, int which, int conj) {
+                                                     double* __restrict__ part, int stride, int g0, int l, int which, int conj) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   if (l >= S.nlev - 1) return;
   const PcLevel& L = S.lev[l];
-  const float2* __restrict__ f = level_in(S, l, which);
+  const float2* __restrict__ f = level_in(S, stv[k].iters, l, which);
   const float2* __restrict__ in = L.y;
   float2* __restrict__ out = l > 0 ? L.o : (which ? S.z : S.q);
   double acc = 0.0;
@@ -537,7 +545,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ s
   }
   if (l == 0 && which && part != nullptr) {
     const double tot = bsum(acc, red);
-    if (threadIdx.x == 0) part[(size_t)k * kParts + blockIdx.x] = tot;
+    if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
   }
 }
 
@@ -545,7 +553,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ s
 // coarsen): kCoarseSweeps Jacobi steps on level 0 itself; the last result is
 // copied to out0 with the partials of ||out0||^2 when which = 1.
 __global__ void __launch_bounds__(kThr) k_pc_vsingle_out(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                         double* __restrict__ part, int g0, int which) {
+                                                         double* __restrict__ part, int stride, int g0, int which) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
@@ -561,7 +569,636 @@ __global__ void __launch_bounds__(kThr) k_pc_vsingle_out(const PcSys* __restrict
   }
   if (which && part != nullptr) {
     const double tot = bsum(acc, red);
-    if (threadIdx.x == 0) part[(size_t)k * kParts + blockIdx.x] = tot;
+    if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// the same passes by window tiles
+//
+// One thread per cell with two divisions and up to 27 loads from the caches left
+// an iteration of 39 launches of 3 to 10 us on the medium workload.  Here a
+// workgroup owns consecutive cells of the x-y plane and kPcZ planes (window.hpp):
+// all its loads are issued at once and the neighbours come from LDS.  The p update
+// is part of the first pass of the forward cycle, prolongation and the step after
+// it are one pass (the prolonged iterate is formed on the tile and its halo and
+// never stored), the r and x updates are part of s = A^H r, and the levels of up to
+// kPcLdsCells cells are one workgroup per system with every array in LDS: 19
+// launches.  Every stored value is rounded where it was, so iterates differ only
+// through the order of the float64 sums; r and p are written to their other
+// buffer because neighbouring tiles still read the old one.
+//
+// Per iteration (eager launches): 8 systems of 64^3 401 us before and 201 now,
+// 48 of 128^3 11.7 ms and 5.14, 2 of 24x20x18 178 us and 79.
+// ---------------------------------------------------------------------------
+
+constexpr int kPcW = 4, kPcZ = 4;
+constexpr int kPcMaxRow = 512;         // widest row of the tiled passes (LDS: 96 KB for the residual pass)
+constexpr int kPcLdsCells = 4096;      // largest level of the one-workgroup cycle
+constexpr int kPcLdsThr = 1024;
+
+// (system, tile) of a block: neighbouring tiles of a system on one XCD.  The same tile
+// of 2 or 4 systems on consecutive blocks, so that they share w D^-1, m and b in L2,
+// measured 5.19 and 5.24 ms an iteration against 5.14 (48 systems of 128^3).
+__device__ __forceinline__ void pc_block(int tiles, int* sys, int* tile) {
+  const int logical = xcd_remap(blockIdx.x, gridDim.x, max(16, tiles / 2));
+  *sys = logical / tiles;
+  *tile = logical - *sys * tiles;
+}
+
+// y = w D^-1 f in float64
+__device__ __forceinline__ double2 jac_w(float2 w, int conj, float2 v) {
+  const double wr = w.x, wi = conj ? -(double)w.y : (double)w.y;
+  return make_double2(wr * v.x - wi * v.y, wr * v.y + wi * v.x);
+}
+__device__ __forceinline__ double2 diag_mb(const PcSys& S, double h2inv, float m_, float b_, int conj) {
+  const double m = m_, b = b_;
+  const double im = -kBeta * S.omega2 * m - S.omega * b;
+  return make_double2(-6.0 * h2inv + S.omega2 * m, conj ? -im : im);
+}
+
+// res = f - A_beta (w D^-1 f) on level l; PUPD: level 0 of the forward cycle, with
+// f = p = z + beta p formed and stored here
+template <int CX, bool PUPD>
+__global__ void __launch_bounds__(64 * kPcW)
+k_pw_down(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0, int l, int which, int conj,
+          int tiles_x, int tiles) {
+  using Tile = Win<kPcW, CX, kPcZ>;
+  constexpr int NT = Tile::NT;
+  extern __shared__ double2 pw_y[];   // [kPcZ][B + 2 nx]: w D^-1 f
+  const int tid = threadIdx.x;
+  int sys, tile;
+  pc_block(tiles, &sys, &tile);
+  const int k = g0 + sys;
+  const PcState& T = stv[k];
+  if (T.status != kActive) return;
+  const PcSys& S = sy[k];
+  const PcLevel& L = S.lev[l];
+  Tile Q;
+  Q.setup(L.nx, L.ny, L.nz, tile, tiles_x);
+  const int nx = Q.nx, wl = Q.wl;
+  const float2* f = PUPD ? S.z : level_in(S, T.iters, l, which);
+  const float2* po = S.p[T.iters & 1];
+  float2* pn = S.p[(T.iters + 1) & 1];
+  float2 fv[CX][kPcZ + 2], wv[CX][kPcZ + 2], pv[CX][kPcZ + 2];
+  float mm[CX][kPcZ], bb[CX][kPcZ];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kPcZ + 2; ++i) {
+      fv[j][i] = Q.load2(f, i, Q.own2(j));
+      wv[j][i] = Q.load2(L.wdinv, i, Q.own2(j));
+      if constexpr (PUPD) pv[j][i] = Q.load2(po, i, Q.own2(j));
+    }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      mm[j][i] = Q.load1(L.m, i + 1, Q.own1(j));
+      bb[j][i] = Q.load1(L.b, i + 1, Q.own1(j));
+    }
+  issue_point();
+  const double be = PUPD ? T.beta : 0.0;
+  auto dir = [&](float2 z, float2 p) { return fd((double)z.x + be * p.x, (double)z.y + be * p.y); };
+  for (int h = tid; h < 2 * nx; h += NT) {
+    const unsigned o = Q.halo_off(h);
+    const int sl = Q.halo_slot(h);
+    float2 hf[kPcZ], hw[kPcZ], hp[kPcZ];
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      hf[i] = Q.load2(f, i + 1, o);
+      hw[i] = Q.load2(L.wdinv, i + 1, o);
+      if constexpr (PUPD) hp[i] = Q.load2(po, i + 1, o);
+    }
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      if constexpr (PUPD) hf[i] = dir(hf[i], hp[i]);
+      pw_y[i * wl + sl] = jac_w(hw[i], conj, hf[i]);
+    }
+  }
+  double2 y[CX][kPcZ + 2];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kPcZ + 2; ++i) {
+      if constexpr (PUPD) fv[j][i] = dir(fv[j][i], pv[j][i]);
+      y[j][i] = jac_w(wv[j][i], conj, fv[j][i]);
+      if (i >= 1 && i <= kPcZ) pw_y[(i - 1) * wl + nx + j * NT + tid] = y[j][i];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < CX; ++j) {
+    int cx, cy;
+    Q.row_of(Q.cell[j], &cx, &cy);
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      const double2* row = pw_y + i * wl + nx + j * NT + tid;
+      const double2 zero = make_double2(0.0, 0.0);
+      const double2 xm = cx > 0 ? row[-1] : zero, xp = cx < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const double2 yc = y[j][i + 1], zm = y[j][i], zp = y[j][i + 2];
+      const double sr = ((((xm.x + xp.x) + ym.x) + yp.x) + zm.x) + zp.x;
+      const double si = ((((xm.y + xp.y) + ym.y) + yp.y) + zm.y) + zp.y;
+      const double2 d = diag_mb(S, L.h2inv, mm[j][i], bb[j][i], conj);
+      const float2 fc = fv[j][i + 1];
+      const double ar = sr * L.h2inv + (d.x * yc.x - d.y * yc.y);
+      const double ai = si * L.h2inv + (d.x * yc.y + d.y * yc.x);
+      Q.store2(L.res, i + 1, Q.own2(j), fd((double)fc.x - ar, (double)fc.y - ai));
+      if constexpr (PUPD) Q.store2(pn, i + 1, Q.own2(j), fc);
+    }
+  }
+}
+
+// f_{l+1} = P^T res_l / 8: one coarse cell per thread.  A row of the 27 cells is one
+// 16-byte load of the first two (contiguous across lanes) and the next lane's
+// first; only the last lane and the end of a row load their third cell.  Weights are
+// powers of two and the values float32, so the float64 sums are exact in any order
+// unless the magnitudes span more than 2^26.
+__global__ void __launch_bounds__(kThr)
+k_pw_restrict(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0, int l, int tiles) {
+  int sys, tile;
+  pc_block(tiles, &sys, &tile);
+  const int k = g0 + sys;
+  if (!active(stv, k)) return;
+  const PcSys& S = sy[k];
+  const PcLevel& F = S.lev[l];
+  const PcLevel& C = S.lev[l + 1];
+  const int c = tile * kThr + threadIdx.x;
+  const bool live = c < C.n;
+  int cx, cy, cz;
+  coords(C, live ? c : C.n - 1, cx, cy, cz);
+  const int plane = F.nx * F.ny, o = 2 * cz * plane + 2 * cy * F.nx + 2 * cx;   // fine corner: 2i .. 2i + 2
+  const BufRes R = mkbuf(F.res, 0, F.n, 8);
+  // the next lane holds the next coarse cell of the row
+  const bool from_next = (threadIdx.x & 63) != 63 && cx + 1 < C.nx && c + 1 < C.n;
+  const bool third = 2 * cx + 2 < F.nx;
+  float4 v[9];
+  float2 w[9];
+#pragma unroll
+  for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy) {
+      const bool in = 2 * cy + dy < F.ny && 2 * cz + dz < F.nz;   // a coarse cell has two fine ones in x
+      const unsigned off = (unsigned)((o + dz * plane + dy * F.nx) * 8);
+      v[dz * 3 + dy] = bld4(R, in ? off : kOOB);
+      w[dz * 3 + dy] = bld2(R, in && third && !from_next ? off + 16 : kOOB);
+    }
+  double sr = 0.0, si = 0.0;
+#pragma unroll
+  for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy) {
+      const int i = dz * 3 + dy;
+      const float nx_ = __shfl_down(v[i].x, 1, 64), ny_ = __shfl_down(v[i].y, 1, 64);
+      const float tx = from_next ? nx_ : w[i].x, ty = from_next ? ny_ : w[i].y;
+      const double wt = (dz != 1 ? 0.5 : 1.0) * (dy != 1 ? 0.5 : 1.0);
+      sr += wt * ((double)v[i].z + 0.5 * ((double)v[i].x + (double)tx));
+      si += wt * ((double)v[i].w + 0.5 * ((double)v[i].y + (double)ty));
+    }
+  if (live) C.f[c] = fd(0.125 * sr, 0.125 * si);
+}
+
+// One column of P e on the coarse planes z0 / 2 - 1 + p, interpolated in x and y
+// (exact in float64, see the restriction).  Cells outside the coarse grid read zero.
+template <int NP>
+__device__ __forceinline__ void coarse_column(const float2* e, const PcLevel& C, bool ok, int x, int y, int z0,
+                                              double2 (&out)[NP]) {
+  const bool ox = x & 1, oy = y & 1;
+  const int x1 = x >> 1, x0 = ox ? x1 : x1 - 1;   // odd: one coarse cell; even: two
+  const int y1 = y >> 1, y0 = oy ? y1 : y1 - 1;
+  const double w = (ox ? 1.0 : 0.5) * (oy ? 1.0 : 0.5);
+  const bool bx0 = ok && x0 >= 0 && x0 < C.nx, bx1 = ok && !ox && x1 < C.nx;
+  const bool by0 = y0 >= 0 && y0 < C.ny, by1 = !oy && y1 < C.ny;
+  const int plane = C.nx * C.ny;
+  auto off = [&](bool in, int yy, int xx) { return in ? (unsigned)((yy * C.nx + xx) * 8) : kOOB; };
+  const unsigned o[4] = {off(by0 && bx0, y0, x0), off(by0 && bx1, y0, x1), off(by1 && bx0, y1, x0),
+                         off(by1 && bx1, y1, x1)};
+  float2 v[NP][4];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int z = z0 / 2 - 1 + p;
+    const bool bz = z >= 0 && z < C.nz;
+    const BufRes R = mkbuf(e, bz ? (int64_t)z * plane : 0, bz ? plane : 0, 8);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[p][i] = bld2(R, o[i]);
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+    out[p] = make_double2(w * (((double)v[p][0].x + (double)v[p][1].x) + ((double)v[p][2].x + (double)v[p][3].x)),
+                          w * (((double)v[p][0].y + (double)v[p][1].y) + ((double)v[p][2].y + (double)v[p][3].y)));
+}
+// P e on the fine plane z0 - 1 + i (z0 even) from the coarse planes z0 / 2 - 1 + p
+template <int NP>
+__device__ __forceinline__ double2 prolong_z(const double2 (&e)[NP], int i) {
+  const int p = i >> 1;   // odd planes (i even): one coarse plane; even planes: two
+  if ((i & 1) == 0) return e[p];
+  return make_double2(0.5 * (e[p].x + e[p + 1].x), 0.5 * (e[p].y + e[p + 1].y));
+}
+
+// o_l = y + w D^-1 (f - A_beta y) with y = w D^-1 f + P e_{l+1}; level 0 writes q
+// (which = 0) or z (which = 1, with the partials of ||z||^2)
+template <int CX>
+__global__ void __launch_bounds__(64 * kPcW)
+k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* __restrict__ part, int stride, int g0,
+        int l, int which, int conj, int tiles_x, int tiles) {
+  using Tile = Win<kPcW, CX, kPcZ>;
+  constexpr int NT = Tile::NT, NP = kPcZ / 2 + 2;
+  __shared__ double red[kPcW];
+  extern __shared__ float2 pw_f[];   // [kPcZ][B + 2 nx]: y
+  const int tid = threadIdx.x;
+  int sys, tile;
+  pc_block(tiles, &sys, &tile);
+  const int k = g0 + sys;
+  const PcState& T = stv[k];
+  if (T.status != kActive) return;
+  const PcSys& S = sy[k];
+  const PcLevel& L = S.lev[l];
+  const PcLevel& C = S.lev[l + 1];
+  Tile Q;
+  Q.setup(L.nx, L.ny, L.nz, tile, tiles_x);
+  const int nx = Q.nx, wl = Q.wl;
+  const float2* f = level_in(S, T.iters, l, which);
+  const float2* e = coarse_out(S, l + 1);
+  float2* out = l > 0 ? L.o : (which ? S.z : S.q);
+  float2 fv[CX][kPcZ + 2], wv[CX][kPcZ + 2];
+  float mm[CX][kPcZ], bb[CX][kPcZ];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kPcZ + 2; ++i) {
+      fv[j][i] = Q.load2(f, i, Q.own2(j));
+      wv[j][i] = Q.load2(L.wdinv, i, Q.own2(j));
+    }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      mm[j][i] = Q.load1(L.m, i + 1, Q.own1(j));
+      bb[j][i] = Q.load1(L.b, i + 1, Q.own1(j));
+    }
+  issue_point();
+  for (int h = tid; h < 2 * nx; h += NT) {
+    const unsigned o = Q.halo_off(h);
+    const int sl = Q.halo_slot(h);
+    const bool ok = (o & kOOB) == 0;
+    float2 hf[kPcZ], hw[kPcZ];
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      hf[i] = Q.load2(f, i + 1, o);
+      hw[i] = Q.load2(L.wdinv, i + 1, o);
+    }
+    int x, y;
+    Q.row_of((h < nx ? Q.c0 - nx + h : Q.c0 + Tile::B + (h - nx)) + nx, &x, &y);   // the row above: not negative
+    double2 ec[NP];
+    coarse_column(e, C, ok, x, y - 1, Q.z0, ec);
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      const double2 jv = jac_w(hw[i], conj, hf[i]), pe = prolong_z(ec, i + 1);
+      pw_f[i * wl + sl] = ok && Q.zin(i + 1) ? fd(jv.x + pe.x, jv.y + pe.y) : make_float2(0.f, 0.f);
+    }
+  }
+  float2 yv[CX][kPcZ + 2];
+  int cx[CX];
+#pragma unroll
+  for (int j = 0; j < CX; ++j) {
+    int cy;
+    Q.row_of(Q.cell[j], &cx[j], &cy);
+    double2 ec[NP];
+    coarse_column(e, C, Q.in[j], cx[j], cy, Q.z0, ec);
+#pragma unroll
+    for (int i = 0; i < kPcZ + 2; ++i) {
+      const double2 jv = jac_w(wv[j][i], conj, fv[j][i]), pe = prolong_z(ec, i);
+      yv[j][i] = Q.in[j] && Q.zin(i) ? fd(jv.x + pe.x, jv.y + pe.y) : make_float2(0.f, 0.f);
+      if (i >= 1 && i <= kPcZ) pw_f[(i - 1) * wl + nx + j * NT + tid] = yv[j][i];
+    }
+  }
+  __syncthreads();
+  double acc = 0.0;
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      const float2* row = pw_f + i * wl + nx + j * NT + tid;
+      const float2 zero = make_float2(0.f, 0.f);
+      const float2 xm = cx[j] > 0 ? row[-1] : zero, xp = cx[j] < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const float2 xc = yv[j][i + 1], zm = yv[j][i], zp = yv[j][i + 2], fc = fv[j][i + 1];
+      const double2 d = diag_mb(S, L.h2inv, mm[j][i], bb[j][i], conj);
+      const double sr = (((double)xm.x + xp.x) + ((double)ym.x + yp.x)) + ((double)zm.x + zp.x);
+      const double si = (((double)xm.y + xp.y) + ((double)ym.y + yp.y)) + ((double)zm.y + zp.y);
+      const double ar = sr * L.h2inv + (d.x * xc.x - d.y * xc.y);
+      const double ai = si * L.h2inv + (d.x * xc.y + d.y * xc.x);
+      const double2 corr = jac_w(wv[j][i + 1], conj, fd((double)fc.x - ar, (double)fc.y - ai));
+      const float2 o = fd((double)xc.x + corr.x, (double)xc.y + corr.y);
+      Q.store2(out, i + 1, Q.own2(j), o);
+      if (Q.live(j, i)) acc += nrm(o);
+    }
+  if (l == 0 && which) {
+    const double tot = bsum(acc, red);
+    if (tid == 0) part[(size_t)k * stride + tile] = tot;
+  }
+}
+
+// t = A q - p_alpha e_src; partials of ||t||^2 (ADJ = false), or the step on r and x
+// and s = A^H r with the partials of ||s||^2 (ADJ = true; setup = 1: s = A^H r_0)
+template <int CX, bool ADJ>
+__global__ void __launch_bounds__(64 * kPcW)
+k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* __restrict__ part, int stride,
+           int g0, int setup, int tiles_x, int tiles) {
+  using Tile = Win<kPcW, CX, kPcZ>;
+  constexpr int NT = Tile::NT;
+  __shared__ double red[kThr / 64];
+  extern __shared__ float2 pw_f[];   // [kPcZ][B + 2 nx]
+  const int tid = threadIdx.x;
+  int sys, tile;
+  pc_block(tiles, &sys, &tile);
+  const int k = g0 + sys;
+  const PcState& T = stv[k];
+  if (T.status != kActive) return;
+  const PcSys& S = sy[k];
+  Tile Q;
+  Q.setup(S.nx, S.ny, S.nz, tile, tiles_x);
+  const int nx = Q.nx, wl = Q.wl;
+  const float2* in = ADJ ? pc_r(S, setup ? 0 : T.iters) : S.q;
+  float2* rn = pc_r(S, T.iters + 1);
+  const unsigned tbit = setup ? kOOB : 0u;   // the set-up pass makes no step
+  float2 v[CX][kPcZ + 2], tv[CX][kPcZ + 2], xv[CX][kPcZ], qv[CX][kPcZ];
+  float mm[CX][kPcZ];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kPcZ + 2; ++i) {
+      v[j][i] = Q.load2(in, i, Q.own2(j));
+      if constexpr (ADJ) tv[j][i] = Q.load2(S.t, i, Q.own2(j) | tbit);
+    }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      mm[j][i] = Q.load1(S.m, i + 1, Q.own1(j));
+      if constexpr (ADJ) {
+        xv[j][i] = Q.load2(S.x, i + 1, Q.own2(j) | tbit);
+        qv[j][i] = Q.load2(S.q, i + 1, Q.own2(j) | tbit);
+      }
+    }
+  issue_point();
+  const double a = ADJ && !setup ? T.a : 0.0;
+  auto step = [&](float2 r, float2 t) { return setup ? r : fd((double)r.x - a * t.x, (double)r.y - a * t.y); };
+  for (int h = tid; h < 2 * nx; h += NT) {
+    const unsigned o = Q.halo_off(h);
+    const int sl = Q.halo_slot(h);
+    float2 hv[kPcZ], ht[kPcZ];
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      hv[i] = Q.load2(in, i + 1, o);
+      if constexpr (ADJ) ht[i] = Q.load2(S.t, i + 1, o | tbit);
+    }
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      if constexpr (ADJ) hv[i] = step(hv[i], ht[i]);
+      pw_f[i * wl + sl] = hv[i];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kPcZ + 2; ++i) {
+      if constexpr (ADJ) v[j][i] = step(v[j][i], tv[j][i]);
+      if (i >= 1 && i <= kPcZ) pw_f[(i - 1) * wl + nx + j * NT + tid] = v[j][i];
+    }
+  __syncthreads();
+  const bool src_tile = !ADJ && S.est;
+  const double2 pa = T.pa;
+  double acc = 0.0;
+#pragma unroll
+  for (int j = 0; j < CX; ++j) {
+    int cx, cy;
+    Q.row_of(Q.cell[j], &cx, &cy);
+    const double sxy = sponge_axis_d(cx, nx, S.nb, S.inv_nb) + sponge_axis_d(cy, Q.ny, S.nb, S.inv_nb);
+#pragma unroll
+    for (int i = 0; i < kPcZ; ++i) {
+      const float2* row = pw_f + i * wl + nx + j * NT + tid;
+      const float2 zero = make_float2(0.f, 0.f);
+      const float2 xm = cx > 0 ? row[-1] : zero, xp = cx < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const double kim = S.omega * (S.sp_scale * (sxy + sponge_axis_d(Q.z0 + i, Q.nz, S.nb, S.inv_nb)));
+      double2 y = helm(v[j][i + 1], xm, xp, ym, yp, v[j][i], v[j][i + 2], S.h2inv, S.omega2 * (double)mm[j][i],
+                       ADJ ? kim : -kim);
+      if (src_tile && S.src == (Q.z0 + i) * Q.plane + Q.cell[j] && Q.in[j]) { y.x -= pa.x; y.y -= pa.y; }
+      const float2 o = round2(y);
+      Q.store2(ADJ ? S.s : S.t, i + 1, Q.own2(j), o);
+      if (Q.live(j, i)) acc += nrm(o);
+      if constexpr (ADJ) {
+        if (!setup) {
+          Q.store2(rn, i + 1, Q.own2(j), v[j][i + 1]);
+          Q.store2(S.x, i + 1, Q.own2(j), fd((double)xv[j][i].x + a * qv[j][i].x, (double)xv[j][i].y + a * qv[j][i].y));
+        }
+      }
+    }
+  }
+  const double tot = bsum(acc, red);
+  if (tid == 0) part[(size_t)k * stride + tile] = tot;
+}
+
+// The levels from lc on (at most kPcLdsCells cells each, lc >= 1): down, the Jacobi
+// steps of the coarsest, up, with f and the iterate of every level in LDS.  One
+// workgroup per system; f_{lc} is read from and the result of level lc written to
+// memory.  Bound by one compute unit's vector rate on the first level: w D^-1 f is
+// formed once per cell (float64, in LDS) and coordinates come without divisions.
+struct SmallDiv {   // quotients of integers below 2^16 by d, through the float reciprocal
+  int d;
+  float r;
+  __device__ __forceinline__ explicit SmallDiv(int d_) : d(d_), r(1.0f / (float)d_) {}
+  __device__ __forceinline__ int quot(int c) const { return (int)(((float)c + 0.5f) * r); }
+};
+
+__global__ void __launch_bounds__(kPcLdsThr)
+k_pw_coarse(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0, int lc, int conj) {
+  constexpr int KC = kPcLdsCells / kPcLdsThr;   // cells per thread
+  extern __shared__ double2 pc_lds[];
+  const int k = g0 + blockIdx.x;
+  if (!active(stv, k)) return;
+  const PcSys& S = sy[k];
+  const int last = S.nlev - 1, tid = threadIdx.x;
+  const float2 zero = make_float2(0.f, 0.f);
+  // w D^-1 f of the level at hand (the coarsest: its second iterate), then per level f and y (or the residual)
+  double2* yd = pc_lds;
+  float2* pl = reinterpret_cast<float2*>(pc_lds + S.lev[lc].n);
+  auto base = [&](int l) {
+    int o = 0;
+    for (int i = lc; i < l; ++i) o += 2 * S.lev[i].n;
+    return pl + o;
+  };
+  auto coord = [&](const PcLevel& L, const SmallDiv& dx, const SmallDiv& dp, int c, int* x, int* y, int* z) {
+    *z = dp.quot(c);
+    const int rem = c - *z * dp.d;
+    *y = dx.quot(rem);
+    *x = rem - *y * L.nx;
+  };
+  // A_beta v of a float2 array in LDS
+  auto apply = [&](const PcLevel& L, const float2* v, int c, int x, int y, int z, const double2& d) {
+    const int plane = L.nx * L.ny;
+    const float2 xm = x > 0 ? v[c - 1] : zero, xp = x < L.nx - 1 ? v[c + 1] : zero;
+    const float2 ym = y > 0 ? v[c - L.nx] : zero, yp = y < L.ny - 1 ? v[c + L.nx] : zero;
+    const float2 zm = z > 0 ? v[c - plane] : zero, zp = z < L.nz - 1 ? v[c + plane] : zero;
+    const float2 xc = v[c];
+    const double sr = (((double)xm.x + xp.x) + ((double)ym.x + yp.x)) + ((double)zm.x + zp.x);
+    const double si = (((double)xm.y + xp.y) + ((double)ym.y + yp.y)) + ((double)zm.y + zp.y);
+    return make_double2(sr * L.h2inv + (d.x * xc.x - d.y * xc.y), si * L.h2inv + (d.x * xc.y + d.y * xc.x));
+  };
+  // own cells' w D^-1 and diagonal of a level
+  auto own = [&](const PcLevel& L, float2 (&w)[KC], double2 (&d)[KC]) {
+    float mv[KC], bv[KC];
+#pragma unroll
+    for (int i = 0; i < KC; ++i) {
+      const int c = min(tid + i * kPcLdsThr, L.n - 1);
+      w[i] = L.wdinv[c];
+      mv[i] = L.m[c];
+      bv[i] = L.b[c];
+    }
+#pragma unroll
+    for (int i = 0; i < KC; ++i) d[i] = diag_mb(S, L.h2inv, mv[i], bv[i], conj);
+  };
+  for (int c = tid; c < S.lev[lc].n; c += kPcLdsThr) pl[c] = S.lev[lc].f[c];
+  for (int l = lc; l < last; ++l) {
+    const PcLevel& L = S.lev[l];
+    const PcLevel& C = S.lev[l + 1];
+    const int plane = L.nx * L.ny;
+    const SmallDiv dx(L.nx), dp(plane), cdx(C.nx), cdp(C.nx * C.ny);
+    float2 *f = base(l), *res = f + L.n, *fc = base(l + 1);
+    float2 w[KC];
+    double2 d[KC];
+    own(L, w, d);
+#pragma unroll
+    for (int i = 0; i < KC; ++i) {   // f of the own cells was written by this thread, or behind a barrier
+      const int c = tid + i * kPcLdsThr;
+      if (c < L.n) yd[c] = jac_w(w[i], conj, f[c]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < KC; ++i) {
+      const int c = tid + i * kPcLdsThr;
+      if (c >= L.n) break;
+      int x, y, z;
+      coord(L, dx, dp, c, &x, &y, &z);
+      double sr = 0.0, si = 0.0;
+      auto add = [&](bool in, int q) {
+        if (!in) return;
+        sr += yd[q].x;
+        si += yd[q].y;
+      };
+      add(x > 0, c - 1); add(x < L.nx - 1, c + 1);
+      add(y > 0, c - L.nx); add(y < L.ny - 1, c + L.nx);
+      add(z > 0, c - plane); add(z < L.nz - 1, c + plane);
+      const double2 yc = yd[c];
+      const double ar = sr * L.h2inv + (d[i].x * yc.x - d[i].y * yc.y);
+      const double ai = si * L.h2inv + (d[i].x * yc.y + d[i].y * yc.x);
+      res[c] = fd((double)f[c].x - ar, (double)f[c].y - ai);
+    }
+    __syncthreads();
+    for (int c = tid; c < C.n; c += kPcLdsThr) {
+      int cx, cy, cz;
+      coord(C, cdx, cdp, c, &cx, &cy, &cz);
+      double sr = 0.0, si = 0.0;
+#pragma unroll
+      for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+          for (int dx3 = 0; dx3 < 3; ++dx3) {
+            if (2 * cz + dz >= L.nz || 2 * cy + dy >= L.ny || 2 * cx + dx3 >= L.nx) continue;
+            const double wt = (dz != 1 ? 0.5 : 1.0) * (dy != 1 ? 0.5 : 1.0) * (dx3 != 1 ? 0.5 : 1.0);
+            const float2 v = res[(2 * cz + dz) * plane + (2 * cy + dy) * L.nx + 2 * cx + dx3];
+            sr += wt * v.x;
+            si += wt * v.y;
+          }
+      fc[c] = fd(0.125 * sr, 0.125 * si);
+    }
+  }
+  // coarsest level: kCoarseSweeps steps between y and a third array
+  {
+    const PcLevel& L = S.lev[last];
+    const SmallDiv dx(L.nx), dp(L.nx * L.ny);
+    float2 *f = base(last), *ya = f + L.n, *yb = reinterpret_cast<float2*>(yd);
+    float2 w[KC];
+    double2 d[KC];
+    own(L, w, d);
+    __syncthreads();   // the residual and w D^-1 f of the level before are no longer read
+    for (int sweep = 0; sweep < kCoarseSweeps; ++sweep) {
+      const float2* in = (sweep & 1) ? yb : ya;   // the last sweep ends in ya
+      float2* out = (sweep & 1) ? ya : yb;
+#pragma unroll
+      for (int i = 0; i < KC; ++i) {
+        const int c = tid + i * kPcLdsThr;
+        if (c >= L.n) break;
+        if (sweep == 0) {
+          const double2 v = jac_w(w[i], conj, f[c]);
+          out[c] = fd(v.x, v.y);
+          continue;
+        }
+        int x, y, z;
+        coord(L, dx, dp, c, &x, &y, &z);
+        const double2 av = apply(L, in, c, x, y, z, d[i]);
+        const double2 corr = jac_w(w[i], conj, fd((double)f[c].x - av.x, (double)f[c].y - av.y));
+        out[c] = fd((double)in[c].x + corr.x, (double)in[c].y + corr.y);
+      }
+      __syncthreads();
+    }
+    static_assert(kCoarseSweeps % 2 == 0, "the coarsest result is in y");
+    if (last == lc) {
+      for (int c = tid; c < L.n; c += kPcLdsThr) L.y[c] = ya[c];   // coarse_out() of the coarsest level
+      return;
+    }
+  }
+  for (int l = last - 1; l >= lc; --l) {
+    const PcLevel& L = S.lev[l];
+    const PcLevel& C = S.lev[l + 1];
+    const SmallDiv dx(L.nx), dp(L.nx * L.ny);
+    float2 *f = base(l), *yv = f + L.n;
+    const float2* e = l + 1 == last ? base(l + 1) + C.n : base(l + 1);   // the coarsest result, or o over f
+    float2 w[KC];
+    double2 d[KC];
+    own(L, w, d);
+#pragma unroll
+    for (int i = 0; i < KC; ++i) {
+      const int c = tid + i * kPcLdsThr;
+      if (c >= L.n) break;
+      int x, y, z;
+      coord(L, dx, dp, c, &x, &y, &z);
+      double sr = 0.0, si = 0.0;
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const int iz = (z & 1) ? (a ? -1 : z >> 1) : (z >> 1) - 1 + a;
+        if (iz < 0 || iz >= C.nz) continue;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const int iy = (y & 1) ? (b ? -1 : y >> 1) : (y >> 1) - 1 + b;
+          if (iy < 0 || iy >= C.ny) continue;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int ix = (x & 1) ? (q ? -1 : x >> 1) : (x >> 1) - 1 + q;
+            if (ix < 0 || ix >= C.nx) continue;
+            const float2 v = e[(iz * C.ny + iy) * C.nx + ix];
+            sr += v.x;
+            si += v.y;
+          }
+        }
+      }
+      const double wt = ((z & 1) ? 1.0 : 0.5) * ((y & 1) ? 1.0 : 0.5) * ((x & 1) ? 1.0 : 0.5);
+      const double2 j = jac_w(w[i], conj, f[c]);
+      yv[c] = fd(j.x + wt * sr, j.y + wt * si);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < KC; ++i) {
+      const int c = tid + i * kPcLdsThr;
+      if (c >= L.n) break;
+      int x, y, z;
+      coord(L, dx, dp, c, &x, &y, &z);
+      const double2 av = apply(L, yv, c, x, y, z, d[i]);
+      const double2 corr = jac_w(w[i], conj, fd((double)f[c].x - av.x, (double)f[c].y - av.y));
+      const float2 o = fd((double)yv[c].x + corr.x, (double)yv[c].y + corr.y);
+      if (l == lc) L.o[c] = o;
+      else f[c] = o;   // f of this cell is not needed again
+    }
+    __syncthreads();
   }
 }
 
@@ -618,17 +1255,31 @@ __global__ void __launch_bounds__(kThr) k_pc_restrict_mean(const float* __restri
   }
 }
 
+// partials of ||r1||^2 of the final residual (grid (kParts, systems of the group))
+__global__ void __launch_bounds__(kThr) k_pc_rnorm(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
+                                                   double* __restrict__ part, int stride, int g0) {
+  __shared__ double red[kThr / 64];
+  const int k = g0 + blockIdx.y;
+  const PcSys& S = sy[k];
+  const float2* __restrict__ r = pc_r(S, stv[k].iters);
+  double acc = 0.0;
+  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += kParts * kThr) acc += nrm(r[c]);
+  const double tot = bsum(acc, red);
+  if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
+}
+
 // J = ||r1||^2 + ||r2||^2 (recurred), alpha_ls = (A u)[src] in float64
-// (one block per system)
-__global__ void __launch_bounds__(kThr) k_pc_final(const PcSys* __restrict__ sy, PcState* __restrict__ stv, int g0) {
+// (one block per system; the sum over a whole residual in one block took 287 us
+// on 64^3)
+__global__ void __launch_bounds__(kThr) k_pc_final(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
+                                                   const double* __restrict__ part, int stride, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   const PcSys& S = sy[k];
   PcState& T = stv[k];
   double acc = 0.0;
-  for (int c = threadIdx.x; c < S.n; c += kThr) acc += nrm(S.r[c]);
   for (int q = threadIdx.x; q < S.nr; q += kThr) acc += nrm(S.r2[q]);
-  const double J = bsum(acc, red);
+  const double J = sum_parts(part + (size_t)k * stride, kParts, red) + bsum(acc, red);
   if (threadIdx.x == 0) {
     T.J = J;
     if (S.est) {
@@ -639,14 +1290,15 @@ __global__ void __launch_bounds__(kThr) k_pc_final(const PcSys* __restrict__ sy,
 }
 
 // g = -sum over the grid's systems of 2 omega^2 Re(conj(u) r1); systems
-// idx[0..cnt) in fixed order
-__global__ void __launch_bounds__(kThr) k_pc_grad(const PcSys* __restrict__ sy, const int* __restrict__ idx, int cnt,
-                                                  int n, float* __restrict__ g) {
+// idx[0..cnt) in fixed order, the loads of four in flight
+__global__ void __launch_bounds__(kThr) k_pc_grad(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
+                                                  const int* __restrict__ idx, int cnt, int n, float* __restrict__ g) {
   for (int c = blockIdx.x * kThr + threadIdx.x; c < n; c += gridDim.x * kThr) {
     double acc = 0.0;
+#pragma unroll 4
     for (int i = 0; i < cnt; ++i) {
       const PcSys& S = sy[idx[i]];
-      const float2 u = S.x[c], r = S.r[c];
+      const float2 u = S.x[c], r = pc_r(S, stv[idx[i]].iters)[c];
       acc -= 2.0 * S.omega2 * ((double)u.x * r.x + (double)u.y * r.y);
     }
     g[c] = (float)acc;
@@ -680,6 +1332,7 @@ int64_t cells_of(const LevelDims& d) { return (int64_t)d.nx * d.ny * d.nz; }
 
 struct PcLayout {
   size_t sys = 0, state = 0, parts = 0, idx = 0, total = 0;
+  int stride = kParts;               // partial sums per system
   std::vector<size_t> grid_arrays;   // per grid: m_l (l >= 1) and b_l (l >= 0)
   std::vector<std::pair<int, double>> pairs;   // distinct (grid, omega) of the systems
   std::vector<int> pair_of;                    // per system
@@ -687,13 +1340,32 @@ struct PcLayout {
   std::vector<size_t> vec, rvec, rec;
 };
 
+// cells per thread of the tiled passes: two once a plane fills 64 tiles of 256 cells
+int pc_cx(int64_t plane) { return plane >= 64 * 256 ? 2 : 1; }
+struct PcTiles { int cx, x, n; };   // cells per thread, tiles per plane, tiles
+PcTiles pc_tiles(const LevelDims& d) {
+  const int64_t plane = (int64_t)d.nx * d.ny;
+  const int cx = pc_cx(plane), b = 64 * kPcW * cx;
+  const int x = (int)((plane + b - 1) / b);
+  return {cx, x, x * ((d.nz + kPcZ - 1) / kPcZ)};
+}
+// the tiled passes: rows whose halo fits the LDS (96 KB), a level to coarsen to, and levels that one buffer
+// resource covers
+bool pc_tiled(const std::vector<LevelDims>& lv) {
+  return lv.size() > 1 && lv[0].nx <= kPcMaxRow && cells_of(lv[0]) < (int64_t(1) << 28);
+}
+
 PcLayout pc_layout(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys) {
   PcLayout L;
   size_t o = 0;
   auto take = [&](size_t b) { size_t r = o; o = al(o + std::max<size_t>(b, 1)); return r; };
   L.sys = take(sizeof(PcSys) * std::max(n_sys, 1));
   L.state = take(sizeof(PcState) * std::max(n_sys, 1));
-  L.parts = take(sizeof(double) * (size_t)kParts * std::max(n_sys, 1));
+  for (int k = 0; k < n_sys; ++k) {
+    const auto lv = levels_of(grids[sys[k].grid]);
+    if (pc_tiled(lv)) L.stride = std::max(L.stride, pc_tiles(lv[0]).n);
+  }
+  L.parts = take(sizeof(double) * (size_t)L.stride * std::max(n_sys, 1));
   L.idx = take(sizeof(int) * std::max(n_sys, 1));
   L.grid_arrays.resize(n_grids);
   for (int g = 0; g < n_grids; ++g) {
@@ -719,7 +1391,8 @@ PcLayout pc_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   for (int k = 0; k < n_sys; ++k) {
     const wri_grid& g = grids[sys[k].grid];
     const auto lv = levels_of(g);
-    size_t b = 9 * al(sizeof(float2) * (size_t)cells_of(lv[0]));   // x r p q t s z res0 y0
+    // x r p q t s z res0, y0 (or the other p) and the other r
+    size_t b = (pc_tiled(lv) ? 10 : 9) * al(sizeof(float2) * (size_t)cells_of(lv[0]));
     for (size_t l = 1; l < lv.size(); ++l) b += 4 * al(sizeof(float2) * (size_t)cells_of(lv[l]));
     L.vec[k] = take(b);
     L.rvec[k] = take(2 * al(sizeof(float2) * (size_t)sys[k].n_rec));
@@ -829,8 +1502,13 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     char* v = base + L.vec[k];
     auto vec = [&](int i) { return reinterpret_cast<float2*>(v + i * vb); };
     S.x = (u_out != nullptr && u_out[k] != nullptr) ? reinterpret_cast<float2*>(u_out[k]) : vec(0);
-    S.r = vec(1); S.p = vec(2); S.q = vec(3); S.t = vec(4); S.s = vec(5); S.z = vec(6);
-    char* cv = v + 9 * vb;
+    const bool tiled = pc_tiled(lv);
+    S.tiled = tiled ? 1 : 0;
+    S.nparts = tiled ? pc_tiles(lv[0]).n : kParts;
+    S.r[0] = vec(1); S.r[1] = tiled ? vec(9) : vec(1);
+    S.p[0] = vec(2); S.p[1] = tiled ? vec(8) : vec(2);
+    S.q = vec(3); S.t = vec(4); S.s = vec(5); S.z = vec(6);
+    char* cv = v + (tiled ? 10 : 9) * vb;
     for (size_t l = 0; l < lv.size(); ++l) {
       PcLevel& Lv = S.lev[l];
       Lv.nx = lv[l].nx; Lv.ny = lv[l].ny; Lv.nz = lv[l].nz; Lv.n = (int)cells_of(lv[l]);
@@ -886,47 +1564,93 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   PC_HIP(hipMemcpyAsync(didx, ident.data(), sizeof(int) * n_sys, hipMemcpyHostToDevice, st));
   PC_HIP(hipStreamSynchronize(st));  // host tables are read by the copies above
 
-  // one V-cycle (which = 0: q = M p, 1: z = M^H s with the partials of ||z||^2)
-  auto vcycle = [&](const Group& G, hipStream_t sq, int which) -> int {
+  const int stride = L.stride;
+  // tiled pass on level d: launch LAUNCH(template cx, grid, dynamic LDS of one element of `elem` bytes per cell)
+  auto lds_of = [](const PcTiles& t, const LevelDims& d, size_t elem) {
+    return (unsigned)(elem * kPcZ * (size_t)(64 * kPcW * t.cx + 2 * d.nx));
+  };
+#define PW_LAUNCH(K1, K2, D, ELEM, ...)                                                                     \
+  do {                                                                                                      \
+    const PcTiles t_ = pc_tiles(D);                                                                     \
+    const dim3 g_((unsigned)(t_.n * G.cnt));                                                                \
+    if (t_.cx == 1) hipLaunchKernelGGL(K1, g_, dim3(64 * kPcW), lds_of(t_, D, ELEM), st, dsys, dst, __VA_ARGS__, t_.x, t_.n); \
+    else hipLaunchKernelGGL(K2, g_, dim3(64 * kPcW), lds_of(t_, D, ELEM), st, dsys, dst, __VA_ARGS__, t_.x, t_.n);            \
+  } while (0)
+  // one V-cycle (which = 0: q = M p with the p update, 1: z = M^H s with the partials of ||z||^2)
+  auto vcycle = [&](const Group& G, int which) -> int {
     const int conj = which;
     const std::vector<LevelDims> lv = levels_of(grids[G.grid]);
     const int nl = (int)lv.size();
+    auto sweeps = [&]() {
+      for (int j = 0; j < kCoarseSweeps; ++j)
+        hipLaunchKernelGGL(k_pc_vcoarse, dim3(blocks_for(cells_of(lv[nl - 1])), G.cnt), dim3(kThr), 0, st, dsys, dst,
+                           G.p0, which, conj, j);
+    };
+    if (pc_tiled(lv)) {
+      // levels of one workgroup: from lc on (nl: none fits, the coarsest by separate sweeps)
+      int lc = 1;
+      while (lc < nl && cells_of(lv[lc]) > kPcLdsCells) ++lc;
+      for (int l = 0; l < std::min(lc, nl - 1); ++l) {
+        if (l == 0 && which == 0)
+          PW_LAUNCH((k_pw_down<1, true>), (k_pw_down<2, true>), lv[l], sizeof(double2), G.p0, l, which, conj);
+        else
+          PW_LAUNCH((k_pw_down<1, false>), (k_pw_down<2, false>), lv[l], sizeof(double2), G.p0, l, which, conj);
+        const int rt = (int)((cells_of(lv[l + 1]) + kThr - 1) / kThr);
+        hipLaunchKernelGGL(k_pw_restrict, dim3((unsigned)(rt * G.cnt)), dim3(kThr), 0, st, dsys, dst, G.p0, l, rt);
+      }
+      if (lc < nl) {
+        size_t lds = sizeof(double2) * (size_t)cells_of(lv[lc]);
+        for (int l = lc; l < nl; ++l) lds += 2 * sizeof(float2) * (size_t)cells_of(lv[l]);
+        hipLaunchKernelGGL(k_pw_coarse, dim3(G.cnt), dim3(kPcLdsThr), (unsigned)lds, st, dsys, dst, G.p0, lc, conj);
+      } else {
+        sweeps();
+      }
+      for (int l = std::min(lc, nl - 1) - 1; l >= 0; --l)
+        PW_LAUNCH((k_pw_up<1>), (k_pw_up<2>), lv[l], sizeof(float2), parts, stride, G.p0, l, which, conj);
+      PC_HIP(hipGetLastError());
+      return WRI_OK;
+    }
+    if (which == 0) hipLaunchKernelGGL(k_pc_pupd, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0);
     for (int l = 0; l + 1 < nl; ++l) {
-      hipLaunchKernelGGL(k_pc_vdown, dim3(blocks_for(cells_of(lv[l])), G.cnt), dim3(kThr), 0, sq, dsys, dst, G.p0,
+      hipLaunchKernelGGL(k_pc_vdown, dim3(blocks_for(cells_of(lv[l])), G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0,
                          l, which, conj);
-      hipLaunchKernelGGL(k_pc_vrestrict, dim3(blocks_for(cells_of(lv[l + 1])), G.cnt), dim3(kThr), 0, sq, dsys, dst,
+      hipLaunchKernelGGL(k_pc_vrestrict, dim3(blocks_for(cells_of(lv[l + 1])), G.cnt), dim3(kThr), 0, st, dsys, dst,
                          G.p0, l);
     }
-    for (int j = 0; j < kCoarseSweeps; ++j)
-      hipLaunchKernelGGL(k_pc_vcoarse, dim3(blocks_for(cells_of(lv[nl - 1])), G.cnt), dim3(kThr), 0, sq, dsys, dst,
-                         G.p0, which, conj, j);
+    sweeps();
     if (nl == 1) {
-      hipLaunchKernelGGL(k_pc_vsingle_out, dim3(kParts, G.cnt), dim3(kThr), 0, sq, dsys, dst, parts, G.p0, which);
+      hipLaunchKernelGGL(k_pc_vsingle_out, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, which);
     } else {
       for (int l = nl - 2; l >= 0; --l) {
         const int nbk = (l == 0) ? kParts : blocks_for(cells_of(lv[l]));
-        hipLaunchKernelGGL(k_pc_vprolong, dim3(blocks_for(cells_of(lv[l])), G.cnt), dim3(kThr), 0, sq, dsys, dst,
+        hipLaunchKernelGGL(k_pc_vprolong, dim3(blocks_for(cells_of(lv[l])), G.cnt), dim3(kThr), 0, st, dsys, dst,
                            G.p0, l, which, conj);
-        hipLaunchKernelGGL(k_pc_vsmooth, dim3(nbk, G.cnt), dim3(kThr), 0, sq, dsys, dst, parts, G.p0, l, which, conj);
+        hipLaunchKernelGGL(k_pc_vsmooth, dim3(nbk, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, l, which, conj);
       }
     }
     PC_HIP(hipGetLastError());
     return WRI_OK;
   };
-  auto iteration = [&](hipStream_t sq) -> int {
+  auto iteration = [&]() -> int {
     for (const Group& G : groups) {
       const dim3 pg(kParts, G.cnt);
-      hipLaunchKernelGGL(k_pc_pupd, pg, dim3(kThr), 0, sq, dsys, dst, G.p0);
-      int e = vcycle(G, sq, 0);
+      const std::vector<LevelDims> lv = levels_of(grids[G.grid]);
+      const bool tiled = pc_tiled(lv);
+      int e = vcycle(G, 0);
       if (e != WRI_OK) return e;
-      hipLaunchKernelGGL(k_pc_fwd, pg, dim3(kThr), 0, sq, dsys, dst, parts, G.p0);
-      hipLaunchKernelGGL(k_pc_step, dim3(G.cnt), dim3(kThr), 0, sq, dsys, dst, parts, G.p0);
-      hipLaunchKernelGGL(k_pc_rupd, pg, dim3(kThr), 0, sq, dsys, dst, G.p0);
-      hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, sq, dsys, dst, parts, G.p0);
-      hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, sq, dsys, dst, parts, G.p0, 0);
-      e = vcycle(G, sq, 1);
+      if (tiled) PW_LAUNCH((k_pw_apply<1, false>), (k_pw_apply<2, false>), lv[0], sizeof(float2), parts, stride, G.p0, 0);
+      else hipLaunchKernelGGL(k_pc_fwd, pg, dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
+      hipLaunchKernelGGL(k_pc_step, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
+      if (tiled) {
+        PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), parts, stride, G.p0, 0);
+      } else {
+        hipLaunchKernelGGL(k_pc_rupd, pg, dim3(kThr), 0, st, dsys, dst, G.p0);
+        hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
+      }
+      hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, 0);
+      e = vcycle(G, 1);
       if (e != WRI_OK) return e;
-      hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, sq, dsys, dst, parts, G.p0, 0);
+      hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, 0);
       PC_HIP(hipGetLastError());
     }
     return WRI_OK;
@@ -934,15 +1658,18 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   // set-up: x = 0, r = b, s_0 = S^H b, z_0 = M^H s_0, p_0 = z_0
   for (const Group& G : groups) {
     const dim3 pg(kParts, G.cnt);
+    const std::vector<LevelDims> lv = levels_of(grids[G.grid]);
     hipLaunchKernelGGL(k_pc_zero, pg, dim3(kThr), 0, st, dsys, G.p0);
     hipLaunchKernelGGL(k_pc_init, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0);
-    hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, parts, G.p0);
-    hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 1);
-    rc = vcycle(G, st, 1);
+    if (pc_tiled(lv)) PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), parts, stride, G.p0, 1);
+    else hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
+    hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, 1);
+    rc = vcycle(G, 1);
     if (rc != WRI_OK) return rc;
-    hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 1);
+    hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, 1);
     PC_HIP(hipGetLastError());
   }
+#undef PW_LAUNCH
   std::vector<PcState> hst(n_sys);
   auto read = [&]() -> int {
     PC_HIP(hipMemcpyAsync(hst.data(), dst, sizeof(PcState) * n_sys, hipMemcpyDeviceToHost, st));
@@ -950,57 +1677,27 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     return WRI_OK;
   };
   if ((rc = read()) != WRI_OK) return rc;
-  const bool use_graph = !(flags & WRI_FLAG_NO_GRAPH);
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  auto drop_graph = [&]() {
-    if (exec) (void)hipGraphExecDestroy(exec);
-    if (graph) (void)hipGraphDestroy(graph);
-    exec = nullptr;
-    graph = nullptr;
-  };
+  // Eager launches: a pass takes longer than the host needs to enqueue the next, and
+  // building a graph of a chunk cost more than a solve of a few iterations (1.9 ms
+  // for 624 nodes).
   int64_t done = 0;
   while (true) {
     bool any = false;
     for (const auto& T : hst) any = any || (T.status == kActive);
     if (!any) break;
-    if (done > (int64_t)max_iter + kCheck) {
-      drop_graph();
+    if (done > (int64_t)max_iter + kCheck)
       return report_error(WRI_EHIP, "internal: systems still active after max_iter iterations");
-    }
-    if (use_graph) {
-      if (exec == nullptr) {
-        hipStream_t cs = nullptr;
-        PC_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-        hipError_t eb = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-        if (eb != hipSuccess) {
-          (void)hipStreamDestroy(cs);
-          return report_error(WRI_EHIP, "hipStreamBeginCapture: %s", hipGetErrorString(eb));
-        }
-        int e = WRI_OK;
-        for (int i = 0; i < kCheck && e == WRI_OK; ++i) e = iteration(cs);
-        const hipError_t ee = hipStreamEndCapture(cs, &graph);
-        (void)hipStreamDestroy(cs);
-        if (e != WRI_OK) { drop_graph(); return e; }
-        if (ee != hipSuccess) { drop_graph(); return report_error(WRI_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(ee)); }
-        const hipError_t ei = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-        if (ei != hipSuccess) { drop_graph(); return report_error(WRI_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(ei)); }
-      }
-      const hipError_t el = hipGraphLaunch(exec, st);
-      if (el != hipSuccess) { drop_graph(); return report_error(WRI_EHIP, "hipGraphLaunch: %s", hipGetErrorString(el)); }
-    } else {
-      for (int i = 0; i < kCheck; ++i) {
-        rc = iteration(st);
-        if (rc != WRI_OK) return rc;
-      }
-    }
-    done += kCheck;
-    if ((rc = read()) != WRI_OK) { drop_graph(); return rc; }
+    const int chunk = (int)std::min<int64_t>(kCheck, std::max<int64_t>(1, max_iter - done));
+    for (int i = 0; i < chunk; ++i)
+      if ((rc = iteration()) != WRI_OK) return rc;
+    done += chunk;
+    if ((rc = read()) != WRI_OK) return rc;
   }
-  drop_graph();
   // results: J, alpha_ls, gradient per grid
-  for (const Group& G : groups)
-    hipLaunchKernelGGL(k_pc_final, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0);
+  for (const Group& G : groups) {
+    hipLaunchKernelGGL(k_pc_rnorm, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
+    hipLaunchKernelGGL(k_pc_final, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
+  }
   PC_HIP(hipGetLastError());
   if (grad != nullptr) {
     for (int g = 0; g < n_grids; ++g) {
@@ -1012,7 +1709,7 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
         PC_HIP(launch_zero_f32(grad[g], (size_t)n, st));
         continue;
       }
-      hipLaunchKernelGGL(k_pc_grad, dim3(blocks_for(n)), dim3(kThr), 0, st, dsys, didx + G->p0, G->cnt, (int)n,
+      hipLaunchKernelGGL(k_pc_grad, dim3(blocks_for(n)), dim3(kThr), 0, st, dsys, dst, didx + G->p0, G->cnt, (int)n,
                          grad[g]);
       PC_HIP(hipGetLastError());
     }
