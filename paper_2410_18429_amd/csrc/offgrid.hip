@@ -7,8 +7,8 @@
 // system pass for the source column, P p and the step a, an adjoint pass
 // (r update, s = A^H r, x update) and a one-block-per-system pass for P^H r2,
 // the source row and beta.  The stencil arithmetic is the fused kernels'
-// (stencil.hpp); step scalars live in device memory; chunks of iterations
-// replay from a hipGraph and the host checks the statuses between them.
+// (stencil.hpp); step scalars live in device memory and the host checks the
+// statuses between chunks of iterations.
 //
 // P p: one thread per receiver sums its weighted cells (reads only).  P^H r2:
 // a gather over the distinct receiver cells of a system (each cell's list of
@@ -18,6 +18,7 @@
 #include "../../include/wri.h"
 #include "wri_impl.hpp"
 #include "stencil.hpp"
+#include "window.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -39,7 +40,8 @@ size_t al(size_t v) { return (v + kAl - 1) / kAl * kAl; }
 
 int nblk(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>((n + kThreads - 1) / kThreads, 4096)); }
 
-constexpr int kParts = 128;  // blocks (and partial sums) per system in the stencil passes
+constexpr int kParts = 128;  // blocks (and partial sums) per system in the column passes and the norms
+constexpr int kMaxCells = 8;  // cells of one point
 constexpr int kCheck = 32;   // iterations between host checks of the statuses
 
 // One system, resident in the workspace.  r and p are ping-pong pairs (the
@@ -52,7 +54,8 @@ struct OgSys {
   const int* uptr; const int* ucell; const int* uq; const double* uw;
   const float* m;
   int n, ns, nr, nu;
-  int est, max_iter, nx, ny, nz, nb, zc, pad2_;
+  int est, max_iter, nx, ny, nz, nb, zc;
+  int nparts;   // partial sums of a stencil pass
   double c, lam, rtol2, omega, omega2, h2inv, sp_scale, inv_nb;
   double2 alpha;  // KNOWN-mode weight
 };
@@ -97,22 +100,6 @@ __global__ void __launch_bounds__(kThreads) k_og_zero(const OgSys* __restrict__ 
     S.x[c] = z;
     S.r[0][c] = z;
     S.p[1][c] = z;
-  }
-}
-
-// t = A x (the least-squares source weight of the result)  (grid (blocks, nsys))
-__global__ void __launch_bounds__(kThreads) k_og_ax(const OgSys* __restrict__ sy) {
-  const OgSys& S = sy[blockIdx.y];
-  const int nx = S.nx, ny = S.ny, nz = S.nz, plane = nx * ny;
-  const float2 zero = make_float2(0.f, 0.f);
-  const float2* __restrict__ in = S.x;
-  for (int c = blockIdx.x * kThreads + threadIdx.x; c < S.n; c += gridDim.x * kThreads) {
-    const int z = c / plane, rem = c - z * plane, y = rem / nx, x = rem - y * nx;
-    const float2 xm = x > 0 ? in[c - 1] : zero, xp = x < nx - 1 ? in[c + 1] : zero;
-    const float2 ym = y > 0 ? in[c - nx] : zero, yp = y < ny - 1 ? in[c + nx] : zero;
-    const float2 zm = z > 0 ? in[c - plane] : zero, zp = z < nz - 1 ? in[c + plane] : zero;
-    S.t[c] = round2(helm(in[c], xm, xp, ym, yp, zm, zp, S.h2inv, S.omega2 * (double)S.m[c],
-                         -(S.omega * sponge_at(S, x, y, z))));
   }
 }
 
@@ -177,7 +164,7 @@ __device__ __forceinline__ void halo_cell(int h, int x0, int y0, int* hx, int* h
 // and its neighbours), t = A p_k, per-block partials of ||t||^2 (the
 // source-column term is added by k_og_alpha).  grid (kParts, nsys).
 __global__ void __launch_bounds__(kThreads) k_og_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv,
-                                                     double* __restrict__ parts) {
+                                                     double* __restrict__ parts, int stride) {
   __shared__ double red[kThreads / 64];
   __shared__ float2 pl[kTy + 2][66];
   const OgSys& S = sy[blockIdx.y];
@@ -223,20 +210,20 @@ __global__ void __launch_bounds__(kThreads) k_og_fwd(const OgSys* __restrict__ s
     }
   }
   acc = bsum(acc, red);
-  if (threadIdx.x == 0) parts[blockIdx.y * kParts + blockIdx.x] = acc;
+  if (threadIdx.x == 0) parts[(size_t)blockIdx.y * stride + blockIdx.x] = acc;
 }
 
 // delta = ||t||^2 with the source column (t[src] -= c p_a w) + ||t2||^2 with
 // t2 = lam P p_k; a = gamma / delta; x_a += a p_a; r2 -= a t2  (grid nsys)
 __global__ void __launch_bounds__(kThreads) k_og_alpha(const OgSys* __restrict__ sy, OgState* __restrict__ stv,
-                                                       const double* __restrict__ parts) {
+                                                       const double* __restrict__ parts, int stride) {
   __shared__ double red[kThreads / 64];
   const OgSys& S = sy[blockIdx.x];
   OgState& T = stv[blockIdx.x];
   if (T.status != kActive) return;  // uniform over the block
   const float2* __restrict__ pk = S.p[T.iters & 1];
   double v = 0.0;
-  for (int i = threadIdx.x; i < kParts; i += kThreads) v += parts[blockIdx.x * kParts + i];
+  for (int i = threadIdx.x; i < S.nparts; i += kThreads) v += parts[(size_t)blockIdx.x * stride + i];
   if (S.est && (int)threadIdx.x < S.ns) {  // distinct source cells, one per thread
     const int c = S.scell[threadIdx.x];
     const double w = S.sw[threadIdx.x];
@@ -247,11 +234,20 @@ __global__ void __launch_bounds__(kThreads) k_og_alpha(const OgSys* __restrict__
   }
   for (int q = threadIdx.x; q < S.nr; q += kThreads) {
     double re = 0.0, im = 0.0;
-    for (int j = S.rptr[q]; j < S.rptr[q + 1]; ++j) {
-      const float2 x = pk[S.rcell[j]];
-      re += S.rw[j] * (double)x.x;
-      im += S.rw[j] * (double)x.y;
+    const int b = S.rptr[q], e = S.rptr[q + 1];   // 1 to kMaxCells cells, all loaded at once
+    float2 x[kMaxCells];
+    double w[kMaxCells];
+#pragma unroll
+    for (int j = 0; j < kMaxCells; ++j) {
+      x[j] = pk[S.rcell[min(b + j, e - 1)]];
+      w[j] = S.rw[min(b + j, e - 1)];
     }
+#pragma unroll
+    for (int j = 0; j < kMaxCells; ++j)
+      if (b + j < e) {
+        re += w[j] * (double)x[j].x;
+        im += w[j] * (double)x[j].y;
+      }
     const float2 t2 = f2d(S.lam * re, S.lam * im);
     S.t2[q] = t2;
     v += nrm(t2);
@@ -279,7 +275,7 @@ __global__ void __launch_bounds__(kThreads) k_og_alpha(const OgSys* __restrict__
 // (s_0 = A^H r_0, copied r_0 into r_1).  Same tiles as k_og_fwd.
 // grid (kParts, nsys).
 __global__ void __launch_bounds__(kThreads) k_og_adj(const OgSys* __restrict__ sy, const OgState* __restrict__ stv,
-                                                     double* __restrict__ parts, int setup) {
+                                                     double* __restrict__ parts, int stride, int setup) {
   __shared__ double red[kThreads / 64];
   __shared__ float2 pl[kTy + 2][66];
   const OgSys& S = sy[blockIdx.y];
@@ -327,24 +323,228 @@ __global__ void __launch_bounds__(kThreads) k_og_adj(const OgSys* __restrict__ s
     }
   }
   acc = bsum(acc, red);
-  if (threadIdx.x == 0) parts[blockIdx.y * kParts + blockIdx.x] = acc;
+  if (threadIdx.x == 0) parts[(size_t)blockIdx.y * stride + blockIdx.x] = acc;
+}
+
+// ---------------------------------------------------------------------------
+// The stencil passes by window tiles (window.hpp): a workgroup owns consecutive
+// cells of the x-y plane and kOwZ planes, all its loads are issued at once and the
+// x/y neighbours come from LDS.  The march above gives a workgroup one tile of 64 x 4
+// columns and a load latency and two barriers per plane: what bounded it on batches
+// that fit the caches.  Every stored value is rounded where it was; only the order of
+// the float64 sums differs.  Per iteration (four launches): 8 systems of 64^3 78 us before
+// and 47 now, 2 of 24x20x18 35 and 23, 48 of 128^3 2.07 ms and 1.74 (88 bytes a cell at
+// 5.1 TB/s: memory).
+// ---------------------------------------------------------------------------
+constexpr int kOwW = 4, kOwZ = 4;
+constexpr int kOwMaxRow = 512;   // wider rows (and planes past one resource) take the march: LDS 48 KB
+
+// (system, tile) of a block: neighbouring tiles of a system on one XCD; tiles are
+// counted for the largest grid of the call
+__device__ __forceinline__ void ow_block(int tiles, int* sys, int* tile) {
+  const int logical = xcd_remap(blockIdx.x, gridDim.x, max(16, tiles / 2));
+  *sys = logical / tiles;
+  *tile = logical - *sys * tiles;
+}
+
+template <int CX>
+__global__ void __launch_bounds__(64 * kOwW)
+k_ow_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, int stride,
+         int tiles) {
+  using Tile = Win<kOwW, CX, kOwZ>;
+  constexpr int NT = Tile::NT;
+  __shared__ double red[kThreads / 64];
+  extern __shared__ float2 ow_f[];   // [kOwZ][B + 2 nx]: p
+  const int tid = threadIdx.x;
+  int sys, tile;
+  ow_block(tiles, &sys, &tile);
+  const OgSys& S = sy[sys];
+  const OgState& T = stv[sys];
+  if (T.status != kActive || tile >= S.nparts) return;
+  Tile Q;
+  Q.setup(S.nx, S.ny, S.nz, tile, (S.nx * S.ny + Tile::B - 1) / Tile::B);
+  const int nx = Q.nx, wl = Q.wl, k = T.iters;
+  const float2* po = S.p[(k + 1) & 1];
+  float2* pn = S.p[k & 1];
+  float2 v[CX][kOwZ + 2], pv[CX][kOwZ + 2];
+  float mm[CX][kOwZ];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kOwZ + 2; ++i) {
+      v[j][i] = Q.load2(S.s, i, Q.own2(j));
+      pv[j][i] = Q.load2(po, i, Q.own2(j));
+    }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kOwZ; ++i) mm[j][i] = Q.load1(S.m, i + 1, Q.own1(j));
+  issue_point();
+  const double beta = T.beta;
+  for (int h = tid; h < 2 * nx; h += NT) {
+    const unsigned o = Q.halo_off(h);
+    const int sl = Q.halo_slot(h);
+    float2 hs[kOwZ], hp[kOwZ];
+#pragma unroll
+    for (int i = 0; i < kOwZ; ++i) {
+      hs[i] = Q.load2(S.s, i + 1, o);
+      hp[i] = Q.load2(po, i + 1, o);
+    }
+#pragma unroll
+    for (int i = 0; i < kOwZ; ++i) ow_f[i * wl + sl] = axpyd(hs[i], beta, hp[i]);
+  }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kOwZ + 2; ++i) {
+      v[j][i] = axpyd(v[j][i], beta, pv[j][i]);
+      if (i >= 1 && i <= kOwZ) ow_f[(i - 1) * wl + nx + j * NT + tid] = v[j][i];
+    }
+  __syncthreads();
+  double acc = 0.0;
+#pragma unroll
+  for (int j = 0; j < CX; ++j) {
+    int cx, cy;
+    Q.row_of(Q.cell[j], &cx, &cy);
+    const double sxy = sponge_axis_d(cx, nx, S.nb, S.inv_nb) + sponge_axis_d(cy, Q.ny, S.nb, S.inv_nb);
+#pragma unroll
+    for (int i = 0; i < kOwZ; ++i) {
+      const float2* row = ow_f + i * wl + nx + j * NT + tid;
+      const float2 zero = make_float2(0.f, 0.f);
+      const float2 xm = cx > 0 ? row[-1] : zero, xp = cx < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const double b = S.sp_scale * (sxy + sponge_axis_d(Q.z0 + i, Q.nz, S.nb, S.inv_nb));
+      const float2 t = round2(helm(v[j][i + 1], xm, xp, ym, yp, v[j][i], v[j][i + 2], S.h2inv,
+                                   S.omega2 * (double)mm[j][i], -(S.omega * b)));
+      Q.store2(pn, i + 1, Q.own2(j), v[j][i + 1]);
+      Q.store2(S.t, i + 1, Q.own2(j), t);
+      if (Q.live(j, i)) acc += nrm(t);
+    }
+  }
+  acc = bsum(acc, red);
+  if (tid == 0) parts[(size_t)sys * stride + tile] = acc;
+}
+
+// SETUP: s_0 = A^H r_0, no update
+template <int CX, bool SETUP>
+__global__ void __launch_bounds__(64 * kOwW)
+k_ow_adj(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, int stride,
+         int tiles) {
+  using Tile = Win<kOwW, CX, kOwZ>;
+  constexpr int NT = Tile::NT;
+  __shared__ double red[kThreads / 64];
+  extern __shared__ float2 ow_f[];   // [kOwZ][B + 2 nx]: r
+  const int tid = threadIdx.x;
+  int sys, tile;
+  ow_block(tiles, &sys, &tile);
+  const OgSys& S = sy[sys];
+  const OgState& T = stv[sys];
+  if (T.status != kActive || tile >= S.nparts) return;
+  Tile Q;
+  Q.setup(S.nx, S.ny, S.nz, tile, (S.nx * S.ny + Tile::B - 1) / Tile::B);
+  const int nx = Q.nx, wl = Q.wl, k = T.iters;
+  const float2* ro = S.r[k & 1];
+  float2* rn = S.r[(k + 1) & 1];
+  const float2* pk = S.p[k & 1];
+  float2 v[CX][kOwZ + 2], tv[CX][kOwZ + 2], xv[CX][kOwZ], pv[CX][kOwZ];
+  float mm[CX][kOwZ];
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kOwZ + 2; ++i) {
+      v[j][i] = Q.load2(ro, i, Q.own2(j));
+      if constexpr (!SETUP) tv[j][i] = Q.load2(S.t, i, Q.own2(j));
+    }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kOwZ; ++i) {
+      mm[j][i] = Q.load1(S.m, i + 1, Q.own1(j));
+      if constexpr (!SETUP) {
+        xv[j][i] = Q.load2(S.x, i + 1, Q.own2(j));
+        pv[j][i] = Q.load2(pk, i + 1, Q.own2(j));
+      }
+    }
+  issue_point();
+  const double a = SETUP ? 0.0 : T.a;
+  for (int h = tid; h < 2 * nx; h += NT) {
+    const unsigned o = Q.halo_off(h);
+    const int sl = Q.halo_slot(h);
+    float2 hr[kOwZ], ht[kOwZ];
+#pragma unroll
+    for (int i = 0; i < kOwZ; ++i) {
+      hr[i] = Q.load2(ro, i + 1, o);
+      if constexpr (!SETUP) ht[i] = Q.load2(S.t, i + 1, o);
+    }
+#pragma unroll
+    for (int i = 0; i < kOwZ; ++i) {
+      if constexpr (!SETUP) hr[i] = axpyd(hr[i], -a, ht[i]);
+      ow_f[i * wl + sl] = hr[i];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < CX; ++j)
+#pragma unroll
+    for (int i = 0; i < kOwZ + 2; ++i) {
+      if constexpr (!SETUP) v[j][i] = axpyd(v[j][i], -a, tv[j][i]);
+      if (i >= 1 && i <= kOwZ) ow_f[(i - 1) * wl + nx + j * NT + tid] = v[j][i];
+    }
+  __syncthreads();
+  double acc = 0.0;
+#pragma unroll
+  for (int j = 0; j < CX; ++j) {
+    int cx, cy;
+    Q.row_of(Q.cell[j], &cx, &cy);
+    const double sxy = sponge_axis_d(cx, nx, S.nb, S.inv_nb) + sponge_axis_d(cy, Q.ny, S.nb, S.inv_nb);
+#pragma unroll
+    for (int i = 0; i < kOwZ; ++i) {
+      const float2* row = ow_f + i * wl + nx + j * NT + tid;
+      const float2 zero = make_float2(0.f, 0.f);
+      const float2 xm = cx > 0 ? row[-1] : zero, xp = cx < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const double b = S.sp_scale * (sxy + sponge_axis_d(Q.z0 + i, Q.nz, S.nb, S.inv_nb));
+      const float2 s = round2(helm(v[j][i + 1], xm, xp, ym, yp, v[j][i], v[j][i + 2], S.h2inv,
+                                   S.omega2 * (double)mm[j][i], S.omega * b));
+      Q.store2(S.s, i + 1, Q.own2(j), s);
+      if (Q.live(j, i)) acc += nrm(s);
+      if constexpr (!SETUP) {
+        Q.store2(rn, i + 1, Q.own2(j), v[j][i + 1]);
+        Q.store2(S.x, i + 1, Q.own2(j), axpyd(xv[j][i], a, pv[j][i]));
+      }
+    }
+  }
+  acc = bsum(acc, red);
+  if (tid == 0) parts[(size_t)sys * stride + tile] = acc;
 }
 
 // The receiver rows of S^H r (s += lam P^H r2 over the distinct receiver
 // cells) and the source row s_a = -c e^H r, with gamma = ||s||^2 + |s_a|^2:
 // shared by the set-up (gamma0) and every iteration (beta, statuses).
-__device__ void og_finish_s(const OgSys& S, const float2* __restrict__ r, double pv, double* red, double* gs,
-                            double2* sa) {
+__device__ void og_finish_s(const OgSys& S, const float2* __restrict__ r, double pv, double* red, double2* src,
+                            double* gs, double2* sa) {
   double v = pv;
+  if (S.est && (int)threadIdx.x < S.ns) {
+    const float2 x = r[S.scell[threadIdx.x]];
+    const double w = S.c * S.sw[threadIdx.x];
+    src[threadIdx.x] = make_double2(w * (double)x.x, w * (double)x.y);
+  }
   for (int u = threadIdx.x; u < S.nu; u += kThreads) {
     double re = 0.0, im = 0.0;
-    for (int j = S.uptr[u]; j < S.uptr[u + 1]; ++j) {
-      const float2 x = S.r2[S.uq[j]];
-      re += S.uw[j] * (double)x.x;
-      im += S.uw[j] * (double)x.y;
-    }
-    const int c = S.ucell[u];
+    const int b = S.uptr[u], e = S.uptr[u + 1], c = S.ucell[u];
     const float2 s0 = S.s[c];
+    for (int j = b; j < e; j += 4) {   // four pairs' loads at once
+      float2 x[4];
+      double w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[i] = S.r2[S.uq[min(j + i, e - 1)]];
+        w[i] = S.uw[min(j + i, e - 1)];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (j + i < e) {
+          re += w[i] * (double)x[i].x;
+          im += w[i] * (double)x[i].y;
+        }
+    }
     const float2 s1 = f2d((double)s0.x + S.lam * re, (double)s0.y + S.lam * im);
     S.s[c] = s1;
     v += nrm(s1) - nrm(s0);
@@ -353,9 +553,8 @@ __device__ void og_finish_s(const OgSys& S, const float2* __restrict__ r, double
   double sr = 0.0, si = 0.0;
   if (S.est)
     for (int i = 0; i < S.ns; ++i) {
-      const float2 x = r[S.scell[i]];
-      sr -= S.c * S.sw[i] * (double)x.x;
-      si -= S.c * S.sw[i] * (double)x.y;
+      sr -= src[i].x;
+      si -= src[i].y;
     }
   *gs = v + sr * sr + si * si;
   *sa = make_double2(sr, si);
@@ -363,15 +562,16 @@ __device__ void og_finish_s(const OgSys& S, const float2* __restrict__ r, double
 
 // gamma0 = ||S^H b||^2 after the set-up pass; p_a = s_a, beta = 0 (p_{-1} = 0)  (grid nsys)
 __global__ void __launch_bounds__(kThreads) k_og_start(const OgSys* __restrict__ sy, OgState* __restrict__ stv,
-                                                       const double* __restrict__ parts) {
+                                                       const double* __restrict__ parts, int stride) {
   __shared__ double red[kThreads / 64];
+  __shared__ double2 src[kMaxCells];
   const OgSys& S = sy[blockIdx.x];
   OgState& T = stv[blockIdx.x];
   double v = 0.0;
-  for (int i = threadIdx.x; i < kParts; i += kThreads) v += parts[blockIdx.x * kParts + i];
+  for (int i = threadIdx.x; i < S.nparts; i += kThreads) v += parts[(size_t)blockIdx.x * stride + i];
   double g;
   double2 sa;
-  og_finish_s(S, S.r[0], v, red, &g, &sa);
+  og_finish_s(S, S.r[0], v, red, src, &g, &sa);
   if (threadIdx.x == 0) {
     T.gamma = T.gamma0 = g;
     T.sa = T.pa = sa;
@@ -384,16 +584,17 @@ __global__ void __launch_bounds__(kThreads) k_og_start(const OgSys* __restrict__
 
 // s_{k+1} completed, gamma' , beta, statuses, p_a; iteration k done  (grid nsys)
 __global__ void __launch_bounds__(kThreads) k_og_beta(const OgSys* __restrict__ sy, OgState* __restrict__ stv,
-                                                      const double* __restrict__ parts) {
+                                                      const double* __restrict__ parts, int stride) {
   __shared__ double red[kThreads / 64];
+  __shared__ double2 src[kMaxCells];
   const OgSys& S = sy[blockIdx.x];
   OgState& T = stv[blockIdx.x];
   if (T.status != kActive) return;  // uniform over the block
   double v = 0.0;
-  for (int i = threadIdx.x; i < kParts; i += kThreads) v += parts[blockIdx.x * kParts + i];
+  for (int i = threadIdx.x; i < S.nparts; i += kThreads) v += parts[(size_t)blockIdx.x * stride + i];
   double gnew;
   double2 sa;
-  og_finish_s(S, S.r[(T.iters + 1) & 1], v, red, &gnew, &sa);
+  og_finish_s(S, S.r[(T.iters + 1) & 1], v, red, src, &gnew, &sa);
   if (threadIdx.x == 0) {
     const double beta = gnew / T.gamma;
     T.beta = beta;
@@ -419,13 +620,28 @@ __global__ void __launch_bounds__(kThreads) k_og_rnorm(const OgSys* __restrict__
   if (threadIdx.x == 0) parts[blockIdx.y * kParts + blockIdx.x] = acc;
 }
 
-// J = ||r||^2 + ||r2||^2; e^H (A u) from t = A x  (grid nsys)
+// J = ||r||^2 + ||r2||^2; e^H (A u) from A x at the source cells, each
+// rounded to float32 as a stored t = A x would be  (grid nsys)
 __global__ void __launch_bounds__(kThreads) k_og_final(const OgSys* __restrict__ sy, OgState* __restrict__ stv,
                                                        const double* __restrict__ parts) {
   __shared__ double red[kThreads / 64];
+  __shared__ double2 ax[kMaxCells];
   const OgSys& S = sy[blockIdx.x];
   OgState& T = stv[blockIdx.x];
   double v = 0.0;
+  if (S.est && (int)threadIdx.x < S.ns) {
+    const int nx = S.nx, ny = S.ny, nz = S.nz, plane = nx * ny, c = S.scell[threadIdx.x];
+    const int z = c / plane, rem = c - z * plane, y = rem / nx, x = rem - y * nx;
+    const float2 zero = make_float2(0.f, 0.f);
+    const float2* __restrict__ in = S.x;
+    const float2 xm = x > 0 ? in[c - 1] : zero, xp = x < nx - 1 ? in[c + 1] : zero;
+    const float2 ym = y > 0 ? in[c - nx] : zero, yp = y < ny - 1 ? in[c + nx] : zero;
+    const float2 zm = z > 0 ? in[c - plane] : zero, zp = z < nz - 1 ? in[c + plane] : zero;
+    const float2 t = round2(helm(in[c], xm, xp, ym, yp, zm, zp, S.h2inv, S.omega2 * (double)S.m[c],
+                                 -(S.omega * sponge_at(S, x, y, z))));
+    const double w = S.sw[threadIdx.x];
+    ax[threadIdx.x] = make_double2(w * (double)t.x, w * (double)t.y);
+  }
   for (int i = threadIdx.x; i < kParts; i += kThreads) v += parts[blockIdx.x * kParts + i];
   for (int q = threadIdx.x; q < S.nr; q += kThreads) v += nrm(S.r2[q]);
   v = bsum(v, red);
@@ -434,9 +650,8 @@ __global__ void __launch_bounds__(kThreads) k_og_final(const OgSys* __restrict__
     double er = 0.0, ei = 0.0;
     if (S.est)
       for (int i = 0; i < S.ns; ++i) {
-        const float2 x = S.t[S.scell[i]];
-        er += S.sw[i] * (double)x.x;
-        ei += S.sw[i] * (double)x.y;
+        er += ax[i].x;
+        ei += ax[i].y;
       }
     T.eau = make_double2(er, ei);
   }
@@ -575,7 +790,29 @@ hipError_t up(void* dst, const std::vector<V>& v, hipStream_t st) {
 
 int64_t ncell(const wri_grid& g) { return (int64_t)g.nx * g.ny * g.nz; }
 
+// Tiles of the window passes of a call (0: the column march), for the largest grid
+struct OgTiles { int cx, n, lds; };
+int ow_tiles(const wri_grid& g, int cx) {
+  const int b = 64 * kOwW * cx;
+  return (g.nx * g.ny + b - 1) / b * ((g.nz + kOwZ - 1) / kOwZ);
+}
+OgTiles og_tiles(const wri_grid* grids, const wri_system* sys, int n_sys) {
+  OgTiles t{1, 0, 0};
+  int nx = 1;
+  for (int k = 0; k < n_sys; ++k) {
+    const wri_grid& g = grids[sys[k].grid];
+    if (g.nx > kOwMaxRow || (int64_t)g.nx * g.ny * g.nz >= (int64_t(1) << 28)) return {1, 0, 0};
+    if (g.nx * g.ny >= 64 * 256) t.cx = 2;   // two cells a thread once a plane fills 64 tiles
+    nx = std::max(nx, g.nx);
+  }
+  for (int k = 0; k < n_sys; ++k) t.n = std::max(t.n, ow_tiles(grids[sys[k].grid], t.cx));
+  t.lds = (int)sizeof(float2) * kOwZ * (64 * kOwW * t.cx + 2 * nx);
+  return t;
+}
+
 struct OgLayout {
+  OgTiles tiles{1, 0, 0};
+  int stride = kParts;            // partial sums per system
   std::vector<size_t> vec, rvec;  // per system: 5 wavefield vectors (x unless u_out), r2 and t2
   size_t sys = 0, state = 0, parts = 0, idx = 0, total = 0;
 };
@@ -616,6 +853,8 @@ int validate_offgrid(const wri_grid* grids, int n_grids, const wri_system* sys, 
 int og_layout(const wri_grid* grids, const wri_system* sys, int n_sys, std::vector<SysTables>* tabs, OgLayout* L) {
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = al(o + std::max<size_t>(bytes, 1)); return r; };
+  L->tiles = og_tiles(grids, sys, n_sys);
+  L->stride = std::max(kParts, L->tiles.n);
   L->vec.resize(n_sys);
   L->rvec.resize(n_sys);
   for (int k = 0; k < n_sys; ++k) {
@@ -624,7 +863,7 @@ int og_layout(const wri_grid* grids, const wri_system* sys, int n_sys, std::vect
   }
   L->sys = take(sizeof(OgSys) * (size_t)std::max(n_sys, 1));
   L->state = take(sizeof(OgState) * (size_t)std::max(n_sys, 1));
-  L->parts = take(sizeof(double) * (size_t)kParts * std::max(n_sys, 1));
+  L->parts = take(sizeof(double) * (size_t)L->stride * std::max(n_sys, 1));
   L->idx = take(sizeof(int) * (size_t)std::max(n_sys, 1));
   for (auto& T : *tabs) {
     T.off = o;
@@ -707,6 +946,7 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     S.m = m[s.grid];
     S.nx = g.nx; S.ny = g.ny; S.nz = g.nz; S.nb = g.nb;
     S.zc = (int)std::max<int64_t>(1, std::min<int64_t>(kZc, n / ((int64_t)kParts * kThreads)));  // >= kParts items
+    S.nparts = L.tiles.n > 0 ? ow_tiles(g, L.tiles.cx) : kParts;
     S.h2inv = 1.0 / (g.h * g.h);
     if (g.nb > 0) {
       const double d0 = 3.0 * g.v_ref * std::log(1000.0) / (2.0 * g.nb * g.h);
@@ -732,14 +972,21 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   const dim3 vgrid(nblk(nmax), n_sys), pgrid(kParts, n_sys);
   (void)rmax;
   (void)umax;
-  // kCheck iterations of every system (finished systems skip inside the
-  // kernels), enqueued on stream sq: four launches per iteration
-  auto enqueue_chunk = [&](hipStream_t sq) -> int {
-    for (int it = 0; it < kCheck; ++it) {
-      hipLaunchKernelGGL(k_og_fwd, pgrid, dim3(kThreads), 0, sq, dsys, dst, parts);
-      hipLaunchKernelGGL(k_og_alpha, dim3(n_sys), dim3(kThreads), 0, sq, dsys, dst, parts);
-      hipLaunchKernelGGL(k_og_adj, pgrid, dim3(kThreads), 0, sq, dsys, dst, parts, 0);
-      hipLaunchKernelGGL(k_og_beta, dim3(n_sys), dim3(kThreads), 0, sq, dsys, dst, parts);
+  const OgTiles W = L.tiles;
+  const dim3 wgrid((unsigned)(W.n * (int64_t)n_sys));
+  // `count` iterations of every system (finished systems skip inside the kernels):
+  // four launches per iteration.  Eager: a graph of the chunk, which holds this
+  // workspace's pointers and so lives for one call only, cost 0.3 ms to build.
+  auto enqueue = [&](int count) -> int {
+    for (int it = 0; it < count; ++it) {
+      if (W.n == 0) hipLaunchKernelGGL(k_og_fwd, pgrid, dim3(kThreads), 0, st, dsys, dst, parts, L.stride);
+      else if (W.cx == 1) hipLaunchKernelGGL(k_ow_fwd<1>, wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
+      else hipLaunchKernelGGL(k_ow_fwd<2>, wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
+      hipLaunchKernelGGL(k_og_alpha, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts, L.stride);
+      if (W.n == 0) hipLaunchKernelGGL(k_og_adj, pgrid, dim3(kThreads), 0, st, dsys, dst, parts, L.stride, 0);
+      else if (W.cx == 1) hipLaunchKernelGGL((k_ow_adj<1, false>), wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
+      else hipLaunchKernelGGL((k_ow_adj<2, false>), wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
+      hipLaunchKernelGGL(k_og_beta, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts, L.stride);
       OG_HIP(hipGetLastError());
     }
     return WRI_OK;
@@ -747,8 +994,10 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   // set-up: x = 0, r_0 = b, s_0 = S^H b, gamma0
   hipLaunchKernelGGL(k_og_zero, vgrid, dim3(kThreads), 0, st, dsys);
   hipLaunchKernelGGL(k_og_init, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst);
-  hipLaunchKernelGGL(k_og_adj, pgrid, dim3(kThreads), 0, st, dsys, dst, parts, 1);
-  hipLaunchKernelGGL(k_og_start, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts);
+  if (W.n == 0) hipLaunchKernelGGL(k_og_adj, pgrid, dim3(kThreads), 0, st, dsys, dst, parts, L.stride, 1);
+  else if (W.cx == 1) hipLaunchKernelGGL((k_ow_adj<1, true>), wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
+  else hipLaunchKernelGGL((k_ow_adj<2, true>), wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
+  hipLaunchKernelGGL(k_og_start, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts, L.stride);
   OG_HIP(hipGetLastError());
   std::vector<OgState> hst(n_sys);
   auto read = [&]() -> int {
@@ -757,65 +1006,19 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     return WRI_OK;
   };
   if ((rc = read()) != WRI_OK) return rc;
-  // A chunk of kCheck iterations is captured once into a hipGraph (kernel
-  // nodes only) and replayed on the caller's stream; the graph lives for this
-  // call only (it holds this workspace's pointers).
-  hipStream_t cs = nullptr;
-  std::map<int, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
-  auto release = [&]() {
-    for (auto& kv : graphs) {
-      (void)hipGraphExecDestroy(kv.second.second);
-      (void)hipGraphDestroy(kv.second.first);
-    }
-    graphs.clear();
-    if (cs != nullptr) (void)hipStreamDestroy(cs);
-    cs = nullptr;
-  };
-  auto run_chunk = [&]() -> int {
-    auto it = graphs.find(0);
-    if (it == graphs.end()) {
-      if (cs == nullptr) OG_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-      OG_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-      const int e = enqueue_chunk(cs);
-      hipGraph_t graph = nullptr;
-      const hipError_t ec = hipStreamEndCapture(cs, &graph);
-      if (e != WRI_OK) {
-        if (graph) (void)hipGraphDestroy(graph);
-        return e;
-      }
-      if (ec != hipSuccess) return report_error(WRI_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(ec));
-      hipGraphExec_t exec = nullptr;
-      const hipError_t ei = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-      if (ei != hipSuccess) {
-        (void)hipGraphDestroy(graph);
-        return report_error(WRI_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(ei));
-      }
-      it = graphs.emplace(0, std::make_pair(graph, exec)).first;
-    }
-    OG_HIP(hipGraphLaunch(it->second.second, st));
-    return WRI_OK;
-  };
-  std::vector<int> active;
-  for (int64_t done = 0;; done += kCheck) {
-    active.clear();
-    for (int k = 0; k < n_sys; ++k)
-      if (hst[k].status == kActive) active.push_back(k);
-    if (active.empty()) break;
-    if (done > (int64_t)max_iter + kCheck) {
-      release();
-      return report_error(WRI_EHIP, "internal: systems active past max_iter");
-    }
-    rc = (flags & WRI_FLAG_NO_GRAPH) ? enqueue_chunk(st) : run_chunk();
+  for (int64_t done = 0;;) {
+    bool active = false;
+    for (int k = 0; k < n_sys; ++k) active |= hst[k].status == kActive;
+    if (!active) break;
+    if (done >= max_iter) return report_error(WRI_EHIP, "internal: systems active past max_iter");
+    const int count = (int)std::min<int64_t>(kCheck, max_iter - done);
+    rc = enqueue(count);
     if (rc == WRI_OK) rc = read();
-    if (rc != WRI_OK) {
-      release();
-      return rc;
-    }
+    if (rc != WRI_OK) return rc;
+    done += count;
   }
-  release();
   // objective, source weights, gradient
   hipLaunchKernelGGL(k_og_rnorm, pgrid, dim3(kThreads), 0, st, dsys, dst, parts);
-  if (mode == WRI_ESTIMATE) hipLaunchKernelGGL(k_og_ax, vgrid, dim3(kThreads), 0, st, dsys);
   OG_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_og_final, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts);
   OG_HIP(hipGetLastError());
