@@ -151,6 +151,10 @@ int validate(const wri_grid* grids, int32_t n_grids, const wri_system* sys, int3
       return fail(WRI_EINVAL, "grid %d: v_ref must be > 0 when nb > 0", i);
   }
   std::vector<int32_t> tmp;
+  auto same_receivers = [&](int a, int b) {
+    return sys[a].grid == sys[b].grid && sys[a].n_rec == sys[b].n_rec &&
+           (sys[a].n_rec <= 0 || std::memcmp(sys[a].rec, sys[b].rec, sizeof(int32_t) * sys[a].n_rec) == 0);
+  };
   for (int k = 0; k < n_sys; ++k) {
     const wri_system& s = sys[k];
     if (s.grid < 0 || s.grid >= n_grids) return fail(WRI_EINVAL, "system %d: grid index %d out of range", k, s.grid);
@@ -165,6 +169,7 @@ int validate(const wri_grid* grids, int32_t n_grids, const wri_system* sys, int3
       return fail(WRI_EINVAL, "system %d: rec or d is NULL", k);
     if (mode == WRI_KNOWN && (!std::isfinite(s.alpha.re) || !std::isfinite(s.alpha.im)))
       return fail(WRI_EINVAL, "system %d: alpha not finite", k);
+    if (k > 0 && same_receivers(k, k - 1)) continue;   // checked with the previous system
     tmp.assign(s.rec, s.rec + s.n_rec);
     for (int32_t c : tmp)
       if (c < 0 || c >= n) return fail(WRI_ERANGE, "system %d: receiver cell %d outside grid", k, c);
@@ -198,6 +203,7 @@ struct Layout {
   std::vector<RecSet> sets;
   size_t off_sysdev = 0, off_state = 0, off_part_d = 0, off_part_s = 0, off_part_j = 0, off_dot = 0;
   size_t off_gdesc = 0;
+  size_t head_bytes = 0;            // sysdev, gdesc and the receiver lists: [0, head_bytes)
   size_t off_nparts = 0;            // per processing slot: partial sums of a set-up pass (warm start)
   std::vector<size_t> off_vec;      // per processing slot: base of its 7 vectors (batched) ; plain: one slot
   std::vector<size_t> off_rvec;     // per processing slot: r2, t2
@@ -227,6 +233,13 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   L.set_of.assign(n_sys, -1);
   std::map<std::pair<int, std::vector<int32_t>>, int> seen;
   for (int i = 0; i < n_sys; ++i) {
+    if (i > 0) {   // most often the previous system's list
+      const RecSet& last = L.sets[L.set_of[i - 1]];
+      if (last.grid == sys[i].grid && std::equal(last.rec.begin(), last.rec.end(), sys[i].rec, sys[i].rec + sys[i].n_rec)) {
+        L.set_of[i] = L.set_of[i - 1];
+        continue;
+      }
+    }
     std::vector<int32_t> r(sys[i].rec, sys[i].rec + sys[i].n_rec);
     auto key = std::make_pair(sys[i].grid, r);
     auto it = seen.find(key);
@@ -243,7 +256,11 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   }
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = align_up(o + std::max<size_t>(bytes, 1)); return r; };
+  // the tables the host writes before the first launch, in one piece
   L.off_sysdev = take(sizeof(SysDev) * std::max(n_sys, 1));
+  L.off_gdesc = take(sizeof(GroupDesc) * (size_t)std::max(n_grids, 1));
+  for (auto& rs : L.sets) rs.off_rec = take(sizeof(int32_t) * rs.rec.size());
+  L.head_bytes = o;
   L.off_state = take(sizeof(SysState) * std::max(n_sys, 1));
   int slots = 0;
   L.slot_base.resize(n_sys);
@@ -264,11 +281,9 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   }
   L.dot_nparts = dot_parts((int)nmax);
   L.off_dot = take(sizeof(double) * (size_t)(L.dot_nparts * 2 + 16));
-  L.off_gdesc = take(sizeof(GroupDesc) * (size_t)std::max(n_grids, 1));
   L.off_nparts = take(sizeof(int32_t) * (size_t)std::max(n_sys, 1));
   for (auto& rs : L.sets) {
     const wri_grid& g = grids[rs.grid];
-    rs.off_rec = take(sizeof(int32_t) * rs.rec.size());
     rs.off_colmap = take(sizeof(int32_t) * 2 * (size_t)g.nx * g.ny);
     rs.off_entries = take(sizeof(int32_t) * 2 * rs.rec.size());
   }
@@ -384,6 +399,8 @@ struct Ctx {
   double* part_j = nullptr;
   double* dot = nullptr;
   int dev = 0;
+  std::vector<char> head;            // host image of the tables (read by an asynchronous copy)
+  bool colmaps = false;              // the receivers' column maps are on the device
 };
 
 template <class T>
@@ -434,17 +451,33 @@ void fill_sysdev(Ctx& C, int p, SysDev& S, float2* x, float2* r0, float2* r1, fl
   S.grid_id = s.grid;
 }
 
-int upload_receivers(Ctx& C) {
+// System table, group table and receiver lists in one copy (C.head lives until the
+// call ends).
+int upload_head(Ctx& C) {
+  C.head.assign(C.L.head_bytes, 0);
+  auto put = [&](size_t off, const void* src, size_t bytes) {
+    if (bytes > 0) std::memcpy(C.head.data() + off, src, bytes);
+  };
+  put(C.L.off_sysdev, C.hsys.data(), sizeof(SysDev) * C.hsys.size());
+  put(C.L.off_gdesc, C.hgd.data(), sizeof(GroupDesc) * C.hgd.size());
+  for (const auto& rs : C.L.sets) put(rs.off_rec, rs.rec.data(), rs.rec.size() * 4);
+  WRI_HIP(hipMemcpyAsync(C.ws, C.head.data(), C.L.head_bytes, hipMemcpyHostToDevice, C.st));
+  return WRI_OK;
+}
+
+// The slab marches find a column's receivers through a map; window tiles read the list.
+int upload_colmaps(Ctx& C) {
+  if (C.colmaps) return WRI_OK;
   for (auto& rs : C.L.sets) {
     if (rs.rec.empty()) continue;
     std::vector<int32_t> colmap, entries;
     build_colmap(C.grids[rs.grid], rs.rec, colmap, entries);
-    WRI_HIP(hipMemcpyAsync(C.ws + rs.off_rec, rs.rec.data(), rs.rec.size() * 4, hipMemcpyHostToDevice, C.st));
     WRI_HIP(hipMemcpyAsync(C.ws + rs.off_colmap, colmap.data(), colmap.size() * 4, hipMemcpyHostToDevice, C.st));
     WRI_HIP(hipMemcpyAsync(C.ws + rs.off_entries, entries.data(), entries.size() * 4, hipMemcpyHostToDevice, C.st));
     // the host vectors die at scope exit: make the copies complete first
     WRI_HIP(hipStreamSynchronize(C.st));
   }
+  C.colmaps = true;
   return WRI_OK;
 }
 
@@ -493,7 +526,8 @@ TileCfg untuned_tile(const Ctx& C) { return tiles_fit(C, kUntunedWindow) ? kUntu
 
 // One tile shape for every group: per-group tile counts and the device table
 // that maps a block of a fused launch to (group, system, tile).
-int set_config(Ctx& C, const TileCfg& cfg) {
+// upload = false: the table goes up with upload_head.
+int set_config(Ctx& C, const TileCfg& cfg, bool upload = true) {
   C.tiling.resize(C.groups.size());
   C.hgd.resize(C.groups.size());
   int b0 = 0;
@@ -529,7 +563,9 @@ int set_config(Ctx& C, const TileCfg& cfg) {
   int tmax = 1;
   for (const auto& d : C.hgd) tmax = std::max(tmax, d.ntiles);
   for (auto& d : C.hgd) d.xchunk = std::max(kMinXChunk, tmax / 2);
-  if (!C.hgd.empty()) {
+  if (cfg.pf != kWindow && !C.hgd.empty())
+    if (const int rc = upload_colmaps(C); rc != WRI_OK) return rc;
+  if (upload && !C.hgd.empty()) {
     WRI_HIP(hipMemcpyAsync(C.dgd, C.hgd.data(), sizeof(GroupDesc) * C.hgd.size(), hipMemcpyHostToDevice, C.st));
     WRI_HIP(hipStreamSynchronize(C.st));  // C.hgd may change before an asynchronous copy would finish
   }
@@ -721,34 +757,54 @@ bool forced_tile(const Ctx& C, TileCfg* out) {
   return true;
 }
 
-// Time a few real iterations of the whole batch per candidate tile shape and
-// keep the fastest; cached per (device, mode, grid shapes and system counts).
-int autotune(Ctx& C) {
-  std::string key;
+// Tuned tiles are cached per (device, mode, grid shapes and system counts).
+std::string tune_key(const Ctx& C, int64_t* total) {
+  char buf[96];
+  snprintf(buf, sizeof(buf), "%d|%d|", C.dev, C.mode);
+  std::string key = buf;
+  *total = 0;
+  for (const auto& G : C.groups) {
+    const wri_grid& g = C.grids[G.grid];
+    snprintf(buf, sizeof(buf), "%dx%dx%d:%d;", g.nx, g.ny, g.nz, G.nrhs);
+    key += buf;
+    *total += cells(g) * G.nrhs;
+  }
+  return key;
+}
+
+// The tile of a batch that needs no timing: forced, cached, or too small for the
+// choice to matter.
+bool known_tile(const Ctx& C, TileCfg* out, bool* forced) {
+  *forced = forced_tile(C, out);
+  if (*forced) return true;
+  *out = untuned_tile(C);
+  if (C.flags & WRI_FLAG_NO_AUTOTUNE) return true;
   int64_t total = 0;
-  {
-    char buf[96];
-    snprintf(buf, sizeof(buf), "%d|%d|", C.dev, C.mode);
-    key = buf;
-    for (const auto& G : C.groups) {
-      const wri_grid& g = C.grids[G.grid];
-      snprintf(buf, sizeof(buf), "%dx%dx%d:%d;", g.nx, g.ny, g.nz, G.nrhs);
-      key += buf;
-      total += cells(g) * G.nrhs;
-    }
-  }
-  auto it = g_tuned.find(key);
-  if (it != g_tuned.end()) return set_config(C, it->second);
-  if (total < (int64_t)64 * 64 * 64) {  // too small for the choice to matter
-    g_tuned[key] = untuned_tile(C);
-    return set_config(C, g_tuned[key]);
-  }
+  const auto it = g_tuned.find(tune_key(C, &total));
+  if (it != g_tuned.end()) *out = it->second;
+  return it != g_tuned.end() || total < (int64_t)64 * 64 * 64;
+}
+
+constexpr int64_t kWindowOnlyCells = 1 << 21, kSlabOnlyCells = 1 << 24;
+
+// Time a few real iterations of the whole batch per candidate tile shape and
+// keep the fastest.
+int autotune(Ctx& C) {
+  int64_t total = 0;
+  const std::string key = tune_key(C, &total);
   hipEvent_t e0, e1;
   WRI_HIP(hipEventCreate(&e0));
   WRI_HIP(hipEventCreate(&e1));
   float best = 1e30f;
   TileCfg best_cfg = kCands[0];
+  // Up to 2^21 cells every window tile's best was faster than every slab tile's (2.1 M
+  // cells: 0.148 ms against 0.230, rows of 500: 0.250 against 0.310), from 2^24 on the
+  // slabs win (16.8 M cells: 0.99 ms against 1.31); between them either may (3.9 M
+  // cells: 0.235 against 0.335 as 64^3, 0.366 against 0.322 with planes of 256 x 256).
+  const bool any_window = tiles_fit(C, kUntunedWindow);
   for (int c = 0; c < kNumCands; ++c) {
+    const bool win = kCands[c].pf == kWindow;
+    if ((!win && any_window && total <= kWindowOnlyCells) || (win && total >= kSlabOnlyCells)) continue;
     if (!tiles_fit(C, kCands[c])) continue;
     int rc = set_config(C, kCands[c]);
     if (rc == WRI_OK) rc = launch_setup(C);
@@ -849,7 +905,6 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
       fill_sysdev(C, p, C.hsys[p], x, v[1], v[2], v[3], v[4], v[5], v[6], r2, t2);
     }
   };
-  fill_tables(!warm);
   // groups: consecutive processing slots on one grid
   C.groups.clear();
   for (int p = 0; p < C.n_sys; ++p) {
@@ -861,18 +916,20 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
   TileCfg main_cfg = kCands[0];  // the tile of the full batch (reported by the timing)
   int n_switches = 0;            // tiling changes of the convergence tail
   if (C.n_sys > 0) {
-    WRI_HIP(hipMemcpyAsync(C.dsys, C.hsys.data(), sizeof(SysDev) * C.n_sys, hipMemcpyHostToDevice, C.st));
-    int rc = upload_receivers(C);
+    TileCfg cfg;
+    bool is_forced = false;
+    const bool known = known_tile(C, &cfg, &is_forced);
+    fill_tables(known || !warm);
+    int rc = set_config(C, cfg, false);
+    if (rc == WRI_OK) rc = upload_head(C);
     if (rc != WRI_OK) return rc;
-    TileCfg forced;
-    const bool is_forced = forced_tile(C, &forced);
-    if (is_forced) rc = set_config(C, forced);
-    else if (!(C.flags & WRI_FLAG_NO_AUTOTUNE)) rc = autotune(C);
-    else rc = set_config(C, untuned_tile(C));
-    if (rc != WRI_OK) return rc;
-    if (warm) {  // the tuned tile is known; now point x at the caller's initial guess
-      fill_tables(true);
-      WRI_HIP(hipMemcpyAsync(C.dsys, C.hsys.data(), sizeof(SysDev) * C.n_sys, hipMemcpyHostToDevice, C.st));
+    if (!known) {
+      rc = autotune(C);
+      if (rc != WRI_OK) return rc;
+      if (warm) {  // the tuned tile is known; now point x at the caller's initial guess
+        fill_tables(true);
+        WRI_HIP(hipMemcpyAsync(C.dsys, C.hsys.data(), sizeof(SysDev) * C.n_sys, hipMemcpyHostToDevice, C.st));
+      }
     }
     if (verbose())
       for (size_t gi = 0; gi < C.groups.size(); ++gi)
@@ -883,7 +940,11 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
     if (rc != WRI_OK) return rc;
     const bool timing = (C.flags & WRI_FLAG_TIMING) != 0;
     const bool use_graph = !(C.flags & WRI_FLAG_NO_GRAPH) && !timing;
-    int chunk = 8;
+    // Iterations between two looks at the statuses: a look leaves the chip idle for
+    // about 50 us, a launch pair on finished systems takes 6.  Every system has
+    // stopped after max_iter + 1 launch pairs.
+    const int64_t last = (int64_t)C.max_iter + 1;
+    int64_t chunk = std::min<int64_t>(16, last);
     int64_t launched = 0;
     auto last_report = std::chrono::steady_clock::now();
     main_cfg = cur_cfg(C);
@@ -902,7 +963,7 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
         }
       } else if (use_graph) {
         hipGraphExec_t ex = nullptr;
-        rc = get_graph(C, launched, chunk, &ex);
+        rc = get_graph(C, launched, (int)chunk, &ex);
         if (rc != WRI_OK) return rc;
         WRI_HIP(hipGraphLaunch(ex, C.st));
       } else {
@@ -913,6 +974,7 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
       }
       const int64_t kstart = launched;
       launched += chunk;
+      if (launched >= last && !timing) break;
       rc = read_states(C, hs);
       if (rc != WRI_OK) return rc;
       if (timing) {
@@ -989,9 +1051,8 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
                     n_active, t.tz);
         }
       }
-      if (launched > (int64_t)C.max_iter + 2)
-        return fail(WRI_EHIP, "internal: systems still active after max_iter+2 iterations");
-      chunk = std::min(chunk * 2, 128);
+      if (launched >= last) break;
+      chunk = std::min<int64_t>(std::min<int64_t>(chunk * 2, 128), last - launched);
     }
   }
   if (C.flags & WRI_FLAG_TIMING) {
@@ -1018,7 +1079,11 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
     WRI_HIP(launch_grad(C.dsys, C.dstate, G->rhs0, G->nrhs, n, gp, C.part_j, L.part_j_stride, cpt, 0, C.st));
     WRI_HIP(launch_finalize(C.dsys, C.dstate, C.part_j, grad_blocks(n, cpt), L.part_j_stride, G->rhs0, G->nrhs, C.st));
   }
-  return read_states(C, hs);
+  const int rc = read_states(C, hs);
+  if (rc != WRI_OK) return rc;
+  for (const auto& T : hs)
+    if (T.status == kActive) return fail(WRI_EHIP, "internal: systems still active after max_iter+1 iterations");
+  return WRI_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -1052,8 +1117,7 @@ int run_plain(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
     fill_sysdev(C, i, C.hsys[i], x, rv, rv, pv, pv, sv, tv, r2, t2);
   }
   if (C.n_sys > 0) {
-    WRI_HIP(hipMemcpyAsync(C.dsys, C.hsys.data(), sizeof(SysDev) * C.n_sys, hipMemcpyHostToDevice, C.st));
-    int rc = upload_receivers(C);
+    const int rc = upload_head(C);
     if (rc != WRI_OK) return rc;
   }
   for (int g = 0; g < C.n_grids; ++g)
@@ -1183,7 +1247,10 @@ int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, 
   WRI_HIP(hipGetDevice(&C.dev));
   std::vector<SysState> hs;
   rc = (flags & WRI_FLAG_PLAIN) ? run_plain(C, grad, hs) : run_batched(C, grad, hs);
-  if (rc != WRI_OK) return rc;
+  if (rc != WRI_OK) {
+    (void)hipStreamSynchronize(C.st);   // the copy of C.head may be in flight
+    return rc;
+  }
   // results (the state array is in processing order)
   std::vector<int> slot_of(n_sys);
   for (int p = 0; p < n_sys; ++p) slot_of[C.L.order[p]] = p;

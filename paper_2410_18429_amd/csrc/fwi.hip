@@ -140,7 +140,7 @@ std::vector<wri_system> forward_systems(const wri_system* sys, int n_sys, int mo
 }
 
 struct FwiLayout {
-  size_t solver = 0, solver_bytes = 0, tab = 0, total = 0;
+  size_t solver = 0, solver_bytes = 0, tab = 0, head_bytes = 0, total = 0;
   std::vector<size_t> w, z, adj, rec;
 };
 
@@ -156,14 +156,16 @@ int fwi_layout(const wri_grid* grids, int n_grids, const std::vector<wri_system>
   auto take = [&](size_t bytes) { size_t r = o; o = al(o + std::max<size_t>(bytes, 1)); return r; };
   L->solver_bytes = std::max(a, b);
   L->solver = take(L->solver_bytes);
-  L->tab = take(sizeof(FwiSys) * (size_t)std::max(n_sys, 1));
   L->w.resize(n_sys); L->z.resize(n_sys); L->adj.resize(n_sys); L->rec.resize(n_sys);
+  // the tables the host writes, in one piece
+  L->tab = take(sizeof(FwiSys) * (size_t)std::max(n_sys, 1));
+  for (int i = 0; i < n_sys; ++i) L->rec[i] = take(sizeof(int32_t) * (size_t)sf[i].n_rec);
+  L->head_bytes = o - L->tab;
   for (int i = 0; i < n_sys; ++i) {
     const size_t vb = sizeof(float2) * (size_t)ncells(grids[sf[i].grid]);
     L->w[i] = take(vb);
     L->z[i] = take(vb);
     L->adj[i] = take(sizeof(float2) * (size_t)sf[i].n_rec);
-    L->rec[i] = take(sizeof(int32_t) * (size_t)sf[i].n_rec);
   }
   L->total = o + kAl;  // slack for aligning the caller's base pointer
   return WRI_OK;
@@ -228,6 +230,8 @@ int fwi_run(const wri_grid* grids, int32_t n_grids, const float* const* m, const
   for (int i = 0; i < n_sys; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sys[a].grid < sys[b].grid; });
   std::vector<FwiSys> tab(n_sys);
+  std::vector<char> head(L.head_bytes, 0);   // image of the tables, one copy
+  struct Drain { hipStream_t st; ~Drain() { (void)hipStreamSynchronize(st); } } drain{st};   // before head goes
   for (int p = 0; p < n_sys; ++p) {
     const int i = order[p];
     FwiSys& T = tab[p];
@@ -243,13 +247,13 @@ int fwi_run(const wri_grid* grids, int32_t n_grids, const float* const* m, const
     T.estimate = mode == WRI_ESTIMATE;
     T.n = (int)ncells(grids[sys[i].grid]);
     if (sys[i].n_rec > 0)
-      FWI_HIP(hipMemcpyAsync(base + L.rec[i], sys[i].rec, sizeof(int32_t) * sys[i].n_rec, hipMemcpyHostToDevice, st));
+      std::memcpy(head.data() + (L.rec[i] - L.tab), sys[i].rec, sizeof(int32_t) * sys[i].n_rec);
   }
   FwiSys* dtab = reinterpret_cast<FwiSys*>(base + L.tab);
-  FWI_HIP(hipMemcpyAsync(dtab, tab.data(), sizeof(FwiSys) * n_sys, hipMemcpyHostToDevice, st));
+  std::memcpy(head.data(), tab.data(), sizeof(FwiSys) * n_sys);
+  FWI_HIP(hipMemcpyAsync(dtab, head.data(), L.head_bytes, hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(k_fwi_residual, dim3(n_sys), dim3(kThreads), 0, st, dtab);
   FWI_HIP(hipGetLastError());
-  FWI_HIP(hipStreamSynchronize(st));  // the host table and receiver lists are read by the copies above
 
   // 3. adjoint solves: A z = P^H conj(rho)
   std::vector<wri_system> sa = sf;

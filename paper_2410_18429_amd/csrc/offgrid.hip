@@ -22,7 +22,7 @@
 
 #include <algorithm>
 #include <cmath>
-#include <map>
+#include <cstring>
 #include <vector>
 
 namespace wri {
@@ -677,12 +677,13 @@ __global__ void __launch_bounds__(kThreads) k_og_grad(const OgSys* __restrict__ 
 // ---- host-side tables ------------------------------------------------------
 
 struct Point {
-  std::vector<int> cells;
-  std::vector<double> w;
+  int n = 0;
+  int cells[kMaxCells];
+  double w[kMaxCells];
 };
 
-// trilinear cells and weights of point xyz [m] on grid g (distinct cells,
-// zero weights dropped); the point is clamped into the grid
+// trilinear cells (ascending) and weights of point xyz [m] on grid g (zero weights
+// dropped, so cells are distinct); the point is clamped into the grid
 Point trilinear(const wri_grid& g, const double* xyz) {
   const int n[3] = {g.nx, g.ny, g.nz};
   int i0[3], i1[3];
@@ -703,89 +704,91 @@ Point trilinear(const wri_grid& g, const double* xyz) {
     w1[a] = xi - k;
     w0[a] = 1.0 - w1[a];
   }
-  std::map<int, double> acc;
+  Point p;
   for (int cz = 0; cz < 2; ++cz)
     for (int cy = 0; cy < 2; ++cy)
       for (int cx = 0; cx < 2; ++cx) {
         const int x = cx ? i1[0] : i0[0], y = cy ? i1[1] : i0[1], z = cz ? i1[2] : i0[2];
         const double w = (cx ? w1[0] : w0[0]) * (cy ? w1[1] : w0[1]) * (cz ? w1[2] : w0[2]);
-        acc[(z * g.ny + y) * g.nx + x] += w;
+        if (w == 0.0) continue;
+        p.cells[p.n] = (z * g.ny + y) * g.nx + x;
+        p.w[p.n++] = w;
       }
-  Point p;
-  for (const auto& kv : acc)
-    if (kv.second != 0.0) {
-      p.cells.push_back(kv.first);
-      p.w.push_back(kv.second);
-    }
   return p;
 }
 
-struct SysTables {
-  Point src;
+// Receiver tables of one system: cells of receiver q, and the (receiver, weight)
+// pairs of distinct cell u
+struct RecTables {
   std::vector<int> rptr, rcell;      // receiver q: cells rcell[rptr[q] .. rptr[q+1])
   std::vector<double> rw;
   std::vector<int> uptr, ucell, uq;  // distinct cell u: pairs [uptr[u] .. uptr[u+1])
   std::vector<double> uw;
-  size_t off = 0;                    // device copy in the workspace
   size_t bytes() const {
-    return al(sizeof(int) * src.cells.size()) + al(sizeof(double) * src.w.size()) + al(sizeof(int) * rptr.size()) +
-           al(sizeof(int) * rcell.size()) + al(sizeof(double) * rw.size()) + al(sizeof(int) * uptr.size()) +
-           al(sizeof(int) * ucell.size()) + al(sizeof(int) * uq.size()) + al(sizeof(double) * uw.size());
+    return al(sizeof(int) * rptr.size()) + al(sizeof(int) * rcell.size()) + al(sizeof(double) * rw.size()) +
+           al(sizeof(int) * uptr.size()) + al(sizeof(int) * ucell.size()) + al(sizeof(int) * uq.size()) +
+           al(sizeof(double) * uw.size());
   }
 };
 
-SysTables build_tables(const wri_grid& g, const wri_positions& pos, int n_rec) {
-  SysTables T;
-  T.src = trilinear(g, pos.src);
+RecTables build_receivers(const wri_grid& g, const wri_positions& pos, int n_rec) {
+  RecTables T;
+  T.rptr.reserve(n_rec + 1);
+  T.rcell.reserve((size_t)kMaxCells * n_rec);
+  T.rw.reserve((size_t)kMaxCells * n_rec);
+  std::vector<std::pair<int, int>> by_cell;   // (cell, entry): pairs of one cell in receiver order
+  by_cell.reserve((size_t)kMaxCells * n_rec);
+  std::vector<int> owner;
+  owner.reserve((size_t)kMaxCells * n_rec);
   T.rptr.push_back(0);
-  std::map<int, std::vector<std::pair<int, double>>> by_cell;
   for (int q = 0; q < n_rec; ++q) {
-    Point r = trilinear(g, pos.rec + 3 * q);
-    for (size_t j = 0; j < r.cells.size(); ++j) {
+    const Point r = trilinear(g, pos.rec + 3 * (size_t)q);
+    for (int j = 0; j < r.n; ++j) {
+      by_cell.push_back({r.cells[j], (int)T.rcell.size()});
+      owner.push_back(q);
       T.rcell.push_back(r.cells[j]);
       T.rw.push_back(r.w[j]);
-      by_cell[r.cells[j]].push_back({q, r.w[j]});
     }
     T.rptr.push_back((int)T.rcell.size());
   }
+  std::sort(by_cell.begin(), by_cell.end());
   T.uptr.push_back(0);
-  for (const auto& kv : by_cell) {
-    T.ucell.push_back(kv.first);
-    for (const auto& pr : kv.second) {
-      T.uq.push_back(pr.first);
-      T.uw.push_back(pr.second);
+  T.uq.reserve(by_cell.size());
+  T.uw.reserve(by_cell.size());
+  for (size_t i = 0; i < by_cell.size(); ++i) {
+    if (i == 0 || by_cell[i].first != by_cell[i - 1].first) {
+      if (i > 0) T.uptr.push_back((int)i);
+      T.ucell.push_back(by_cell[i].first);
     }
-    T.uptr.push_back((int)T.uq.size());
+    T.uq.push_back(owner[by_cell[i].second]);
+    T.uw.push_back(T.rw[by_cell[i].second]);
   }
+  if (!by_cell.empty()) T.uptr.push_back((int)by_cell.size());
   return T;
 }
 
-struct DevTables {  // pointers into the workspace
-  int* scell; double* sw;
-  int* rptr; int* rcell; double* rw;
-  int* uptr; int* ucell; int* uq; double* uw;
+// Tables of a call.  Systems with the previous system's receivers share its tables.
+struct SysTables {
+  std::vector<Point> src;
+  std::vector<int> set_of;
+  std::vector<RecTables> sets;
+  size_t bytes(int k) const {   // of system k's own copy
+    return al(sizeof(int) * src[k].n) + al(sizeof(double) * src[k].n) + sets[set_of[k]].bytes();
+  }
 };
 
-DevTables place(char* base, const SysTables& T) {
-  DevTables D;
-  size_t o = T.off;
-  auto take = [&](size_t bytes) { char* p = base + o; o += al(bytes); return p; };
-  D.scell = reinterpret_cast<int*>(take(sizeof(int) * T.src.cells.size()));
-  D.sw = reinterpret_cast<double*>(take(sizeof(double) * T.src.w.size()));
-  D.rptr = reinterpret_cast<int*>(take(sizeof(int) * T.rptr.size()));
-  D.rcell = reinterpret_cast<int*>(take(sizeof(int) * T.rcell.size()));
-  D.rw = reinterpret_cast<double*>(take(sizeof(double) * T.rw.size()));
-  D.uptr = reinterpret_cast<int*>(take(sizeof(int) * T.uptr.size()));
-  D.ucell = reinterpret_cast<int*>(take(sizeof(int) * T.ucell.size()));
-  D.uq = reinterpret_cast<int*>(take(sizeof(int) * T.uq.size()));
-  D.uw = reinterpret_cast<double*>(take(sizeof(double) * T.uw.size()));
-  return D;
-}
-
-template <class V>
-hipError_t up(void* dst, const std::vector<V>& v, hipStream_t st) {
-  if (v.empty()) return hipSuccess;
-  return hipMemcpyAsync(dst, v.data(), sizeof(V) * v.size(), hipMemcpyHostToDevice, st);
+SysTables build_tables(const wri_grid* grids, const wri_system* sys, int n_sys, const wri_positions* pos) {
+  SysTables T;
+  for (int k = 0; k < n_sys; ++k) {
+    const wri_grid& g = grids[sys[k].grid];
+    T.src.push_back(trilinear(g, pos[k].src));
+    const bool same = k > 0 && sys[k].grid == sys[k - 1].grid && sys[k].n_rec == sys[k - 1].n_rec &&
+                      (sys[k].n_rec == 0 ||
+                       std::memcmp(pos[k].rec, pos[k - 1].rec, sizeof(double) * 3 * (size_t)sys[k].n_rec) == 0);
+    if (!same) T.sets.push_back(build_receivers(g, pos[k], sys[k].n_rec));
+    T.set_of.push_back((int)T.sets.size() - 1);
+  }
+  return T;
 }
 
 int64_t ncell(const wri_grid& g) { return (int64_t)g.nx * g.ny * g.nz; }
@@ -813,8 +816,8 @@ OgTiles og_tiles(const wri_grid* grids, const wri_system* sys, int n_sys) {
 struct OgLayout {
   OgTiles tiles{1, 0, 0};
   int stride = kParts;            // partial sums per system
-  std::vector<size_t> vec, rvec;  // per system: 5 wavefield vectors (x unless u_out), r2 and t2
-  size_t sys = 0, state = 0, parts = 0, idx = 0, total = 0;
+  std::vector<size_t> vec, rvec;  // per system: 7 wavefield vectors (x unless u_out), r2 and t2
+  size_t sys = 0, state = 0, parts = 0, idx = 0, tables = 0, total = 0;
 };
 
 int validate_offgrid(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, const wri_positions* pos,
@@ -850,7 +853,7 @@ int validate_offgrid(const wri_grid* grids, int n_grids, const wri_system* sys, 
   return WRI_OK;
 }
 
-int og_layout(const wri_grid* grids, const wri_system* sys, int n_sys, std::vector<SysTables>* tabs, OgLayout* L) {
+int og_layout(const wri_grid* grids, const wri_system* sys, int n_sys, const SysTables& T, OgLayout* L) {
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = al(o + std::max<size_t>(bytes, 1)); return r; };
   L->tiles = og_tiles(grids, sys, n_sys);
@@ -861,14 +864,13 @@ int og_layout(const wri_grid* grids, const wri_system* sys, int n_sys, std::vect
     L->vec[k] = take(7 * al(sizeof(float2) * (size_t)ncell(grids[sys[k].grid])));
     L->rvec[k] = take(2 * al(sizeof(float2) * (size_t)sys[k].n_rec));
   }
-  L->sys = take(sizeof(OgSys) * (size_t)std::max(n_sys, 1));
   L->state = take(sizeof(OgState) * (size_t)std::max(n_sys, 1));
   L->parts = take(sizeof(double) * (size_t)L->stride * std::max(n_sys, 1));
+  // the tables the host writes, in one piece
+  L->sys = take(sizeof(OgSys) * (size_t)std::max(n_sys, 1));
   L->idx = take(sizeof(int) * (size_t)std::max(n_sys, 1));
-  for (auto& T : *tabs) {
-    T.off = o;
-    o = al(o + T.bytes());
-  }
+  L->tables = o;
+  for (int k = 0; k < n_sys; ++k) o = al(o + T.bytes(k));
   L->total = o + kAl;
   return WRI_OK;
 }
@@ -885,10 +887,9 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   for (int g = 0; g < n_grids; ++g)
     if (m[g] == nullptr || (grad != nullptr && grad[g] == nullptr))
       return report_error(WRI_EINVAL, "m[%d] or grad[%d] is NULL", g, g);
-  std::vector<SysTables> tabs(n_sys);
-  for (int k = 0; k < n_sys; ++k) tabs[k] = build_tables(grids[sys[k].grid], pos[k], sys[k].n_rec);
+  const SysTables tabs = build_tables(grids, sys, n_sys, pos);
   OgLayout L;
-  og_layout(grids, sys, n_sys, &tabs, &L);
+  og_layout(grids, sys, n_sys, tabs, &L);
   if (ws == nullptr || ws_bytes < L.total)
     return report_error(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, L.total);
   char* base = reinterpret_cast<char*>(al(reinterpret_cast<uintptr_t>(ws)));
@@ -899,19 +900,27 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     OG_HIP(hipStreamSynchronize(st));
     return WRI_OK;
   }
-  // device tables
+  // device tables: one image of [sys, end of the receiver tables), one copy
   std::vector<OgSys> hs(n_sys);
+  std::vector<char> head;
+  struct Drain { hipStream_t st; ~Drain() { (void)hipStreamSynchronize(st); } } drain{st};   // before head goes
+  head.resize(L.tables - L.sys);
+  auto put = [&](const void* v, size_t bytes) {   // appended; its device address
+    const size_t at = head.size();
+    head.resize(at + al(bytes));
+    if (bytes > 0) std::memcpy(head.data() + at, v, bytes);
+    return base + L.sys + at;
+  };
+  auto ints = [&](const std::vector<int>& v) { return reinterpret_cast<const int*>(put(v.data(), sizeof(int) * v.size())); };
+  auto dbls = [&](const std::vector<double>& v) {
+    return reinterpret_cast<const double*>(put(v.data(), sizeof(double) * v.size()));
+  };
   int64_t nmax = 1;
-  int rmax = 1, umax = 1;
   for (int k = 0; k < n_sys; ++k) {
     const wri_system& s = sys[k];
     const wri_grid& g = grids[s.grid];
-    const SysTables& T = tabs[k];
-    const DevTables D = place(base, T);
-    OG_HIP(up(D.scell, T.src.cells, st)); OG_HIP(up(D.sw, T.src.w, st));
-    OG_HIP(up(D.rptr, T.rptr, st)); OG_HIP(up(D.rcell, T.rcell, st)); OG_HIP(up(D.rw, T.rw, st));
-    OG_HIP(up(D.uptr, T.uptr, st)); OG_HIP(up(D.ucell, T.ucell, st)); OG_HIP(up(D.uq, T.uq, st));
-    OG_HIP(up(D.uw, T.uw, st));
+    const Point& src = tabs.src[k];
+    const RecTables& T = tabs.sets[tabs.set_of[k]];
     const int64_t n = ncell(g);
     const size_t vb = al(sizeof(float2) * (size_t)n);
     const size_t rb = al(sizeof(float2) * (size_t)s.n_rec);
@@ -928,11 +937,18 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     S.r2 = reinterpret_cast<float2*>(base + L.rvec[k]);
     S.t2 = reinterpret_cast<float2*>(base + L.rvec[k] + rb);
     S.d = reinterpret_cast<const float2*>(s.d);
-    S.scell = D.scell; S.sw = D.sw;
-    S.rptr = D.rptr; S.rcell = D.rcell; S.rw = D.rw;
-    S.uptr = D.uptr; S.ucell = D.ucell; S.uq = D.uq; S.uw = D.uw;
+    S.scell = reinterpret_cast<const int*>(put(src.cells, sizeof(int) * src.n));
+    S.sw = reinterpret_cast<const double*>(put(src.w, sizeof(double) * src.n));
+    if (k > 0 && tabs.set_of[k] == tabs.set_of[k - 1]) {
+      const OgSys& B = hs[k - 1];
+      S.rptr = B.rptr; S.rcell = B.rcell; S.rw = B.rw;
+      S.uptr = B.uptr; S.ucell = B.ucell; S.uq = B.uq; S.uw = B.uw;
+    } else {
+      S.rptr = ints(T.rptr); S.rcell = ints(T.rcell); S.rw = dbls(T.rw);
+      S.uptr = ints(T.uptr); S.ucell = ints(T.ucell); S.uq = ints(T.uq); S.uw = dbls(T.uw);
+    }
     S.n = (int)n;
-    S.ns = (int)T.src.cells.size();
+    S.ns = src.n;
     S.nr = s.n_rec;
     S.nu = (int)T.ucell.size();
     S.est = mode == WRI_ESTIMATE;
@@ -954,24 +970,20 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       S.inv_nb = 1.0 / g.nb;
     }
     nmax = std::max<int64_t>(nmax, n);
-    rmax = std::max(rmax, S.nr);
-    umax = std::max(umax, S.nu);
   }
   OgSys* dsys = reinterpret_cast<OgSys*>(base + L.sys);
   OgState* dst = reinterpret_cast<OgState*>(base + L.state);
   double* parts = reinterpret_cast<double*>(base + L.parts);
   int* didx = reinterpret_cast<int*>(base + L.idx);
-  OG_HIP(hipMemcpyAsync(dsys, hs.data(), sizeof(OgSys) * n_sys, hipMemcpyHostToDevice, st));
   // systems grouped by grid for the gradient pass
   std::vector<int> order(n_sys);
   for (int k = 0; k < n_sys; ++k) order[k] = k;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sys[a].grid < sys[b].grid; });
-  OG_HIP(hipMemcpyAsync(didx, order.data(), sizeof(int) * n_sys, hipMemcpyHostToDevice, st));
-  OG_HIP(hipStreamSynchronize(st));  // the host tables are read by the copies above
+  std::memcpy(head.data(), hs.data(), sizeof(OgSys) * n_sys);
+  std::memcpy(head.data() + (L.idx - L.sys), order.data(), sizeof(int) * n_sys);
+  OG_HIP(hipMemcpyAsync(base + L.sys, head.data(), head.size(), hipMemcpyHostToDevice, st));
 
   const dim3 vgrid(nblk(nmax), n_sys), pgrid(kParts, n_sys);
-  (void)rmax;
-  (void)umax;
   const OgTiles W = L.tiles;
   const dim3 wgrid((unsigned)(W.n * (int64_t)n_sys));
   // `count` iterations of every system (finished systems skip inside the kernels):
@@ -1005,17 +1017,17 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     OG_HIP(hipStreamSynchronize(st));
     return WRI_OK;
   };
-  if ((rc = read()) != WRI_OK) return rc;
-  for (int64_t done = 0;;) {
-    bool active = false;
-    for (int k = 0; k < n_sys; ++k) active |= hst[k].status == kActive;
-    if (!active) break;
-    if (done >= max_iter) return report_error(WRI_EHIP, "internal: systems active past max_iter");
-    const int count = (int)std::min<int64_t>(kCheck, max_iter - done);
-    rc = enqueue(count);
-    if (rc == WRI_OK) rc = read();
-    if (rc != WRI_OK) return rc;
+  // Every system has stopped after max_iter iterations, so the statuses are looked at
+  // between chunks only.
+  for (int64_t done = 0, chunk = kCheck / 2; done < max_iter; chunk = kCheck) {
+    const int count = (int)std::min<int64_t>(chunk, max_iter - done);
+    if ((rc = enqueue(count)) != WRI_OK) return rc;
     done += count;
+    if (done >= max_iter) break;
+    if ((rc = read()) != WRI_OK) return rc;
+    bool active = false;
+    for (const auto& T : hst) active |= T.status == kActive;
+    if (!active) break;
   }
   // objective, source weights, gradient
   hipLaunchKernelGGL(k_og_rnorm, pgrid, dim3(kThreads), 0, st, dsys, dst, parts);
@@ -1033,12 +1045,14 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       p0 += cnt;
     }
   if ((rc = read()) != WRI_OK) return rc;
+  for (const auto& T : hst)
+    if (T.status == kActive) return report_error(WRI_EHIP, "internal: systems active past max_iter");
   double Jtot = 0.0;
   int ret = WRI_OK;
   for (int k = 0; k < n_sys; ++k) {
     const OgState& T = hst[k];
     double ee = 0.0;
-    for (double w : tabs[k].src.w) ee += w * w;
+    for (int i = 0; i < tabs.src[k].n; ++i) ee += tabs.src[k].w[i] * tabs.src[k].w[i];
     wri_result& r = res[k];
     r.iters = T.iters;
     r.status = T.status;
@@ -1071,10 +1085,8 @@ size_t wri_offgrid_workspace_bytes(const wri_grid* grids, int32_t n_grids, const
                                    const wri_positions* pos) {
   try {
     if (validate_offgrid(grids, n_grids, sys, n_sys, pos, WRI_ESTIMATE, 0) != WRI_OK) return 0;
-    std::vector<SysTables> tabs(n_sys);
-    for (int k = 0; k < n_sys; ++k) tabs[k] = build_tables(grids[sys[k].grid], pos[k], sys[k].n_rec);
     OgLayout L;
-    og_layout(grids, sys, n_sys, &tabs, &L);
+    og_layout(grids, sys, n_sys, build_tables(grids, sys, n_sys, pos), &L);
     return L.total;
   } catch (const std::exception& e) {
     report_error(WRI_EINVAL, "exception: %s", e.what());

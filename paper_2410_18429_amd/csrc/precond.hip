@@ -28,6 +28,7 @@
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 namespace wri {
@@ -1331,7 +1332,7 @@ std::vector<LevelDims> levels_of(const wri_grid& g) {
 int64_t cells_of(const LevelDims& d) { return (int64_t)d.nx * d.ny * d.nz; }
 
 struct PcLayout {
-  size_t sys = 0, state = 0, parts = 0, idx = 0, total = 0;
+  size_t sys = 0, state = 0, parts = 0, idx = 0, head_bytes = 0, total = 0;
   int stride = kParts;               // partial sums per system
   std::vector<size_t> grid_arrays;   // per grid: m_l (l >= 1) and b_l (l >= 0)
   std::vector<std::pair<int, double>> pairs;   // distinct (grid, omega) of the systems
@@ -1359,14 +1360,18 @@ PcLayout pc_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   PcLayout L;
   size_t o = 0;
   auto take = [&](size_t b) { size_t r = o; o = al(o + std::max<size_t>(b, 1)); return r; };
+  // the tables the host writes, in one piece
+  L.rec.resize(n_sys);
   L.sys = take(sizeof(PcSys) * std::max(n_sys, 1));
+  L.idx = take(sizeof(int) * std::max(n_sys, 1));
+  for (int k = 0; k < n_sys; ++k) L.rec[k] = take(sizeof(int) * (size_t)sys[k].n_rec);
+  L.head_bytes = o;
   L.state = take(sizeof(PcState) * std::max(n_sys, 1));
   for (int k = 0; k < n_sys; ++k) {
     const auto lv = levels_of(grids[sys[k].grid]);
     if (pc_tiled(lv)) L.stride = std::max(L.stride, pc_tiles(lv[0]).n);
   }
   L.parts = take(sizeof(double) * (size_t)L.stride * std::max(n_sys, 1));
-  L.idx = take(sizeof(int) * std::max(n_sys, 1));
   L.grid_arrays.resize(n_grids);
   for (int g = 0; g < n_grids; ++g) {
     size_t b = 0;
@@ -1387,7 +1392,6 @@ PcLayout pc_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   }
   L.vec.resize(n_sys);
   L.rvec.resize(n_sys);
-  L.rec.resize(n_sys);
   for (int k = 0; k < n_sys; ++k) {
     const wri_grid& g = grids[sys[k].grid];
     const auto lv = levels_of(g);
@@ -1396,7 +1400,6 @@ PcLayout pc_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
     for (size_t l = 1; l < lv.size(); ++l) b += 4 * al(sizeof(float2) * (size_t)cells_of(lv[l]));
     L.vec[k] = take(b);
     L.rvec[k] = take(2 * al(sizeof(float2) * (size_t)sys[k].n_rec));
-    L.rec[k] = take(sizeof(int) * (size_t)sys[k].n_rec);
   }
   L.total = o + kAl;
   return L;
@@ -1488,6 +1491,8 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   struct Group { int grid, p0, cnt; int64_t n; };
   std::vector<Group> groups;
   std::vector<PcSys> hs(n_sys);
+  std::vector<char> head(L.head_bytes, 0);   // image of the tables, one copy
+  struct Drain { hipStream_t st; ~Drain() { (void)hipStreamSynchronize(st); } } drain{st};   // before head goes
   for (int p = 0; p < n_sys; ++p) {
     const int k = order[p];
     const wri_system& s = sys[k];
@@ -1535,7 +1540,7 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     S.t2 = reinterpret_cast<float2*>(base + L.rvec[k] + rb);
     S.d = reinterpret_cast<const float2*>(s.d);
     int* drec = reinterpret_cast<int*>(base + L.rec[k]);
-    if (s.n_rec > 0) PC_HIP(hipMemcpyAsync(drec, s.rec, sizeof(int) * s.n_rec, hipMemcpyHostToDevice, st));
+    if (s.n_rec > 0) std::memcpy(head.data() + L.rec[k], s.rec, sizeof(int) * s.n_rec);
     S.rec = drec;
     S.m = m[s.grid];
     S.n = (int)n; S.nx = g.nx; S.ny = g.ny; S.nz = g.nz; S.nb = g.nb; S.nr = s.n_rec;
@@ -1558,11 +1563,9 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   PcState* dst = reinterpret_cast<PcState*>(base + L.state);
   double* parts = reinterpret_cast<double*>(base + L.parts);
   int* didx = reinterpret_cast<int*>(base + L.idx);
-  std::vector<int> ident(n_sys);
-  for (int p = 0; p < n_sys; ++p) ident[p] = p;
-  PC_HIP(hipMemcpyAsync(dsys, hs.data(), sizeof(PcSys) * n_sys, hipMemcpyHostToDevice, st));
-  PC_HIP(hipMemcpyAsync(didx, ident.data(), sizeof(int) * n_sys, hipMemcpyHostToDevice, st));
-  PC_HIP(hipStreamSynchronize(st));  // host tables are read by the copies above
+  std::memcpy(head.data() + L.sys, hs.data(), sizeof(PcSys) * n_sys);
+  for (int p = 0; p < n_sys; ++p) std::memcpy(head.data() + L.idx + sizeof(int) * p, &p, sizeof(int));
+  PC_HIP(hipMemcpyAsync(base, head.data(), L.head_bytes, hipMemcpyHostToDevice, st));
 
   const int stride = L.stride;
   // tiled pass on level d: launch LAUNCH(template cx, grid, dynamic LDS of one element of `elem` bytes per cell)
@@ -1676,22 +1679,20 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     PC_HIP(hipStreamSynchronize(st));
     return WRI_OK;
   };
-  if ((rc = read()) != WRI_OK) return rc;
   // Eager launches: a pass takes longer than the host needs to enqueue the next, and
   // building a graph of a chunk cost more than a solve of a few iterations (1.9 ms
-  // for 624 nodes).
-  int64_t done = 0;
-  while (true) {
-    bool any = false;
-    for (const auto& T : hst) any = any || (T.status == kActive);
-    if (!any) break;
-    if (done > (int64_t)max_iter + kCheck)
-      return report_error(WRI_EHIP, "internal: systems still active after max_iter iterations");
-    const int chunk = (int)std::min<int64_t>(kCheck, std::max<int64_t>(1, max_iter - done));
+  // for 624 nodes).  Every system has stopped after max_iter iterations, so the
+  // statuses are looked at between chunks only.
+  for (int64_t done = 0; done < max_iter;) {
+    const int chunk = (int)std::min<int64_t>(kCheck, max_iter - done);
     for (int i = 0; i < chunk; ++i)
       if ((rc = iteration()) != WRI_OK) return rc;
     done += chunk;
+    if (done >= max_iter) break;
     if ((rc = read()) != WRI_OK) return rc;
+    bool any = false;
+    for (const auto& T : hst) any = any || (T.status == kActive);
+    if (!any) break;
   }
   // results: J, alpha_ls, gradient per grid
   for (const Group& G : groups) {
@@ -1715,6 +1716,8 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     }
   }
   if ((rc = read()) != WRI_OK) return rc;
+  for (const auto& T : hst)
+    if (T.status == kActive) return report_error(WRI_EHIP, "internal: systems still active after max_iter iterations");
   int ret = WRI_OK;
   double J = 0.0;
   for (int p = 0; p < n_sys; ++p) {
