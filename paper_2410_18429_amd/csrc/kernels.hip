@@ -1973,12 +1973,13 @@ k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
   for (int j = 0; j < CX; ++j) {
     int x, y;
     Q.row_of(Q.cell[j], &x, &y);
+    const unsigned mxm = row_mask(x > 0), mxp = row_mask(x < nx - 1);
     const double sxy2 = sponge_axis_d(x, nx, nb, inv_nb) + sponge_axis_d(y, Q.ny, nb, inv_nb);
 #pragma unroll
     for (int i = 0; i < TZ; ++i) {
       const float2* row = win + i * wl + nx + j * NT + tid;
-      const float2 xm = x > 0 ? row[-1] : f2(0.f, 0.f);
-      const float2 xp = x < nx - 1 ? row[1] : f2(0.f, 0.f);
+      const float2 xm = masked(row[-1], mxm);
+      const float2 xp = masked(row[1], mxp);
       const float2 ym = row[-nx], yp = row[nx];
       const double b = sp_scale * (sxy2 + sponge_axis_d(Q.z0 + i, Q.nz, nb, inv_nb));
       double2 td = helm(pv[j][i + 1], xm, xp, ym, yp, pv[j][i], pv[j][i + 2], h2inv, w2 * (double)mm[j][i], -(om * b));
@@ -2132,12 +2133,13 @@ k_adj_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
   for (int j = 0; j < CX; ++j) {
     int x, y;
     Q.row_of(Q.cell[j], &x, &y);
+    const unsigned mxm = row_mask(x > 0), mxp = row_mask(x < nx - 1);
     const double sxy2 = sponge_axis_d(x, nx, nb, inv_nb) + sponge_axis_d(y, Q.ny, nb, inv_nb);
 #pragma unroll
     for (int i = 0; i < TZ; ++i) {
       const float2* row = win + i * wl + nx + j * NT + tid;
-      const float2 xm = x > 0 ? row[-1] : f2(0.f, 0.f);
-      const float2 xp = x < nx - 1 ? row[1] : f2(0.f, 0.f);
+      const float2 xm = masked(row[-1], mxm);
+      const float2 xp = masked(row[1], mxp);
       const float2 ym = row[-nx], yp = row[nx];
       const double b = sp_scale * (sxy2 + sponge_axis_d(Q.z0 + i, Q.nz, nb, inv_nb));
       double2 sd = helm(rv[j][i + 1], xm, xp, ym, yp, rv[j][i], rv[j][i + 2], h2inv, w2 * (double)mm[j][i], om * b);
@@ -2544,12 +2546,13 @@ k_apply_win(int nx, int ny, int nz, int nbw, double h2inv, double sp_scale, doub
   for (int j = 0; j < kApplyC; ++j) {
     int x, y;
     Q.row_of(Q.cell[j], &x, &y);
+    const unsigned mxm = row_mask(x > 0), mxp = row_mask(x < nx - 1);
     const double sxy2 = sponge_axis_d(x, nx, nbw, inv_nb) + sponge_axis_d(y, ny, nbw, inv_nb);
 #pragma unroll
     for (int i = 0; i < kApplyZ; ++i) {
       const float2* row = win + i * wl + nx + j * NT + tid;
-      const float2 xm = x > 0 ? row[-1] : f2(0.f, 0.f);
-      const float2 xp = x < nx - 1 ? row[1] : f2(0.f, 0.f);
+      const float2 xm = masked(row[-1], mxm);
+      const float2 xp = masked(row[1], mxp);
       const float2 ym = row[-nx], yp = row[nx];
       const double b = sp_scale * (sxy2 + sponge_axis_d(Q.z0 + i, nz, nbw, inv_nb));
       double2 o = helm(v[j][i + 1], xm, xp, ym, yp, v[j][i], v[j][i + 2], h2inv, w2 * (double)mm[j][i],

@@ -333,7 +333,7 @@ __global__ void __launch_bounds__(kThreads) k_og_adj(const OgSys* __restrict__ s
 // columns and a load latency and two barriers per plane: what bounded it on batches
 // that fit the caches.  Every stored value is rounded where it was; only the order of
 // the float64 sums differs.  Per iteration (four launches): 8 systems of 64^3 78 us before
-// and 47 now, 2 of 24x20x18 35 and 23, 48 of 128^3 2.07 ms and 1.74 (88 bytes a cell at
+// and 44 now, 2 of 24x20x18 35 and 23, 48 of 128^3 2.07 ms and 1.74 (88 bytes a cell at
 // 5.1 TB/s: memory).
 // ---------------------------------------------------------------------------
 constexpr int kOwW = 4, kOwZ = 4;
@@ -406,12 +406,12 @@ k_ow_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* 
   for (int j = 0; j < CX; ++j) {
     int cx, cy;
     Q.row_of(Q.cell[j], &cx, &cy);
+    const unsigned mxm = row_mask(cx > 0), mxp = row_mask(cx < nx - 1);
     const double sxy = sponge_axis_d(cx, nx, S.nb, S.inv_nb) + sponge_axis_d(cy, Q.ny, S.nb, S.inv_nb);
 #pragma unroll
     for (int i = 0; i < kOwZ; ++i) {
       const float2* row = ow_f + i * wl + nx + j * NT + tid;
-      const float2 zero = make_float2(0.f, 0.f);
-      const float2 xm = cx > 0 ? row[-1] : zero, xp = cx < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const float2 xm = masked(row[-1], mxm), xp = masked(row[1], mxp), ym = row[-nx], yp = row[nx];
       const double b = S.sp_scale * (sxy + sponge_axis_d(Q.z0 + i, Q.nz, S.nb, S.inv_nb));
       const float2 t = round2(helm(v[j][i + 1], xm, xp, ym, yp, v[j][i], v[j][i + 2], S.h2inv,
                                    S.omega2 * (double)mm[j][i], -(S.omega * b)));
@@ -494,12 +494,12 @@ k_ow_adj(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* 
   for (int j = 0; j < CX; ++j) {
     int cx, cy;
     Q.row_of(Q.cell[j], &cx, &cy);
+    const unsigned mxm = row_mask(cx > 0), mxp = row_mask(cx < nx - 1);
     const double sxy = sponge_axis_d(cx, nx, S.nb, S.inv_nb) + sponge_axis_d(cy, Q.ny, S.nb, S.inv_nb);
 #pragma unroll
     for (int i = 0; i < kOwZ; ++i) {
       const float2* row = ow_f + i * wl + nx + j * NT + tid;
-      const float2 zero = make_float2(0.f, 0.f);
-      const float2 xm = cx > 0 ? row[-1] : zero, xp = cx < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const float2 xm = masked(row[-1], mxm), xp = masked(row[1], mxp), ym = row[-nx], yp = row[nx];
       const double b = S.sp_scale * (sxy + sponge_axis_d(Q.z0 + i, Q.nz, S.nb, S.inv_nb));
       const float2 s = round2(helm(v[j][i + 1], xm, xp, ym, yp, v[j][i], v[j][i + 2], S.h2inv,
                                    S.omega2 * (double)mm[j][i], S.omega * b));

@@ -589,8 +589,8 @@ __global__ void __launch_bounds__(kThr) k_pc_vsingle_out(const PcSys* __restrict
 // through the order of the float64 sums; r and p are written to their other
 // buffer because neighbouring tiles still read the old one.
 //
-// Per iteration (eager launches): 8 systems of 64^3 401 us before and 201 now,
-// 48 of 128^3 11.7 ms and 5.14, 2 of 24x20x18 178 us and 79.
+// Per iteration (eager launches): 8 systems of 64^3 401 us before and 195 now,
+// 48 of 128^3 11.7 ms and 5.04, 2 of 24x20x18 178 us and 77.
 // ---------------------------------------------------------------------------
 
 constexpr int kPcW = 4, kPcZ = 4;
@@ -691,11 +691,11 @@ k_pw_down(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0,
   for (int j = 0; j < CX; ++j) {
     int cx, cy;
     Q.row_of(Q.cell[j], &cx, &cy);
+    const unsigned mxm = row_mask(cx > 0), mxp = row_mask(cx < nx - 1);
 #pragma unroll
     for (int i = 0; i < kPcZ; ++i) {
       const double2* row = pw_y + i * wl + nx + j * NT + tid;
-      const double2 zero = make_double2(0.0, 0.0);
-      const double2 xm = cx > 0 ? row[-1] : zero, xp = cx < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const double2 xm = masked(row[-1], mxm), xp = masked(row[1], mxp), ym = row[-nx], yp = row[nx];
       const double2 yc = y[j][i + 1], zm = y[j][i], zp = y[j][i + 2];
       const double sr = ((((xm.x + xp.x) + ym.x) + yp.x) + zm.x) + zp.x;
       const double si = ((((xm.y + xp.y) + ym.y) + yp.y) + zm.y) + zp.y;
@@ -761,7 +761,7 @@ k_pw_restrict(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int
 // One column of P e on the coarse planes z0 / 2 - 1 + p, interpolated in x and y
 // (exact in float64, see the restriction).  Cells outside the coarse grid read zero.
 template <int NP>
-__device__ __forceinline__ void coarse_column(const float2* e, const PcLevel& C, bool ok, int x, int y, int z0,
+__device__ __forceinline__ void coarse_column(BufRes R, const PcLevel& C, bool ok, int x, int y, int z0,
                                               double2 (&out)[NP]) {
   const bool ox = x & 1, oy = y & 1;
   const int x1 = x >> 1, x0 = ox ? x1 : x1 - 1;   // odd: one coarse cell; even: two
@@ -777,10 +777,9 @@ __device__ __forceinline__ void coarse_column(const float2* e, const PcLevel& C,
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     const int z = z0 / 2 - 1 + p;
-    const bool bz = z >= 0 && z < C.nz;
-    const BufRes R = mkbuf(e, bz ? (int64_t)z * plane : 0, bz ? plane : 0, 8);
+    const unsigned zo = z >= 0 && z < C.nz ? (unsigned)(z * plane * 8) : kOOB;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[p][i] = bld2(R, o[i]);
+    for (int i = 0; i < 4; ++i) v[p][i] = bld2(R, (o[i] & kOOB) ? kOOB : o[i] + zo);
   }
 #pragma unroll
   for (int p = 0; p < NP; ++p)
@@ -818,7 +817,7 @@ k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* _
   Q.setup(L.nx, L.ny, L.nz, tile, tiles_x);
   const int nx = Q.nx, wl = Q.wl;
   const float2* f = level_in(S, T.iters, l, which);
-  const float2* e = coarse_out(S, l + 1);
+  const BufRes Re = mkbuf(coarse_out(S, l + 1), 0, C.n, 8);   // one resource: per plane ones became a loop per load
   float2* out = l > 0 ? L.o : (which ? S.z : S.q);
   float2 fv[CX][kPcZ + 2], wv[CX][kPcZ + 2];
   float mm[CX][kPcZ], bb[CX][kPcZ];
@@ -850,7 +849,7 @@ k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* _
     int x, y;
     Q.row_of((h < nx ? Q.c0 - nx + h : Q.c0 + Tile::B + (h - nx)) + nx, &x, &y);   // the row above: not negative
     double2 ec[NP];
-    coarse_column(e, C, ok, x, y - 1, Q.z0, ec);
+    coarse_column(Re, C, ok, x, y - 1, Q.z0, ec);
 #pragma unroll
     for (int i = 0; i < kPcZ; ++i) {
       const double2 jv = jac_w(hw[i], conj, hf[i]), pe = prolong_z(ec, i + 1);
@@ -864,7 +863,7 @@ k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* _
     int cy;
     Q.row_of(Q.cell[j], &cx[j], &cy);
     double2 ec[NP];
-    coarse_column(e, C, Q.in[j], cx[j], cy, Q.z0, ec);
+    coarse_column(Re, C, Q.in[j], cx[j], cy, Q.z0, ec);
 #pragma unroll
     for (int i = 0; i < kPcZ + 2; ++i) {
       const double2 jv = jac_w(wv[j][i], conj, fv[j][i]), pe = prolong_z(ec, i);
@@ -875,12 +874,12 @@ k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* _
   __syncthreads();
   double acc = 0.0;
 #pragma unroll
-  for (int j = 0; j < CX; ++j)
+  for (int j = 0; j < CX; ++j) {
+    const unsigned mxm = row_mask(cx[j] > 0), mxp = row_mask(cx[j] < nx - 1);
 #pragma unroll
     for (int i = 0; i < kPcZ; ++i) {
       const float2* row = pw_f + i * wl + nx + j * NT + tid;
-      const float2 zero = make_float2(0.f, 0.f);
-      const float2 xm = cx[j] > 0 ? row[-1] : zero, xp = cx[j] < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const float2 xm = masked(row[-1], mxm), xp = masked(row[1], mxp), ym = row[-nx], yp = row[nx];
       const float2 xc = yv[j][i + 1], zm = yv[j][i], zp = yv[j][i + 2], fc = fv[j][i + 1];
       const double2 d = diag_mb(S, L.h2inv, mm[j][i], bb[j][i], conj);
       const double sr = (((double)xm.x + xp.x) + ((double)ym.x + yp.x)) + ((double)zm.x + zp.x);
@@ -892,6 +891,7 @@ k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* _
       Q.store2(out, i + 1, Q.own2(j), o);
       if (Q.live(j, i)) acc += nrm(o);
     }
+  }
   if (l == 0 && which) {
     const double tot = bsum(acc, red);
     if (tid == 0) part[(size_t)k * stride + tile] = tot;
@@ -973,12 +973,12 @@ k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double
   for (int j = 0; j < CX; ++j) {
     int cx, cy;
     Q.row_of(Q.cell[j], &cx, &cy);
+    const unsigned mxm = row_mask(cx > 0), mxp = row_mask(cx < nx - 1);
     const double sxy = sponge_axis_d(cx, nx, S.nb, S.inv_nb) + sponge_axis_d(cy, Q.ny, S.nb, S.inv_nb);
 #pragma unroll
     for (int i = 0; i < kPcZ; ++i) {
       const float2* row = pw_f + i * wl + nx + j * NT + tid;
-      const float2 zero = make_float2(0.f, 0.f);
-      const float2 xm = cx > 0 ? row[-1] : zero, xp = cx < nx - 1 ? row[1] : zero, ym = row[-nx], yp = row[nx];
+      const float2 xm = masked(row[-1], mxm), xp = masked(row[1], mxp), ym = row[-nx], yp = row[nx];
       const double kim = S.omega * (S.sp_scale * (sxy + sponge_axis_d(Q.z0 + i, Q.nz, S.nb, S.inv_nb)));
       double2 y = helm(v[j][i + 1], xm, xp, ym, yp, v[j][i], v[j][i + 2], S.h2inv, S.omega2 * (double)mm[j][i],
                        ADJ ? kim : -kim);
