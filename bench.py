@@ -57,7 +57,8 @@ def kernel_label(dominant, pf):
 # probe with the tile forced), each scaled by what the counter reads for a 1 GiB device copy
 # (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000).  "fwd_x" is the forward launch that also updates x
 # (even iterations).  Valid only for the solver sources it was measured on (sha256 prefix of
-# kernels.hip + capi.hip + wri_impl.hpp + stencil.hpp) and for the tile shape in the key;
+# kernels.hip + capi.hip + wri_impl.hpp + stencil.hpp + wave.hpp + window.hpp) and for the
+# tile shape in the key;
 # summary and commands: profiles/fused_cgls_kernels_128cube_48sys_hbm_traffic.md
 TRAFFIC = {
     "sources_sha256": "1d0cda1bde45a0f6",
@@ -76,7 +77,7 @@ TRAFFIC = {
 def _sources_sha():
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hip", "capi.hip", "wri_impl.hpp", "stencil.hpp"):
+    for f in ("kernels.hip", "capi.hip", "wri_impl.hpp", "stencil.hpp", "wave.hpp", "window.hpp"):
         with open(os.path.join(ROOT, "paper_2410_18429_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -97,8 +98,7 @@ def _cpu_worker(args):
     return out["iters"], out["seconds"], time.perf_counter() - t0
 
 
-# Cores this job may use on the GPU machine: the box allots 16 host cores per GPU
-# (more worker processes than that are killed), whatever os.cpu_count() says.
+# Host cores per GPU that this job may use, whatever os.cpu_count() says.
 HOST_CORE_SHARE = 16
 
 
