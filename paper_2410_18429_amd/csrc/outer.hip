@@ -432,9 +432,12 @@ int grid_blocks(int64_t n) { return (int)std::min<int64_t>(kRedBlocks, std::max<
 // ---- host helpers ----------------------------------------------------------------
 size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
-// per-block partials of the value and their sum
+// Room for three float64 arrays of the grid and kRedBlocks + 1 sums (what the query has
+// always returned).  The one pass keeps only per-workgroup partials (at most kTvBlocks,
+// and at most one a cell) in the first part and their sum in the last.
 constexpr int kTvBlocks = 2048;
-size_t tv_ws_bytes() { return al(sizeof(double) * (kTvBlocks + 1)); }
+size_t tv_sum_off(int64_t n) { return 3 * al(sizeof(double) * n); }
+size_t tv_ws_bytes(int64_t n) { return tv_sum_off(n) + al(sizeof(double) * (kRedBlocks + 1)); }
 
 // sum of n partials in one fixed order (one block)
 __global__ void __launch_bounds__(kRedThreads) k_sum_parts(const double* __restrict__ part, int n, double* __restrict__ out) {
@@ -471,15 +474,17 @@ int tv_launch(const wri_grid& g, const float* m, double eps, double scale, float
 // TV(m) (host value) and, if grad != null, grad += gamma * grad TV
 int tv_run(const wri_grid& g, const float* m, double eps, double gamma, double* value, float* grad, char* ws,
            hipStream_t st) {
+  const int64_t n = (int64_t)g.nx * g.ny * g.nz;
   double* part = reinterpret_cast<double*>(ws);
+  double* sum = reinterpret_cast<double*>(ws + tv_sum_off(n));
   float* gr = gamma != 0.0 ? grad : nullptr;
-  const int nb = (int64_t)g.nx * g.ny * g.nz < (int64_t(1) << 31)
+  const int nb = n < (int64_t(1) << 31)
                      ? tv_launch<int>(g, m, eps, gamma / g.h, gr, part, st)
                      : tv_launch<int64_t>(g, m, eps, gamma / g.h, gr, part, st);
   OUTER_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(kRedThreads), 0, st, part, nb, part + kTvBlocks);
+  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(kRedThreads), 0, st, part, nb, sum);
   OUTER_HIP(hipGetLastError());
-  OUTER_HIP(hipMemcpyAsync(value, part + kTvBlocks, sizeof(double), hipMemcpyDeviceToHost, st));
+  OUTER_HIP(hipMemcpyAsync(value, sum, sizeof(double), hipMemcpyDeviceToHost, st));
   OUTER_HIP(hipStreamSynchronize(st));
   return WRI_OK;
 }
@@ -596,7 +601,7 @@ AwriLayout awri_layout(int64_t n, size_t solver_bytes, int memory, int n_sys, bo
   const size_t vb = al(sizeof(float) * n);
   size_t off = L.off_vec + vb * (size_t)(5 + 2 * std::max(memory, 0));  // g, g_try, m_try, dir, tmp, S, Y
   L.off_tv = off;
-  off += tv_ws_bytes();
+  off += tv_ws_bytes(n);
   L.off_lb = off;
   off += lb_ws_bytes(std::max(memory, 1));
   L.off_red = off;
@@ -640,7 +645,7 @@ extern "C" {
 
 size_t wri_tv_workspace_bytes(const wri_grid* grid) {
   if (grid == nullptr || grid->nx < 1 || grid->ny < 1 || grid->nz < 1) return 0;
-  return tv_ws_bytes() + 256;
+  return tv_ws_bytes((int64_t)grid->nx * grid->ny * grid->nz) + 256;
 }
 
 int wri_tv(const wri_grid* grid, const float* m, double eps, double gamma, double* value, float* grad, void* ws,
