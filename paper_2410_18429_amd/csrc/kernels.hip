@@ -2510,7 +2510,8 @@ k_apply(int nx, int ny, int nz, int nbw, double h2inv, double sp_scale, double i
 
 // The same operator by window tiles (see the window march): every load of the
 // tile at once, no division per cell.  256x256x192: 116 -> 50 us (252 MB, 5.0
-// TB/s), 128^3 22 -> 10 us; the widest rows (over 512 cells) keep the kernel above.
+// TB/s), 128^3 22 -> 10 us; the widest rows (over 512 cells) and the smallest grids keep
+// the kernel above.
 constexpr int kApplyW = 4, kApplyC = 4, kApplyZ = 4;
 constexpr size_t kApplyMaxLds = 64 * 1024;
 
@@ -2589,7 +2590,10 @@ hipError_t launch_apply(int nx, int ny, int nz, int nb, double h2inv, double sp_
   if (n == 0) return hipSuccess;
   const TileCfg c{kApplyW, kApplyC, kApplyZ, kWindow, 0};
   const size_t lds = win_lds_bytes(c, nx);
-  if (lds <= kApplyMaxLds) {   // rows of up to 512 cells
+  // rows of up to 512 cells; grids of up to 64^3 are a launch's latency either way, and one
+  // cell a thread is the shorter one (a call and its wait 19.9 us against 21.5 on 48^3, 20.1
+  // against 21.6 on 64^3; 25.2 against 22.0 on 96^3)
+  if (lds <= kApplyMaxLds && n > ((size_t)1 << 18)) {
     const int64_t tx = ((int64_t)nx * ny + c.win_cells() - 1) / c.win_cells(), tz = (nz + kApplyZ - 1) / kApplyZ;
     hipLaunchKernelGGL(k_apply_win, dim3((unsigned)(tx * tz)), dim3(64 * kApplyW), (unsigned)lds, s, nx, ny, nz, nb,
                        h2inv, sp_scale, inv_nb, omega, m, in, out, adjoint, src, src_sub, (int)tx,

@@ -23,10 +23,12 @@ def rel(a, b):
     return float(np.linalg.norm(np.asarray(a) - np.asarray(b)) / max(np.linalg.norm(np.asarray(b)), 1e-300))
 
 
-# planes of one tile (1024 cells) less one, exactly and more; rows wider than a
-# workgroup, the widest row of the tiled kernel (512) and wider; 1 to 9 planes
+# small grids (one cell a thread); the largest of them and the first larger grids:
+# planes of whole and ragged tiles (1024 cells), narrow rows, one row, the widest row of
+# the tiled kernel (512) and wider, slabs of one to four planes at the end
 @pytest.mark.parametrize("shape", [(1, 1, 1), (31, 33, 4), (32, 32, 5), (41, 25, 3), (300, 4, 9), (512, 3, 2),
-                                   (513, 3, 2), (1, 1500, 1)])
+                                   (513, 3, 2), (1, 1500, 1), (64, 64, 64), (64, 64, 65), (67, 61, 65), (512, 129, 4),
+                                   (513, 128, 4), (1, 70001, 4), (300, 4, 222), (511, 523, 1)])
 @pytest.mark.parametrize("adjoint", [False, True])
 def test_operator_tiles(shape, adjoint):
     print(f"operator {shape} adjoint={adjoint}", flush=True)
