@@ -61,14 +61,14 @@ def kernel_label(dominant, pf):
 # tile shape in the key;
 # summary and commands: profiles/fused_cgls_kernels_128cube_48sys_hbm_traffic.md
 TRAFFIC = {
-    "sources_sha256": "1d0cda1bde45a0f6",
+    "sources_sha256": "b541bde9e5750e92",
     "tiles": {
-        "8,4,64,2,4": {"fwd_x": {"fetch_kib": 1802998.8, "write_kib": 1573197.4},
-                       "fwd": {"fetch_kib": 974238.8, "write_kib": 786607.1},
-                       "adj": {"fetch_kib": 928214.9, "write_kib": 1573033.0}},
-        "8,4,64,2,2": {"fwd_x": {"fetch_kib": 1815348.9, "write_kib": 1573197.9},
-                       "fwd": {"fetch_kib": 1032783.0, "write_kib": 786610.6},
-                       "adj": {"fetch_kib": 976969.6, "write_kib": 1573040.8}},
+        "8,4,64,2,4": {"fwd_x": {"fetch_kib": 1802740.6, "write_kib": 1573199.5},
+                       "fwd": {"fetch_kib": 977260.3, "write_kib": 786607.1},
+                       "adj": {"fetch_kib": 924592.3, "write_kib": 1573033.2}},
+        "8,4,64,2,2": {"fwd_x": {"fetch_kib": 1814694.3, "write_kib": 1573200.5},
+                       "fwd": {"fetch_kib": 1033210.9, "write_kib": 786608.3},
+                       "adj": {"fetch_kib": 976241.2, "write_kib": 1573040.3}},
     },
     "fetch_scale": 2.000, "write_scale": 1.000,
 }
@@ -186,7 +186,7 @@ def _cpu_complete_worker(args):
 
 
 def cpu_validate(dev, big):
-    """The CPU oracle on the host of the GPU machine, run to completion: complex128
+    """The CPU oracle on the host, run to completion: complex128
     CGLS on every system of the medium workload (and on `big` systems of the
     128^3 workload), one process per job within the box's core share, next to
     the direct oracle (sparse LU) at 16^3 and 32^3; the GPU's iteration counts
