@@ -801,10 +801,13 @@ int autotune(Ctx& C) {
   // cells: 0.148 ms against 0.230, rows of 500: 0.250 against 0.310), from 2^24 on the
   // slabs win (16.8 M cells: 0.99 ms against 1.31); between them either may (3.9 M
   // cells: 0.235 against 0.335 as 64^3, 0.366 against 0.322 with planes of 256 x 256).
-  const bool any_window = tiles_fit(C, kUntunedWindow);
+  // Above 2^21 cells one cell a thread loses to two wherever those fit (6.3 M cells: 0.487
+  // ms against 0.458, 10.6 M: 0.975 against 0.784).
+  const bool any_window = tiles_fit(C, kUntunedWindow), two_cells = tiles_fit(C, TileCfg{4, 2, 4, kWindow, 0});
   for (int c = 0; c < kNumCands; ++c) {
     const bool win = kCands[c].pf == kWindow;
     if ((!win && any_window && total <= kWindowOnlyCells) || (win && total >= kSlabOnlyCells)) continue;
+    if (win && kCands[c].ry == 1 && two_cells && total > kWindowOnlyCells) continue;
     if (!tiles_fit(C, kCands[c])) continue;
     int rc = set_config(C, kCands[c]);
     if (rc == WRI_OK) rc = launch_setup(C);
@@ -944,7 +947,8 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
     // about 50 us, a launch pair on finished systems takes 6.  Every system has
     // stopped after max_iter + 1 launch pairs.
     const int64_t last = (int64_t)C.max_iter + 1;
-    int64_t chunk = std::min<int64_t>(16, last);
+    constexpr int64_t kFirstChunk = 16;
+    int64_t chunk = std::min<int64_t>(kFirstChunk, last);
     int64_t launched = 0;
     auto last_report = std::chrono::steady_clock::now();
     main_cfg = cur_cfg(C);
@@ -961,13 +965,18 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
           rc = launch_iteration_timed(C, (int)(launched + i), pool, ev_fwd, ev_adj);
           if (rc != WRI_OK) return rc;
         }
-      } else if (use_graph) {
-        hipGraphExec_t ex = nullptr;
-        rc = get_graph(C, launched, (int)chunk, &ex);
-        if (rc != WRI_OK) return rc;
-        WRI_HIP(hipGraphLaunch(ex, C.st));
       } else {
-        for (int i = 0; i < chunk; ++i) {
+        // Graphs of 16, 32, 64 and 128 iterations only, whatever max_iter cuts a chunk
+        // to: a length of its own would be captured for every max_iter.
+        int64_t i = 0;
+        for (int64_t piece = 128; use_graph && piece >= kFirstChunk; piece /= 2)
+          for (; chunk - i >= piece; i += piece) {
+            hipGraphExec_t ex = nullptr;
+            rc = get_graph(C, launched + i, (int)piece, &ex);
+            if (rc != WRI_OK) return rc;
+            WRI_HIP(hipGraphLaunch(ex, C.st));
+          }
+        for (; i < chunk; ++i) {
           rc = launch_iteration(C, (int)(launched + i), C.st);
           if (rc != WRI_OK) return rc;
         }
