@@ -61,14 +61,14 @@ def kernel_label(dominant, pf):
 # tile shape in the key;
 # summary and commands: profiles/fused_cgls_kernels_128cube_48sys_hbm_traffic.md
 TRAFFIC = {
-    "sources_sha256": "b541bde9e5750e92",
+    "sources_sha256": "938bdc87f537aeb7",
     "tiles": {
-        "8,4,64,2,4": {"fwd_x": {"fetch_kib": 1802740.6, "write_kib": 1573199.5},
-                       "fwd": {"fetch_kib": 977260.3, "write_kib": 786607.1},
-                       "adj": {"fetch_kib": 924592.3, "write_kib": 1573033.2}},
-        "8,4,64,2,2": {"fwd_x": {"fetch_kib": 1814694.3, "write_kib": 1573200.5},
-                       "fwd": {"fetch_kib": 1033210.9, "write_kib": 786608.3},
-                       "adj": {"fetch_kib": 976241.2, "write_kib": 1573040.3}},
+        "8,4,64,2,4": {"fwd_x": {"fetch_kib": 1801633.9, "write_kib": 1573199.9},
+                       "fwd": {"fetch_kib": 976798.7, "write_kib": 786608.1},
+                       "adj": {"fetch_kib": 925137.8, "write_kib": 1573035.8}},
+        "8,4,64,2,2": {"fwd_x": {"fetch_kib": 1816373.8, "write_kib": 1573199.3},
+                       "fwd": {"fetch_kib": 1031479.1, "write_kib": 786611.2},
+                       "adj": {"fetch_kib": 976953.5, "write_kib": 1573040.3}},
     },
     "fetch_scale": 2.000, "write_scale": 1.000,
 }
