@@ -861,6 +861,12 @@ int get_graph(Ctx& C, int64_t k0, int chunk, hipGraphExec_t* out) {
   const std::string key = graph_key(C, k0, chunk);
   auto it = g_graphs.find(key);
   if (it != g_graphs.end()) { *out = it->second.exec; return WRI_OK; }
+  if (g_graphs.size() > 64) {  // bound the cache: drop everything (rare)
+    // earlier pieces of this chunk may be replaying from it; other calls have ended with a wait
+    WRI_HIP(hipStreamSynchronize(C.st));
+    for (auto& kv : g_graphs) { (void)hipGraphExecDestroy(kv.second.exec); (void)hipGraphDestroy(kv.second.graph); }
+    g_graphs.clear();
+  }
   hipStream_t cs = capture_stream(C.dev);
   if (cs == nullptr) return fail(WRI_EHIP, "cannot create the capture stream");
   GraphEntry e;
@@ -873,10 +879,6 @@ int get_graph(Ctx& C, int64_t k0, int chunk, hipGraphExec_t* out) {
   if (ec != hipSuccess) return fail(WRI_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(ec));
   e.graph = graph;
   WRI_HIP(hipGraphInstantiate(&e.exec, graph, nullptr, nullptr, 0));
-  if (g_graphs.size() > 64) {  // bound the cache: drop everything (rare)
-    for (auto& kv : g_graphs) { (void)hipGraphExecDestroy(kv.second.exec); (void)hipGraphDestroy(kv.second.graph); }
-    g_graphs.clear();
-  }
   g_graphs[key] = e;
   *out = e.exec;
   return WRI_OK;
