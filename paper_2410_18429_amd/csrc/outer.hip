@@ -520,10 +520,11 @@ int lbfgs_fused(const LbPairs& P, int64_t n, const float* g, double h0, float* d
   return WRI_OK;
 }
 
-// dir = -H g, two-loop recursion over `count` ring slots ending at `newest`.
+// dir = -H g, two-loop recursion over `count` ring slots ending at `newest`; slot i
+// of S and Y starts at i * stride.
 // h0 > 0: H0 = h0 I; otherwise H0 = s.y / y.y of the newest pair.
-int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int cap, int count, int newest, double h0,
-              float* dir, char* ws, hipStream_t st) {
+int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int64_t stride, int cap, int count, int newest,
+              double h0, float* dir, char* ws, hipStream_t st) {
   LbWs w = lb_ws(ws);
   const int rho0 = 0, alp0 = cap, ih0 = 2 * cap, it0 = 2 * cap + 1, it1 = 2 * cap + 2;
   const int nbk = grid_blocks(n);
@@ -536,8 +537,8 @@ int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int cap
   if (count <= kLbFused) {
     LbPairs P{};
     for (int j = 0; j < count; ++j) {
-      P.s[j] = S + (int64_t)slot(j) * n;
-      P.y[j] = Y + (int64_t)slot(j) * n;
+      P.s[j] = S + slot(j) * stride;
+      P.y[j] = Y + slot(j) * stride;
     }
     switch (count) {
       case 1: return lbfgs_fused<1>(P, n, g, h0, dir, w, st);
@@ -555,8 +556,8 @@ int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int cap
   int rc;
   for (int j = count - 1; j >= 0; --j) {
     const int i = slot(j);
-    const float* s = S + (int64_t)i * n;
-    const float* y = Y + (int64_t)i * n;
+    const float* s = S + i * stride;
+    const float* y = Y + i * stride;
     if ((rc = dot_to(y, s, n, w, kOpRho, rho0 + i, 0, 0, st)) != WRI_OK) return rc;
     if ((rc = dot_to(s, dir, n, w, kOpAlpha, alp0 + i, rho0 + i, 0, st)) != WRI_OK) return rc;
     hipLaunchKernelGGL(k_axpy_sc, dim3(nbk), dim3(kRedThreads), 0, st, dir, y, n, -1.0, w.sc, alp0 + i);
@@ -566,8 +567,8 @@ int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int cap
     const double hh = h0;
     OUTER_HIP(hipMemcpyAsync(w.sc + ih0, &hh, sizeof(double), hipMemcpyHostToDevice, st));
   } else {
-    const float* s = S + (int64_t)slot(count - 1) * n;
-    const float* y = Y + (int64_t)slot(count - 1) * n;
+    const float* s = S + slot(count - 1) * stride;
+    const float* y = Y + slot(count - 1) * stride;
     if ((rc = dot_to(s, y, n, w, kOpSum, it0, 0, 0, st)) != WRI_OK) return rc;
     if ((rc = dot_to(y, y, n, w, kOpRatio, ih0, it0, 0, st)) != WRI_OK) return rc;
   }
@@ -576,8 +577,8 @@ int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int cap
   OUTER_HIP(hipGetLastError());
   for (int j = 0; j < count; ++j) {
     const int i = slot(j);
-    const float* s = S + (int64_t)i * n;
-    const float* y = Y + (int64_t)i * n;
+    const float* s = S + i * stride;
+    const float* y = Y + i * stride;
     if ((rc = dot_to(y, dir, n, w, kOpBeta, it1, alp0 + i, rho0 + i, st)) != WRI_OK) return rc;
     hipLaunchKernelGGL(k_axpy_sc, dim3(nbk), dim3(kRedThreads), 0, st, dir, s, n, 1.0, w.sc, it1);
     OUTER_HIP(hipGetLastError());
@@ -675,7 +676,7 @@ int wri_lbfgs_direction(int64_t n, const float* g, const float* S, const float* 
   const size_t need = wri_lbfgs_workspace_bytes(capacity);
   if (ws == nullptr || ws_bytes < need) return report_error(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, need);
   char* w = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
-  return lbfgs_run(n, g, S, Y, std::max(capacity, 1), count, newest, h0, dir, w, reinterpret_cast<hipStream_t>(stream));
+  return lbfgs_run(n, g, S, Y, n, std::max(capacity, 1), count, newest, h0, dir, w, reinterpret_cast<hipStream_t>(stream));
 }
 
 size_t wri_awri_workspace_bytes(const wri_grid* grid, const wri_system* sys, int32_t n_sys, int32_t mode,
@@ -716,7 +717,8 @@ int wri_awri(const wri_grid* grid, float* m, const wri_system* sys, int32_t n_sy
   float* dir = reinterpret_cast<float*>(base + L.off_vec + 3 * vb);
   float* tmp = reinterpret_cast<float*>(base + L.off_vec + 4 * vb);
   float* Sring = reinterpret_cast<float*>(base + L.off_vec + 5 * vb);
-  float* Yring = Sring + (size_t)o.memory * (vb / sizeof(float));
+  const int64_t ring = vb / sizeof(float);   // stride of the pairs
+  float* Yring = Sring + o.memory * ring;
   char* tvw = base + L.off_tv;
   char* lbw = base + L.off_lb;
   float* fpart = reinterpret_cast<float*>(base + L.off_red);
@@ -805,8 +807,8 @@ int wri_awri(const wri_grid* grid, float* m, const wri_system* sys, int32_t n_sy
       if (!(gmax > 0.0)) break;  // stationary
       h0 = o.step0 * mmax / gmax;
     }
-    if ((rc = lbfgs_run(n, g, Sring, Yring, std::max(o.memory, 1), count, std::max(newest, 0), h0, dir, lbw, st)) !=
-        WRI_OK)
+    if ((rc = lbfgs_run(n, g, Sring, Yring, ring, std::max(o.memory, 1), count, std::max(newest, 0), h0, dir, lbw,
+                        st)) != WRI_OK)
       return rc;
     double scale = 1.0;
     if (o.max_step > 0.0) {
@@ -847,8 +849,8 @@ int wri_awri(const wri_grid* grid, float* m, const wri_system* sys, int32_t n_sy
       if ((rc = dot_host(y, y, n, dpart, st, &yy)) != WRI_OK) return rc;
       if (sy > 0.0 && yy > 0.0) {
         const int slot = (newest + 1) % o.memory;
-        hipLaunchKernelGGL(k_copy32, dim3(nbk), dim3(kRedThreads), 0, st, Sring + (size_t)slot * (vb / sizeof(float)), s, n);
-        hipLaunchKernelGGL(k_copy32, dim3(nbk), dim3(kRedThreads), 0, st, Yring + (size_t)slot * (vb / sizeof(float)), y, n);
+        hipLaunchKernelGGL(k_copy32, dim3(nbk), dim3(kRedThreads), 0, st, Sring + slot * ring, s, n);
+        hipLaunchKernelGGL(k_copy32, dim3(nbk), dim3(kRedThreads), 0, st, Yring + slot * ring, y, n);
         OUTER_HIP(hipGetLastError());
         newest = slot;
         count = std::min(count + 1, o.memory);
