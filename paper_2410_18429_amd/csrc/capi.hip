@@ -193,6 +193,8 @@ struct RecSet {       // one distinct receiver list on one grid
   int grid;
   std::vector<int32_t> rec;
   size_t off_rec = 0, off_colmap = 0, off_entries = 0;
+  size_t off_bstart = 0, off_bentry = 0;   // buckets of a long list (window march)
+  bool bucketed() const { return rec.size() > (size_t)kListRecs; }
 };
 
 struct Layout {
@@ -205,6 +207,7 @@ struct Layout {
   size_t off_gdesc = 0;
   size_t head_bytes = 0;            // sysdev, gdesc and the receiver lists: [0, head_bytes)
   size_t off_nparts = 0;            // per processing slot: partial sums of a set-up pass (warm start)
+  size_t off_wrec = 0;              // per processing slot: WinRec (0: every list is short)
   std::vector<size_t> off_vec;      // per processing slot: base of its 7 vectors (batched) ; plain: one slot
   std::vector<size_t> off_rvec;     // per processing slot: r2, t2
   std::vector<int> slot_base;       // per processing slot
@@ -220,6 +223,8 @@ struct Group {
   int grid;
   int rhs0, nrhs;  // processing slots
 };
+
+int64_t n_buckets(const wri_grid& g) { return (cells(g) >> kBucketShift) + 2; }   // and the end of the last
 
 Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, int flags,
                    bool window = true) {
@@ -317,6 +322,12 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
     L.part_j_stride = gb;
     L.fine_grad = true;
     L.off_part_j = take(sizeof(double) * (size_t)gb * std::max(n_sys, 1));
+    for (auto& rs : L.sets) {
+      if (!rs.bucketed()) continue;
+      if (L.off_wrec == 0) L.off_wrec = take(sizeof(WinRec) * (size_t)n_sys);
+      rs.off_bstart = take(sizeof(int32_t) * (size_t)n_buckets(grids[rs.grid]));
+      rs.off_bentry = take(sizeof(int32_t) * 2 * rs.rec.size());
+    }
   }
   L.total = o + kAlign;
   return L;
@@ -344,6 +355,20 @@ void build_colmap(const wri_grid& g, const std::vector<int32_t>& rec, std::vecto
     colmap[2 * col] = (int32_t)i;
     colmap[2 * col + 1] = (int32_t)j;
     i = j;
+  }
+}
+
+// receivers by buckets of cells, in list order within a bucket
+void build_buckets(const wri_grid& g, const std::vector<int32_t>& rec, int32_t* start, int32_t* entry) {
+  const int64_t nb = n_buckets(g);
+  std::fill(start, start + nb, 0);
+  for (int32_t c : rec) ++start[(c >> kBucketShift) + 1];
+  for (int64_t i = 1; i < nb; ++i) start[i] += start[i - 1];
+  std::vector<int32_t> next(start, start + nb);
+  for (size_t q = 0; q < rec.size(); ++q) {
+    const int32_t at = next[rec[q] >> kBucketShift]++;
+    entry[2 * (size_t)at] = rec[q];
+    entry[2 * (size_t)at + 1] = (int32_t)q;
   }
 }
 
@@ -401,6 +426,8 @@ struct Ctx {
   int dev = 0;
   std::vector<char> head;            // host image of the tables (read by an asynchronous copy)
   bool colmaps = false;              // the receivers' column maps are on the device
+  bool buckets = false;              // and the buckets of the long lists
+  const WinRec* wrec = nullptr;      // null: every list is short
 };
 
 template <class T>
@@ -490,6 +517,31 @@ int read_states(Ctx& C, std::vector<SysState>& hs) {
 }
 
 // one CGLS iteration (fwd then adj) for every group
+// Window tiles find the receivers of a long list through its buckets.
+int upload_buckets(Ctx& C) {
+  if (C.buckets || C.L.off_wrec == 0) return WRI_OK;
+  std::vector<WinRec> table(C.n_sys, WinRec{nullptr, nullptr});
+  std::vector<std::vector<int32_t>> host(2 * C.L.sets.size());   // read by the copies below
+  for (size_t i = 0; i < C.L.sets.size(); ++i) {
+    const RecSet& rs = C.L.sets[i];
+    if (!rs.bucketed()) continue;
+    auto &start = host[2 * i], &entry = host[2 * i + 1];
+    start.resize((size_t)n_buckets(C.grids[rs.grid]));
+    entry.resize(2 * rs.rec.size());
+    build_buckets(C.grids[rs.grid], rs.rec, start.data(), entry.data());
+    WRI_HIP(hipMemcpyAsync(C.ws + rs.off_bstart, start.data(), start.size() * 4, hipMemcpyHostToDevice, C.st));
+    WRI_HIP(hipMemcpyAsync(C.ws + rs.off_bentry, entry.data(), entry.size() * 4, hipMemcpyHostToDevice, C.st));
+  }
+  for (int p = 0; p < C.n_sys; ++p) {
+    const RecSet& rs = C.L.sets[C.L.set_of[C.L.order[p]]];
+    if (rs.bucketed()) table[p] = {at<int>(C.ws, rs.off_bstart), at<int2>(C.ws, rs.off_bentry)};
+  }
+  WRI_HIP(hipMemcpyAsync(C.ws + C.L.off_wrec, table.data(), sizeof(WinRec) * table.size(), hipMemcpyHostToDevice, C.st));
+  WRI_HIP(hipStreamSynchronize(C.st));
+  C.buckets = true;
+  return WRI_OK;
+}
+
 struct EventPool {
   std::vector<hipEvent_t> ev;
   size_t used = 0;
@@ -563,8 +615,8 @@ int set_config(Ctx& C, const TileCfg& cfg, bool upload = true) {
   int tmax = 1;
   for (const auto& d : C.hgd) tmax = std::max(tmax, d.ntiles);
   for (auto& d : C.hgd) d.xchunk = std::max(kMinXChunk, tmax / 2);
-  if (cfg.pf != kWindow && !C.hgd.empty())
-    if (const int rc = upload_colmaps(C); rc != WRI_OK) return rc;
+  if (!C.hgd.empty())
+    if (const int rc = cfg.pf == kWindow ? upload_buckets(C) : upload_colmaps(C); rc != WRI_OK) return rc;
   if (upload && !C.hgd.empty()) {
     WRI_HIP(hipMemcpyAsync(C.dgd, C.hgd.data(), sizeof(GroupDesc) * C.hgd.size(), hipMemcpyHostToDevice, C.st));
     WRI_HIP(hipStreamSynchronize(C.st));  // C.hgd may change before an asynchronous copy would finish
@@ -691,6 +743,19 @@ int switch_tiling(Ctx& C, const TileCfg& cfg) {
   return WRI_OK;
 }
 
+// the forward launch of CGLS iteration k and the adjoint launch, each over all groups
+int forward(Ctx& C, int k, hipStream_t s) {
+  WRI_HIP(launch_fwd(cur_cfg(C), C.dsys, C.dstate, C.part_s, C.part_d, C.dgd, C.hgd.data(), (int)C.hgd.size(),
+                     C.nblocks, C.nx_max, C.wrec, k, s));
+  return WRI_OK;
+}
+
+int adjoint(Ctx& C, hipStream_t s) {
+  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(),
+                     C.nblocks, C.nx_max, C.wrec, s));
+  return WRI_OK;
+}
+
 // eager iteration with an event pair around the forward and adjoint launches
 int launch_iteration_timed(Ctx& C, int k, EventPool& pool, std::vector<std::pair<hipEvent_t, hipEvent_t>>& fwd,
                            std::vector<std::pair<hipEvent_t, hipEvent_t>>& adj) {
@@ -698,42 +763,38 @@ int launch_iteration_timed(Ctx& C, int k, EventPool& pool, std::vector<std::pair
     hipEvent_t a = pool.next(), b = pool.next();
     if (!a || !b) return fail(WRI_EHIP, "hipEventCreate failed");
     WRI_HIP(hipEventRecord(a, C.st));
-    if (phase == 0)
-      WRI_HIP(launch_fwd(cur_cfg(C), C.dsys, C.dstate, C.part_s, C.part_d, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, k,
-                         C.st));
-    else
-      WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, C.st));
+    const int rc = phase == 0 ? forward(C, k, C.st) : adjoint(C, C.st);
+    if (rc != WRI_OK) return rc;
     WRI_HIP(hipEventRecord(b, C.st));
     (phase == 0 ? fwd : adj).emplace_back(a, b);
   }
   return WRI_OK;
 }
 
-// CGLS iteration k: the forward launch then the adjoint launch, each over all groups
 int launch_iteration(Ctx& C, int k, hipStream_t s) {
-  WRI_HIP(launch_fwd(cur_cfg(C), C.dsys, C.dstate, C.part_s, C.part_d, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, k, s));
-  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, s));
-  return WRI_OK;
+  const int rc = forward(C, k, s);
+  return rc != WRI_OK ? rc : adjoint(C, s);
 }
 
 int launch_setup(Ctx& C) {
   WRI_HIP(launch_init(C.dsys, C.dstate, C.n_sys, C.st, 0, (C.flags & WRI_FLAG_ADJOINT_SOURCE) ? 1 : 0));
-  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, C.st));
-  return WRI_OK;
+  return adjoint(C, C.st);
 }
 
 // Warm start (WRI_FLAG_WARM_START): x holds x0.  S^H b gives the reference
 // ||S^H b||^2, then r = b - S x0 and s0 = S^H r.
 int launch_setup_warm(Ctx& C) {
   WRI_HIP(launch_init(C.dsys, C.dstate, C.n_sys, C.st, 1));
-  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, C.st));
+  int rc = adjoint(C, C.st);
+  if (rc != WRI_OK) return rc;
   std::vector<int32_t> np(C.n_sys);
   for (size_t gi = 0; gi < C.hgd.size(); ++gi)
     for (int r = 0; r < C.hgd[gi].nrhs; ++r) np[C.hgd[gi].rhs0 + r] = C.hgd[gi].ntiles;
   int32_t* dnp = at<int32_t>(C.ws, C.L.off_nparts);
   WRI_HIP(hipMemcpyAsync(dnp, np.data(), sizeof(int32_t) * np.size(), hipMemcpyHostToDevice, C.st));
   WRI_HIP(launch_warm_residual(C.dsys, C.dstate, C.part_s, dnp, C.n_sys, C.st));
-  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(), C.nblocks, C.nx_max, C.st));
+  rc = adjoint(C, C.st);
+  if (rc != WRI_OK) return rc;
   WRI_HIP(hipStreamSynchronize(C.st));  // np is host memory
   return WRI_OK;
 }
@@ -832,7 +893,7 @@ int autotune(Ctx& C) {
 }
 
 // A captured chunk bakes in every kernel argument of its launches: the tile
-// (template and grid size), the group count and the five table pointers.  The
+// (template and grid size), the group count and the six table pointers.  The
 // table pointers are workspace offsets that depend on every grid's cell count,
 // the number of grids and the receiver sets, so two batches that share the
 // workspace base and the tile can still place them differently; the key holds
@@ -843,8 +904,8 @@ std::string graph_key(const Ctx& C, int64_t k0, int chunk) {
   // the kernels of a chunk depend on k0 only through fwd_x_step(k0 + i)
   snprintf(buf, sizeof(buf), "%d|%d|%d|%d|", C.dev, chunk, (int)(k0 & 1), k0 >= 2 ? 1 : (int)k0);
   k += buf;
-  snprintf(buf, sizeof(buf), "%p,%p,%p,%p,%p,%d|", (const void*)C.dsys, (const void*)C.dstate,
-           (const void*)C.part_s, (const void*)C.part_d, (const void*)C.dgd, (int)C.hgd.size());
+  snprintf(buf, sizeof(buf), "%p,%p,%p,%p,%p,%p,%d|", (const void*)C.dsys, (const void*)C.dstate,
+           (const void*)C.part_s, (const void*)C.part_d, (const void*)C.dgd, (const void*)C.wrec, (int)C.hgd.size());
   k += buf;
   const TileCfg& c = cur_cfg(C);
   snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d,%d,%d;", c.w, c.ry, c.tz, c.pf, c.order, C.nblocks, C.nx_max);
@@ -1254,6 +1315,7 @@ int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, 
   C.part_j = at<double>(C.ws, C.L.off_part_j);
   C.dot = at<double>(C.ws, C.L.off_dot);
   C.dgd = at<GroupDesc>(C.ws, C.L.off_gdesc);
+  if (C.L.off_wrec > 0) C.wrec = at<WinRec>(C.ws, C.L.off_wrec);
   std::lock_guard<std::mutex> lock(g_mutex);
   WRI_HIP(hipGetDevice(&C.dev));
   std::vector<SysState> hs;

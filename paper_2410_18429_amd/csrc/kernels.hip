@@ -1784,41 +1784,87 @@ __device__ __forceinline__ GroupDesc win_group(const WinGroups& G, int logical) 
   return d;
 }
 
-// Receiver cell tid of the system's list (-1 past its end).
-__device__ __forceinline__ int first_receiver(const SysDev& S) {
-  return (int)threadIdx.x < S.n_rec ? gptr(S.rec)[threadIdx.x] : -1;
-}
+// Receivers of the tile, in two steps: the loads that find them, issued with the
+// tile's other loads, and recq[], the receiver index of each own cell (-1: none; a
+// receiver cell occurs once in a system's list).  Every workgroup scans a list of up to
+// kListRecs receivers; with LONG, longer ones are read through their buckets, two
+// dependent loads whatever the length.  64 iterations of 8 systems of 64^3 with 32768
+// receivers each: 12.4 ms by scans, 9.1 with the slab marches' column map, 3.8 by
+// buckets; with 4096 3.72, 5.2 and 3.09; with 512 2.69 by scans and 3.00 by buckets
+// (4 of 70x37x19 with 1024: 1.20 and 1.19, hence the line).  Kernels of their own: the
+// branch alone cost the short lists 3 to 7 %.
+template <int W, int CX, int TZ, bool LONG>
+struct TileRecs {
+  using Tile = Win<W, CX, TZ>;
+  static constexpr int NT = Tile::NT, B = Tile::B;
+  int rec0;              // list: receiver cell tid (-1 past the end)
+  bool bucket;
+  int b[TZ], e[TZ];      // buckets: entries of the buckets that cover plane i of the tile
 
-// Receivers of the tile: recq[] takes the receiver index of each own cell (-1:
-// none; a receiver cell occurs once in a system's list).  Returns whether the
-// tile holds any; only then is recq written, and the caller's next barrier
-// publishes it.  rec0: first_receiver().
-template <int W, int CX, int TZ>
-__device__ __forceinline__ bool find_receivers(const Win<W, CX, TZ>& Q, const SysDev& S, int rec0, int* recq) {
-  constexpr int NT = Win<W, CX, TZ>::NT, B = Win<W, CX, TZ>::B;
-  const GLOBAL int* rec = gptr(S.rec);
-  const int first = Q.z0 * Q.plane, span = (min(Q.z0 + TZ, Q.nz) - Q.z0) * Q.plane;
-  auto slot = [&](int q) -> int {   // own-cell slot of receiver q, or -1
-    const int d = (q == (int)threadIdx.x ? rec0 : rec[q]) - first;
-    if (d < 0 || d >= span) return -1;
-    int z = 0;
+  __device__ __forceinline__ void load(const Tile& Q, const SysDev& S, const WinRec* wrec, int rhs) {
+    rec0 = (int)threadIdx.x < S.n_rec ? gptr(S.rec)[threadIdx.x] : -1;
+    if constexpr (LONG) {
+      const GLOBAL int* start = gptr(wrec[rhs].start);
+      bucket = start != nullptr;
 #pragma unroll
-    for (int i = 1; i < TZ; ++i) z += d >= i * Q.plane ? 1 : 0;
-    const int o = d - z * Q.plane - Q.c0;
-    return o >= 0 && o < B ? z * B + o : -1;
-  };
-  bool any = false;
-  for (int q = threadIdx.x; q < S.n_rec; q += NT) any = any || slot(q) >= 0;
-  if (!__syncthreads_or(any)) return false;
-#pragma unroll
-  for (int i = 0; i < CX * TZ; ++i) recq[i * NT + (int)threadIdx.x] = -1;
-  __syncthreads();
-  for (int q = threadIdx.x; q < S.n_rec; q += NT) {
-    const int o = slot(q);
-    if (o >= 0) recq[o] = q;
+      for (int i = 0; i < TZ; ++i) {
+        const int first = min(Q.z0 + i, Q.nz - 1) * Q.plane + Q.c0, last = first + min(B, Q.plane - Q.c0) - 1;
+        b[i] = bucket ? start[first >> kBucketShift] : 0;
+        e[i] = bucket && Q.z0 + i < Q.nz ? start[(last >> kBucketShift) + 1] : b[i];
+      }
+    }
   }
-  return true;
-}
+  // Returns whether the tile may hold any; only then is recq written, and the caller's
+  // next barrier publishes it.
+  __device__ __forceinline__ bool find(const Tile& Q, const SysDev& S, const WinRec* wrec, int rhs, int* recq) const {
+    if constexpr (LONG)
+      if (bucket) return find_bucket(Q, wrec, rhs, recq);
+    return S.n_rec > 0 && find_list(Q, S, recq);
+  }
+  __device__ __forceinline__ bool find_list(const Tile& Q, const SysDev& S, int* recq) const {
+    const GLOBAL int* rec = gptr(S.rec);
+    const int first = Q.z0 * Q.plane, span = (min(Q.z0 + TZ, Q.nz) - Q.z0) * Q.plane;
+    auto slot = [&](int q) -> int {   // own-cell slot of receiver q, or -1
+      const int d = (q == (int)threadIdx.x ? rec0 : rec[q]) - first;
+      if (d < 0 || d >= span) return -1;
+      int z = 0;
+#pragma unroll
+      for (int i = 1; i < TZ; ++i) z += d >= i * Q.plane ? 1 : 0;
+      const int o = d - z * Q.plane - Q.c0;
+      return o >= 0 && o < B ? z * B + o : -1;
+    };
+    bool any = false;
+    for (int q = threadIdx.x; q < S.n_rec; q += NT) any = any || slot(q) >= 0;
+    if (!__syncthreads_or(any)) return false;
+#pragma unroll
+    for (int i = 0; i < CX * TZ; ++i) recq[i * NT + (int)threadIdx.x] = -1;
+    __syncthreads();
+    for (int q = threadIdx.x; q < S.n_rec; q += NT) {
+      const int o = slot(q);
+      if (o >= 0) recq[o] = q;
+    }
+    return true;
+  }
+  __device__ __forceinline__ bool find_bucket(const Tile& Q, const WinRec* wrec, int rhs, int* recq) const {
+    int any = 0;         // the same in every thread
+#pragma unroll
+    for (int i = 0; i < TZ; ++i) any += e[i] - b[i];
+    if (any == 0) return false;
+#pragma unroll
+    for (int i = 0; i < CX * TZ; ++i) recq[i * NT + (int)threadIdx.x] = -1;
+    __syncthreads();
+    const GLOBAL int* entry = gptr(reinterpret_cast<const int*>(wrec[rhs].entry));
+#pragma unroll
+    for (int i = 0; i < TZ; ++i) {
+      const int first = (Q.z0 + i) * Q.plane + Q.c0, cells = min(B, Q.plane - Q.c0);
+      for (int q = b[i] + (int)threadIdx.x; q < e[i]; q += NT) {
+        const int o = entry[2 * q] - first, r = entry[2 * q + 1];
+        if (o >= 0 && o < cells) recq[i * B + o] = r;
+      }
+    }
+    return true;
+  }
+};
 
 // Whether the tile's planes and cells hold the source, and the thread's own cell
 // that does, as j * TZ + i (-1: none).
@@ -1834,10 +1880,10 @@ __device__ __forceinline__ bool source_tile(const Win<W, CX, TZ>& Q, const SysDe
   return true;
 }
 
-template <int W, int CX, int TZ, int XS>
+template <int W, int CX, int TZ, int XS, bool LONG>
 __global__ void __launch_bounds__(64 * W)
 k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const double* __restrict__ part_s,
-          double* __restrict__ part_d, WinGroups G) {
+          double* __restrict__ part_d, WinGroups G, const WinRec* __restrict__ wrec) {
   using Tile = Win<W, CX, TZ>;
   constexpr int NT = Tile::NT, B = Tile::B;
   __shared__ int recq[B * TZ];
@@ -1866,7 +1912,8 @@ k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
   float2* tout = S.t;
   // every load of the tile, before the scalars they are combined with
   const SlotSum slots(part_s + S.slot_base, ntiles);
-  const int rec0 = first_receiver(S);
+  TileRecs<W, CX, TZ, LONG> recs;
+  recs.load(Q, S, wrec, rhs);
   float2 rs[CX][TZ + 2], rp[CX][TZ + 2], rx[CX][TZ], rq[CX][TZ];
   float mm[CX][TZ];
 #pragma unroll
@@ -1894,7 +1941,7 @@ k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
     hp[i] = Q.load2(po, i + 1, ho);
   }
   issue_point();
-  const bool has_rec = S.n_rec > 0 && find_receivers(Q, S, rec0, recq);
+  const bool has_rec = recs.find(Q, S, wrec, rhs, recq);
 
   const double gk = slots.sum(part_s + S.slot_base, ntiles);
   const bool warm = T->warm != 0;
@@ -2020,10 +2067,10 @@ k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
   if (srcji >= 0) T->pa = pa_new;
 }
 
-template <int W, int CX, int TZ>
+template <int W, int CX, int TZ, bool LONG>
 __global__ void __launch_bounds__(64 * W)
 k_adj_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const double* __restrict__ part_d,
-          double* __restrict__ part_s, WinGroups G, int setup_only) {
+          double* __restrict__ part_s, WinGroups G, const WinRec* __restrict__ wrec, int setup_only) {
   using Tile = Win<W, CX, TZ>;
   constexpr int NT = Tile::NT, B = Tile::B;
   __shared__ int recq[B * TZ];
@@ -2055,7 +2102,8 @@ k_adj_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
   const unsigned tbit = setup ? kOOB : 0u;
 
   const SlotSum slots(part_d + S.slot_base, setup ? 0 : ntiles);
-  const int rec0 = first_receiver(S);
+  TileRecs<W, CX, TZ, LONG> recs;
+  recs.load(Q, S, wrec, rhs);
   float2 rr[CX][TZ + 2], rt[CX][TZ + 2];
   float mm[CX][TZ];
 #pragma unroll
@@ -2077,7 +2125,7 @@ k_adj_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
     ht[i] = Q.load2(tv, i + 1, ho | tbit);
   }
   issue_point();
-  const bool has_rec = S.n_rec > 0 && find_receivers(Q, S, rec0, recq);
+  const bool has_rec = recs.find(Q, S, wrec, rhs, recq);
 
   double a = 0.0;
   if (!setup) {
@@ -2196,6 +2244,30 @@ static WinGroups win_groups(const GroupDesc* host_gd, const GroupDesc* gd, int n
   return G;
 }
 
+template <int W, int CX, int TZ>
+static void win_fwd_launch(unsigned nb, unsigned lds, hipStream_t s, const SysDev* sys, SysState* st,
+                           const double* part_s, double* part_d, const WinGroups& G, const WinRec* wrec, bool xs) {
+  const dim3 g(nb), b(64 * W);
+  if (wrec == nullptr) {
+    if (xs) hipLaunchKernelGGL((k_fwd_win<W, CX, TZ, 1, false>), g, b, lds, s, sys, st, part_s, part_d, G, wrec);
+    else hipLaunchKernelGGL((k_fwd_win<W, CX, TZ, 0, false>), g, b, lds, s, sys, st, part_s, part_d, G, wrec);
+  } else {
+    if (xs) hipLaunchKernelGGL((k_fwd_win<W, CX, TZ, 1, true>), g, b, lds, s, sys, st, part_s, part_d, G, wrec);
+    else hipLaunchKernelGGL((k_fwd_win<W, CX, TZ, 0, true>), g, b, lds, s, sys, st, part_s, part_d, G, wrec);
+  }
+}
+
+template <int W, int CX, int TZ>
+static void win_adj_launch(unsigned nb, unsigned lds, hipStream_t s, const SysDev* sys, SysState* st,
+                           const double* part_d, double* part_s, const WinGroups& G, const WinRec* wrec,
+                           int setup_only) {
+  const dim3 g(nb), b(64 * W);
+  if (wrec == nullptr)
+    hipLaunchKernelGGL((k_adj_win<W, CX, TZ, false>), g, b, lds, s, sys, st, part_d, part_s, G, wrec, setup_only);
+  else
+    hipLaunchKernelGGL((k_adj_win<W, CX, TZ, true>), g, b, lds, s, sys, st, part_d, part_s, G, wrec, setup_only);
+}
+
 size_t win_lds_bytes(const TileCfg& c, int nx) { return sizeof(float2) * (size_t)c.tz * (64 * c.w * c.ry + 2 * nx); }
 
 bool cfg_supported(const TileCfg& c) {
@@ -2212,21 +2284,17 @@ bool cfg_supported(const TileCfg& c) {
 }
 
 hipError_t launch_fwd(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_s, double* part_d,
-                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max, int k, hipStream_t s) {
+                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max,
+                      const WinRec* wrec, int k, hipStream_t s) {
   if (nblocks <= 0 || ngroups <= 0) return hipSuccess;
   const unsigned nb = (unsigned)nblocks;
   if (c.pf == kWindow) {
     const unsigned lds = (unsigned)win_lds_bytes(c, nx_max);
     const WinGroups G = win_groups(host_gd, gd, ngroups);
-#define X(W_, C_, Z_)                                                                                    \
-    if (c.w == W_ && c.ry == C_ && c.tz == Z_) {                                                         \
-      if (fwd_x_step(k))                                                                                 \
-        hipLaunchKernelGGL((k_fwd_win<W_, C_, Z_, 1>), dim3(nb), dim3(64 * W_), lds, s, sys, st, part_s,   \
-                           part_d, G);                                                                   \
-      else                                                                                               \
-        hipLaunchKernelGGL((k_fwd_win<W_, C_, Z_, 0>), dim3(nb), dim3(64 * W_), lds, s, sys, st, part_s,   \
-                           part_d, G);                                                                   \
-      return hipGetLastError();                                                                          \
+#define X(W_, C_, Z_)                                                                                        \
+    if (c.w == W_ && c.ry == C_ && c.tz == Z_) {                                                             \
+      win_fwd_launch<W_, C_, Z_>(nb, lds, s, sys, st, part_s, part_d, G, wrec, fwd_x_step(k));               \
+      return hipGetLastError();                                                                              \
     }
     WRI_WIN_LIST(X)
 #undef X
@@ -2272,7 +2340,8 @@ int adj_blocks_per_cu(const TileCfg& c) {
 }
 
 hipError_t launch_adj(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_d, double* part_s,
-                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max, hipStream_t s, int setup_only) {
+                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max,
+                      const WinRec* wrec, hipStream_t s, int setup_only) {
   if (nblocks <= 0 || ngroups <= 0) return hipSuccess;
   const unsigned nb = (unsigned)nblocks;
   if (c.pf == kWindow) {
@@ -2280,8 +2349,7 @@ hipError_t launch_adj(const TileCfg& c, const SysDev* sys, SysState* st, const d
     const WinGroups G = win_groups(host_gd, gd, ngroups);
 #define X(W_, C_, Z_)                                                                                  \
     if (c.w == W_ && c.ry == C_ && c.tz == Z_) {                                                       \
-      hipLaunchKernelGGL((k_adj_win<W_, C_, Z_>), dim3(nb), dim3(64 * W_), lds, s, sys, st, part_d,      \
-                         part_s, G, setup_only);                                                       \
+      win_adj_launch<W_, C_, Z_>(nb, lds, s, sys, st, part_d, part_s, G, wrec, setup_only);              \
       return hipGetLastError();                                                                        \
     }
     WRI_WIN_LIST(X)

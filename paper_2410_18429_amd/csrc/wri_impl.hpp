@@ -102,6 +102,16 @@ struct GroupDesc {
   int xchunk;      // tiles per XCD chunk (same value in every entry of a table)
 };
 
+// Receivers of one system for the window march, by buckets of 64 consecutive cells:
+// entry[start[b] .. start[b + 1]) are the (cell, receiver) pairs of cells 64 b to
+// 64 b + 63.  start is null for lists of up to kListRecs receivers.
+constexpr int kListRecs = 1024;
+constexpr int kBucketShift = 6;
+struct WinRec {
+  const int* start;
+  const int2* entry;
+};
+
 // Launch arguments of the window march: the first groups by value (the table
 // when there are more).
 constexpr int kWinGroups = 4;
@@ -132,12 +142,15 @@ hipError_t launch_fold_partials(const SysDev* sys, double* part_s, int rhs0, int
 // call iterate in lockstep); selects the variant of the forward kernel that
 // updates x (even k >= 2) or leaves it alone (odd k, k = 0).  nx_max: the
 // widest row of the launch's grids (sizes the window march's LDS).  host_gd:
-// host copy of gd.
+// host copy of gd.  wrec: the systems' receiver buckets (window march; null when
+// every list is short).
 inline bool fwd_x_step(int64_t k) { return k >= 2 && (k & 1) == 0; }
 hipError_t launch_fwd(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_s, double* part_d,
-                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max, int k, hipStream_t s);
+                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max,
+                      const WinRec* wrec, int k, hipStream_t s);
 hipError_t launch_adj(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_d, double* part_s,
-                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max, hipStream_t s, int setup_only = 0);
+                      const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max,
+                      const WinRec* wrec, hipStream_t s, int setup_only = 0);
 hipError_t launch_grad(const SysDev* sys, SysState* st, int rhs0, int nrhs, int n, float* grad,
                        double* part_j, int stride, int cpt, int accumulate, hipStream_t s);
 hipError_t launch_finalize(const SysDev* sys, SysState* st, const double* part_j, int nparts,
