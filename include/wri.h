@@ -149,7 +149,7 @@ enum {
                                scalars (the straightforward transcription of the
                                iterative solver; the baseline of the batched form) */
   WRI_FLAG_NO_GRAPH = 2,    /* launch the batched iterations eagerly (no hipGraph) */
-  WRI_FLAG_NO_AUTOTUNE = 4, /* use the default tile instead of the tuned one */
+  WRI_FLAG_NO_AUTOTUNE = 4, /* use each grid's default tile instead of the batch's tuned one */
   WRI_FLAG_UNSCALED_ALPHA = 8, /* ESTIMATE: use the source column -e exactly as printed
                                (default: -c e with c = sqrt(42)/h^2, same minimiser,
                                better-conditioned iteration) */
@@ -205,16 +205,18 @@ int wri_solve(const wri_grid* grids, int32_t n_grids, const float* const* m,
 /* wri_solve for callers that cannot allocate device memory: code under HIP
  * graph capture, allocation-free serving loops, harnesses that forbid
  * hipMalloc.  Arguments and results as in wri_solve, without ws / ws_bytes.
- *   Workspace: a fixed scratch array of WRI_NOALLOC_SCRATCH_BYTES (64 MiB; and 4
- *   MiB for partial sums, outside the limit below) in the library's device code, one copy per device, held from the library's
+ *   Workspace: a fixed scratch array of WRI_NOALLOC_SCRATCH_BYTES (64 MiB; and 16
+ *   MiB for partial sums and receiver tables, outside the limit below) in the
+ *   library's device code, one copy per device, held from the library's
  *   first use on that device until the process ends.  The call allocates
  *   nothing (no hipMalloc/hipFree, no graph, no events): the iterations are
- *   launched eagerly on `stream` with the untuned tile (WRI_FLAG_NO_GRAPH
+ *   launched eagerly on `stream` with the untuned tiles (WRI_FLAG_NO_GRAPH
  *   and WRI_FLAG_NO_AUTOTUNE are implied; the WRI_TILE environment variable
  *   still forces a tile).
  *   Limit: systems whose wri_workspace_bytes() (without the window march's
- *   partial sums) exceeds WRI_NOALLOC_SCRATCH_BYTES are rejected with WRI_ENOWS before any device work (e.g. up to about 8
- *   systems of 64^3 cells fit).  WRI_FLAG_TIMING is rejected (WRI_EINVAL).
+ *   partial sums and receiver tables) exceeds WRI_NOALLOC_SCRATCH_BYTES are
+ *   rejected with WRI_ENOWS before any device work (e.g. up to about 4 systems of
+ *   64^3 cells fit).  WRI_FLAG_TIMING is rejected (WRI_EINVAL).
  *   Sharing: every call on a device uses that device's one scratch and leaves
  *   its contents behind (the solver initialises everything it reads).  Calls
  *   that overlapped on one device would race on it; the library serialises

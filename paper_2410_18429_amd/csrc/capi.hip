@@ -212,7 +212,8 @@ struct Layout {
   std::vector<size_t> off_rvec;     // per processing slot: r2, t2
   std::vector<int> slot_base;       // per processing slot
   int part_j_stride = 1;
-  bool fine_grad = false;           // part_j has room for the gradient pass with one cell per thread
+  bool fine_grad = false;           // off_part_g has room for the gradient pass with one cell per thread
+  std::vector<size_t> off_part_g;   // per grid: partial sums of ||r1||^2 of its systems
   int dot_nparts = 1;
   size_t vec_bytes_plain = 0, rvec_bytes_plain = 0;
   size_t total_slab = 0;            // total without the window march's slots
@@ -226,11 +227,10 @@ struct Group {
 
 int64_t n_buckets(const wri_grid& g) { return (cells(g) >> kBucketShift) + 2; }   // and the end of the last
 
-Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, int flags,
-                   bool window = true) {
+Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, int flags) {
   Layout L;
   L.plain = (flags & WRI_FLAG_PLAIN) != 0;
-  L.window = window && !L.plain;
+  L.window = !L.plain;
   L.order.resize(n_sys);
   for (int i = 0; i < n_sys; ++i) L.order[i] = i;
   std::stable_sort(L.order.begin(), L.order.end(), [&](int a, int b) { return sys[a].grid < sys[b].grid; });
@@ -318,10 +318,12 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
     L.off_part_d = take(sizeof(double) * std::max(slots, 1));
     L.off_part_s = take(sizeof(double) * std::max(slots, 1));
     // the gradient pass with one cell per thread, too
-    for (int g = 0; g < n_grids; ++g) gb = std::max(gb, grad_blocks((int)cells(grids[g]), grad_cpt(grids[g], true)));
-    L.part_j_stride = gb;
     L.fine_grad = true;
-    L.off_part_j = take(sizeof(double) * (size_t)gb * std::max(n_sys, 1));
+    std::vector<int> count(n_grids, 0);
+    for (int i = 0; i < n_sys; ++i) ++count[sys[i].grid];
+    for (int g = 0; g < n_grids; ++g)
+      L.off_part_g.push_back(count[g] == 0 ? 0 : take(sizeof(double) * (size_t)count[g] *
+                                                      grad_blocks((int)cells(grids[g]), grad_cpt(grids[g], true))));
     for (auto& rs : L.sets) {
       if (!rs.bucketed()) continue;
       if (L.off_wrec == 0) L.off_wrec = take(sizeof(WinRec) * (size_t)n_sys);
@@ -399,6 +401,14 @@ hipStream_t capture_stream(int dev) {
 // solver context for one call
 // ---------------------------------------------------------------------------
 
+// Groups launched together with one tile shape: entries g0 to g0 + ng of the group table.
+struct Part {
+  TileCfg cfg;
+  int g0, ng;
+  int nblocks;   // blocks of one fused launch
+  int nx_max;    // widest row of the groups' grids
+};
+
 struct Ctx {
   const wri_grid* grids;
   int n_grids;
@@ -412,10 +422,10 @@ struct Ctx {
   Layout L;
   std::vector<SysDev> hsys;          // processing order
   std::vector<Group> groups;
-  std::vector<Tiling> tiling;        // per group (one tile shape for all groups)
+  std::vector<Tiling> tiling;        // per group
+  std::vector<Part> parts;           // the launches of one pass
+  std::vector<int> order;            // group at each entry of the device group table
   std::vector<GroupDesc> hgd;        // host copy of the device group table
-  int nblocks = 0;                   // blocks of one fused launch over all groups
-  int nx_max = 1;                    // widest row of the groups' grids
   GroupDesc* dgd = nullptr;
   SysDev* dsys = nullptr;
   SysState* dstate = nullptr;
@@ -568,42 +578,42 @@ bool tiles_fit(const Ctx& C, const TileCfg& t) {
   return true;
 }
 
-// The tile of batches that are not tuned (too small for the timing to tell, or
+// The tile of grids in batches that are not tuned (too small for the timing to tell, or
 // WRI_FLAG_NO_AUTOTUNE): the window march with the shortest chain of work per
 // workgroup, 13.8 us per iteration on 4 systems of 70x37x19 cells against 164 us
-// with the slab tile 4,4,32,0,0.  It depends on the grids only, so a system gives
-// the same bits alone and in a batch.
+// with the slab tile 4,4,32,0,0, which grids that it does not fit keep.  It depends on
+// the system's own grid only, so a system gives the same bits alone and in a batch;
+// where both kinds of grid are in the batch each kind has launches of its own.
 constexpr TileCfg kUntunedWindow{4, 1, 2, kWindow, 0};
-TileCfg untuned_tile(const Ctx& C) { return tiles_fit(C, kUntunedWindow) ? kUntunedWindow : kCands[0]; }
 
-// One tile shape for every group: per-group tile counts and the device table
-// that maps a block of a fused launch to (group, system, tile).
-// upload = false: the table goes up with upload_head.
-int set_config(Ctx& C, const TileCfg& cfg, bool upload = true) {
-  C.tiling.resize(C.groups.size());
-  C.hgd.resize(C.groups.size());
-  int b0 = 0;
-  C.nx_max = 1;
-  for (size_t gi = 0; gi < C.groups.size(); ++gi) {
+// Entries [g0, size of C.order) of the group table: the groups of a part, which maps a block
+// of its launches to (group, system, tile).
+int add_part(Ctx& C, const TileCfg& cfg, const std::vector<int>& groups) {
+  if (groups.empty()) return WRI_OK;
+  Part P{cfg, (int)C.order.size(), (int)groups.size(), 0, 1};
+  int tmax = 1;
+  for (int gi : groups) {
     const wri_grid& g = C.grids[C.groups[gi].grid];
     const Tiling t = make_tiling(cfg, g);
-    C.nx_max = std::max(C.nx_max, (int)g.nx);
+    P.nx_max = std::max(P.nx_max, (int)g.nx);
     if (!cfg_supported(cfg) || !tile_fits(C, cfg, g))
       return fail(WRI_EINVAL, "tile w=%d ry=%d tz=%d pf=%d: %d tiles per system, %d partial slots", cfg.w, cfg.ry,
                   cfg.tz, cfg.pf, t.ntiles(), max_tiles(g, C.L.window));
     C.tiling[gi] = t;
-    GroupDesc& d = C.hgd[gi];
+    C.order.push_back(gi);
+    GroupDesc d{};
     d.rhs0 = C.groups[gi].rhs0;
     d.nrhs = C.groups[gi].nrhs;
     d.tiles_x = t.tx;
     d.tiles_y = t.ty;
     d.tz = cfg.tz;
     d.ntiles = t.ntiles();
-    d.block0 = b0;
+    d.block0 = P.nblocks;
     d.tile_major = cfg.order;
-    b0 += d.nrhs * d.ntiles;
+    P.nblocks += d.nrhs * d.ntiles;
+    tmax = std::max(tmax, d.ntiles);
+    C.hgd.push_back(d);
   }
-  C.nblocks = b0;
   // XCD chunk: half of the largest system's tiles, and at least 16 workgroups.
   // Measured on the 48-system 128^3 batch (whole solves): with the 64 x 16 x 32
   // tile (64 tiles per system) halves 18.20 solves/s, whole systems 18.15,
@@ -612,11 +622,36 @@ int set_config(Ctx& C, const TileCfg& cfg, bool upload = true) {
   // tile (16 tiles per system) chunks of 8, 16 and 32 workgroups took 2.424,
   // 2.399 and 2.401 s per evaluation.
   constexpr int kMinXChunk = 16;
-  int tmax = 1;
-  for (const auto& d : C.hgd) tmax = std::max(tmax, d.ntiles);
-  for (auto& d : C.hgd) d.xchunk = std::max(kMinXChunk, tmax / 2);
-  if (!C.hgd.empty())
-    if (const int rc = cfg.pf == kWindow ? upload_buckets(C) : upload_colmaps(C); rc != WRI_OK) return rc;
+  for (int e = P.g0; e < P.g0 + P.ng; ++e) C.hgd[e].xchunk = std::max(kMinXChunk, tmax / 2);
+  C.parts.push_back(P);
+  return cfg.pf == kWindow ? upload_buckets(C) : upload_colmaps(C);
+}
+
+void clear_parts(Ctx& C) {
+  C.tiling.resize(C.groups.size());
+  C.parts.clear();
+  C.order.clear();
+  C.hgd.clear();
+}
+
+// Each group's untuned tile; the group table goes up with upload_head.
+int set_untuned(Ctx& C) {
+  clear_parts(C);
+  std::vector<int> window, slab;
+  for (int gi = 0; gi < (int)C.groups.size(); ++gi)
+    (tile_fits(C, kUntunedWindow, C.grids[C.groups[gi].grid]) ? window : slab).push_back(gi);
+  const int rc = add_part(C, kUntunedWindow, window);
+  return rc != WRI_OK ? rc : add_part(C, kCands[0], slab);
+}
+
+// One tile shape for every group.
+// upload = false: the table goes up with upload_head.
+int set_config(Ctx& C, const TileCfg& cfg, bool upload = true) {
+  clear_parts(C);
+  std::vector<int> all(C.groups.size());
+  for (size_t gi = 0; gi < all.size(); ++gi) all[gi] = (int)gi;
+  const int rc = add_part(C, cfg, all);
+  if (rc != WRI_OK) return rc;
   if (upload && !C.hgd.empty()) {
     WRI_HIP(hipMemcpyAsync(C.dgd, C.hgd.data(), sizeof(GroupDesc) * C.hgd.size(), hipMemcpyHostToDevice, C.st));
     WRI_HIP(hipStreamSynchronize(C.st));  // C.hgd may change before an asynchronous copy would finish
@@ -624,8 +659,7 @@ int set_config(Ctx& C, const TileCfg& cfg, bool upload = true) {
   return WRI_OK;
 }
 
-const TileCfg& cur_cfg(const Ctx& C) { return C.tiling.front().cfg; }
-
+const TileCfg& cur_cfg(const Ctx& C) { return C.parts.front().cfg; }
 
 // Convergence tail.  Once few systems still iterate, the tiling tuned for the
 // full batch leaves compute units idle, or ends every launch with a partly
@@ -734,25 +768,28 @@ TileCfg tail_tile(const Ctx& C, const std::vector<SysState>& hs, const TailPlan&
 // partials of ||s||^2 that the next forward launch reads folded to the new tile
 // count.
 int switch_tiling(Ctx& C, const TileCfg& cfg) {
-  std::vector<int> n_old(C.hgd.size());
-  for (size_t gi = 0; gi < C.hgd.size(); ++gi) n_old[gi] = C.hgd[gi].ntiles;
+  std::vector<int> n_old(C.groups.size());
+  for (size_t gi = 0; gi < C.groups.size(); ++gi) n_old[gi] = C.tiling[gi].ntiles();
   const int rc = set_config(C, cfg);
   if (rc != WRI_OK) return rc;
-  for (size_t gi = 0; gi < C.hgd.size(); ++gi)
-    WRI_HIP(launch_fold_partials(C.dsys, C.part_s, C.hgd[gi].rhs0, C.hgd[gi].nrhs, n_old[gi], C.hgd[gi].ntiles, C.st));
+  for (size_t gi = 0; gi < C.groups.size(); ++gi)
+    WRI_HIP(launch_fold_partials(C.dsys, C.part_s, C.groups[gi].rhs0, C.groups[gi].nrhs, n_old[gi],
+                                 C.tiling[gi].ntiles(), C.st));
   return WRI_OK;
 }
 
-// the forward launch of CGLS iteration k and the adjoint launch, each over all groups
+// the forward pass of CGLS iteration k and the adjoint pass: a launch for each part
 int forward(Ctx& C, int k, hipStream_t s) {
-  WRI_HIP(launch_fwd(cur_cfg(C), C.dsys, C.dstate, C.part_s, C.part_d, C.dgd, C.hgd.data(), (int)C.hgd.size(),
-                     C.nblocks, C.nx_max, C.wrec, k, s));
+  for (const Part& P : C.parts)
+    WRI_HIP(launch_fwd(P.cfg, C.dsys, C.dstate, C.part_s, C.part_d, C.dgd + P.g0, C.hgd.data() + P.g0, P.ng,
+                       P.nblocks, P.nx_max, C.wrec, k, s));
   return WRI_OK;
 }
 
 int adjoint(Ctx& C, hipStream_t s) {
-  WRI_HIP(launch_adj(cur_cfg(C), C.dsys, C.dstate, C.part_d, C.part_s, C.dgd, C.hgd.data(), (int)C.hgd.size(),
-                     C.nblocks, C.nx_max, C.wrec, s));
+  for (const Part& P : C.parts)
+    WRI_HIP(launch_adj(P.cfg, C.dsys, C.dstate, C.part_d, C.part_s, C.dgd + P.g0, C.hgd.data() + P.g0, P.ng,
+                       P.nblocks, P.nx_max, C.wrec, s));
   return WRI_OK;
 }
 
@@ -833,17 +870,19 @@ std::string tune_key(const Ctx& C, int64_t* total) {
   return key;
 }
 
-// The tile of a batch that needs no timing: forced, cached, or too small for the
-// choice to matter.
-bool known_tile(const Ctx& C, TileCfg* out, bool* forced) {
-  *forced = forced_tile(C, out);
-  if (*forced) return true;
-  *out = untuned_tile(C);
-  if (C.flags & WRI_FLAG_NO_AUTOTUNE) return true;
+// The tiles of a batch before any timing: forced, cached or untuned.  *known: they need
+// no timing (the last of them where the batch is too small for the choice to matter).
+int first_tiles(Ctx& C, bool* forced, bool* known) {
+  TileCfg t;
+  *known = true;
+  *forced = forced_tile(C, &t);
+  if (*forced) return set_config(C, t, false);
+  if (C.flags & WRI_FLAG_NO_AUTOTUNE) return set_untuned(C);
   int64_t total = 0;
   const auto it = g_tuned.find(tune_key(C, &total));
-  if (it != g_tuned.end()) *out = it->second;
-  return it != g_tuned.end() || total < (int64_t)64 * 64 * 64;
+  if (it != g_tuned.end()) return set_config(C, it->second, false);
+  *known = total < (int64_t)64 * 64 * 64;
+  return set_untuned(C);
 }
 
 constexpr int64_t kWindowOnlyCells = 1 << 21, kSlabOnlyCells = 1 << 24;
@@ -907,9 +946,11 @@ std::string graph_key(const Ctx& C, int64_t k0, int chunk) {
   snprintf(buf, sizeof(buf), "%p,%p,%p,%p,%p,%p,%d|", (const void*)C.dsys, (const void*)C.dstate,
            (const void*)C.part_s, (const void*)C.part_d, (const void*)C.dgd, (const void*)C.wrec, (int)C.hgd.size());
   k += buf;
-  const TileCfg& c = cur_cfg(C);
-  snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d,%d,%d;", c.w, c.ry, c.tz, c.pf, c.order, C.nblocks, C.nx_max);
-  k += buf;
+  for (const Part& P : C.parts) {
+    const TileCfg& c = P.cfg;
+    snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d,%d,%d,%d;", c.w, c.ry, c.tz, c.pf, c.order, P.ng, P.nblocks, P.nx_max);
+    k += buf;
+  }
   for (const auto& d : C.hgd) {
     snprintf(buf, sizeof(buf), "%d,%d,%d,%d,%d,%d,%d,%d;", d.rhs0, d.nrhs, d.tiles_x, d.tiles_y, d.tz, d.ntiles,
              d.block0, d.xchunk);
@@ -982,12 +1023,11 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
   TileCfg main_cfg = kCands[0];  // the tile of the full batch (reported by the timing)
   int n_switches = 0;            // tiling changes of the convergence tail
   if (C.n_sys > 0) {
-    TileCfg cfg;
-    bool is_forced = false;
-    const bool known = known_tile(C, &cfg, &is_forced);
+    bool is_forced = false, known = false;
+    int rc = first_tiles(C, &is_forced, &known);
+    if (rc != WRI_OK) return rc;
     fill_tables(known || !warm);
-    int rc = set_config(C, cfg, false);
-    if (rc == WRI_OK) rc = upload_head(C);
+    rc = upload_head(C);
     if (rc != WRI_OK) return rc;
     if (!known) {
       rc = autotune(C);
@@ -1147,9 +1187,11 @@ int run_batched(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
       if (gp) WRI_HIP(launch_zero_f32(gp, (size_t)n, C.st));
       continue;
     }
-    const int cpt = grad_cpt(C.grids[g], L.fine_grad);
-    WRI_HIP(launch_grad(C.dsys, C.dstate, G->rhs0, G->nrhs, n, gp, C.part_j, L.part_j_stride, cpt, 0, C.st));
-    WRI_HIP(launch_finalize(C.dsys, C.dstate, C.part_j, grad_blocks(n, cpt), L.part_j_stride, G->rhs0, G->nrhs, C.st));
+    const int cpt = grad_cpt(C.grids[g], L.fine_grad), nparts = grad_blocks(n, cpt);
+    double* part_j = L.fine_grad ? at<double>(C.ws, L.off_part_g[g]) : C.part_j + (size_t)G->rhs0 * L.part_j_stride;
+    const int stride = L.fine_grad ? nparts : L.part_j_stride;
+    WRI_HIP(launch_grad(C.dsys, C.dstate, G->rhs0, G->nrhs, n, gp, part_j, stride, cpt, 0, C.st));
+    WRI_HIP(launch_finalize(C.dsys, C.dstate, part_j, nparts, stride, G->rhs0, G->nrhs, C.st));
   }
   const int rc = read_states(C, hs);
   if (rc != WRI_OK) return rc;
@@ -1278,7 +1320,7 @@ int run_plain(Ctx& C, float* const* grad, std::vector<SysState>& hs) {
 int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, const wri_system* sys,
                  int32_t n_sys, int32_t mode, int32_t max_iter, int32_t flags, wri_c32* const* u_out,
                  wri_result* res, void* ws, size_t ws_bytes, void* stream, float* const* grad, double* J_out,
-                 wri_c64* alpha_out, bool window = true) {
+                 wri_c64* alpha_out) {
   int rc = validate(grids, n_grids, sys, n_sys, mode, max_iter);
   if (rc != WRI_OK) return rc;
   if (n_sys > 0 && res == nullptr) return fail(WRI_EINVAL, "res is NULL");
@@ -1304,7 +1346,7 @@ int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, 
   C.grids = grids; C.n_grids = n_grids; C.m = m; C.sys = sys; C.n_sys = n_sys;
   C.mode = mode; C.max_iter = max_iter; C.flags = flags; C.u_out = u_out;
   C.st = reinterpret_cast<hipStream_t>(stream);
-  C.L = make_layout(grids, n_grids, sys, n_sys, flags, window);
+  C.L = make_layout(grids, n_grids, sys, n_sys, flags);
   if (ws == nullptr || ws_bytes < C.L.total)
     return fail(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, C.L.total);
   C.ws = reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(ws)));
@@ -1364,11 +1406,13 @@ int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, 
 // device, held by the loaded code object until the process ends.  On the host
 // the name `scratch` is only a stand-in symbol: every kernel argument and copy
 // uses the per-device address that hipGetSymbolAddress returns.
-// Beyond the documented size it has room for the window march's partial sums,
-// which do not count against the limit; a batch whose sums exceed that room runs
-// the slab tile.
+// Beyond the documented size it has room for the window march's partial sums and
+// receiver buckets, which do not count against the limit.  The largest shares of the
+// limit that they can come to: sums a seventh (16 B a tile of two cells beside 7 vectors
+// of 8 B a cell, on planes of one cell) and buckets a tenth (8 B a receiver beside 28, and
+// 56 a cell).
 constexpr size_t kNoAllocBytes = WRI_NOALLOC_SCRATCH_BYTES;
-constexpr size_t kScratchBytes = kNoAllocBytes + ((size_t)4 << 20);
+constexpr size_t kScratchBytes = kNoAllocBytes + kNoAllocBytes / 4;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 std::mutex g_scratch_mutex;
@@ -1439,8 +1483,7 @@ int wri_solve_noalloc(const wri_grid* grids, int32_t n_grids, const float* const
     if (flags & WRI_FLAG_TIMING) return fail(WRI_EINVAL, "wri_solve_noalloc: WRI_FLAG_TIMING creates events");
     int rc = validate(grids, n_grids, sys, n_sys, mode, max_iter);
     if (rc != WRI_OK) return rc;
-    const Layout L = make_layout(grids, n_grids, sys, n_sys, flags);
-    const size_t need = L.total_slab;
+    const size_t need = make_layout(grids, n_grids, sys, n_sys, flags).total_slab;
     if (need > kNoAllocBytes)
       return fail(WRI_ENOWS,
                   "wri_solve_noalloc: these systems need %zu bytes of workspace; the fixed scratch holds %zu "
@@ -1454,7 +1497,7 @@ int wri_solve_noalloc(const wri_grid* grids, int32_t n_grids, const float* const
     // autotuner's events would allocate); the default tile unless WRI_TILE forces one
     return solve_common(grids, n_grids, m, sys, n_sys, mode, max_iter,
                         flags | WRI_FLAG_NO_GRAPH | WRI_FLAG_NO_AUTOTUNE, u_out, res, ws, kScratchBytes, stream,
-                        nullptr, nullptr, nullptr, L.total <= kScratchBytes);
+                        nullptr, nullptr, nullptr);
   } catch (const std::exception& e) {
     return fail(WRI_EINVAL, "exception: %s", e.what());
   }

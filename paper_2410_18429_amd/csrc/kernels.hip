@@ -2458,7 +2458,7 @@ k_grad(const SysDev* __restrict__ sysv, const SysState* __restrict__ stv, int rh
         double tot = 0.0;
 #pragma unroll
         for (int i = 0; i < NW; ++i) tot += red[i][tid];
-        part_j[(size_t)(rhs0 + t0 + r0 + tid) * stride + blockIdx.x] = tot;
+        part_j[(size_t)(t0 + r0 + tid) * stride + blockIdx.x] = tot;
       }
       __syncthreads();
     }
@@ -2490,7 +2490,7 @@ k_finalize(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const do
   SysState* T = stv + rhs;
   double v = 0.0;
   if (part_j != nullptr)
-    for (int i = threadIdx.x; i < nparts; i += 64) v += part_j[(size_t)rhs * stride + i];
+    for (int i = threadIdx.x; i < nparts; i += 64) v += part_j[(size_t)blockIdx.x * stride + i];
   for (int q = threadIdx.x; q < S.n_rec; q += 64) v += norm2d(S.r2[q]);
   v = wave_sum(v);
   if (threadIdx.x == 0) {

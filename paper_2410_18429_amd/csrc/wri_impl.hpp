@@ -151,6 +151,7 @@ hipError_t launch_fwd(const TileCfg& c, const SysDev* sys, SysState* st, const d
 hipError_t launch_adj(const TileCfg& c, const SysDev* sys, SysState* st, const double* part_d, double* part_s,
                       const GroupDesc* gd, const GroupDesc* host_gd, int ngroups, int nblocks, int nx_max,
                       const WinRec* wrec, hipStream_t s, int setup_only = 0);
+// part_j: stride partial sums for each of the nrhs systems
 hipError_t launch_grad(const SysDev* sys, SysState* st, int rhs0, int nrhs, int n, float* grad,
                        double* part_j, int stride, int cpt, int accumulate, hipStream_t s);
 hipError_t launch_finalize(const SysDev* sys, SysState* st, const double* part_j, int nparts,
