@@ -1768,22 +1768,6 @@ struct SlotSum {
   }
 };
 
-// The group of a block, from the launch arguments (up to kWinGroups groups; a
-// load from the device table would be one more memory latency in every launch).
-__device__ __forceinline__ GroupDesc win_group(const WinGroups& G, int logical) {
-  GroupDesc d = G.g[0];
-  if (G.n <= kWinGroups) {
-#pragma unroll
-    for (int i = 1; i < kWinGroups; ++i)
-      if (i < G.n && logical >= G.g[i].block0) d = G.g[i];
-  } else {
-    int g = 0;
-    while (g + 1 < G.n && logical >= G.table[g + 1].block0) ++g;
-    d = G.table[g];
-  }
-  return d;
-}
-
 // Receivers of the tile, in two steps: the loads that find them, issued with the
 // tile's other loads, and recq[], the receiver index of each own cell (-1: none; a
 // receiver cell occurs once in a system's list).  Every workgroup scans a list of up to

@@ -54,8 +54,8 @@ struct OgSys {
   const int* uptr; const int* ucell; const int* uq; const double* uw;
   const float* m;
   int n, ns, nr, nu;
-  int est, max_iter, nx, ny, nz, nb, zc;
-  int nparts;   // partial sums of a stencil pass
+  int est, max_iter, nx, ny, nz, nb;
+  int part0, nparts;   // first partial sum of the system, and partial sums of a stencil pass
   double c, lam, rtol2, omega, omega2, h2inv, sp_scale, inv_nb;
   double2 alpha;  // KNOWN-mode weight
 };
@@ -120,7 +120,8 @@ __global__ void __launch_bounds__(kThreads) k_og_init(const OgSys* __restrict__ 
 }
 
 // Work items of the stencil passes: a 64 x 4 tile of (x, y) columns (one
-// thread each) and a chunk of S.zc planes marched in z.  Each plane of the
+// thread each) and a chunk of planes marched in z (up to 16, and so few that there
+// are items for kParts blocks).  Each plane of the
 // recomputed vector (p_k or r_{k+1}) is staged with a one-cell halo in LDS for
 // the x/y neighbours; the z-neighbours stay in registers.  Every block runs
 // the same number of items and planes (the barriers are uniform); threads
@@ -134,18 +135,21 @@ struct TileWork {
   bool in;
 };
 
+__device__ __forceinline__ int chunk_planes(const OgSys& S) { return max(1, min(kZc, S.n / (kParts * kThreads))); }
+
 __device__ __forceinline__ int tile_items(const OgSys& S) {
-  return ((S.nx + 63) / 64) * ((S.ny + kTy - 1) / kTy) * ((S.nz + S.zc - 1) / S.zc);
+  const int zc = chunk_planes(S);
+  return ((S.nx + 63) / 64) * ((S.ny + kTy - 1) / kTy) * ((S.nz + zc - 1) / zc);
 }
 
 __device__ __forceinline__ TileWork tile_work(const OgSys& S, int w) {
   const int tx_n = (S.nx + 63) / 64, ty_n = (S.ny + kTy - 1) / kTy;
-  const int t = w % (tx_n * ty_n), zc = w / (tx_n * ty_n);
+  const int t = w % (tx_n * ty_n), chunk = w / (tx_n * ty_n), planes = chunk_planes(S);
   TileWork W;
   W.x = (t % tx_n) * 64 + (threadIdx.x & 63);
   W.y = (t / tx_n) * kTy + (threadIdx.x >> 6);
-  W.z0 = zc * S.zc;
-  W.z1 = min(W.z0 + S.zc, S.nz);
+  W.z0 = chunk * planes;
+  W.z1 = min(W.z0 + planes, S.nz);
   W.in = W.x < S.nx && W.y < S.ny;
   W.col = W.y * S.nx + W.x;
   return W;
@@ -162,13 +166,13 @@ __device__ __forceinline__ void halo_cell(int h, int x0, int y0, int* hx, int* h
 
 // Forward pass of iteration k: p_k = s_k + beta p_{k-1} (computed at the cell
 // and its neighbours), t = A p_k, per-block partials of ||t||^2 (the
-// source-column term is added by k_og_alpha).  grid (kParts, nsys).
+// source-column term is added by k_og_alpha).  grid (kParts, systems from s0 on).
 __global__ void __launch_bounds__(kThreads) k_og_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv,
-                                                     double* __restrict__ parts, int stride) {
+                                                     double* __restrict__ parts, int s0) {
   __shared__ double red[kThreads / 64];
   __shared__ float2 pl[kTy + 2][66];
-  const OgSys& S = sy[blockIdx.y];
-  const OgState& T = stv[blockIdx.y];
+  const OgSys& S = sy[s0 + blockIdx.y];
+  const OgState& T = stv[s0 + blockIdx.y];
   double acc = 0.0;
   if (T.status == kActive) {  // uniform over the block
     const int k = T.iters;
@@ -210,20 +214,20 @@ __global__ void __launch_bounds__(kThreads) k_og_fwd(const OgSys* __restrict__ s
     }
   }
   acc = bsum(acc, red);
-  if (threadIdx.x == 0) parts[(size_t)blockIdx.y * stride + blockIdx.x] = acc;
+  if (threadIdx.x == 0) parts[S.part0 + blockIdx.x] = acc;
 }
 
 // delta = ||t||^2 with the source column (t[src] -= c p_a w) + ||t2||^2 with
 // t2 = lam P p_k; a = gamma / delta; x_a += a p_a; r2 -= a t2  (grid nsys)
 __global__ void __launch_bounds__(kThreads) k_og_alpha(const OgSys* __restrict__ sy, OgState* __restrict__ stv,
-                                                       const double* __restrict__ parts, int stride) {
+                                                       const double* __restrict__ parts) {
   __shared__ double red[kThreads / 64];
   const OgSys& S = sy[blockIdx.x];
   OgState& T = stv[blockIdx.x];
   if (T.status != kActive) return;  // uniform over the block
   const float2* __restrict__ pk = S.p[T.iters & 1];
   double v = 0.0;
-  for (int i = threadIdx.x; i < S.nparts; i += kThreads) v += parts[(size_t)blockIdx.x * stride + i];
+  for (int i = threadIdx.x; i < S.nparts; i += kThreads) v += parts[S.part0 + i];
   if (S.est && (int)threadIdx.x < S.ns) {  // distinct source cells, one per thread
     const int c = S.scell[threadIdx.x];
     const double w = S.sw[threadIdx.x];
@@ -273,13 +277,13 @@ __global__ void __launch_bounds__(kThreads) k_og_alpha(const OgSys* __restrict__
 // s = A^H r_{k+1}, x += a p_k, per-block partials of ||s||^2 (the receiver
 // rows are added by k_og_beta).  setup = 1: the pass on r_0 with no update
 // (s_0 = A^H r_0, copied r_0 into r_1).  Same tiles as k_og_fwd.
-// grid (kParts, nsys).
+// grid (kParts, systems from s0 on).
 __global__ void __launch_bounds__(kThreads) k_og_adj(const OgSys* __restrict__ sy, const OgState* __restrict__ stv,
-                                                     double* __restrict__ parts, int stride, int setup) {
+                                                     double* __restrict__ parts, int s0, int setup) {
   __shared__ double red[kThreads / 64];
   __shared__ float2 pl[kTy + 2][66];
-  const OgSys& S = sy[blockIdx.y];
-  const OgState& T = stv[blockIdx.y];
+  const OgSys& S = sy[s0 + blockIdx.y];
+  const OgState& T = stv[s0 + blockIdx.y];
   double acc = 0.0;
   if (setup || T.status == kActive) {  // uniform over the block
     const int k = setup ? 0 : T.iters;
@@ -323,7 +327,7 @@ __global__ void __launch_bounds__(kThreads) k_og_adj(const OgSys* __restrict__ s
     }
   }
   acc = bsum(acc, red);
-  if (threadIdx.x == 0) parts[(size_t)blockIdx.y * stride + blockIdx.x] = acc;
+  if (threadIdx.x == 0) parts[S.part0 + blockIdx.x] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -339,28 +343,28 @@ __global__ void __launch_bounds__(kThreads) k_og_adj(const OgSys* __restrict__ s
 constexpr int kOwW = 4, kOwZ = 4;
 constexpr int kOwMaxRow = 512;   // wider rows (and planes past one resource) take the march: LDS 48 KB
 
-// (system, tile) of a block: neighbouring tiles of a system on one XCD; tiles are
-// counted for the largest grid of the call
-__device__ __forceinline__ void ow_block(int tiles, int* sys, int* tile) {
-  const int logical = xcd_remap(blockIdx.x, gridDim.x, max(16, tiles / 2));
-  *sys = logical / tiles;
-  *tile = logical - *sys * tiles;
+// (system, tile) of a block: neighbouring tiles of a system on one XCD
+__device__ __forceinline__ int ow_block(const WinGroups& G, int* sys) {
+  const int logical = xcd_remap(blockIdx.x, gridDim.x, G.g[0].xchunk);
+  const GroupDesc d = win_group(G, logical);
+  const int local = logical - d.block0, q = local / d.ntiles;
+  *sys = d.rhs0 + q;
+  return local - q * d.ntiles;
 }
 
 template <int CX>
 __global__ void __launch_bounds__(64 * kOwW)
-k_ow_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, int stride,
-         int tiles) {
+k_ow_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, WinGroups G) {
   using Tile = Win<kOwW, CX, kOwZ>;
   constexpr int NT = Tile::NT;
   __shared__ double red[kThreads / 64];
   extern __shared__ float2 ow_f[];   // [kOwZ][B + 2 nx]: p
   const int tid = threadIdx.x;
-  int sys, tile;
-  ow_block(tiles, &sys, &tile);
+  int sys;
+  const int tile = ow_block(G, &sys);
   const OgSys& S = sy[sys];
   const OgState& T = stv[sys];
-  if (T.status != kActive || tile >= S.nparts) return;
+  if (T.status != kActive) return;
   Tile Q;
   Q.setup(S.nx, S.ny, S.nz, tile, (S.nx * S.ny + Tile::B - 1) / Tile::B);
   const int nx = Q.nx, wl = Q.wl, k = T.iters;
@@ -421,24 +425,23 @@ k_ow_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* 
     }
   }
   acc = bsum(acc, red);
-  if (tid == 0) parts[(size_t)sys * stride + tile] = acc;
+  if (tid == 0) parts[S.part0 + tile] = acc;
 }
 
 // SETUP: s_0 = A^H r_0, no update
 template <int CX, bool SETUP>
 __global__ void __launch_bounds__(64 * kOwW)
-k_ow_adj(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, int stride,
-         int tiles) {
+k_ow_adj(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, WinGroups G) {
   using Tile = Win<kOwW, CX, kOwZ>;
   constexpr int NT = Tile::NT;
   __shared__ double red[kThreads / 64];
   extern __shared__ float2 ow_f[];   // [kOwZ][B + 2 nx]: r
   const int tid = threadIdx.x;
-  int sys, tile;
-  ow_block(tiles, &sys, &tile);
+  int sys;
+  const int tile = ow_block(G, &sys);
   const OgSys& S = sy[sys];
   const OgState& T = stv[sys];
-  if (T.status != kActive || tile >= S.nparts) return;
+  if (T.status != kActive) return;
   Tile Q;
   Q.setup(S.nx, S.ny, S.nz, tile, (S.nx * S.ny + Tile::B - 1) / Tile::B);
   const int nx = Q.nx, wl = Q.wl, k = T.iters;
@@ -512,7 +515,7 @@ k_ow_adj(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* 
     }
   }
   acc = bsum(acc, red);
-  if (tid == 0) parts[(size_t)sys * stride + tile] = acc;
+  if (tid == 0) parts[S.part0 + tile] = acc;
 }
 
 // The receiver rows of S^H r (s += lam P^H r2 over the distinct receiver
@@ -562,13 +565,13 @@ __device__ void og_finish_s(const OgSys& S, const float2* __restrict__ r, double
 
 // gamma0 = ||S^H b||^2 after the set-up pass; p_a = s_a, beta = 0 (p_{-1} = 0)  (grid nsys)
 __global__ void __launch_bounds__(kThreads) k_og_start(const OgSys* __restrict__ sy, OgState* __restrict__ stv,
-                                                       const double* __restrict__ parts, int stride) {
+                                                       const double* __restrict__ parts) {
   __shared__ double red[kThreads / 64];
   __shared__ double2 src[kMaxCells];
   const OgSys& S = sy[blockIdx.x];
   OgState& T = stv[blockIdx.x];
   double v = 0.0;
-  for (int i = threadIdx.x; i < S.nparts; i += kThreads) v += parts[(size_t)blockIdx.x * stride + i];
+  for (int i = threadIdx.x; i < S.nparts; i += kThreads) v += parts[S.part0 + i];
   double g;
   double2 sa;
   og_finish_s(S, S.r[0], v, red, src, &g, &sa);
@@ -584,14 +587,14 @@ __global__ void __launch_bounds__(kThreads) k_og_start(const OgSys* __restrict__
 
 // s_{k+1} completed, gamma' , beta, statuses, p_a; iteration k done  (grid nsys)
 __global__ void __launch_bounds__(kThreads) k_og_beta(const OgSys* __restrict__ sy, OgState* __restrict__ stv,
-                                                      const double* __restrict__ parts, int stride) {
+                                                      const double* __restrict__ parts) {
   __shared__ double red[kThreads / 64];
   __shared__ double2 src[kMaxCells];
   const OgSys& S = sy[blockIdx.x];
   OgState& T = stv[blockIdx.x];
   if (T.status != kActive) return;  // uniform over the block
   double v = 0.0;
-  for (int i = threadIdx.x; i < S.nparts; i += kThreads) v += parts[(size_t)blockIdx.x * stride + i];
+  for (int i = threadIdx.x; i < S.nparts; i += kThreads) v += parts[S.part0 + i];
   double gnew;
   double2 sa;
   og_finish_s(S, S.r[(T.iters + 1) & 1], v, red, src, &gnew, &sa);
@@ -617,7 +620,7 @@ __global__ void __launch_bounds__(kThreads) k_og_rnorm(const OgSys* __restrict__
   double acc = 0.0;
   for (int c = blockIdx.x * kThreads + threadIdx.x; c < S.n; c += kParts * kThreads) acc += nrm(r[c]);
   acc = bsum(acc, red);
-  if (threadIdx.x == 0) parts[blockIdx.y * kParts + blockIdx.x] = acc;
+  if (threadIdx.x == 0) parts[S.part0 + blockIdx.x] = acc;
 }
 
 // J = ||r||^2 + ||r2||^2; e^H (A u) from A x at the source cells, each
@@ -642,7 +645,7 @@ __global__ void __launch_bounds__(kThreads) k_og_final(const OgSys* __restrict__
     const double w = S.sw[threadIdx.x];
     ax[threadIdx.x] = make_double2(w * (double)t.x, w * (double)t.y);
   }
-  for (int i = threadIdx.x; i < kParts; i += kThreads) v += parts[blockIdx.x * kParts + i];
+  for (int i = threadIdx.x; i < kParts; i += kThreads) v += parts[S.part0 + i];
   for (int q = threadIdx.x; q < S.nr; q += kThreads) v += nrm(S.r2[q]);
   v = bsum(v, red);
   if (threadIdx.x == 0) {
@@ -657,14 +660,12 @@ __global__ void __launch_bounds__(kThreads) k_og_final(const OgSys* __restrict__
   }
 }
 
-// g = -sum over the grid's systems of 2 omega^2 Re(conj(x) r)  (systems idx[0..k))
+// g = -sum over the grid's systems of 2 omega^2 Re(conj(x) r)  (systems s0 to s0 + k)
 __global__ void __launch_bounds__(kThreads) k_og_grad(const OgSys* __restrict__ sy, const OgState* __restrict__ stv,
-                                                      const int* __restrict__ idx, int k, int n,
-                                                      float* __restrict__ g) {
+                                                      int s0, int k, int n, float* __restrict__ g) {
   for (int c = blockIdx.x * kThreads + threadIdx.x; c < n; c += gridDim.x * kThreads) {
     double acc = 0.0;
-    for (int j = 0; j < k; ++j) {
-      const int i = idx[j];
+    for (int i = s0; i < s0 + k; ++i) {
       if (stv[i].status == kBreakdown) continue;
       const OgSys& S = sy[i];
       const float2 a = S.x[c], b = S.r[stv[i].iters & 1][c];
@@ -793,31 +794,67 @@ SysTables build_tables(const wri_grid* grids, const wri_system* sys, int n_sys, 
 
 int64_t ncell(const wri_grid& g) { return (int64_t)g.nx * g.ny * g.nz; }
 
-// Tiles of the window passes of a call (0: the column march), for the largest grid
-struct OgTiles { int cx, n, lds; };
+// Cells per thread of a grid's window passes (two once a plane fills 64 tiles); 0: the
+// column march.  By the grid alone: a system gives the same bits in any batch.
+int ow_cx(const wri_grid& g) {
+  if (g.nx > kOwMaxRow || ncell(g) >= (int64_t(1) << 28)) return 0;
+  return g.nx * g.ny >= 64 * 256 ? 2 : 1;
+}
 int ow_tiles(const wri_grid& g, int cx) {
   const int b = 64 * kOwW * cx;
   return (g.nx * g.ny + b - 1) / b * ((g.nz + kOwZ - 1) / kOwZ);
 }
-OgTiles og_tiles(const wri_grid* grids, const wri_system* sys, int n_sys) {
-  OgTiles t{1, 0, 0};
-  int nx = 1;
-  for (int k = 0; k < n_sys; ++k) {
-    const wri_grid& g = grids[sys[k].grid];
-    if (g.nx > kOwMaxRow || (int64_t)g.nx * g.ny * g.nz >= (int64_t(1) << 28)) return {1, 0, 0};
-    if (g.nx * g.ny >= 64 * 256) t.cx = 2;   // two cells a thread once a plane fills 64 tiles
-    nx = std::max(nx, g.nx);
+
+// Systems sorted by passes and grid; the groups (systems of one grid) of each kind of passes.
+struct OgPlan {
+  std::vector<int> order;              // slot -> system
+  std::vector<int> cx;                 // per slot
+  std::vector<GroupDesc> groups[3];    // by cx: rhs0, nrhs; window passes: ntiles, block0, xchunk
+  int blocks[3] = {0, 0, 0}, nx[3] = {1, 1, 1};
+  size_t table_entries() const {       // of the groups that do not ride in the launch arguments
+    size_t n = 0;
+    for (int c = 1; c <= 2; ++c)
+      if (groups[c].size() > (size_t)kWinGroups) n += groups[c].size();
+    return n;
   }
-  for (int k = 0; k < n_sys; ++k) t.n = std::max(t.n, ow_tiles(grids[sys[k].grid], t.cx));
-  t.lds = (int)sizeof(float2) * kOwZ * (64 * kOwW * t.cx + 2 * nx);
-  return t;
+};
+
+OgPlan og_plan(const wri_grid* grids, const wri_system* sys, int n_sys) {
+  OgPlan P;
+  P.order.resize(n_sys);
+  for (int k = 0; k < n_sys; ++k) P.order[k] = k;
+  std::stable_sort(P.order.begin(), P.order.end(), [&](int a, int b) {
+    const int ga = sys[a].grid, gb = sys[b].grid, ca = ow_cx(grids[ga]), cb = ow_cx(grids[gb]);
+    return ca != cb ? ca < cb : ga < gb;
+  });
+  for (int p = 0; p < n_sys; ++p) {
+    const wri_grid& g = grids[sys[P.order[p]].grid];
+    const int cx = ow_cx(g);
+    P.cx.push_back(cx);
+    auto& v = P.groups[cx];
+    if (v.empty() || sys[P.order[p - 1]].grid != sys[P.order[p]].grid) {
+      GroupDesc d{};
+      d.rhs0 = p;
+      d.ntiles = cx > 0 ? ow_tiles(g, cx) : kParts;
+      d.block0 = P.blocks[cx];
+      v.push_back(d);
+    }
+    v.back().nrhs++;
+    P.blocks[cx] += v.back().ntiles;
+    P.nx[cx] = std::max(P.nx[cx], (int)g.nx);
+  }
+  for (auto& v : P.groups) {
+    int most = 1;
+    for (const auto& d : v) most = std::max(most, d.ntiles);
+    for (auto& d : v) d.xchunk = std::max(16, most / 2);
+  }
+  return P;
 }
 
 struct OgLayout {
-  OgTiles tiles{1, 0, 0};
-  int stride = kParts;            // partial sums per system
+  std::vector<int> part0;         // per slot: first partial sum
   std::vector<size_t> vec, rvec;  // per system: 7 wavefield vectors (x unless u_out), r2 and t2
-  size_t sys = 0, state = 0, parts = 0, idx = 0, tables = 0, total = 0;
+  size_t sys = 0, state = 0, parts = 0, groups = 0, tables = 0, total = 0;
 };
 
 int validate_offgrid(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, const wri_positions* pos,
@@ -853,11 +890,16 @@ int validate_offgrid(const wri_grid* grids, int n_grids, const wri_system* sys, 
   return WRI_OK;
 }
 
-int og_layout(const wri_grid* grids, const wri_system* sys, int n_sys, const SysTables& T, OgLayout* L) {
+int og_layout(const wri_grid* grids, const wri_system* sys, int n_sys, const OgPlan& P, const SysTables& T, OgLayout* L) {
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = al(o + std::max<size_t>(bytes, 1)); return r; };
-  L->tiles = og_tiles(grids, sys, n_sys);
-  L->stride = std::max(kParts, L->tiles.n);
+  int64_t sums = 0;
+  L->part0.resize(n_sys);
+  for (int p = 0; p < n_sys; ++p) {
+    const wri_grid& g = grids[sys[P.order[p]].grid];
+    L->part0[p] = (int)sums;
+    sums += std::max(kParts, P.cx[p] > 0 ? ow_tiles(g, P.cx[p]) : kParts);
+  }
   L->vec.resize(n_sys);
   L->rvec.resize(n_sys);
   for (int k = 0; k < n_sys; ++k) {
@@ -865,10 +907,10 @@ int og_layout(const wri_grid* grids, const wri_system* sys, int n_sys, const Sys
     L->rvec[k] = take(2 * al(sizeof(float2) * (size_t)sys[k].n_rec));
   }
   L->state = take(sizeof(OgState) * (size_t)std::max(n_sys, 1));
-  L->parts = take(sizeof(double) * (size_t)L->stride * std::max(n_sys, 1));
+  L->parts = take(sizeof(double) * (size_t)std::max<int64_t>(sums, kParts));
   // the tables the host writes, in one piece
   L->sys = take(sizeof(OgSys) * (size_t)std::max(n_sys, 1));
-  L->idx = take(sizeof(int) * (size_t)std::max(n_sys, 1));
+  L->groups = take(std::max(sizeof(GroupDesc) * P.table_entries(), sizeof(int) * (size_t)std::max(n_sys, 1)));
   L->tables = o;
   for (int k = 0; k < n_sys; ++k) o = al(o + T.bytes(k));
   L->total = o + kAl;
@@ -888,8 +930,9 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     if (m[g] == nullptr || (grad != nullptr && grad[g] == nullptr))
       return report_error(WRI_EINVAL, "m[%d] or grad[%d] is NULL", g, g);
   const SysTables tabs = build_tables(grids, sys, n_sys, pos);
+  const OgPlan P = og_plan(grids, sys, n_sys);
   OgLayout L;
-  og_layout(grids, sys, n_sys, tabs, &L);
+  og_layout(grids, sys, n_sys, P, tabs, &L);
   if (ws == nullptr || ws_bytes < L.total)
     return report_error(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, L.total);
   char* base = reinterpret_cast<char*>(al(reinterpret_cast<uintptr_t>(ws)));
@@ -916,7 +959,9 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     return reinterpret_cast<const double*>(put(v.data(), sizeof(double) * v.size()));
   };
   int64_t nmax = 1;
-  for (int k = 0; k < n_sys; ++k) {
+  std::vector<int> first(tabs.sets.size(), -1);   // slot whose tables a set's later systems share
+  for (int p = 0; p < n_sys; ++p) {
+    const int k = P.order[p];
     const wri_system& s = sys[k];
     const wri_grid& g = grids[s.grid];
     const Point& src = tabs.src[k];
@@ -925,7 +970,7 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     const size_t vb = al(sizeof(float2) * (size_t)n);
     const size_t rb = al(sizeof(float2) * (size_t)s.n_rec);
     float2* v = reinterpret_cast<float2*>(base + L.vec[k]);
-    OgSys& S = hs[k];
+    OgSys& S = hs[p];
     S = OgSys{};
     S.x = (u_out != nullptr && u_out[k] != nullptr) ? reinterpret_cast<float2*>(u_out[k]) : v;
     S.r[0] = reinterpret_cast<float2*>(base + L.vec[k] + vb);
@@ -939,13 +984,15 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     S.d = reinterpret_cast<const float2*>(s.d);
     S.scell = reinterpret_cast<const int*>(put(src.cells, sizeof(int) * src.n));
     S.sw = reinterpret_cast<const double*>(put(src.w, sizeof(double) * src.n));
-    if (k > 0 && tabs.set_of[k] == tabs.set_of[k - 1]) {
-      const OgSys& B = hs[k - 1];
+    int& f = first[tabs.set_of[k]];
+    if (f >= 0) {
+      const OgSys& B = hs[f];
       S.rptr = B.rptr; S.rcell = B.rcell; S.rw = B.rw;
       S.uptr = B.uptr; S.ucell = B.ucell; S.uq = B.uq; S.uw = B.uw;
     } else {
       S.rptr = ints(T.rptr); S.rcell = ints(T.rcell); S.rw = dbls(T.rw);
       S.uptr = ints(T.uptr); S.ucell = ints(T.ucell); S.uq = ints(T.uq); S.uw = dbls(T.uw);
+      f = p;
     }
     S.n = (int)n;
     S.ns = src.n;
@@ -961,8 +1008,8 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     S.alpha = make_double2(s.alpha.re, s.alpha.im);
     S.m = m[s.grid];
     S.nx = g.nx; S.ny = g.ny; S.nz = g.nz; S.nb = g.nb;
-    S.zc = (int)std::max<int64_t>(1, std::min<int64_t>(kZc, n / ((int64_t)kParts * kThreads)));  // >= kParts items
-    S.nparts = L.tiles.n > 0 ? ow_tiles(g, L.tiles.cx) : kParts;
+    S.part0 = L.part0[p];
+    S.nparts = P.cx[p] > 0 ? ow_tiles(g, P.cx[p]) : kParts;
     S.h2inv = 1.0 / (g.h * g.h);
     if (g.nb > 0) {
       const double d0 = 3.0 * g.v_ref * std::log(1000.0) / (2.0 * g.nb * g.h);
@@ -974,31 +1021,49 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   OgSys* dsys = reinterpret_cast<OgSys*>(base + L.sys);
   OgState* dst = reinterpret_cast<OgState*>(base + L.state);
   double* parts = reinterpret_cast<double*>(base + L.parts);
-  int* didx = reinterpret_cast<int*>(base + L.idx);
-  // systems grouped by grid for the gradient pass
-  std::vector<int> order(n_sys);
-  for (int k = 0; k < n_sys; ++k) order[k] = k;
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sys[a].grid < sys[b].grid; });
   std::memcpy(head.data(), hs.data(), sizeof(OgSys) * n_sys);
-  std::memcpy(head.data() + (L.idx - L.sys), order.data(), sizeof(int) * n_sys);
+  WinGroups win[3] = {};
+  size_t at = L.groups - L.sys;
+  for (int c = 1; c <= 2; ++c) {
+    const auto& v = P.groups[c];
+    win[c].n = (int)v.size();
+    std::copy_n(v.begin(), std::min(v.size(), (size_t)kWinGroups), win[c].g);
+    if (v.size() <= (size_t)kWinGroups) continue;
+    win[c].table = reinterpret_cast<const GroupDesc*>(base + L.sys + at);
+    std::memcpy(head.data() + at, v.data(), sizeof(GroupDesc) * v.size());
+    at += sizeof(GroupDesc) * v.size();
+  }
   OG_HIP(hipMemcpyAsync(base + L.sys, head.data(), head.size(), hipMemcpyHostToDevice, st));
 
   const dim3 vgrid(nblk(nmax), n_sys), pgrid(kParts, n_sys);
-  const OgTiles W = L.tiles;
-  const dim3 wgrid((unsigned)(W.n * (int64_t)n_sys));
+  auto lds = [&](int c) { return (unsigned)(sizeof(float2) * kOwZ * (64 * kOwW * c + 2 * P.nx[c])); };
+  const int march = P.groups[0].empty() ? 0 : P.blocks[0] / kParts;   // the first systems
+  // a stencil pass: a launch for each kind of passes in the call
+  auto fwd = [&]() {
+    if (march > 0) hipLaunchKernelGGL(k_og_fwd, dim3(kParts, march), dim3(kThreads), 0, st, dsys, dst, parts, 0);
+    if (win[1].n > 0) hipLaunchKernelGGL(k_ow_fwd<1>, dim3(P.blocks[1]), dim3(kThreads), lds(1), st, dsys, dst, parts, win[1]);
+    if (win[2].n > 0) hipLaunchKernelGGL(k_ow_fwd<2>, dim3(P.blocks[2]), dim3(kThreads), lds(2), st, dsys, dst, parts, win[2]);
+  };
+  auto adj = [&](bool setup) {
+    if (march > 0) hipLaunchKernelGGL(k_og_adj, dim3(kParts, march), dim3(kThreads), 0, st, dsys, dst, parts, 0, setup ? 1 : 0);
+    if (win[1].n > 0) {
+      if (setup) hipLaunchKernelGGL((k_ow_adj<1, true>), dim3(P.blocks[1]), dim3(kThreads), lds(1), st, dsys, dst, parts, win[1]);
+      else hipLaunchKernelGGL((k_ow_adj<1, false>), dim3(P.blocks[1]), dim3(kThreads), lds(1), st, dsys, dst, parts, win[1]);
+    }
+    if (win[2].n > 0) {
+      if (setup) hipLaunchKernelGGL((k_ow_adj<2, true>), dim3(P.blocks[2]), dim3(kThreads), lds(2), st, dsys, dst, parts, win[2]);
+      else hipLaunchKernelGGL((k_ow_adj<2, false>), dim3(P.blocks[2]), dim3(kThreads), lds(2), st, dsys, dst, parts, win[2]);
+    }
+  };
   // `count` iterations of every system (finished systems skip inside the kernels):
   // four launches per iteration.  Eager: a graph of the chunk, which holds this
   // workspace's pointers and so lives for one call only, cost 0.3 ms to build.
   auto enqueue = [&](int count) -> int {
     for (int it = 0; it < count; ++it) {
-      if (W.n == 0) hipLaunchKernelGGL(k_og_fwd, pgrid, dim3(kThreads), 0, st, dsys, dst, parts, L.stride);
-      else if (W.cx == 1) hipLaunchKernelGGL(k_ow_fwd<1>, wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
-      else hipLaunchKernelGGL(k_ow_fwd<2>, wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
-      hipLaunchKernelGGL(k_og_alpha, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts, L.stride);
-      if (W.n == 0) hipLaunchKernelGGL(k_og_adj, pgrid, dim3(kThreads), 0, st, dsys, dst, parts, L.stride, 0);
-      else if (W.cx == 1) hipLaunchKernelGGL((k_ow_adj<1, false>), wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
-      else hipLaunchKernelGGL((k_ow_adj<2, false>), wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
-      hipLaunchKernelGGL(k_og_beta, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts, L.stride);
+      fwd();
+      hipLaunchKernelGGL(k_og_alpha, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts);
+      adj(false);
+      hipLaunchKernelGGL(k_og_beta, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts);
       OG_HIP(hipGetLastError());
     }
     return WRI_OK;
@@ -1006,10 +1071,8 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   // set-up: x = 0, r_0 = b, s_0 = S^H b, gamma0
   hipLaunchKernelGGL(k_og_zero, vgrid, dim3(kThreads), 0, st, dsys);
   hipLaunchKernelGGL(k_og_init, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst);
-  if (W.n == 0) hipLaunchKernelGGL(k_og_adj, pgrid, dim3(kThreads), 0, st, dsys, dst, parts, L.stride, 1);
-  else if (W.cx == 1) hipLaunchKernelGGL((k_ow_adj<1, true>), wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
-  else hipLaunchKernelGGL((k_ow_adj<2, true>), wgrid, dim3(kThreads), W.lds, st, dsys, dst, parts, L.stride, W.n);
-  hipLaunchKernelGGL(k_og_start, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts, L.stride);
+  adj(true);
+  hipLaunchKernelGGL(k_og_start, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts);
   OG_HIP(hipGetLastError());
   std::vector<OgState> hst(n_sys);
   auto read = [&]() -> int {
@@ -1035,22 +1098,24 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   hipLaunchKernelGGL(k_og_final, dim3(n_sys), dim3(kThreads), 0, st, dsys, dst, parts);
   OG_HIP(hipGetLastError());
   if (grad != nullptr)
-    for (int g = 0, p0 = 0; g < n_grids; ++g) {
-      int cnt = 0;
-      while (p0 + cnt < n_sys && sys[order[p0 + cnt]].grid == g) ++cnt;
+    for (int g = 0; g < n_grids; ++g) {
+      GroupDesc d{};
+      for (const auto& v : P.groups)
+        for (const auto& e : v)
+          if (sys[P.order[e.rhs0]].grid == g) d = e;
       const int64_t n = ncell(grids[g]);
-      hipLaunchKernelGGL(k_og_grad, dim3(nblk(n)), dim3(kThreads), 0, st, dsys, dst, didx + p0, cnt, (int)n,
-                         grad[g]);
+      hipLaunchKernelGGL(k_og_grad, dim3(nblk(n)), dim3(kThreads), 0, st, dsys, dst, d.rhs0, d.nrhs, (int)n, grad[g]);
       OG_HIP(hipGetLastError());
-      p0 += cnt;
     }
   if ((rc = read()) != WRI_OK) return rc;
   for (const auto& T : hst)
     if (T.status == kActive) return report_error(WRI_EHIP, "internal: systems active past max_iter");
   double Jtot = 0.0;
   int ret = WRI_OK;
+  std::vector<int> slot(n_sys);
+  for (int p = 0; p < n_sys; ++p) slot[P.order[p]] = p;
   for (int k = 0; k < n_sys; ++k) {
-    const OgState& T = hst[k];
+    const OgState& T = hst[slot[k]];
     double ee = 0.0;
     for (int i = 0; i < tabs.src[k].n; ++i) ee += tabs.src[k].w[i] * tabs.src[k].w[i];
     wri_result& r = res[k];
@@ -1059,7 +1124,7 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     r.relres = T.gamma0 > 0.0 ? std::sqrt(std::max(T.gamma, 0.0) / T.gamma0) : 0.0;
     r.J = T.J;
     if (mode == WRI_ESTIMATE) {
-      r.alpha = wri_c64{hs[k].c * T.xa.x, hs[k].c * T.xa.y};
+      r.alpha = wri_c64{hs[slot[k]].c * T.xa.x, hs[slot[k]].c * T.xa.y};
       r.alpha_ls = ee > 0.0 ? wri_c64{T.eau.x / ee, T.eau.y / ee} : wri_c64{0.0, 0.0};
     } else {
       r.alpha = sys[k].alpha;
@@ -1086,7 +1151,7 @@ size_t wri_offgrid_workspace_bytes(const wri_grid* grids, int32_t n_grids, const
   try {
     if (validate_offgrid(grids, n_grids, sys, n_sys, pos, WRI_ESTIMATE, 0) != WRI_OK) return 0;
     OgLayout L;
-    og_layout(grids, sys, n_sys, build_tables(grids, sys, n_sys, pos), &L);
+    og_layout(grids, sys, n_sys, og_plan(grids, sys, n_sys), build_tables(grids, sys, n_sys, pos), &L);
     return L.total;
   } catch (const std::exception& e) {
     report_error(WRI_EINVAL, "exception: %s", e.what());

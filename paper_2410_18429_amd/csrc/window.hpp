@@ -24,6 +24,26 @@ __device__ __forceinline__ int xcd_remap(int b, int nb, int q) {
   return (round * kXCD + xcd) * q + off;
 }
 
+// The group of a block, from the launch arguments (up to kWinGroups groups; a
+// load from the device table would be one more memory latency in every launch).
+__device__ __forceinline__ GroupDesc win_group(const WinGroups& G, int logical) {
+  GroupDesc d = G.g[0];
+  if (G.n <= kWinGroups) {
+#pragma unroll
+    for (int i = 1; i < kWinGroups; ++i)
+      if (i < G.n && logical >= G.g[i].block0) d = G.g[i];
+  } else {
+    int g = 0, end = G.n;
+    while (end - g > 1) {
+      const int mid = (g + end) / 2;
+      if (logical >= G.table[mid].block0) g = mid;
+      else end = mid;
+    }
+    d = G.table[g];
+  }
+  return d;
+}
+
 typedef __amdgpu_buffer_rsrc_t BufRes;
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr unsigned kOOB = 0x80000000u;   // beyond any resource (records < 2^31)
