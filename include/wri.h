@@ -193,7 +193,9 @@ int wri_validate(const wri_grid* grids, int32_t n_grids,
  *   u_out     host array of n_sys DEVICE pointers (n(grid) complex each) receiving u,
  *             or NULL (u is then kept in the workspace only)
  *   res       HOST, n_sys results (required)
- *   ws        DEVICE workspace of ws_bytes >= wri_workspace_bytes(...) */
+ *   ws        DEVICE workspace of ws_bytes >= wri_workspace_bytes(...); one without
+ *             room for the window march's sums and receiver tables (about a
+ *             thousandth of it) is accepted and solved by the slab marches */
 int wri_solve(const wri_grid* grids, int32_t n_grids, const float* const* m,
               const wri_system* sys, int32_t n_sys, int32_t mode, int32_t max_iter,
               int32_t flags, wri_c32* const* u_out, wri_result* res,

@@ -227,10 +227,12 @@ struct Group {
 
 int64_t n_buckets(const wri_grid& g) { return (cells(g) >> kBucketShift) + 2; }   // and the end of the last
 
-Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, int flags) {
+// window = false: without the window march (slab tiles only), in less memory.
+Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, int flags,
+                   bool window = true) {
   Layout L;
   L.plain = (flags & WRI_FLAG_PLAIN) != 0;
-  L.window = !L.plain;
+  L.window = window && !L.plain;
   L.order.resize(n_sys);
   for (int i = 0; i < n_sys; ++i) L.order[i] = i;
   std::stable_sort(L.order.begin(), L.order.end(), [&](int a, int b) { return sys[a].grid < sys[b].grid; });
@@ -309,21 +311,33 @@ Layout make_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
     L.off_rvec.assign(1, take(2 * L.rvec_bytes_plain));
   }
   L.total_slab = o + kAlign;  // slack for aligning the caller's base pointer
-  if (L.window) {  // the window march has more tiles: partial sums of their own, at the end
+  if (L.window) {
+    // The window march has more tiles, and the gradient pass with one cell per thread
+    // more workgroups: partial sums of their own at the end where the slabs' have no
+    // room for them.
+    auto widen = [&](size_t* off, size_t have, size_t need) {
+      if (align_up(std::max<size_t>(have, 1)) < need) *off = take(need);
+    };
+    const int slab_slots = slots;
     slots = 0;
     for (int p = 0; p < n_sys; ++p) {
       L.slot_base[p] = slots;
       slots += max_tiles(grids[sys[L.order[p]].grid], true);
     }
-    L.off_part_d = take(sizeof(double) * std::max(slots, 1));
-    L.off_part_s = take(sizeof(double) * std::max(slots, 1));
-    // the gradient pass with one cell per thread, too
+    widen(&L.off_part_d, sizeof(double) * slab_slots, sizeof(double) * slots);
+    widen(&L.off_part_s, sizeof(double) * slab_slots, sizeof(double) * slots);
     L.fine_grad = true;
     std::vector<int> count(n_grids, 0);
     for (int i = 0; i < n_sys; ++i) ++count[sys[i].grid];
-    for (int g = 0; g < n_grids; ++g)
-      L.off_part_g.push_back(count[g] == 0 ? 0 : take(sizeof(double) * (size_t)count[g] *
-                                                      grad_blocks((int)cells(grids[g]), grad_cpt(grids[g], true))));
+    size_t sums = 0;
+    L.off_part_g.resize(n_grids);
+    for (int g = 0; g < n_grids; ++g) {
+      L.off_part_g[g] = sizeof(double) * sums;
+      sums += (size_t)count[g] * grad_blocks((int)cells(grids[g]), grad_cpt(grids[g], true));
+    }
+    size_t off = L.off_part_j;
+    widen(&off, sizeof(double) * (size_t)gb * std::max(n_sys, 1), sizeof(double) * sums);
+    for (auto& g : L.off_part_g) g += off;
     for (auto& rs : L.sets) {
       if (!rs.bucketed()) continue;
       if (L.off_wrec == 0) L.off_wrec = take(sizeof(WinRec) * (size_t)n_sys);
@@ -855,10 +869,11 @@ bool forced_tile(const Ctx& C, TileCfg* out) {
   return true;
 }
 
-// Tuned tiles are cached per (device, mode, grid shapes and system counts).
+// Tuned tiles are cached per (device, mode, room for the window march, grid shapes and
+// system counts).
 std::string tune_key(const Ctx& C, int64_t* total) {
   char buf[96];
-  snprintf(buf, sizeof(buf), "%d|%d|", C.dev, C.mode);
+  snprintf(buf, sizeof(buf), "%d|%d|%d|", C.dev, C.mode, C.L.window ? 1 : 0);
   std::string key = buf;
   *total = 0;
   for (const auto& G : C.groups) {
@@ -1347,6 +1362,8 @@ int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, 
   C.mode = mode; C.max_iter = max_iter; C.flags = flags; C.u_out = u_out;
   C.st = reinterpret_cast<hipStream_t>(stream);
   C.L = make_layout(grids, n_grids, sys, n_sys, flags);
+  if (ws != nullptr && ws_bytes < C.L.total && ws_bytes >= C.L.total_slab)
+    C.L = make_layout(grids, n_grids, sys, n_sys, flags, false);   // the slab marches' own size is enough for them
   if (ws == nullptr || ws_bytes < C.L.total)
     return fail(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, C.L.total);
   C.ws = reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(ws)));
@@ -1448,6 +1465,12 @@ int report_error(int code, const char* fmt, ...) {
   return code;
 }
 
+size_t solver_bytes(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, int mode, int flags,
+                    bool window) {
+  if (validate(grids, n_grids, sys, n_sys, mode, 0) != WRI_OK) return 0;
+  return make_layout(grids, n_grids, sys, n_sys, flags, window).total;
+}
+
 }  // namespace wri
 
 using namespace wri;
@@ -1456,8 +1479,7 @@ extern "C" {
 
 size_t wri_workspace_bytes(const wri_grid* grids, int32_t n_grids, const wri_system* sys, int32_t n_sys,
                            int32_t mode, int32_t flags) {
-  if (validate(grids, n_grids, sys, n_sys, mode, 0) != WRI_OK) return 0;
-  return make_layout(grids, n_grids, sys, n_sys, flags).total;
+  return solver_bytes(grids, n_grids, sys, n_sys, mode, flags, true);
 }
 
 int wri_validate(const wri_grid* grids, int32_t n_grids, const wri_system* sys, int32_t n_sys, int32_t mode,

@@ -144,13 +144,13 @@ struct FwiLayout {
   std::vector<size_t> w, z, adj, rec;
 };
 
-int fwi_layout(const wri_grid* grids, int n_grids, const std::vector<wri_system>& sf, int mode, int flags,
+// window: see solver_bytes
+int fwi_layout(const wri_grid* grids, int n_grids, const std::vector<wri_system>& sf, int flags, bool window,
                FwiLayout* L) {
-  (void)mode;
   const int n_sys = (int)sf.size();
-  const size_t a = wri_workspace_bytes(grids, n_grids, sf.data(), n_sys, WRI_KNOWN, flags);
+  const size_t a = solver_bytes(grids, n_grids, sf.data(), n_sys, WRI_KNOWN, flags, window);
   if (a == 0) return WRI_EINVAL;
-  const size_t b = wri_workspace_bytes(grids, n_grids, sf.data(), n_sys, WRI_KNOWN, flags | WRI_FLAG_ADJOINT_SOURCE);
+  const size_t b = solver_bytes(grids, n_grids, sf.data(), n_sys, WRI_KNOWN, flags | WRI_FLAG_ADJOINT_SOURCE, window);
   if (b == 0) return WRI_EINVAL;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = al(o + std::max<size_t>(bytes, 1)); return r; };
@@ -189,8 +189,11 @@ int fwi_run(const wri_grid* grids, int32_t n_grids, const float* const* m, const
       if (u_out[i] == nullptr) return report_error(WRI_EINVAL, "u_out[%d] is NULL", i);
   std::vector<wri_system> sf = forward_systems(sys, n_sys, mode);
   FwiLayout L;
-  rc = fwi_layout(grids, n_grids, sf, mode, flags, &L);
+  rc = fwi_layout(grids, n_grids, sf, flags, true, &L);
   if (rc != WRI_OK) return rc;
+  if (FwiLayout slab; ws_bytes < L.total && fwi_layout(grids, n_grids, sf, flags, false, &slab) == WRI_OK &&
+                      ws_bytes >= slab.total)
+    L = slab;
   if (ws == nullptr || ws_bytes < L.total)
     return report_error(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, L.total);
   char* base = reinterpret_cast<char*>(al(reinterpret_cast<uintptr_t>(ws)));
@@ -314,7 +317,7 @@ size_t wri_fwi_workspace_bytes(const wri_grid* grids, int32_t n_grids, const wri
   try {
     if (wri_validate(grids, n_grids, sys, n_sys, mode, 0) != WRI_OK) return 0;
     FwiLayout L;
-    if (fwi_layout(grids, n_grids, forward_systems(sys, n_sys, mode), mode, flags, &L) != WRI_OK) return 0;
+    if (fwi_layout(grids, n_grids, forward_systems(sys, n_sys, mode), flags, true, &L) != WRI_OK) return 0;
     return L.total;
   } catch (const std::exception& e) {
     report_error(WRI_EINVAL, "exception: %s", e.what());

@@ -239,13 +239,14 @@ struct ModelLayout {
   std::vector<size_t> m, g;
 };
 
+// window: see solver_bytes
 int model_layout(const wri_grid* model, const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys,
-                 int mode, int flags, ModelLayout* L) {
+                 int mode, int flags, bool window, ModelLayout* L) {
   for (int gi = 0; gi < n_grids; ++gi) {
     int rc = check_pair(model, grids + gi);
     if (rc != WRI_OK) return rc;
   }
-  const size_t sb = wri_workspace_bytes(grids, n_grids, sys, n_sys, mode, flags);
+  const size_t sb = solver_bytes(grids, n_grids, sys, n_sys, mode, flags, window);
   if (sb == 0) return WRI_EINVAL;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t r = o; o = al(o + std::max<size_t>(bytes, 1)); return r; };
@@ -295,7 +296,7 @@ size_t wri_model_workspace_bytes(const wri_grid* model_grid, const wri_grid* gri
       return 0;
     }
     ModelLayout L;
-    if (model_layout(model_grid, grids, n_grids, sys, n_sys, mode, flags, &L) != WRI_OK) return 0;
+    if (model_layout(model_grid, grids, n_grids, sys, n_sys, mode, flags, true, &L) != WRI_OK) return 0;
     return L.total;
   } catch (const std::exception& e) {
     report_error(WRI_EINVAL, "exception: %s", e.what());
@@ -314,8 +315,12 @@ int wri_objective_grad_model(const wri_grid* model_grid, const float* m_model, c
     int rc = wri_validate(grids, n_grids, sys, n_sys, mode, max_iter);
     if (rc != WRI_OK) return rc;
     ModelLayout L;
-    rc = model_layout(model_grid, grids, n_grids, sys, n_sys, mode, flags, &L);
+    rc = model_layout(model_grid, grids, n_grids, sys, n_sys, mode, flags, true, &L);
     if (rc != WRI_OK) return rc;
+    if (ModelLayout slab; ws_bytes < L.total &&
+                          model_layout(model_grid, grids, n_grids, sys, n_sys, mode, flags, false, &slab) == WRI_OK &&
+                          ws_bytes >= slab.total)
+      L = slab;
     if (ws == nullptr || ws_bytes < L.total)
       return report_error(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, L.total);
     char* base = reinterpret_cast<char*>(al(reinterpret_cast<uintptr_t>(ws)));

@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "../../include/wri.h"
+
 namespace wri {
 
 // x-extent of a slab tile: one 64-wide wavefront spans a row of cells.
@@ -120,6 +122,11 @@ struct WinGroups {
   const GroupDesc* table;
   GroupDesc g[kWinGroups];
 };
+
+// Workspace of the batched solver (0: invalid arguments); window = false: the least it
+// accepts, with which it runs the slab marches only.
+size_t solver_bytes(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys, int mode, int flags,
+                    bool window);
 
 // Records a failure for wri_last_error (thread-local) and returns code.
 int report_error(int code, const char* fmt, ...);
