@@ -277,7 +277,9 @@ int wri_tv(const wri_grid* grid, const float* m, double eps, double gamma, doubl
  *   rings of curvature pairs s_i = m_{i+1} - m_i, y_i = g_{i+1} - g_i; the
  *   `count` pairs in use end at slot `newest` (older pairs in the slots
  *   before it, cyclically).  Dot products are float64.  Stream-ordered (no
- *   synchronisation).  ws: DEVICE, wri_lbfgs_workspace_bytes(capacity). */
+ *   synchronisation).  ws: DEVICE, wri_lbfgs_workspace_bytes(capacity); the two-loop
+ *   recursion, which runs where the inner products' partial sums have no room, takes
+ *   less (8704 bytes up to capacity 14). */
 size_t wri_lbfgs_workspace_bytes(int32_t capacity);
 int wri_lbfgs_direction(int64_t n, const float* g, const float* S, const float* Y, int32_t capacity,
                         int32_t count, int32_t newest, double h0, float* dir, void* ws, size_t ws_bytes,

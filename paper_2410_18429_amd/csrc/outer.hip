@@ -230,8 +230,9 @@ __global__ void k_scale_sc(float* __restrict__ y, int64_t n, const double* __res
 // 128^3: 36 launches and 219 us -> 3 launches and 47 us; 256x256x192 847 -> 215
 // us, 290 -> 92 bytes per cell at 5.4 TB/s).  Inner products and
 // coefficients are float64; dir is rounded once instead of after every update.
-// Up to kLbFused pairs (the accumulators live in registers: 88 for 8 pairs);
-// longer memories take the recursion below.
+// Up to kLbFused pairs (the accumulators live in registers: 88 for 8 pairs); longer
+// memories, and workspaces without room for the partials of all inner products, take the
+// recursion below.
 constexpr int kLbFused = 8;
 constexpr int kLbBlocks = 512;   // partial sums per inner product
 
@@ -303,7 +304,7 @@ k_lb_gram(LbPairs P, const float* __restrict__ g, int64_t n, double* __restrict_
     double v = 0.0;
 #pragma unroll
     for (int k = 0; k < kRedThreads / 64; ++k) v += red[k][i];
-    part[(int64_t)i * kLbBlocks + blockIdx.x] = v;
+    part[(int64_t)i * gridDim.x + blockIdx.x] = v;
   }
 }
 
@@ -321,7 +322,7 @@ __global__ void __launch_bounds__(1024) k_lb_coef(const double* __restrict__ par
 #pragma unroll
     for (int k = 0; k < kLbBlocks / 64; ++k) {
       const int b = lane + 64 * k;
-      v += b < nparts ? part[(int64_t)i * kLbBlocks + b] : 0.0;
+      v += b < nparts ? part[(int64_t)i * nparts + b] : 0.0;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -432,12 +433,12 @@ int grid_blocks(int64_t n) { return (int)std::min<int64_t>(kRedBlocks, std::max<
 // ---- host helpers ----------------------------------------------------------------
 size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Room for three float64 arrays of the grid and kRedBlocks + 1 sums (what the query has
-// always returned).  The one pass keeps only per-workgroup partials (at most kTvBlocks,
-// and at most one a cell) in the first part and their sum in the last.
+// The pass keeps per-workgroup partials (at most kTvBlocks, and at most one a cell) and
+// their sum.  The query returns what it always has, room for three float64 arrays of the
+// grid and kRedBlocks + 1 sums.
 constexpr int kTvBlocks = 2048;
-size_t tv_sum_off(int64_t n) { return 3 * al(sizeof(double) * n); }
-size_t tv_ws_bytes(int64_t n) { return tv_sum_off(n) + al(sizeof(double) * (kRedBlocks + 1)); }
+size_t tv_ws_bytes(int64_t n) { return 3 * al(sizeof(double) * n) + al(sizeof(double) * (kRedBlocks + 1)); }
+size_t tv_used_bytes(int64_t n) { return al(sizeof(double) * (std::min<int64_t>(n, kTvBlocks) + 1)); }
 
 // sum of n partials in one fixed order (one block)
 __global__ void __launch_bounds__(kRedThreads) k_sum_parts(const double* __restrict__ part, int n, double* __restrict__ out) {
@@ -475,8 +476,8 @@ int tv_launch(const wri_grid& g, const float* m, double eps, double scale, float
 int tv_run(const wri_grid& g, const float* m, double eps, double gamma, double* value, float* grad, char* ws,
            hipStream_t st) {
   const int64_t n = (int64_t)g.nx * g.ny * g.nz;
-  double* part = reinterpret_cast<double*>(ws);
-  double* sum = reinterpret_cast<double*>(ws + tv_sum_off(n));
+  double* sum = reinterpret_cast<double*>(ws);
+  double* part = sum + 1;
   float* gr = gamma != 0.0 ? grad : nullptr;
   const int nb = n < (int64_t(1) << 31)
                      ? tv_launch<int>(g, m, eps, gamma / g.h, gr, part, st)
@@ -489,15 +490,19 @@ int tv_run(const wri_grid& g, const float* m, double eps, double gamma, double* 
   return WRI_OK;
 }
 
-struct LbWs { double* part; double* sc; };
+// Workspace of a direction: the scalars, then partial sums in what is left of it.
+struct LbWs {
+  double *sc, *part;
+  int64_t parts;   // room for partial sums
+};
 constexpr int kLbParts = std::max(kRedBlocks, kLbBlocks * LbIndex<kLbFused>::kCount);
-size_t lb_ws_bytes(int cap) { return al(sizeof(double) * kLbParts) + al(sizeof(double) * (2 * cap + 4)); }
-LbWs lb_ws(char* ws) {
-  LbWs w;
-  w.part = reinterpret_cast<double*>(ws);
-  w.sc = reinterpret_cast<double*>(ws + al(sizeof(double) * kLbParts));
-  return w;
+size_t lb_ws_bytes(int cap, int64_t parts) { return al(sizeof(double) * (2 * cap + 4)) + al(sizeof(double) * parts); }
+LbWs lb_ws(char* ws, size_t bytes, int cap) {
+  const size_t sc = lb_ws_bytes(cap, 0);
+  return {reinterpret_cast<double*>(ws), reinterpret_cast<double*>(ws + sc), (int64_t)((bytes - sc) / sizeof(double))};
 }
+int lb_blocks(int64_t n) { return (int)std::min<int64_t>(kLbBlocks, (n + kRedThreads - 1) / kRedThreads); }
+int lb_count(int m) { return 2 * m + m * (m + 1); }   // LbIndex<m>::kCount
 
 int dot_to(const float* a, const float* b, int64_t n, const LbWs& w, int op, int dst, int ia, int ib, hipStream_t st) {
   hipLaunchKernelGGL(k_dot32, dim3(kRedBlocks), dim3(kRedThreads), 0, st, a, b, n, w.part);
@@ -509,7 +514,8 @@ int dot_to(const float* a, const float* b, int64_t n, const LbWs& w, int op, int
 
 template <int M>
 int lbfgs_fused(const LbPairs& P, int64_t n, const float* g, double h0, float* dir, const LbWs& w, hipStream_t st) {
-  const int nb = (int)std::min<int64_t>(kLbBlocks, (n + kRedThreads - 1) / kRedThreads);
+  static_assert(LbIndex<M>::kCount == 2 * M + M * (M + 1), "");
+  const int nb = lb_blocks(n);
   hipLaunchKernelGGL((k_lb_gram<M>), dim3(nb), dim3(kRedThreads), 0, st, P, g, n, w.part);
   OUTER_HIP(hipGetLastError());
   hipLaunchKernelGGL((k_lb_coef<M>), dim3(1), dim3(1024), 0, st, w.part, nb, h0, w.sc);
@@ -524,8 +530,7 @@ int lbfgs_fused(const LbPairs& P, int64_t n, const float* g, double h0, float* d
 // of S and Y starts at i * stride.
 // h0 > 0: H0 = h0 I; otherwise H0 = s.y / y.y of the newest pair.
 int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int64_t stride, int cap, int count, int newest,
-              double h0, float* dir, char* ws, hipStream_t st) {
-  LbWs w = lb_ws(ws);
+              double h0, float* dir, const LbWs& w, hipStream_t st) {
   const int rho0 = 0, alp0 = cap, ih0 = 2 * cap, it0 = 2 * cap + 1, it1 = 2 * cap + 2;
   const int nbk = grid_blocks(n);
   auto slot = [&](int j) { return ((newest - (count - 1) + j) % cap + cap) % cap; };  // j = 0 oldest
@@ -534,7 +539,8 @@ int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int64_t
     OUTER_HIP(hipGetLastError());
     return WRI_OK;
   }
-  if (count <= kLbFused) {
+  // (the recursion needs the partials of one inner product only)
+  if (count <= kLbFused && (int64_t)lb_count(count) * lb_blocks(n) <= w.parts) {
     LbPairs P{};
     for (int j = 0; j < count; ++j) {
       P.s[j] = S + slot(j) * stride;
@@ -593,24 +599,45 @@ int lbfgs_run(int64_t n, const float* g, const float* S, const float* Y, int64_t
 
 // ---- the adaptive-tolerance driver (Algorithm 2) ------------------------------------
 struct AwriLayout {
-  size_t solver = 0, off_vec = 0, off_tv = 0, off_lb = 0, off_red = 0, off_u = 0, total = 0;
+  size_t solver = 0, off_vec = 0, off_tv = 0, off_lb = 0, lb_bytes = 0, off_red = 0, off_u = 0, total = 0;
 };
-AwriLayout awri_layout(int64_t n, size_t solver_bytes, int memory, int n_sys, bool warm) {
+AwriLayout awri_layout(int64_t n, size_t solver_bytes, size_t tv_bytes, size_t lb_bytes, int memory, int n_sys,
+                       bool warm) {
   AwriLayout L;
-  L.solver = al(solver_bytes);
-  L.off_vec = L.solver;
+  L.solver = solver_bytes;
+  L.off_vec = al(solver_bytes);
   const size_t vb = al(sizeof(float) * n);
   size_t off = L.off_vec + vb * (size_t)(5 + 2 * std::max(memory, 0));  // g, g_try, m_try, dir, tmp, S, Y
   L.off_tv = off;
-  off += tv_ws_bytes(n);
+  off += tv_bytes;
   L.off_lb = off;
-  off += lb_ws_bytes(std::max(memory, 1));
+  L.lb_bytes = lb_bytes;
+  off += lb_bytes;
   L.off_red = off;
   off += al(sizeof(float) * kRedBlocks) + al(sizeof(double) * kRedBlocks);
   L.off_u = off;  // warm start: wavefields at the current model, then at the trial model
   if (warm) off += 2 * (size_t)std::max(n_sys, 0) * al(sizeof(float) * 2 * n);
   L.total = off + 256;
   return L;
+}
+
+// The workspace has always held room for a TV pass with three float64 arrays (24 B a
+// cell).  The direction's partials (at most 2.8 B) and, for up to some 200 systems, what
+// the solver's window march needs beyond its slab marches fit in that.
+struct AwriPlan {
+  AwriLayout full, least;   // with the window march, and the former size with the slab marches
+  size_t query() const { return std::max(full.total, least.total); }
+};
+AwriPlan awri_plan(const wri_grid& g, const wri_system* sys, int n_sys, int mode, int flags, int memory, bool warm) {
+  const int64_t n = (int64_t)g.nx * g.ny * g.nz;
+  const int cap = std::max(memory, 1);
+  const size_t with = solver_bytes(&g, 1, sys, n_sys, mode, flags, true);
+  const size_t slab = solver_bytes(&g, 1, sys, n_sys, mode, flags, false);
+  if (with == 0 || slab == 0) return {};
+  const size_t tv = tv_used_bytes(n), lb_least = lb_ws_bytes(cap, kRedBlocks);
+  const int64_t parts = std::max<int64_t>(kRedBlocks, (int64_t)lb_count(std::min(cap, kLbFused)) * lb_blocks(n));
+  return {awri_layout(n, with, tv, lb_ws_bytes(cap, parts), memory, n_sys, warm),
+          awri_layout(n, slab, tv, tv_ws_bytes(n) - tv + lb_least, memory, n_sys, warm)};
 }
 
 int absmax_host(const float* a, int64_t n, float* part, hipStream_t st, double* out) {
@@ -662,7 +689,7 @@ int wri_tv(const wri_grid* grid, const float* m, double eps, double gamma, doubl
 
 size_t wri_lbfgs_workspace_bytes(int32_t capacity) {
   if (capacity < 0) return 0;
-  return lb_ws_bytes(std::max(capacity, 1)) + 256;
+  return lb_ws_bytes(std::max(capacity, 1), kLbParts) + 256;
 }
 
 int wri_lbfgs_direction(int64_t n, const float* g, const float* S, const float* Y, int32_t capacity, int32_t count,
@@ -673,19 +700,19 @@ int wri_lbfgs_direction(int64_t n, const float* g, const float* S, const float* 
     return report_error(WRI_EINVAL, "invalid pair ring (capacity %d, count %d, newest %d)", capacity, count, newest);
   if (count == 0 && !(h0 > 0.0)) return report_error(WRI_EINVAL, "h0 must be > 0 without curvature pairs");
   if (!std::isfinite(h0)) return report_error(WRI_EINVAL, "h0 is not finite");
-  const size_t need = wri_lbfgs_workspace_bytes(capacity);
+  const int cap = std::max(capacity, 1);
+  const size_t need = lb_ws_bytes(cap, kRedBlocks) + 256;   // the recursion's
   if (ws == nullptr || ws_bytes < need) return report_error(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, need);
   char* w = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
-  return lbfgs_run(n, g, S, Y, n, std::max(capacity, 1), count, newest, h0, dir, w, reinterpret_cast<hipStream_t>(stream));
+  return lbfgs_run(n, g, S, Y, n, cap, count, newest, h0, dir, lb_ws(w, ws_bytes - 256, cap),
+                   reinterpret_cast<hipStream_t>(stream));
 }
 
 size_t wri_awri_workspace_bytes(const wri_grid* grid, const wri_system* sys, int32_t n_sys, int32_t mode,
                                 int32_t flags, int32_t memory) {
   if (grid == nullptr || memory < 0) return 0;
-  const size_t sb = wri_workspace_bytes(grid, 1, sys, n_sys, mode, flags);
-  if (sb == 0) return 0;
-  return awri_layout((int64_t)grid->nx * grid->ny * grid->nz, sb, memory, n_sys,
-                     (flags & WRI_FLAG_WARM_START) != 0).total;
+  const AwriPlan P = awri_plan(*grid, sys, n_sys, mode, flags, memory, (flags & WRI_FLAG_WARM_START) != 0);
+  return P.query();
 }
 
 int wri_awri(const wri_grid* grid, float* m, const wri_system* sys, int32_t n_sys, int32_t mode,
@@ -700,13 +727,13 @@ int wri_awri(const wri_grid* grid, float* m, const wri_system* sys, int32_t n_sy
       (o.m_min > 0.0 && o.m_max > 0.0 && o.m_min > o.m_max))
     return report_error(WRI_EINVAL, "invalid options");
   if (history_cap > 0 && history == nullptr) return report_error(WRI_EINVAL, "history is NULL");
-  const size_t sb = wri_workspace_bytes(grid, 1, sys, n_sys, mode, o.flags);
-  if (sb == 0) return report_error(WRI_EINVAL, "invalid grid or systems: %s", wri_last_error());
   const int64_t n = (int64_t)grid->nx * grid->ny * grid->nz;
   const bool warm = o.warm_start != 0;
-  const AwriLayout L = awri_layout(n, sb, o.memory, n_sys, warm);
-  if (ws == nullptr || ws_bytes < L.total)
-    return report_error(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, L.total);
+  const AwriPlan P = awri_plan(*grid, sys, n_sys, mode, o.flags, o.memory, warm);
+  if (P.query() == 0) return report_error(WRI_EINVAL, "invalid grid or systems: %s", wri_last_error());
+  const AwriLayout L = ws_bytes >= P.query() ? P.full : P.least;
+  if (ws == nullptr || ws_bytes < P.least.total)
+    return report_error(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, P.least.total);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
   char* solver_ws = base;
@@ -720,7 +747,7 @@ int wri_awri(const wri_grid* grid, float* m, const wri_system* sys, int32_t n_sy
   const int64_t ring = vb / sizeof(float);   // stride of the pairs
   float* Yring = Sring + o.memory * ring;
   char* tvw = base + L.off_tv;
-  char* lbw = base + L.off_lb;
+  const LbWs lbw = lb_ws(base + L.off_lb, L.lb_bytes, std::max(o.memory, 1));
   float* fpart = reinterpret_cast<float*>(base + L.off_red);
   double* dpart = reinterpret_cast<double*>(base + L.off_red + al(sizeof(float) * kRedBlocks));
   const int nbk = grid_blocks(n);
@@ -763,7 +790,7 @@ int wri_awri(const wri_grid* grid, float* m, const wri_system* sys, int32_t n_sy
     const float* mp[1] = {mm};
     float* gp[1] = {grad};
     int rc = wri_objective_grad(grid, 1, mp, se.data(), n_sys, mode, o.max_iter, fl, J, gp,
-                                warm ? into->data() : nullptr, res.data(), solver_ws, sb, stream);
+                                warm ? into->data() : nullptr, res.data(), solver_ws, L.solver, stream);
     if (rc < 0) return rc;
     if (warm)
       for (int i = 0; i < n_sys; ++i) (*alphas_out)[i] = res[i].alpha;

@@ -1,9 +1,12 @@
 """Solves in workspaces without room for the window passes' sums and tables give the
 general passes' results, before and after calls with room for them."""
+import ctypes
 
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import wri_synth
 from paper_2410_18429_amd import wri
 
@@ -50,3 +53,53 @@ def test_fwi(monkeypatch):
     assert full > 14206976
     fs, gs, _ = wri.fwi_objective_grad(b, max_iter=400)
     assert abs(fs - f) <= 1e-4 * abs(f) and _close(gs[0], g[0], 1e-2)
+
+
+@pytest.mark.parametrize("n,count", [(1000, 5), (6400, 5), (6657, 5), (200000, 3), (200000, 8)])
+def test_direction(n, count):
+    """The former 8704 bytes hold the partials of all inner products on small vectors
+    only (5 pairs: up to 25 workgroups of 256 cells); past that the recursion runs.  Both
+    against the oracle, with the tolerance of the direction's own test."""
+    rng = np.random.default_rng(7)
+    g, S = rng.standard_normal(n).astype(np.float32), rng.standard_normal((count, n)).astype(np.float32)
+    Y = (S * (1.0 + 9.0 * rng.random(n)).astype(np.float32)).astype(np.float32)
+    pairs = [(S[i].astype(np.float64), Y[i].astype(np.float64)) for i in range(count)]
+    s, y = pairs[-1]
+    want = -oracle.lbfgs_two_loop(g.astype(np.float64), pairs, np.dot(s, y) / np.dot(y, y))
+    dev = [torch.as_tensor(a, device="cuda:0") for a in (g, S, Y)]
+    for size in (8704, wri.lib().wri_lbfgs_workspace_bytes(count)):
+        ws = torch.full((size,), 255, dtype=torch.uint8, device="cuda:0")
+        d = torch.empty_like(dev[0])
+        p = [ctypes.c_void_p(t.data_ptr()) for t in dev]
+        code = wri.lib().wri_lbfgs_direction(n, *p, count, count, count - 1, 0.0, ctypes.c_void_p(d.data_ptr()),
+                                             ctypes.c_void_p(ws.data_ptr()), size, None)
+        torch.cuda.synchronize()
+        assert code == wri.OK
+        assert np.linalg.norm(d.cpu().numpy() - want) < 1e-5 * np.linalg.norm(want), size
+
+
+def test_outer_loop_with_many_systems():
+    """600 systems: the window march's sums no longer fit beside the TV pass, and the query
+    grows; the former size runs the slab marches.  One update of each agrees to the
+    difference of the solves."""
+    p = wri_synth.custom_problem((22, 19, 17), nb=2, n_src=12, n_rec=8, seed=3, freqs=tuple(9.0 + 0.1 * i for i in range(50)),
+                                 rtol=1e-3, data="none")
+    rng = np.random.default_rng(2)
+    p = p.with_data([1e-3 * (rng.standard_normal(len(s.rec)) + 1j * rng.standard_normal(len(s.rec))) for s in p.systems])
+    out = []
+    for was in (False, True):
+        b = wri.Batch(p, device="cuda:0")
+        L = wri.lib()
+        query = L.wri_awri_workspace_bytes(b.cgrids, b.csys, b.nsys, b.mode, 0, 2)
+        size = query - 4096 if was else query
+        o = wri.WriAwriOptions(0.0, 1e-9, 1e-3, 1e-6, 0.02, 0.0, 0.0, 0.0, 1, 2, 2000, 0, 1, 0)
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+        rec = ctypes.c_int32(0)
+        hist = (wri.WriAwriRecord * 8)()
+        code = L.wri_awri(b.cgrids, ctypes.c_void_p(b.m[0].data_ptr()), b.csys, b.nsys, b.mode, ctypes.byref(o), hist, 8,
+                          ctypes.byref(rec), ctypes.c_void_p(ws.data_ptr()), size, None)
+        assert code == wri.OK and rec.value == 2
+        out.append((b.m[0].clone(), hist[1].F))
+    assert abs(out[0][1] - out[1][1]) <= 1e-4 * abs(out[0][1])
+    m0 = torch.as_tensor(p.m[0].reshape(-1), dtype=torch.float32, device="cuda:0")
+    assert _close(out[1][0] - m0, out[0][0] - m0, 1e-2)

@@ -65,3 +65,30 @@ def test_solver_fwi_and_model_grid(name):
     _check(lambda b: L.wri_objective_grad_model(ctypes.byref(model), FAKE, g, ng, s, n, wri.ESTIMATE, 10, 0, J, None,
                                                 None, res, FAKE, b, None),
            L.wri_model_workspace_bytes(ctypes.byref(model), g, ng, s, n, wri.ESTIMATE, 0), SOLVER[name][2])
+
+
+AWRI = {"tiny": (138496, 137984), "ragged": (15217920, 17580288), "medium": (139558912, 168919040),
+        "receivers": (139832320, 169192448), "none": (411262720, 444817152)}
+
+
+@no_device
+@pytest.mark.parametrize("name", AWRI)
+def test_outer_loop(name):
+    """Memory 5 cold and memory 3 warm started: no more than before for these."""
+    L = wri.lib()
+    _, g, s, n, keep = _case(name)
+    for (memory, warm), was in zip(((5, 0), (3, 1)), AWRI[name]):
+        o = wri.WriAwriOptions(0.0, 1e-9, 1e-2, 1e-6, 0.01, 0.0, 0.0, 0.0, 3, memory, 100, 0, 1, warm)
+        rec = ctypes.c_int32(0)
+        query = L.wri_awri_workspace_bytes(g, s, n, wri.ESTIMATE, wri.FLAG_WARM_START if warm else 0, memory)
+        assert query == was
+        _check(lambda b: L.wri_awri(g, FAKE, s, n, wri.ESTIMATE, ctypes.byref(o), None, 0, ctypes.byref(rec), FAKE, b, None),
+               query, was)
+
+
+@no_device
+@pytest.mark.parametrize("capacity,was", [(1, 8704), (5, 8704), (8, 8704), (9, 8704), (40, 9216)])
+def test_direction(capacity, was):
+    L = wri.lib()
+    _check(lambda b: L.wri_lbfgs_direction(100000, FAKE, FAKE, FAKE, capacity, capacity, 0, 0.0, FAKE, FAKE, b, None),
+           L.wri_lbfgs_workspace_bytes(capacity), was)
