@@ -442,7 +442,9 @@ typedef struct {
   const double* rec;     /* HOST, 3 * n_rec receiver positions (x, y, z) [m]        */
 } wri_positions;
 
-/* Workspace bytes (host-only; 0 on invalid input).  pos: n_sys entries. */
+/* Workspace bytes (host-only; 0 on invalid input).  pos: n_sys entries.  A workspace
+ * without room for the window passes' partial sums (8 B for each 1024 cells beyond
+ * 131072 of a system) is accepted and solved by the column march. */
 size_t wri_offgrid_workspace_bytes(const wri_grid* grids, int32_t n_grids, const wri_system* sys, int32_t n_sys,
                                    const wri_positions* pos);
 /* As wri_objective_grad, with sys[k].src and sys[k].rec replaced by pos[k]

@@ -819,17 +819,19 @@ struct OgPlan {
   }
 };
 
-OgPlan og_plan(const wri_grid* grids, const wri_system* sys, int n_sys) {
+// window = false: the column march for all, in less memory.
+OgPlan og_plan(const wri_grid* grids, const wri_system* sys, int n_sys, bool window) {
   OgPlan P;
+  auto cells_a_thread = [&](int k) { return window ? ow_cx(grids[sys[k].grid]) : 0; };
   P.order.resize(n_sys);
   for (int k = 0; k < n_sys; ++k) P.order[k] = k;
   std::stable_sort(P.order.begin(), P.order.end(), [&](int a, int b) {
-    const int ga = sys[a].grid, gb = sys[b].grid, ca = ow_cx(grids[ga]), cb = ow_cx(grids[gb]);
+    const int ga = sys[a].grid, gb = sys[b].grid, ca = cells_a_thread(a), cb = cells_a_thread(b);
     return ca != cb ? ca < cb : ga < gb;
   });
   for (int p = 0; p < n_sys; ++p) {
     const wri_grid& g = grids[sys[P.order[p]].grid];
-    const int cx = ow_cx(g);
+    const int cx = cells_a_thread(P.order[p]);
     P.cx.push_back(cx);
     auto& v = P.groups[cx];
     if (v.empty() || sys[P.order[p - 1]].grid != sys[P.order[p]].grid) {
@@ -930,9 +932,13 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     if (m[g] == nullptr || (grad != nullptr && grad[g] == nullptr))
       return report_error(WRI_EINVAL, "m[%d] or grad[%d] is NULL", g, g);
   const SysTables tabs = build_tables(grids, sys, n_sys, pos);
-  const OgPlan P = og_plan(grids, sys, n_sys);
+  OgPlan P = og_plan(grids, sys, n_sys, true);
   OgLayout L;
   og_layout(grids, sys, n_sys, P, tabs, &L);
+  if (ws_bytes < L.total) {   // the march's own size is enough for it
+    P = og_plan(grids, sys, n_sys, false);
+    og_layout(grids, sys, n_sys, P, tabs, &L);
+  }
   if (ws == nullptr || ws_bytes < L.total)
     return report_error(WRI_ENOWS, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, L.total);
   char* base = reinterpret_cast<char*>(al(reinterpret_cast<uintptr_t>(ws)));
@@ -1151,7 +1157,7 @@ size_t wri_offgrid_workspace_bytes(const wri_grid* grids, int32_t n_grids, const
   try {
     if (validate_offgrid(grids, n_grids, sys, n_sys, pos, WRI_ESTIMATE, 0) != WRI_OK) return 0;
     OgLayout L;
-    og_layout(grids, sys, n_sys, og_plan(grids, sys, n_sys), build_tables(grids, sys, n_sys, pos), &L);
+    og_layout(grids, sys, n_sys, og_plan(grids, sys, n_sys, true), build_tables(grids, sys, n_sys, pos), &L);
     return L.total;
   } catch (const std::exception& e) {
     report_error(WRI_EINVAL, "exception: %s", e.what());

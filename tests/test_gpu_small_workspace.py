@@ -1,6 +1,7 @@
 """Solves in workspaces without room for the window passes' sums and tables give the
 general passes' results, before and after calls with room for them."""
 import ctypes
+import dataclasses
 
 import numpy as np
 import pytest
@@ -103,3 +104,26 @@ def test_outer_loop_with_many_systems():
     assert abs(out[0][1] - out[1][1]) <= 1e-4 * abs(out[0][1])
     m0 = torch.as_tensor(p.m[0].reshape(-1), dtype=torch.float32, device="cuda:0")
     assert _close(out[1][0] - m0, out[0][0] - m0, 1e-2)
+
+
+def test_offgrid(monkeypatch):
+    """One system of 64^3, large enough for more sums than the march has, beside a small one."""
+    parts = [wri_synth.custom_problem(s, nb=4, n_src=1, n_rec=9, seed=3, freqs=(9.0,), rtol=0.0)
+             for s in ((64, 64, 64), (22, 19, 17))]
+    systems = [dataclasses.replace(q.systems[0], grid=i) for i, q in enumerate(parts)]
+    p = wri_synth.Problem("two", [q.grids[0] for q in parts], [q.m[0] for q in parts], [q.m[0] for q in parts], systems)
+    b = wri.Batch(p, device="cuda:0")
+    rng = np.random.default_rng(1)
+    src, rec = rng.uniform(40.0, 120.0, (2, 3)), rng.uniform(40.0, 120.0, (2, 9, 3))
+    run = lambda: wri.objective_grad_offgrid(b, list(src), list(rec), max_iter=9)
+    J, g, _ = run()
+    full = b._ws[("offgrid",)].numel()
+    monkeypatch.setattr(wri.lib(), "wri_offgrid_workspace_bytes", lambda *a: full - 512)
+    del b._ws[("offgrid",)]
+    Js, gs, _ = run()
+    assert b._ws[("offgrid",)].numel() == full - 512
+    assert abs(Js - J) <= 1e-6 * abs(J) and _close(gs[0], g[0], 1e-4) and _close(gs[1], g[1], 1e-4)
+    monkeypatch.setattr(wri.lib(), "wri_offgrid_workspace_bytes", lambda *a: full - 2048)
+    del b._ws[("offgrid",)]
+    with pytest.raises(wri.WriError):
+        run()

@@ -92,3 +92,26 @@ def test_direction(capacity, was):
     L = wri.lib()
     _check(lambda b: L.wri_lbfgs_direction(100000, FAKE, FAKE, FAKE, capacity, capacity, 0, 0.0, FAKE, FAKE, b, None),
            L.wri_lbfgs_workspace_bytes(capacity), was)
+
+
+OFFGRID = {"tiny": 46336, "ragged": 11058432, "medium": 117591808, "receivers": 120901376, "three": 563667200,
+           "none": 234887168, "wide": 34871296}
+
+
+@no_device
+@pytest.mark.parametrize("name", OFFGRID)
+def test_offgrid(name):
+    L = wri.lib()
+    shapes, g, s, n, keep = _case(name)
+    n_rec = CASES[name][2]
+    rng = np.random.default_rng(0)
+    xyz = [rng.uniform(0, 80, (n_rec, 3)) for _ in shapes]
+    pos = (wri.WriPositions * n)(*[wri.WriPositions(
+        (ctypes.c_double * 3)(41.0, 33.0, 21.0),
+        xyz[s[i].grid].ctypes.data_as(ctypes.POINTER(ctypes.c_double)) if n_rec else None) for i in range(n)])
+    ptr = (ctypes.c_void_p * len(shapes))(*[0x2000] * len(shapes))
+    res = (wri.WriResult * n)()
+    J = ctypes.c_double(0.0)
+    _check(lambda b: L.wri_objective_grad_offgrid(g, len(shapes), ptr, s, n, pos, wri.ESTIMATE, 10, 0, J, None, None, res,
+                                                  FAKE, b, None),
+           L.wri_offgrid_workspace_bytes(g, len(shapes), s, n, pos), OFFGRID[name])
