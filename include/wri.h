@@ -505,7 +505,7 @@ int wri_kernel_times(wri_timing* out);
  *   flags        0 or WRI_FLAG_NO_GRAPH (no effect: launches are eager; anything
  *                else: WRI_EINVAL)
  *   ws           DEVICE workspace of ws_bytes >= wri_precond_workspace_bytes()
- *                (9 or 10 complex vectors per system plus 4/7 of one for the
+ *                (about 9 complex vectors per system plus 4/7 of one for the
  *                coarse levels)
  *   res[k].relres is sqrt(||S^H r||^2 / ||S^H b||^2), res[k].alpha the CGLS
  *   unknown and res[k].alpha_ls = (A u)[src] in float64 (ESTIMATE).

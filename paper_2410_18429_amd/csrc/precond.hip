@@ -64,12 +64,17 @@ struct PcLevel {
 };
 
 struct PcSys {
-  float2 *x, *r[2], *p[2], *q, *t, *s, *z, *r2, *t2;   // r, p: current vector by iteration parity (tiled passes)
+  float2 *x, *r, *p, *q, *t, *s, *z, *r2, *t2;
   const float2* d;
   const int* rec;
   const float* m;
   int n, nx, ny, nz, nb, nr, est, max_iter, nlev, src;
-  int tiled;    // 1: the passes by window tiles; 0: one thread per cell, r and p updated in place
+  // The passes by window tiles (bit 0), or one thread per cell with r and p updated in place.
+  // Tiled passes write r and p to another buffer: that of odd residuals is lev[0].o, that
+  // of even directions lev[0].y, which they use for nothing else; their level-0 residual
+  // lev[0].res shares t, as t is dead during a cycle.  So nine vectors are enough.
+  // Bit 1: their partial sums lie in lev[1].y, else in lev[1].res (see pc_part).
+  int tiled;
   int nparts;   // partial sums of a level-0 pass
   double lam, rtol2, omega, omega2, h2inv, sp_scale, inv_nb;
   double2 alpha;  // KNOWN-mode weight
@@ -96,8 +101,15 @@ __device__ __forceinline__ double bsum(double v, double* red) {  // block total,
 }
 
 // residual after `iters` iterations, and the direction p that iteration's forward cycle reads
-__device__ __forceinline__ float2* pc_r(const PcSys& S, int iters) { return S.r[S.tiled & iters & 1]; }
-__device__ __forceinline__ float2* pc_p(const PcSys& S, int iters) { return S.p[S.tiled & (iters + 1) & 1]; }
+__device__ __forceinline__ float2* pc_r(const PcSys& S, int iters) { return (S.tiled & iters & 1) ? S.lev[0].o : S.r; }
+__device__ __forceinline__ float2* pc_p(const PcSys& S, int iters) { return (S.tiled & (iters + 1) & 1) ? S.lev[0].y : S.p; }
+// Partial sums of system k's level-0 passes.  The tiles' are more than kParts on large
+// grids: they lie in an array of level 1 that no tiled pass touches, the iterate of a level
+// that goes through the residual and prolongation passes in memory, else the residual.
+__device__ __forceinline__ double* pc_part(const PcSys& S, double* part, int k) {
+  if (S.tiled) return reinterpret_cast<double*>((S.tiled & 2) ? S.lev[1].y : S.lev[1].res);
+  return part + (size_t)k * kParts;
+}
 
 __device__ __forceinline__ double nrm(float2 v) { return (double)v.x * v.x + (double)v.y * v.y; }
 __device__ __forceinline__ float2 fd(double a, double b) { return make_float2((float)a, (float)b); }
@@ -121,8 +133,8 @@ __global__ void __launch_bounds__(kThr) k_pc_zero(const PcSys* __restrict__ sy, 
   const float2 z = make_float2(0.f, 0.f);
   for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
     S.x[c] = z;
-    S.r[0][c] = z;
-    S.p[0][c] = z;
+    S.r[c] = z;
+    S.p[c] = z;
   }
 }
 
@@ -135,7 +147,7 @@ __global__ void __launch_bounds__(kThr) k_pc_init(const PcSys* __restrict__ sy, 
     S.r2[q] = fd(S.lam * dv.x, S.lam * dv.y);
   }
   if (threadIdx.x == 0) {
-    if (!S.est) S.r[0][S.src] = fd(S.alpha.x, S.alpha.y);
+    if (!S.est) S.r[S.src] = fd(S.alpha.x, S.alpha.y);
     PcState& T = stv[k];
     T = PcState{};
     T.status = kActive;
@@ -150,8 +162,8 @@ __global__ void __launch_bounds__(kThr) k_pc_pupd(const PcSys* __restrict__ sy, 
   const PcSys& S = sy[k];
   const double be = stv[k].beta;
   for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
-    const float2 zv = S.z[c], pv = S.p[0][c];
-    S.p[0][c] = fd((double)zv.x + be * pv.x, (double)zv.y + be * pv.y);
+    const float2 zv = S.z[c], pv = S.p[c];
+    S.p[c] = fd((double)zv.x + be * pv.x, (double)zv.y + be * pv.y);
   }
 }
 
@@ -174,7 +186,7 @@ __device__ __forceinline__ double2 apply_cell(const PcSys& S, const float2* __re
 
 // t = A q - p_alpha e_src (ESTIMATE; q_alpha = p_alpha); partials of ||t||^2
 __global__ void __launch_bounds__(kThr) k_pc_fwd(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                 double* __restrict__ part, int stride, int g0) {
+                                                 double* __restrict__ part, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
@@ -189,13 +201,13 @@ __global__ void __launch_bounds__(kThr) k_pc_fwd(const PcSys* __restrict__ sy, c
     acc += nrm(t);
   }
   const double tot = bsum(acc, red);
-  if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
+  if (threadIdx.x == 0) pc_part(S, part, k)[blockIdx.x] = tot;
 }
 
 // receiver rows t2 = lam q[rec]; delta, a; x_alpha += a p_alpha; r2 -= a t2
 // (one block per system)
 __global__ void __launch_bounds__(kThr) k_pc_step(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                  const double* __restrict__ part, int stride, int g0) {
+                                                  double* __restrict__ part, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   if (!active(stv, k)) return;
@@ -208,7 +220,7 @@ __global__ void __launch_bounds__(kThr) k_pc_step(const PcSys* __restrict__ sy, 
     S.t2[q] = t2;
     acc += nrm(t2);
   }
-  const double delta = sum_parts(part + (size_t)k * stride, S.nparts, red) + bsum(acc, red);
+  const double delta = sum_parts(pc_part(S, part, k), S.nparts, red) + bsum(acc, red);
   const bool bad = !(delta > 0.0) || !(delta <= DBL_MAX) || !(T.gamma <= DBL_MAX);
   const double a = bad ? 0.0 : T.gamma / delta;
   for (int q = threadIdx.x; q < S.nr; q += kThr) {
@@ -234,33 +246,33 @@ __global__ void __launch_bounds__(kThr) k_pc_rupd(const PcSys* __restrict__ sy, 
   const PcSys& S = sy[k];
   const double a = stv[k].a;
   for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
-    const float2 r = S.r[0][c], t = S.t[c], x = S.x[c], q = S.q[c];
-    S.r[0][c] = fd((double)r.x - a * t.x, (double)r.y - a * t.y);
+    const float2 r = S.r[c], t = S.t[c], x = S.x[c], q = S.q[c];
+    S.r[c] = fd((double)r.x - a * t.x, (double)r.y - a * t.y);
     S.x[c] = fd((double)x.x + a * q.x, (double)x.y + a * q.y);
   }
 }
 
 // s = A^H r (the receiver and source-row terms are added per system); partials of ||s||^2
 __global__ void __launch_bounds__(kThr) k_pc_adj(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                 double* __restrict__ part, int stride, int g0) {
+                                                 double* __restrict__ part, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   double acc = 0.0;
   for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
-    const float2 s = round2(apply_cell(S, S.r[0], c, true));
+    const float2 s = round2(apply_cell(S, S.r, c, true));
     S.s[c] = s;
     acc += nrm(s);
   }
   const double tot = bsum(acc, red);
-  if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
+  if (threadIdx.x == 0) pc_part(S, part, k)[blockIdx.x] = tot;
 }
 
 // s += lam P^H r2 (distinct receiver cells), s_alpha = -r1[src] (ESTIMATE);
 // ||s||^2, the stopping test (one block per system).  setup = 1: ||s_0||^2.
 __global__ void __launch_bounds__(kThr) k_pc_check(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                   const double* __restrict__ part, int stride, int g0, int setup) {
+                                                   double* __restrict__ part, int g0, int setup) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   if (!active(stv, k)) return;
@@ -274,7 +286,7 @@ __global__ void __launch_bounds__(kThr) k_pc_check(const PcSys* __restrict__ sy,
     S.s[c] = s1;
     corr += nrm(s1) - nrm(s0);
   }
-  const double ss_u = sum_parts(part + (size_t)k * stride, S.nparts, red) + bsum(corr, red);
+  const double ss_u = sum_parts(pc_part(S, part, k), S.nparts, red) + bsum(corr, red);
   if (threadIdx.x == 0) {
     double2 sa = make_double2(0.0, 0.0);
     if (S.est) {
@@ -308,13 +320,13 @@ __global__ void __launch_bounds__(kThr) k_pc_check(const PcSys* __restrict__ sy,
 // gamma' = ||z||^2, beta = gamma'/gamma, p_alpha = z_alpha + beta p_alpha
 // (one block per system).  setup = 1: gamma = ||z_0||^2, beta = 0.
 __global__ void __launch_bounds__(kThr) k_pc_beta(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                  const double* __restrict__ part, int stride, int g0, int setup) {
+                                                  double* __restrict__ part, int g0, int setup) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   PcState& T = stv[k];
-  const double zz = sum_parts(part + (size_t)k * stride, S.nparts, red) + (T.za.x * T.za.x + T.za.y * T.za.y);
+  const double zz = sum_parts(pc_part(S, part, k), S.nparts, red) + (T.za.x * T.za.x + T.za.y * T.za.y);
   if (threadIdx.x == 0) {
     const double be = setup ? 0.0 : zz / T.gamma;
     T.beta = be;
@@ -513,7 +525,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vprolong(const PcSys* __restrict__ 
 // o_l = y + w D^-1 (f - A_beta y); level 0 writes `out0` (q: which = 0, z:
 // which = 1) and, for z, the partials of ||z||^2
 __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                     double* __restrict__ part, int stride, int g0, int l, int which, int conj) {
+                                                     double* __restrict__ part, int g0, int l, int which, int conj) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
@@ -546,7 +558,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ s
   }
   if (l == 0 && which && part != nullptr) {
     const double tot = bsum(acc, red);
-    if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
+    if (threadIdx.x == 0) pc_part(S, part, k)[blockIdx.x] = tot;
   }
 }
 
@@ -554,7 +566,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ s
 // coarsen): kCoarseSweeps Jacobi steps on level 0 itself; the last result is
 // copied to out0 with the partials of ||out0||^2 when which = 1.
 __global__ void __launch_bounds__(kThr) k_pc_vsingle_out(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                         double* __restrict__ part, int stride, int g0, int which) {
+                                                         double* __restrict__ part, int g0, int which) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
@@ -570,7 +582,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vsingle_out(const PcSys* __restrict
   }
   if (which && part != nullptr) {
     const double tot = bsum(acc, red);
-    if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
+    if (threadIdx.x == 0) pc_part(S, part, k)[blockIdx.x] = tot;
   }
 }
 
@@ -639,8 +651,8 @@ k_pw_down(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0,
   Q.setup(L.nx, L.ny, L.nz, tile, tiles_x);
   const int nx = Q.nx, wl = Q.wl;
   const float2* f = PUPD ? S.z : level_in(S, T.iters, l, which);
-  const float2* po = S.p[T.iters & 1];
-  float2* pn = S.p[(T.iters + 1) & 1];
+  const float2* po = pc_p(S, T.iters + 1);
+  float2* pn = pc_p(S, T.iters);
   float2 fv[CX][kPcZ + 2], wv[CX][kPcZ + 2], pv[CX][kPcZ + 2];
   float mm[CX][kPcZ], bb[CX][kPcZ];
 #pragma unroll
@@ -798,7 +810,7 @@ __device__ __forceinline__ double2 prolong_z(const double2 (&e)[NP], int i) {
 // (which = 0) or z (which = 1, with the partials of ||z||^2)
 template <int CX>
 __global__ void __launch_bounds__(64 * kPcW)
-k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* __restrict__ part, int stride, int g0,
+k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* __restrict__ part, int g0,
         int l, int which, int conj, int tiles_x, int tiles) {
   using Tile = Win<kPcW, CX, kPcZ>;
   constexpr int NT = Tile::NT, NP = kPcZ / 2 + 2;
@@ -894,7 +906,7 @@ k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* _
   }
   if (l == 0 && which) {
     const double tot = bsum(acc, red);
-    if (tid == 0) part[(size_t)k * stride + tile] = tot;
+    if (tid == 0) pc_part(S, part, k)[tile] = tot;
   }
 }
 
@@ -902,7 +914,7 @@ k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* _
 // and s = A^H r with the partials of ||s||^2 (ADJ = true; setup = 1: s = A^H r_0)
 template <int CX, bool ADJ>
 __global__ void __launch_bounds__(64 * kPcW)
-k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* __restrict__ part, int stride,
+k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* __restrict__ part,
            int g0, int setup, int tiles_x, int tiles) {
   using Tile = Win<kPcW, CX, kPcZ>;
   constexpr int NT = Tile::NT;
@@ -995,7 +1007,7 @@ k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double
     }
   }
   const double tot = bsum(acc, red);
-  if (tid == 0) part[(size_t)k * stride + tile] = tot;
+  if (tid == 0) pc_part(S, part, k)[tile] = tot;
 }
 
 // The levels from lc on (at most kPcLdsCells cells each, lc >= 1): down, the Jacobi
@@ -1258,7 +1270,7 @@ __global__ void __launch_bounds__(kThr) k_pc_restrict_mean(const float* __restri
 
 // partials of ||r1||^2 of the final residual (grid (kParts, systems of the group))
 __global__ void __launch_bounds__(kThr) k_pc_rnorm(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                   double* __restrict__ part, int stride, int g0) {
+                                                   double* __restrict__ part, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   const PcSys& S = sy[k];
@@ -1266,21 +1278,21 @@ __global__ void __launch_bounds__(kThr) k_pc_rnorm(const PcSys* __restrict__ sy,
   double acc = 0.0;
   for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += kParts * kThr) acc += nrm(r[c]);
   const double tot = bsum(acc, red);
-  if (threadIdx.x == 0) part[(size_t)k * stride + blockIdx.x] = tot;
+  if (threadIdx.x == 0) part[(size_t)k * kParts + blockIdx.x] = tot;
 }
 
 // J = ||r1||^2 + ||r2||^2 (recurred), alpha_ls = (A u)[src] in float64
 // (one block per system; the sum over a whole residual in one block took 287 us
 // on 64^3)
 __global__ void __launch_bounds__(kThr) k_pc_final(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                   const double* __restrict__ part, int stride, int g0) {
+                                                   double* __restrict__ part, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   const PcSys& S = sy[k];
   PcState& T = stv[k];
   double acc = 0.0;
   for (int q = threadIdx.x; q < S.nr; q += kThr) acc += nrm(S.r2[q]);
-  const double J = sum_parts(part + (size_t)k * stride, kParts, red) + bsum(acc, red);
+  const double J = sum_parts(part + (size_t)k * kParts, kParts, red) + bsum(acc, red);
   if (threadIdx.x == 0) {
     T.J = J;
     if (S.est) {
@@ -1333,7 +1345,6 @@ int64_t cells_of(const LevelDims& d) { return (int64_t)d.nx * d.ny * d.nz; }
 
 struct PcLayout {
   size_t sys = 0, state = 0, parts = 0, idx = 0, head_bytes = 0, total = 0;
-  int stride = kParts;               // partial sums per system
   std::vector<size_t> grid_arrays;   // per grid: m_l (l >= 1) and b_l (l >= 0)
   std::vector<std::pair<int, double>> pairs;   // distinct (grid, omega) of the systems
   std::vector<int> pair_of;                    // per system
@@ -1356,6 +1367,15 @@ bool pc_tiled(const std::vector<LevelDims>& lv) {
   return lv.size() > 1 && lv[0].nx <= kPcMaxRow && cells_of(lv[0]) < (int64_t(1) << 28);
 }
 
+// first level of the one-workgroup cycle (the number of levels: none fits)
+int pc_lds_level(const std::vector<LevelDims>& lv) {
+  int lc = 1;
+  while (lc < (int)lv.size() && cells_of(lv[lc]) > kPcLdsCells) ++lc;
+  return lc;
+}
+// levels with a residual and a prolongation pass in memory
+int pc_memory_levels(const std::vector<LevelDims>& lv) { return std::min(pc_lds_level(lv), (int)lv.size() - 1); }
+
 PcLayout pc_layout(const wri_grid* grids, int n_grids, const wri_system* sys, int n_sys) {
   PcLayout L;
   size_t o = 0;
@@ -1367,11 +1387,7 @@ PcLayout pc_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   for (int k = 0; k < n_sys; ++k) L.rec[k] = take(sizeof(int) * (size_t)sys[k].n_rec);
   L.head_bytes = o;
   L.state = take(sizeof(PcState) * std::max(n_sys, 1));
-  for (int k = 0; k < n_sys; ++k) {
-    const auto lv = levels_of(grids[sys[k].grid]);
-    if (pc_tiled(lv)) L.stride = std::max(L.stride, pc_tiles(lv[0]).n);
-  }
-  L.parts = take(sizeof(double) * (size_t)L.stride * std::max(n_sys, 1));
+  L.parts = take(sizeof(double) * (size_t)kParts * std::max(n_sys, 1));
   L.grid_arrays.resize(n_grids);
   for (int g = 0; g < n_grids; ++g) {
     size_t b = 0;
@@ -1395,8 +1411,7 @@ PcLayout pc_layout(const wri_grid* grids, int n_grids, const wri_system* sys, in
   for (int k = 0; k < n_sys; ++k) {
     const wri_grid& g = grids[sys[k].grid];
     const auto lv = levels_of(g);
-    // x r p q t s z res0, y0 (or the other p) and the other r
-    size_t b = (pc_tiled(lv) ? 10 : 9) * al(sizeof(float2) * (size_t)cells_of(lv[0]));
+    size_t b = 9 * al(sizeof(float2) * (size_t)cells_of(lv[0]));   // x r p q t s z, res0 and y0 or the other r and p
     for (size_t l = 1; l < lv.size(); ++l) b += 4 * al(sizeof(float2) * (size_t)cells_of(lv[l]));
     L.vec[k] = take(b);
     L.rvec[k] = take(2 * al(sizeof(float2) * (size_t)sys[k].n_rec));
@@ -1508,12 +1523,10 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     auto vec = [&](int i) { return reinterpret_cast<float2*>(v + i * vb); };
     S.x = (u_out != nullptr && u_out[k] != nullptr) ? reinterpret_cast<float2*>(u_out[k]) : vec(0);
     const bool tiled = pc_tiled(lv);
-    S.tiled = tiled ? 1 : 0;
+    S.tiled = tiled ? (pc_memory_levels(lv) > 1 ? 3 : 1) : 0;
     S.nparts = tiled ? pc_tiles(lv[0]).n : kParts;
-    S.r[0] = vec(1); S.r[1] = tiled ? vec(9) : vec(1);
-    S.p[0] = vec(2); S.p[1] = tiled ? vec(8) : vec(2);
-    S.q = vec(3); S.t = vec(4); S.s = vec(5); S.z = vec(6);
-    char* cv = v + (tiled ? 10 : 9) * vb;
+    S.r = vec(1); S.p = vec(2); S.q = vec(3); S.t = vec(4); S.s = vec(5); S.z = vec(6);
+    char* cv = v + 9 * vb;
     for (size_t l = 0; l < lv.size(); ++l) {
       PcLevel& Lv = S.lev[l];
       Lv.nx = lv[l].nx; Lv.ny = lv[l].ny; Lv.nz = lv[l].nz; Lv.n = (int)cells_of(lv[l]);
@@ -1522,8 +1535,8 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       Lv.b = gb[s.grid][l];
       Lv.wdinv = pw[L.pair_of[k]][l];
       if (l == 0) {
-        Lv.f = nullptr; Lv.o = nullptr;
-        Lv.res = vec(7); Lv.y = vec(8);
+        Lv.f = nullptr; Lv.o = tiled ? vec(7) : nullptr;
+        Lv.res = tiled ? vec(4) : vec(7); Lv.y = vec(8);
       } else {
         const size_t cb = al(sizeof(float2) * (size_t)Lv.n);
         Lv.f = reinterpret_cast<float2*>(cv);
@@ -1567,7 +1580,6 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   for (int p = 0; p < n_sys; ++p) std::memcpy(head.data() + L.idx + sizeof(int) * p, &p, sizeof(int));
   PC_HIP(hipMemcpyAsync(base, head.data(), L.head_bytes, hipMemcpyHostToDevice, st));
 
-  const int stride = L.stride;
   // tiled pass on level d: launch LAUNCH(template cx, grid, dynamic LDS of one element of `elem` bytes per cell)
   auto lds_of = [](const PcTiles& t, const LevelDims& d, size_t elem) {
     return (unsigned)(elem * kPcZ * (size_t)(64 * kPcW * t.cx + 2 * d.nx));
@@ -1591,9 +1603,8 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     };
     if (pc_tiled(lv)) {
       // levels of one workgroup: from lc on (nl: none fits, the coarsest by separate sweeps)
-      int lc = 1;
-      while (lc < nl && cells_of(lv[lc]) > kPcLdsCells) ++lc;
-      for (int l = 0; l < std::min(lc, nl - 1); ++l) {
+      const int lc = pc_lds_level(lv), lm = pc_memory_levels(lv);
+      for (int l = 0; l < lm; ++l) {
         if (l == 0 && which == 0)
           PW_LAUNCH((k_pw_down<1, true>), (k_pw_down<2, true>), lv[l], sizeof(double2), G.p0, l, which, conj);
         else
@@ -1608,8 +1619,8 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       } else {
         sweeps();
       }
-      for (int l = std::min(lc, nl - 1) - 1; l >= 0; --l)
-        PW_LAUNCH((k_pw_up<1>), (k_pw_up<2>), lv[l], sizeof(float2), parts, stride, G.p0, l, which, conj);
+      for (int l = lm - 1; l >= 0; --l)
+        PW_LAUNCH((k_pw_up<1>), (k_pw_up<2>), lv[l], sizeof(float2), parts, G.p0, l, which, conj);
       PC_HIP(hipGetLastError());
       return WRI_OK;
     }
@@ -1622,13 +1633,13 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     }
     sweeps();
     if (nl == 1) {
-      hipLaunchKernelGGL(k_pc_vsingle_out, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, which);
+      hipLaunchKernelGGL(k_pc_vsingle_out, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, which);
     } else {
       for (int l = nl - 2; l >= 0; --l) {
         const int nbk = (l == 0) ? kParts : blocks_for(cells_of(lv[l]));
         hipLaunchKernelGGL(k_pc_vprolong, dim3(blocks_for(cells_of(lv[l])), G.cnt), dim3(kThr), 0, st, dsys, dst,
                            G.p0, l, which, conj);
-        hipLaunchKernelGGL(k_pc_vsmooth, dim3(nbk, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, l, which, conj);
+        hipLaunchKernelGGL(k_pc_vsmooth, dim3(nbk, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, l, which, conj);
       }
     }
     PC_HIP(hipGetLastError());
@@ -1641,19 +1652,19 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       const bool tiled = pc_tiled(lv);
       int e = vcycle(G, 0);
       if (e != WRI_OK) return e;
-      if (tiled) PW_LAUNCH((k_pw_apply<1, false>), (k_pw_apply<2, false>), lv[0], sizeof(float2), parts, stride, G.p0, 0);
-      else hipLaunchKernelGGL(k_pc_fwd, pg, dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
-      hipLaunchKernelGGL(k_pc_step, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
+      if (tiled) PW_LAUNCH((k_pw_apply<1, false>), (k_pw_apply<2, false>), lv[0], sizeof(float2), parts, G.p0, 0);
+      else hipLaunchKernelGGL(k_pc_fwd, pg, dim3(kThr), 0, st, dsys, dst, parts, G.p0);
+      hipLaunchKernelGGL(k_pc_step, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0);
       if (tiled) {
-        PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), parts, stride, G.p0, 0);
+        PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), parts, G.p0, 0);
       } else {
         hipLaunchKernelGGL(k_pc_rupd, pg, dim3(kThr), 0, st, dsys, dst, G.p0);
-        hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
+        hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, parts, G.p0);
       }
-      hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, 0);
+      hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 0);
       e = vcycle(G, 1);
       if (e != WRI_OK) return e;
-      hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, 0);
+      hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 0);
       PC_HIP(hipGetLastError());
     }
     return WRI_OK;
@@ -1664,12 +1675,12 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     const std::vector<LevelDims> lv = levels_of(grids[G.grid]);
     hipLaunchKernelGGL(k_pc_zero, pg, dim3(kThr), 0, st, dsys, G.p0);
     hipLaunchKernelGGL(k_pc_init, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0);
-    if (pc_tiled(lv)) PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), parts, stride, G.p0, 1);
-    else hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
-    hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, 1);
+    if (pc_tiled(lv)) PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), parts, G.p0, 1);
+    else hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, parts, G.p0);
+    hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 1);
     rc = vcycle(G, 1);
     if (rc != WRI_OK) return rc;
-    hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0, 1);
+    hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 1);
     PC_HIP(hipGetLastError());
   }
 #undef PW_LAUNCH
@@ -1696,8 +1707,8 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   }
   // results: J, alpha_ls, gradient per grid
   for (const Group& G : groups) {
-    hipLaunchKernelGGL(k_pc_rnorm, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
-    hipLaunchKernelGGL(k_pc_final, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, stride, G.p0);
+    hipLaunchKernelGGL(k_pc_rnorm, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0);
+    hipLaunchKernelGGL(k_pc_final, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0);
   }
   PC_HIP(hipGetLastError());
   if (grad != nullptr) {

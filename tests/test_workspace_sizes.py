@@ -115,3 +115,22 @@ def test_offgrid(name):
     _check(lambda b: L.wri_objective_grad_offgrid(g, len(shapes), ptr, s, n, pos, wri.ESTIMATE, 10, 0, J, None, None, res,
                                                   FAKE, b, None),
            L.wri_offgrid_workspace_bytes(g, len(shapes), s, n, pos), OFFGRID[name])
+
+
+PRECOND = {"tiny": 74752, "ragged": 15900416, "medium": 165393152, "receivers": 165706496, "three": 793365248,
+           "none": 359514368, "wide": 54234624}
+
+
+@no_device
+@pytest.mark.parametrize("name", PRECOND)
+def test_precond(name):
+    """The query is the former size: the tiled passes share what they need more."""
+    L = wri.lib()
+    shapes, g, s, n, keep = _case(name)
+    ptr = (ctypes.c_void_p * len(shapes))(*[0x2000] * len(shapes))
+    res = (wri.WriResult * n)()
+    J = ctypes.c_double(0.0)
+    query = L.wri_precond_workspace_bytes(g, len(shapes), s, n, wri.ESTIMATE)
+    assert query == PRECOND[name]
+    _check(lambda b: L.wri_objective_grad_precond(g, len(shapes), ptr, s, n, wri.ESTIMATE, 10, 0, J, None, None, res, FAKE,
+                                                  b, None), query, query)
