@@ -64,19 +64,15 @@ struct PcLevel {
 };
 
 struct PcSys {
-  float2 *x, *r, *p, *q, *t, *s, *z, *r2, *t2;
+  float2 *x, *r[2], *p[2], *q, *t, *s, *z, *r2, *t2;   // r, p: current vector by iteration parity (tiled passes)
+  double* part;   // partial sums of a level-0 pass
   const float2* d;
   const int* rec;
   const float* m;
-  int n, nx, ny, nz, nb, nr, est, max_iter, nlev, src;
-  // The passes by window tiles (bit 0), or one thread per cell with r and p updated in place.
-  // Tiled passes write r and p to another buffer: that of odd residuals is lev[0].o, that
-  // of even directions lev[0].y, which they use for nothing else; their level-0 residual
-  // lev[0].res shares t, as t is dead during a cycle.  So nine vectors are enough.
-  // Bit 1: their partial sums lie in lev[1].y, else in lev[1].res (see pc_part).
-  int tiled;
-  int nparts;   // partial sums of a level-0 pass
-  double lam, rtol2, omega, omega2, h2inv, sp_scale, inv_nb;
+  int nb, nr, est, max_iter, nlev, src;
+  int tiled;    // 1: the passes by window tiles; 0: one thread per cell, r and p updated in place
+  int nparts;   // partial sums in part
+  double lam, rtol2, omega, omega2, sp_scale, inv_nb;
   double2 alpha;  // KNOWN-mode weight
   PcLevel lev[kMaxLev];
 };
@@ -101,15 +97,8 @@ __device__ __forceinline__ double bsum(double v, double* red) {  // block total,
 }
 
 // residual after `iters` iterations, and the direction p that iteration's forward cycle reads
-__device__ __forceinline__ float2* pc_r(const PcSys& S, int iters) { return (S.tiled & iters & 1) ? S.lev[0].o : S.r; }
-__device__ __forceinline__ float2* pc_p(const PcSys& S, int iters) { return (S.tiled & (iters + 1) & 1) ? S.lev[0].y : S.p; }
-// Partial sums of system k's level-0 passes.  The tiles' are more than kParts on large
-// grids: they lie in an array of level 1 that no tiled pass touches, the iterate of a level
-// that goes through the residual and prolongation passes in memory, else the residual.
-__device__ __forceinline__ double* pc_part(const PcSys& S, double* part, int k) {
-  if (S.tiled) return reinterpret_cast<double*>((S.tiled & 2) ? S.lev[1].y : S.lev[1].res);
-  return part + (size_t)k * kParts;
-}
+__device__ __forceinline__ float2* pc_r(const PcSys& S, int iters) { return S.r[S.tiled & iters & 1]; }
+__device__ __forceinline__ float2* pc_p(const PcSys& S, int iters) { return S.p[S.tiled & (iters + 1) & 1]; }
 
 __device__ __forceinline__ double nrm(float2 v) { return (double)v.x * v.x + (double)v.y * v.y; }
 __device__ __forceinline__ float2 fd(double a, double b) { return make_float2((float)a, (float)b); }
@@ -131,10 +120,10 @@ __device__ __forceinline__ bool active(const PcState* stv, int k) { return stv[k
 __global__ void __launch_bounds__(kThr) k_pc_zero(const PcSys* __restrict__ sy, int g0) {
   const PcSys& S = sy[g0 + blockIdx.y];
   const float2 z = make_float2(0.f, 0.f);
-  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
+  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += gridDim.x * kThr) {
     S.x[c] = z;
-    S.r[c] = z;
-    S.p[c] = z;
+    S.r[0][c] = z;
+    S.p[0][c] = z;
   }
 }
 
@@ -147,7 +136,7 @@ __global__ void __launch_bounds__(kThr) k_pc_init(const PcSys* __restrict__ sy, 
     S.r2[q] = fd(S.lam * dv.x, S.lam * dv.y);
   }
   if (threadIdx.x == 0) {
-    if (!S.est) S.r[S.src] = fd(S.alpha.x, S.alpha.y);
+    if (!S.est) S.r[0][S.src] = fd(S.alpha.x, S.alpha.y);
     PcState& T = stv[k];
     T = PcState{};
     T.status = kActive;
@@ -161,39 +150,39 @@ __global__ void __launch_bounds__(kThr) k_pc_pupd(const PcSys* __restrict__ sy, 
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   const double be = stv[k].beta;
-  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
-    const float2 zv = S.z[c], pv = S.p[c];
-    S.p[c] = fd((double)zv.x + be * pv.x, (double)zv.y + be * pv.y);
+  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += gridDim.x * kThr) {
+    const float2 zv = S.z[c], pv = S.p[0][c];
+    S.p[0][c] = fd((double)zv.x + be * pv.x, (double)zv.y + be * pv.y);
   }
 }
 
 __device__ __forceinline__ double sponge_at(const PcSys& S, int x, int y, int z) {
-  return S.sp_scale * ((sponge_axis_d(x, S.nx, S.nb, S.inv_nb) + sponge_axis_d(y, S.ny, S.nb, S.inv_nb)) +
-                       sponge_axis_d(z, S.nz, S.nb, S.inv_nb));
+  return S.sp_scale * ((sponge_axis_d(x, S.lev[0].nx, S.nb, S.inv_nb) + sponge_axis_d(y, S.lev[0].ny, S.nb, S.inv_nb)) +
+                       sponge_axis_d(z, S.lev[0].nz, S.nb, S.inv_nb));
 }
 
 // one cell of A v (adj = 0) or A^H v (adj = 1) in float64 from float32 storage
 __device__ __forceinline__ double2 apply_cell(const PcSys& S, const float2* __restrict__ v, int c, bool adj) {
-  const int plane = S.nx * S.ny;
-  const int z = c / plane, rem = c - z * plane, y = rem / S.nx, x = rem - y * S.nx;
+  const int plane = S.lev[0].nx * S.lev[0].ny;
+  const int z = c / plane, rem = c - z * plane, y = rem / S.lev[0].nx, x = rem - y * S.lev[0].nx;
   const float2 zero = make_float2(0.f, 0.f);
-  const float2 xm = x > 0 ? v[c - 1] : zero, xp = x < S.nx - 1 ? v[c + 1] : zero;
-  const float2 ym = y > 0 ? v[c - S.nx] : zero, yp = y < S.ny - 1 ? v[c + S.nx] : zero;
-  const float2 zm = z > 0 ? v[c - plane] : zero, zp = z < S.nz - 1 ? v[c + plane] : zero;
+  const float2 xm = x > 0 ? v[c - 1] : zero, xp = x < S.lev[0].nx - 1 ? v[c + 1] : zero;
+  const float2 ym = y > 0 ? v[c - S.lev[0].nx] : zero, yp = y < S.lev[0].ny - 1 ? v[c + S.lev[0].nx] : zero;
+  const float2 zm = z > 0 ? v[c - plane] : zero, zp = z < S.lev[0].nz - 1 ? v[c + plane] : zero;
   const double kim = S.omega * sponge_at(S, x, y, z);
-  return helm(v[c], xm, xp, ym, yp, zm, zp, S.h2inv, S.omega2 * (double)S.m[c], adj ? kim : -kim);
+  return helm(v[c], xm, xp, ym, yp, zm, zp, S.lev[0].h2inv, S.omega2 * (double)S.m[c], adj ? kim : -kim);
 }
 
 // t = A q - p_alpha e_src (ESTIMATE; q_alpha = p_alpha); partials of ||t||^2
 __global__ void __launch_bounds__(kThr) k_pc_fwd(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                 double* __restrict__ part, int g0) {
+                                                 int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   const double2 pa = stv[k].pa;
   double acc = 0.0;
-  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
+  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += gridDim.x * kThr) {
     double2 tv = apply_cell(S, S.q, c, false);
     if (S.est && c == S.src) { tv.x -= pa.x; tv.y -= pa.y; }
     const float2 t = round2(tv);
@@ -201,13 +190,12 @@ __global__ void __launch_bounds__(kThr) k_pc_fwd(const PcSys* __restrict__ sy, c
     acc += nrm(t);
   }
   const double tot = bsum(acc, red);
-  if (threadIdx.x == 0) pc_part(S, part, k)[blockIdx.x] = tot;
+  if (threadIdx.x == 0) S.part[blockIdx.x] = tot;
 }
 
 // receiver rows t2 = lam q[rec]; delta, a; x_alpha += a p_alpha; r2 -= a t2
 // (one block per system)
-__global__ void __launch_bounds__(kThr) k_pc_step(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                  double* __restrict__ part, int g0) {
+__global__ void __launch_bounds__(kThr) k_pc_step(const PcSys* __restrict__ sy, PcState* __restrict__ stv, int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   if (!active(stv, k)) return;
@@ -220,7 +208,7 @@ __global__ void __launch_bounds__(kThr) k_pc_step(const PcSys* __restrict__ sy, 
     S.t2[q] = t2;
     acc += nrm(t2);
   }
-  const double delta = sum_parts(pc_part(S, part, k), S.nparts, red) + bsum(acc, red);
+  const double delta = sum_parts(S.part, S.nparts, red) + bsum(acc, red);
   const bool bad = !(delta > 0.0) || !(delta <= DBL_MAX) || !(T.gamma <= DBL_MAX);
   const double a = bad ? 0.0 : T.gamma / delta;
   for (int q = threadIdx.x; q < S.nr; q += kThr) {
@@ -245,34 +233,34 @@ __global__ void __launch_bounds__(kThr) k_pc_rupd(const PcSys* __restrict__ sy, 
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   const double a = stv[k].a;
-  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
-    const float2 r = S.r[c], t = S.t[c], x = S.x[c], q = S.q[c];
-    S.r[c] = fd((double)r.x - a * t.x, (double)r.y - a * t.y);
+  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += gridDim.x * kThr) {
+    const float2 r = S.r[0][c], t = S.t[c], x = S.x[c], q = S.q[c];
+    S.r[0][c] = fd((double)r.x - a * t.x, (double)r.y - a * t.y);
     S.x[c] = fd((double)x.x + a * q.x, (double)x.y + a * q.y);
   }
 }
 
 // s = A^H r (the receiver and source-row terms are added per system); partials of ||s||^2
 __global__ void __launch_bounds__(kThr) k_pc_adj(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                 double* __restrict__ part, int g0) {
+                                                 int g0) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   double acc = 0.0;
-  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
-    const float2 s = round2(apply_cell(S, S.r, c, true));
+  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += gridDim.x * kThr) {
+    const float2 s = round2(apply_cell(S, S.r[0], c, true));
     S.s[c] = s;
     acc += nrm(s);
   }
   const double tot = bsum(acc, red);
-  if (threadIdx.x == 0) pc_part(S, part, k)[blockIdx.x] = tot;
+  if (threadIdx.x == 0) S.part[blockIdx.x] = tot;
 }
 
 // s += lam P^H r2 (distinct receiver cells), s_alpha = -r1[src] (ESTIMATE);
 // ||s||^2, the stopping test (one block per system).  setup = 1: ||s_0||^2.
 __global__ void __launch_bounds__(kThr) k_pc_check(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                   double* __restrict__ part, int g0, int setup) {
+                                                   int g0, int setup) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   if (!active(stv, k)) return;
@@ -286,7 +274,7 @@ __global__ void __launch_bounds__(kThr) k_pc_check(const PcSys* __restrict__ sy,
     S.s[c] = s1;
     corr += nrm(s1) - nrm(s0);
   }
-  const double ss_u = sum_parts(pc_part(S, part, k), S.nparts, red) + bsum(corr, red);
+  const double ss_u = sum_parts(S.part, S.nparts, red) + bsum(corr, red);
   if (threadIdx.x == 0) {
     double2 sa = make_double2(0.0, 0.0);
     if (S.est) {
@@ -320,13 +308,13 @@ __global__ void __launch_bounds__(kThr) k_pc_check(const PcSys* __restrict__ sy,
 // gamma' = ||z||^2, beta = gamma'/gamma, p_alpha = z_alpha + beta p_alpha
 // (one block per system).  setup = 1: gamma = ||z_0||^2, beta = 0.
 __global__ void __launch_bounds__(kThr) k_pc_beta(const PcSys* __restrict__ sy, PcState* __restrict__ stv,
-                                                  double* __restrict__ part, int g0, int setup) {
+                                                  int g0, int setup) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.x;
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   PcState& T = stv[k];
-  const double zz = sum_parts(pc_part(S, part, k), S.nparts, red) + (T.za.x * T.za.x + T.za.y * T.za.y);
+  const double zz = sum_parts(S.part, S.nparts, red) + (T.za.x * T.za.x + T.za.y * T.za.y);
   if (threadIdx.x == 0) {
     const double be = setup ? 0.0 : zz / T.gamma;
     T.beta = be;
@@ -525,7 +513,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vprolong(const PcSys* __restrict__ 
 // o_l = y + w D^-1 (f - A_beta y); level 0 writes `out0` (q: which = 0, z:
 // which = 1) and, for z, the partials of ||z||^2
 __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                     double* __restrict__ part, int g0, int l, int which, int conj) {
+                                                     int g0, int l, int which, int conj) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
@@ -556,9 +544,9 @@ __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ s
     out[c] = o;
     acc += nrm(o);
   }
-  if (l == 0 && which && part != nullptr) {
+  if (l == 0 && which) {
     const double tot = bsum(acc, red);
-    if (threadIdx.x == 0) pc_part(S, part, k)[blockIdx.x] = tot;
+    if (threadIdx.x == 0) S.part[blockIdx.x] = tot;
   }
 }
 
@@ -566,7 +554,7 @@ __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ s
 // coarsen): kCoarseSweeps Jacobi steps on level 0 itself; the last result is
 // copied to out0 with the partials of ||out0||^2 when which = 1.
 __global__ void __launch_bounds__(kThr) k_pc_vsingle_out(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                         double* __restrict__ part, int g0, int which) {
+                                                         int g0, int which) {
   __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
@@ -575,14 +563,14 @@ __global__ void __launch_bounds__(kThr) k_pc_vsingle_out(const PcSys* __restrict
   const float2* __restrict__ src = coarse_out(S, 0);
   float2* __restrict__ out = which ? S.z : S.q;
   double acc = 0.0;
-  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += gridDim.x * kThr) {
+  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += gridDim.x * kThr) {
     const float2 o = src[c];
     out[c] = o;
     acc += nrm(o);
   }
-  if (which && part != nullptr) {
+  if (which) {
     const double tot = bsum(acc, red);
-    if (threadIdx.x == 0) pc_part(S, part, k)[blockIdx.x] = tot;
+    if (threadIdx.x == 0) S.part[blockIdx.x] = tot;
   }
 }
 
@@ -651,8 +639,8 @@ k_pw_down(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0,
   Q.setup(L.nx, L.ny, L.nz, tile, tiles_x);
   const int nx = Q.nx, wl = Q.wl;
   const float2* f = PUPD ? S.z : level_in(S, T.iters, l, which);
-  const float2* po = pc_p(S, T.iters + 1);
-  float2* pn = pc_p(S, T.iters);
+  const float2* po = S.p[T.iters & 1];
+  float2* pn = S.p[(T.iters + 1) & 1];
   float2 fv[CX][kPcZ + 2], wv[CX][kPcZ + 2], pv[CX][kPcZ + 2];
   float mm[CX][kPcZ], bb[CX][kPcZ];
 #pragma unroll
@@ -810,8 +798,8 @@ __device__ __forceinline__ double2 prolong_z(const double2 (&e)[NP], int i) {
 // (which = 0) or z (which = 1, with the partials of ||z||^2)
 template <int CX>
 __global__ void __launch_bounds__(64 * kPcW)
-k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* __restrict__ part, int g0,
-        int l, int which, int conj, int tiles_x, int tiles) {
+k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0, int l, int which, int conj,
+        int tiles_x, int tiles) {
   using Tile = Win<kPcW, CX, kPcZ>;
   constexpr int NT = Tile::NT, NP = kPcZ / 2 + 2;
   __shared__ double red[kPcW];
@@ -906,7 +894,7 @@ k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* _
   }
   if (l == 0 && which) {
     const double tot = bsum(acc, red);
-    if (tid == 0) pc_part(S, part, k)[tile] = tot;
+    if (tid == 0) S.part[tile] = tot;
   }
 }
 
@@ -914,8 +902,7 @@ k_pw_up(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* _
 // and s = A^H r with the partials of ||s||^2 (ADJ = true; setup = 1: s = A^H r_0)
 template <int CX, bool ADJ>
 __global__ void __launch_bounds__(64 * kPcW)
-k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double* __restrict__ part,
-           int g0, int setup, int tiles_x, int tiles) {
+k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0, int setup, int tiles_x, int tiles) {
   using Tile = Win<kPcW, CX, kPcZ>;
   constexpr int NT = Tile::NT;
   __shared__ double red[kThr / 64];
@@ -928,7 +915,7 @@ k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double
   if (T.status != kActive) return;
   const PcSys& S = sy[k];
   Tile Q;
-  Q.setup(S.nx, S.ny, S.nz, tile, tiles_x);
+  Q.setup(S.lev[0].nx, S.lev[0].ny, S.lev[0].nz, tile, tiles_x);
   const int nx = Q.nx, wl = Q.wl;
   const float2* in = ADJ ? pc_r(S, setup ? 0 : T.iters) : S.q;
   float2* rn = pc_r(S, T.iters + 1);
@@ -992,7 +979,7 @@ k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double
       const float2* row = pw_f + i * wl + nx + j * NT + tid;
       const float2 xm = masked(row[-1], mxm), xp = masked(row[1], mxp), ym = row[-nx], yp = row[nx];
       const double kim = S.omega * (S.sp_scale * (sxy + sponge_axis_d(Q.z0 + i, Q.nz, S.nb, S.inv_nb)));
-      double2 y = helm(v[j][i + 1], xm, xp, ym, yp, v[j][i], v[j][i + 2], S.h2inv, S.omega2 * (double)mm[j][i],
+      double2 y = helm(v[j][i + 1], xm, xp, ym, yp, v[j][i], v[j][i + 2], S.lev[0].h2inv, S.omega2 * (double)mm[j][i],
                        ADJ ? kim : -kim);
       if (src_tile && S.src == (Q.z0 + i) * Q.plane + Q.cell[j] && Q.in[j]) { y.x -= pa.x; y.y -= pa.y; }
       const float2 o = round2(y);
@@ -1007,7 +994,7 @@ k_pw_apply(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, double
     }
   }
   const double tot = bsum(acc, red);
-  if (tid == 0) pc_part(S, part, k)[tile] = tot;
+  if (tid == 0) S.part[tile] = tot;
 }
 
 // The levels from lc on (at most kPcLdsCells cells each, lc >= 1): down, the Jacobi
@@ -1276,7 +1263,7 @@ __global__ void __launch_bounds__(kThr) k_pc_rnorm(const PcSys* __restrict__ sy,
   const PcSys& S = sy[k];
   const float2* __restrict__ r = pc_r(S, stv[k].iters);
   double acc = 0.0;
-  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.n; c += kParts * kThr) acc += nrm(r[c]);
+  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += kParts * kThr) acc += nrm(r[c]);
   const double tot = bsum(acc, red);
   if (threadIdx.x == 0) part[(size_t)k * kParts + blockIdx.x] = tot;
 }
@@ -1523,9 +1510,14 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     auto vec = [&](int i) { return reinterpret_cast<float2*>(v + i * vb); };
     S.x = (u_out != nullptr && u_out[k] != nullptr) ? reinterpret_cast<float2*>(u_out[k]) : vec(0);
     const bool tiled = pc_tiled(lv);
-    S.tiled = tiled ? (pc_memory_levels(lv) > 1 ? 3 : 1) : 0;
+    S.tiled = tiled ? 1 : 0;
     S.nparts = tiled ? pc_tiles(lv[0]).n : kParts;
-    S.r = vec(1); S.p = vec(2); S.q = vec(3); S.t = vec(4); S.s = vec(5); S.z = vec(6);
+    // Tiled passes take the two vectors that they use for nothing else (the level-0
+    // iterate and, as t is dead during a cycle and shares the residual, the residual)
+    // for the other r and p: nine vectors either way.
+    S.r[0] = vec(1); S.r[1] = tiled ? vec(7) : vec(1);
+    S.p[0] = vec(2); S.p[1] = tiled ? vec(8) : vec(2);
+    S.q = vec(3); S.t = vec(4); S.s = vec(5); S.z = vec(6);
     char* cv = v + 9 * vb;
     for (size_t l = 0; l < lv.size(); ++l) {
       PcLevel& Lv = S.lev[l];
@@ -1535,8 +1527,8 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       Lv.b = gb[s.grid][l];
       Lv.wdinv = pw[L.pair_of[k]][l];
       if (l == 0) {
-        Lv.f = nullptr; Lv.o = tiled ? vec(7) : nullptr;
-        Lv.res = tiled ? vec(4) : vec(7); Lv.y = vec(8);
+        Lv.f = nullptr; Lv.o = nullptr;
+        Lv.res = tiled ? vec(4) : vec(7); Lv.y = tiled ? nullptr : vec(8);
       } else {
         const size_t cb = al(sizeof(float2) * (size_t)Lv.n);
         Lv.f = reinterpret_cast<float2*>(cv);
@@ -1547,6 +1539,11 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       }
     }
     if (lv.size() == 1) S.lev[0].o = vec(7);   // single-level cycle: Jacobi steps ping-pong between y and o
+    // The tiles' partial sums are more than kParts on large grids: they lie in an array of
+    // level 1 (at most a quarter of it) that no tiled pass touches, the iterate of a level
+    // that goes through the residual and prolongation passes in memory, else the residual.
+    S.part = !tiled ? reinterpret_cast<double*>(base + L.parts) + (size_t)p * kParts
+                    : reinterpret_cast<double*>(pc_memory_levels(lv) > 1 ? S.lev[1].y : S.lev[1].res);
     S.nlev = (int)lv.size();
     const size_t rb = al(sizeof(float2) * (size_t)s.n_rec);
     S.r2 = reinterpret_cast<float2*>(base + L.rvec[k]);
@@ -1556,7 +1553,7 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     if (s.n_rec > 0) std::memcpy(head.data() + L.rec[k], s.rec, sizeof(int) * s.n_rec);
     S.rec = drec;
     S.m = m[s.grid];
-    S.n = (int)n; S.nx = g.nx; S.ny = g.ny; S.nz = g.nz; S.nb = g.nb; S.nr = s.n_rec;
+    S.nb = g.nb; S.nr = s.n_rec;
     S.est = mode == WRI_ESTIMATE;
     S.max_iter = max_iter;
     S.src = s.src;
@@ -1564,7 +1561,6 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     S.rtol2 = s.rtol * s.rtol;
     S.omega = s.omega;
     S.omega2 = s.omega * s.omega;
-    S.h2inv = 1.0 / (g.h * g.h);
     if (g.nb > 0) {
       const double d0 = 3.0 * g.v_ref * std::log(1000.0) / (2.0 * g.nb * g.h);
       S.sp_scale = 2.0 * d0 / (g.v_ref * g.v_ref);
@@ -1620,7 +1616,7 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
         sweeps();
       }
       for (int l = lm - 1; l >= 0; --l)
-        PW_LAUNCH((k_pw_up<1>), (k_pw_up<2>), lv[l], sizeof(float2), parts, G.p0, l, which, conj);
+        PW_LAUNCH((k_pw_up<1>), (k_pw_up<2>), lv[l], sizeof(float2), G.p0, l, which, conj);
       PC_HIP(hipGetLastError());
       return WRI_OK;
     }
@@ -1633,13 +1629,13 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     }
     sweeps();
     if (nl == 1) {
-      hipLaunchKernelGGL(k_pc_vsingle_out, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, which);
+      hipLaunchKernelGGL(k_pc_vsingle_out, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, which);
     } else {
       for (int l = nl - 2; l >= 0; --l) {
         const int nbk = (l == 0) ? kParts : blocks_for(cells_of(lv[l]));
         hipLaunchKernelGGL(k_pc_vprolong, dim3(blocks_for(cells_of(lv[l])), G.cnt), dim3(kThr), 0, st, dsys, dst,
                            G.p0, l, which, conj);
-        hipLaunchKernelGGL(k_pc_vsmooth, dim3(nbk, G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, l, which, conj);
+        hipLaunchKernelGGL(k_pc_vsmooth, dim3(nbk, G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, l, which, conj);
       }
     }
     PC_HIP(hipGetLastError());
@@ -1652,19 +1648,19 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       const bool tiled = pc_tiled(lv);
       int e = vcycle(G, 0);
       if (e != WRI_OK) return e;
-      if (tiled) PW_LAUNCH((k_pw_apply<1, false>), (k_pw_apply<2, false>), lv[0], sizeof(float2), parts, G.p0, 0);
-      else hipLaunchKernelGGL(k_pc_fwd, pg, dim3(kThr), 0, st, dsys, dst, parts, G.p0);
-      hipLaunchKernelGGL(k_pc_step, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0);
+      if (tiled) PW_LAUNCH((k_pw_apply<1, false>), (k_pw_apply<2, false>), lv[0], sizeof(float2), G.p0, 0);
+      else hipLaunchKernelGGL(k_pc_fwd, pg, dim3(kThr), 0, st, dsys, dst, G.p0);
+      hipLaunchKernelGGL(k_pc_step, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0);
       if (tiled) {
-        PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), parts, G.p0, 0);
+        PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), G.p0, 0);
       } else {
         hipLaunchKernelGGL(k_pc_rupd, pg, dim3(kThr), 0, st, dsys, dst, G.p0);
-        hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, parts, G.p0);
+        hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, G.p0);
       }
-      hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 0);
+      hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, 0);
       e = vcycle(G, 1);
       if (e != WRI_OK) return e;
-      hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 0);
+      hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, 0);
       PC_HIP(hipGetLastError());
     }
     return WRI_OK;
@@ -1675,12 +1671,12 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     const std::vector<LevelDims> lv = levels_of(grids[G.grid]);
     hipLaunchKernelGGL(k_pc_zero, pg, dim3(kThr), 0, st, dsys, G.p0);
     hipLaunchKernelGGL(k_pc_init, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0);
-    if (pc_tiled(lv)) PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), parts, G.p0, 1);
-    else hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, parts, G.p0);
-    hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 1);
+    if (pc_tiled(lv)) PW_LAUNCH((k_pw_apply<1, true>), (k_pw_apply<2, true>), lv[0], sizeof(float2), G.p0, 1);
+    else hipLaunchKernelGGL(k_pc_adj, pg, dim3(kThr), 0, st, dsys, dst, G.p0);
+    hipLaunchKernelGGL(k_pc_check, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, 1);
     rc = vcycle(G, 1);
     if (rc != WRI_OK) return rc;
-    hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, parts, G.p0, 1);
+    hipLaunchKernelGGL(k_pc_beta, dim3(G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, 1);
     PC_HIP(hipGetLastError());
   }
 #undef PW_LAUNCH
