@@ -1876,7 +1876,7 @@ k_fwd_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
 
   const int tid = threadIdx.x;
   const int logical = xcd_remap(blockIdx.x, gridDim.x, G.g[0].xchunk);
-  const GroupDesc gd = win_group(G, logical);
+  const GroupDesc gd = group_of(G.g, G.table, G.n, logical);
   const int ntiles = gd.ntiles, tiles_x = gd.tiles_x;
   int rl, tile;
   block_map(gd, logical - gd.block0, &rl, &tile);
@@ -2063,7 +2063,7 @@ k_adj_win(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const dou
 
   const int tid = threadIdx.x;
   const int logical = xcd_remap(blockIdx.x, gridDim.x, G.g[0].xchunk);
-  const GroupDesc gd = win_group(G, logical);
+  const GroupDesc gd = group_of(G.g, G.table, G.n, logical);
   const int ntiles = gd.ntiles, tiles_x = gd.tiles_x;
   int rl, tile;
   block_map(gd, logical - gd.block0, &rl, &tile);

@@ -343,10 +343,21 @@ __global__ void __launch_bounds__(kThreads) k_og_adj(const OgSys* __restrict__ s
 constexpr int kOwW = 4, kOwZ = 4;
 constexpr int kOwMaxRow = 512;   // wider rows (and planes past one resource) take the march: LDS 48 KB
 
+// The systems of one grid in a launch; the first kOwGroups of them ride in its arguments.
+constexpr int kOwGroups = 4;
+struct OwGroup {
+  int rhs0, ntiles, block0;
+};
+struct OwGroups {
+  int n, xchunk;
+  const OwGroup* table;   // when there are more
+  OwGroup g[kOwGroups];
+};
+
 // (system, tile) of a block: neighbouring tiles of a system on one XCD
-__device__ __forceinline__ int ow_block(const WinGroups& G, int* sys) {
-  const int logical = xcd_remap(blockIdx.x, gridDim.x, G.g[0].xchunk);
-  const GroupDesc d = win_group(G, logical);
+__device__ __forceinline__ int ow_block(const OwGroups& G, int* sys) {
+  const int logical = xcd_remap(blockIdx.x, gridDim.x, G.xchunk);
+  const OwGroup d = group_of(G.g, G.table, G.n, logical);
   const int local = logical - d.block0, q = local / d.ntiles;
   *sys = d.rhs0 + q;
   return local - q * d.ntiles;
@@ -354,7 +365,7 @@ __device__ __forceinline__ int ow_block(const WinGroups& G, int* sys) {
 
 template <int CX>
 __global__ void __launch_bounds__(64 * kOwW)
-k_ow_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, WinGroups G) {
+k_ow_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, OwGroups G) {
   using Tile = Win<kOwW, CX, kOwZ>;
   constexpr int NT = Tile::NT;
   __shared__ double red[kThreads / 64];
@@ -431,7 +442,7 @@ k_ow_fwd(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* 
 // SETUP: s_0 = A^H r_0, no update
 template <int CX, bool SETUP>
 __global__ void __launch_bounds__(64 * kOwW)
-k_ow_adj(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, WinGroups G) {
+k_ow_adj(const OgSys* __restrict__ sy, const OgState* __restrict__ stv, double* __restrict__ parts, OwGroups G) {
   using Tile = Win<kOwW, CX, kOwZ>;
   constexpr int NT = Tile::NT;
   __shared__ double red[kThreads / 64];
@@ -809,12 +820,12 @@ int ow_tiles(const wri_grid& g, int cx) {
 struct OgPlan {
   std::vector<int> order;              // slot -> system
   std::vector<int> cx;                 // per slot
-  std::vector<GroupDesc> groups[3];    // by cx: rhs0, nrhs; window passes: ntiles, block0, xchunk
-  int blocks[3] = {0, 0, 0}, nx[3] = {1, 1, 1};
+  std::vector<OwGroup> groups[3];      // by cx (0: rhs0 only)
+  int blocks[3] = {0, 0, 0}, nx[3] = {1, 1, 1}, xchunk[3] = {16, 16, 16};
   size_t table_entries() const {       // of the groups that do not ride in the launch arguments
     size_t n = 0;
     for (int c = 1; c <= 2; ++c)
-      if (groups[c].size() > (size_t)kWinGroups) n += groups[c].size();
+      if (groups[c].size() > (size_t)kOwGroups) n += groups[c].size();
     return n;
   }
 };
@@ -834,21 +845,11 @@ OgPlan og_plan(const wri_grid* grids, const wri_system* sys, int n_sys, bool win
     const int cx = cells_a_thread(P.order[p]);
     P.cx.push_back(cx);
     auto& v = P.groups[cx];
-    if (v.empty() || sys[P.order[p - 1]].grid != sys[P.order[p]].grid) {
-      GroupDesc d{};
-      d.rhs0 = p;
-      d.ntiles = cx > 0 ? ow_tiles(g, cx) : kParts;
-      d.block0 = P.blocks[cx];
-      v.push_back(d);
-    }
-    v.back().nrhs++;
+    if (v.empty() || sys[P.order[p - 1]].grid != sys[P.order[p]].grid)
+      v.push_back({p, cx > 0 ? ow_tiles(g, cx) : kParts, P.blocks[cx]});
     P.blocks[cx] += v.back().ntiles;
     P.nx[cx] = std::max(P.nx[cx], (int)g.nx);
-  }
-  for (auto& v : P.groups) {
-    int most = 1;
-    for (const auto& d : v) most = std::max(most, d.ntiles);
-    for (auto& d : v) d.xchunk = std::max(16, most / 2);
+    P.xchunk[cx] = std::max(P.xchunk[cx], v.back().ntiles / 2);
   }
   return P;
 }
@@ -912,7 +913,7 @@ int og_layout(const wri_grid* grids, const wri_system* sys, int n_sys, const OgP
   L->parts = take(sizeof(double) * (size_t)std::max<int64_t>(sums, kParts));
   // the tables the host writes, in one piece
   L->sys = take(sizeof(OgSys) * (size_t)std::max(n_sys, 1));
-  L->groups = take(std::max(sizeof(GroupDesc) * P.table_entries(), sizeof(int) * (size_t)std::max(n_sys, 1)));
+  L->groups = take(std::max(sizeof(OwGroup) * P.table_entries(), sizeof(int) * (size_t)std::max(n_sys, 1)));
   L->tables = o;
   for (int k = 0; k < n_sys; ++k) o = al(o + T.bytes(k));
   L->total = o + kAl;
@@ -1028,16 +1029,17 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   OgState* dst = reinterpret_cast<OgState*>(base + L.state);
   double* parts = reinterpret_cast<double*>(base + L.parts);
   std::memcpy(head.data(), hs.data(), sizeof(OgSys) * n_sys);
-  WinGroups win[3] = {};
+  OwGroups win[3] = {};
   size_t at = L.groups - L.sys;
   for (int c = 1; c <= 2; ++c) {
     const auto& v = P.groups[c];
     win[c].n = (int)v.size();
-    std::copy_n(v.begin(), std::min(v.size(), (size_t)kWinGroups), win[c].g);
-    if (v.size() <= (size_t)kWinGroups) continue;
-    win[c].table = reinterpret_cast<const GroupDesc*>(base + L.sys + at);
-    std::memcpy(head.data() + at, v.data(), sizeof(GroupDesc) * v.size());
-    at += sizeof(GroupDesc) * v.size();
+    win[c].xchunk = P.xchunk[c];
+    std::copy_n(v.begin(), std::min(v.size(), (size_t)kOwGroups), win[c].g);
+    if (v.size() <= (size_t)kOwGroups) continue;
+    win[c].table = reinterpret_cast<const OwGroup*>(base + L.sys + at);
+    std::memcpy(head.data() + at, v.data(), sizeof(OwGroup) * v.size());
+    at += sizeof(OwGroup) * v.size();
   }
   OG_HIP(hipMemcpyAsync(base + L.sys, head.data(), head.size(), hipMemcpyHostToDevice, st));
 
@@ -1105,12 +1107,13 @@ int og_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
   OG_HIP(hipGetLastError());
   if (grad != nullptr)
     for (int g = 0; g < n_grids; ++g) {
-      GroupDesc d{};
+      int s0 = 0, cnt = 0;
       for (const auto& v : P.groups)
         for (const auto& e : v)
-          if (sys[P.order[e.rhs0]].grid == g) d = e;
+          if (sys[P.order[e.rhs0]].grid == g) s0 = e.rhs0;
+      while (s0 + cnt < n_sys && sys[P.order[s0 + cnt]].grid == g) ++cnt;
       const int64_t n = ncell(grids[g]);
-      hipLaunchKernelGGL(k_og_grad, dim3(nblk(n)), dim3(kThreads), 0, st, dsys, dst, d.rhs0, d.nrhs, (int)n, grad[g]);
+      hipLaunchKernelGGL(k_og_grad, dim3(nblk(n)), dim3(kThreads), 0, st, dsys, dst, s0, cnt, (int)n, grad[g]);
       OG_HIP(hipGetLastError());
     }
   if ((rc = read()) != WRI_OK) return rc;

@@ -24,22 +24,23 @@ __device__ __forceinline__ int xcd_remap(int b, int nb, int q) {
   return (round * kXCD + xcd) * q + off;
 }
 
-// The group of a block, from the launch arguments (up to kWinGroups groups; a
-// load from the device table would be one more memory latency in every launch).
-__device__ __forceinline__ GroupDesc win_group(const WinGroups& G, int logical) {
-  GroupDesc d = G.g[0];
-  if (G.n <= kWinGroups) {
+// The group of a block, from the launch arguments (up to N groups; a load from the
+// device table would be one more memory latency in every launch).
+template <class Group, int N>
+__device__ __forceinline__ Group group_of(const Group (&first)[N], const Group* table, int n, int logical) {
+  Group d = first[0];
+  if (n <= N) {
 #pragma unroll
-    for (int i = 1; i < kWinGroups; ++i)
-      if (i < G.n && logical >= G.g[i].block0) d = G.g[i];
+    for (int i = 1; i < N; ++i)
+      if (i < n && logical >= first[i].block0) d = first[i];
   } else {
-    int g = 0, end = G.n;
+    int g = 0, end = n;
     while (end - g > 1) {
       const int mid = (g + end) / 2;
-      if (logical >= G.table[mid].block0) g = mid;
+      if (logical >= table[mid].block0) g = mid;
       else end = mid;
     }
-    d = G.table[g];
+    d = table[g];
   }
   return d;
 }
