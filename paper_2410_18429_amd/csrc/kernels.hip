@@ -55,6 +55,12 @@ __device__ __forceinline__ const GLOBAL T* gptr(const T* p) { return (const GLOB
 __device__ __forceinline__ float2 ld2(const GLOBAL float2* p, int i) {
   return __builtin_bit_cast(float2, *((const GLOBAL unsigned long long*)p + i));
 }
+// Read once, past the caches (as a vector of floats: the hint is lost on a load of 64 bits).
+__device__ __forceinline__ float2 ld2nt(const GLOBAL float2* p, int i) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  const f32x2 v = __builtin_nontemporal_load((const GLOBAL f32x2*)p + i);
+  return make_float2(v.x, v.y);
+}
 __device__ __forceinline__ void st2(GLOBAL float2* p, int i, float2 v) {
   *((GLOBAL unsigned long long*)p + i) = __builtin_bit_cast(unsigned long long, v);
 }
@@ -2368,12 +2374,14 @@ hipError_t launch_adj(const TileCfg& c, const SysDev* sys, SysState* st, const d
 
 // The systems' pointers and weights are gathered into LDS once (each is three
 // dependent loads away) and the loads of NS systems are in flight together; their
-// ||r1||^2 are summed over the workgroup at once.  One system after the other,
-// with its own loads and two barriers, was a serial chain.  CPT = 1 spreads small
-// grids over the chip (256 cells per workgroup), CPT = 4 spends a quarter of the
-// shuffles per cell (1024 cells per workgroup).  us per call before -> now:
-// 48 systems of 32^3 112 -> 16, 8 of 64^3 21 -> 9, 48 of 128^3 297 -> 320 (1.6 GB,
-// 5.0 TB/s: at the rate of a large copy either way).
+// ||r1||^2 are summed over the workgroup once per table of systems.  One system after
+// the other, with its own loads and two barriers, was a serial chain.  CPT = 1 spreads
+// small grids over the chip (256 cells per workgroup; eight systems at once).  CPT = 4
+// spends a quarter of the shuffles per cell (1024 cells per workgroup): its batches do
+// not fit the caches, so each wave streams one system at a time past them.  us per call,
+// one system after the other / now: 48 systems of 32^3 114 -> 15, 8 of 64^3 22 -> 8, 48 of
+// 128^3 293 -> 250 (1.6 GB, 6.4 TB/s); the last with two, four and eight systems at once
+// 282, 280 and 274, and with cached loads of one and four 297 and 303.
 constexpr int kGradThreads = 256;
 constexpr int kGradTable = 64;   // systems per table load
 
@@ -2385,7 +2393,7 @@ k_grad(const SysDev* __restrict__ sysv, const SysState* __restrict__ stv, int rh
        float* __restrict__ grad, double* __restrict__ part_j, int stride, int accumulate) {
   constexpr int NW = kGradThreads / 64;
   __shared__ const float2 *tr[kGradTable], *tu[kGradTable];   // tr null: broken down, contributes nothing
-  __shared__ double tw[kGradTable], red[NW][NS];
+  __shared__ double tw[kGradTable], red[NW][kGradTable];
   const int tid = threadIdx.x, w = tid >> 6;
   int c[CPT];
   bool in[CPT];
@@ -2418,8 +2426,13 @@ k_grad(const SysDev* __restrict__ sysv, const SysState* __restrict__ stv, int rh
         const GLOBAL float2 *pu = gptr(tu[r]), *pr = ok ? gptr(tr[r]) : pu;
 #pragma unroll
         for (int i = 0; i < CPT; ++i) {
-          rv[k][i] = ld2(pr, c[i]);
-          uv[k][i] = ld2(pu, c[i]);
+          if constexpr (CPT > 1) {
+            rv[k][i] = ld2nt(pr, c[i]);
+            uv[k][i] = ld2nt(pu, c[i]);
+          } else {
+            rv[k][i] = ld2(pr, c[i]);
+            uv[k][i] = ld2(pu, c[i]);
+          }
         }
       }
       double jj[NS];
@@ -2436,15 +2449,14 @@ k_grad(const SysDev* __restrict__ sysv, const SysState* __restrict__ stv, int rh
       }
       int id = 0, left = NS;
       const double s = wave_sums<NS>(jj, 32, &id, &left);
-      red[w][id] = s;
-      __syncthreads();
-      if (tid < NS && r0 + tid < nt) {
-        double tot = 0.0;
+      red[w][r0 + id] = s;
+    }
+    __syncthreads();
+    if (tid < nt) {
+      double tot = 0.0;
 #pragma unroll
-        for (int i = 0; i < NW; ++i) tot += red[i][tid];
-        part_j[(size_t)(t0 + r0 + tid) * stride + blockIdx.x] = tot;
-      }
-      __syncthreads();
+      for (int i = 0; i < NW; ++i) tot += red[i][tid];
+      part_j[(size_t)(t0 + tid) * stride + blockIdx.x] = tot;
     }
   }
   if (grad == nullptr) return;
@@ -2460,7 +2472,7 @@ hipError_t launch_grad(const SysDev* sys, SysState* st, int rhs0, int nrhs, int 
     hipLaunchKernelGGL((k_grad<1, 8>), dim3(grad_blocks(n, 1)), dim3(kGradThreads), 0, s, sys, st, rhs0, nrhs, n, grad,
                        part_j, stride, accumulate);
   else
-    hipLaunchKernelGGL((k_grad<4, 4>), dim3(grad_blocks(n, 4)), dim3(kGradThreads), 0, s, sys, st, rhs0, nrhs, n, grad,
+    hipLaunchKernelGGL((k_grad<4, 1>), dim3(grad_blocks(n, 4)), dim3(kGradThreads), 0, s, sys, st, rhs0, nrhs, n, grad,
                        part_j, stride, accumulate);
   return hipGetLastError();
 }

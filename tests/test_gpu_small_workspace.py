@@ -127,3 +127,24 @@ def test_offgrid(monkeypatch):
     del b._ws[("offgrid",)]
     with pytest.raises(wri.WriError):
         run()
+
+
+@pytest.mark.parametrize("shape,n_src,n_freq", [((33, 31, 1), 13, 5), ((32, 32, 1), 16, 4), ((41, 25, 1), 14, 5),
+                                                ((41, 25, 4), 13, 1)])
+def test_gradient_with_four_cells_a_thread(monkeypatch, shape, n_src, n_freq):
+    """One workgroup's 1024 cells less one, exactly and one more, and 13 to 70 systems (a
+    table of 64 and a second): on the same iterates (a forced slab tile) the gradient has
+    the bits of the pass with one cell a thread, and J differs in the order of its sums."""
+    print(f"gradient {shape} {n_src}x{n_freq}", flush=True)
+    p = wri_synth.custom_problem(shape, nb=1, n_src=n_src, n_rec=min(4, shape[2]), seed=9,
+                                 freqs=tuple(12.0 + k for k in range(n_freq)), rtol=0.0)
+    b = wri.Batch(p, device="cuda:0")
+    full = b.workspace(b.mode, 0).numel()
+    monkeypatch.setenv("WRI_TILE", "4,4,32,0,0")
+    J, g, res = wri.objective_grad(b, max_iter=3)
+    monkeypatch.setattr(b, "workspace", lambda mode, flags: torch.empty(full - 256, dtype=torch.uint8, device="cuda:0"))
+    Js, gs, rs = wri.objective_grad(b, max_iter=3)
+    assert torch.equal(gs[0], g[0])
+    for x, y in zip(rs, res):   # some 4000 terms in float64
+        assert x["relres"] == y["relres"] and abs(x["J"] - y["J"]) <= 1e-12 * y["J"]
+    assert abs(Js - J) <= 1e-12 * abs(J)
