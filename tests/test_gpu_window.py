@@ -12,6 +12,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import wri_synth
 from paper_2410_18429_amd import wri
 
@@ -78,3 +79,32 @@ def test_window_march_warm_start_and_many_grids(monkeypatch, tile):
         for a, b in ((u[i], ref_u[i]), (warm[1][i], warm[0][i])):
             assert float((a - b).abs().max()) <= 1e-5 * float(b.abs().max()), (tile, i)
         assert abs(res[i]["J"] - ref[i]["J"]) <= 1e-6 * abs(ref[i]["J"]), (tile, i)
+
+
+@pytest.mark.parametrize("mode", ["estimate", "known"])
+@pytest.mark.parametrize("shape", [(16, 16, 4), (15, 17, 5), (257, 1, 2), (1, 513, 3), (32, 32, 1), (70, 37, 9),
+                                   (380, 3, 6), (300, 2, 4)])
+def test_window_march_gives_the_oracle_iterates(monkeypatch, shape, mode):
+    """Two steps against the oracle's complex128 CGLS (float32 storage: 1e-4, as in the other
+    solvers' tile tests), receivers on the top plane, sources in the first and last cell."""
+    print(f"window oracle {shape} {mode}", flush=True)
+    p = wri_synth.custom_problem(shape, nb=1, n_src=1, n_rec=min(shape[2], 8), seed=3, freqs=(14.0, 19.0), rtol=0.0)
+    g = p.grids[0]
+    p.systems[0].src, p.systems[1].src = 0, g.n - 1
+    n = min(600, g.nx * g.ny)
+    p.systems[1].rec = np.arange(n, dtype=np.int32)
+    p.systems[1].d = np.exp(0.1j * np.arange(n)) * 1e-3
+    k = 2
+    m32 = np.asarray(p.m[0], dtype=np.float32).astype(np.float64).reshape(-1)
+    refs = []
+    for i, s in enumerate(p.systems):
+        A, P, _ = oracle.system_operators(p, i, m=m32)
+        d = np.asarray(s.d).astype(np.complex64).astype(np.complex128)
+        refs.append(oracle.cgls(A, P, s.lam, s.src, mode, s.alpha, d, 0.0, k, alpha_scale=np.sqrt(42.0) / g.h ** 2))
+    for tile in WINDOWS:
+        u, res = _solve(p, mode, monkeypatch, tile, k)
+        for i, ref in enumerate(refs):
+            err = np.linalg.norm(u[i].cpu().numpy() - ref["u"]) / np.linalg.norm(ref["u"])
+            print(f"  {tile} sys {i}: u err {err:.2e} relres {res[i]['relres']:.6e} oracle {ref['relres']:.6e}", flush=True)
+            assert res[i]["iters"] == k and err < 1e-4
+            assert abs(res[i]["relres"] - ref["relres"]) <= 1e-4 * ref["relres"]
