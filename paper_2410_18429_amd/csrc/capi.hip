@@ -1378,9 +1378,14 @@ int solve_common(const wri_grid* grids, int32_t n_grids, const float* const* m, 
   std::lock_guard<std::mutex> lock(g_mutex);
   WRI_HIP(hipGetDevice(&C.dev));
   std::vector<SysState> hs;
-  rc = (flags & WRI_FLAG_PLAIN) ? run_plain(C, grad, hs) : run_batched(C, grad, hs);
+  try {
+    rc = (flags & WRI_FLAG_PLAIN) ? run_plain(C, grad, hs) : run_batched(C, grad, hs);
+  } catch (...) {
+    (void)hipStreamSynchronize(C.st);   // the copy of C.head, or launches on the workspace
+    throw;
+  }
   if (rc != WRI_OK) {
-    (void)hipStreamSynchronize(C.st);   // the copy of C.head may be in flight
+    (void)hipStreamSynchronize(C.st);
     return rc;
   }
   // results (the state array is in processing order)
