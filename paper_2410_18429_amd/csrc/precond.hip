@@ -143,6 +143,11 @@ __global__ void __launch_bounds__(kThr) k_pc_init(const PcSys* __restrict__ sy, 
   }
 }
 
+__device__ __forceinline__ float2 pc_pupd(const PcSys& S, double be, int c) {
+  const float2 zv = S.z[c], pv = S.p[0][c], p = fd((double)zv.x + be * pv.x, (double)zv.y + be * pv.y);
+  S.p[0][c] = p;
+  return p;
+}
 // p = z + beta p (beta of the state; 0 at the start)
 __global__ void __launch_bounds__(kThr) k_pc_pupd(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
                                                   int g0) {
@@ -150,10 +155,7 @@ __global__ void __launch_bounds__(kThr) k_pc_pupd(const PcSys* __restrict__ sy, 
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
   const double be = stv[k].beta;
-  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += gridDim.x * kThr) {
-    const float2 zv = S.z[c], pv = S.p[0][c];
-    S.p[0][c] = fd((double)zv.x + be * pv.x, (double)zv.y + be * pv.y);
-  }
+  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += gridDim.x * kThr) pc_pupd(S, be, c);
 }
 
 __device__ __forceinline__ double sponge_at(const PcSys& S, int x, int y, int z) {
@@ -420,9 +422,13 @@ __global__ void __launch_bounds__(kThr) k_pc_vrestrict(const PcSys* __restrict__
 }
 
 // Jacobi step on the coarsest level: sweep 0: o = w D^-1 f; sweep j > 0:
-// out = in + w D^-1 (f - A_beta in), in/out alternating o (j odd reads o) and y
+// out = in + w D^-1 (f - A_beta in), in/out alternating o (j odd reads o) and y.
+// Where level 0 is the only one (a grid too small or too thin to coarsen), the first
+// sweep of the forward cycle also updates p, and the last one writes q or z, with the
+// partials of ||z||^2 (kParts blocks).
 __global__ void __launch_bounds__(kThr) k_pc_vcoarse(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
                                                      int g0, int which, int conj, int sweep) {
+  __shared__ double red[kThr / 64];
   const int k = g0 + blockIdx.y;
   if (!active(stv, k)) return;
   const PcSys& S = sy[k];
@@ -430,11 +436,13 @@ __global__ void __launch_bounds__(kThr) k_pc_vcoarse(const PcSys* __restrict__ s
   const PcLevel& L = S.lev[l];
   const float2* __restrict__ f = level_in(S, stv[k].iters, l, which);
   const float2* __restrict__ in = (sweep & 1) ? L.o : L.y;
-  float2* __restrict__ out = (sweep & 1) ? L.y : L.o;
+  const bool final = S.nlev == 1 && sweep == kCoarseSweeps - 1;
+  float2* __restrict__ out = final ? (which ? S.z : S.q) : (sweep & 1) ? L.y : L.o;
+  double acc = 0.0;
   for (int c = blockIdx.x * kThr + threadIdx.x; c < L.n; c += gridDim.x * kThr) {
     const double2 d = diag_beta(S, L, c, conj);
     if (sweep == 0) {
-      const double2 v = jac(L, c, conj, f[c]);
+      const double2 v = jac(L, c, conj, S.nlev == 1 && which == 0 ? pc_pupd(S, stv[k].beta, c) : f[c]);
       out[c] = fd(v.x, v.y);
       continue;
     }
@@ -452,7 +460,13 @@ __global__ void __launch_bounds__(kThr) k_pc_vcoarse(const PcSys* __restrict__ s
     const double ai = si * L.h2inv + (d.x * xc.y + d.y * xc.x);
     const float2 fc = f[c];
     const double2 corr = jac(L, c, conj, fd((double)fc.x - ar, (double)fc.y - ai));
-    out[c] = fd((double)xc.x + corr.x, (double)xc.y + corr.y);
+    const float2 o = fd((double)xc.x + corr.x, (double)xc.y + corr.y);
+    out[c] = o;
+    acc += nrm(o);
+  }
+  if (final && which) {
+    const double tot = bsum(acc, red);
+    if (threadIdx.x == 0) S.part[blockIdx.x] = tot;
   }
 }
 
@@ -545,30 +559,6 @@ __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ s
     acc += nrm(o);
   }
   if (l == 0 && which) {
-    const double tot = bsum(acc, red);
-    if (threadIdx.x == 0) S.part[blockIdx.x] = tot;
-  }
-}
-
-// A V-cycle whose only level is level 0 (a grid too small or too thin to
-// coarsen): kCoarseSweeps Jacobi steps on level 0 itself; the last result is
-// copied to out0 with the partials of ||out0||^2 when which = 1.
-__global__ void __launch_bounds__(kThr) k_pc_vsingle_out(const PcSys* __restrict__ sy, const PcState* __restrict__ stv,
-                                                         int g0, int which) {
-  __shared__ double red[kThr / 64];
-  const int k = g0 + blockIdx.y;
-  if (!active(stv, k)) return;
-  const PcSys& S = sy[k];
-  if (S.nlev != 1) return;
-  const float2* __restrict__ src = coarse_out(S, 0);
-  float2* __restrict__ out = which ? S.z : S.q;
-  double acc = 0.0;
-  for (int c = blockIdx.x * kThr + threadIdx.x; c < S.lev[0].n; c += gridDim.x * kThr) {
-    const float2 o = src[c];
-    out[c] = o;
-    acc += nrm(o);
-  }
-  if (which) {
     const double tot = bsum(acc, red);
     if (threadIdx.x == 0) S.part[blockIdx.x] = tot;
   }
@@ -1009,8 +999,13 @@ struct SmallDiv {   // quotients of integers below 2^16 by d, through the float 
   __device__ __forceinline__ int quot(int c) const { return (int)(((float)c + 0.5f) * r); }
 };
 
+// SINGLE: the whole cycle of a grid of one level (lc = 0), with the partials of ||z||^2 as
+// the per-cell passes form them: a grid this small is bound by its launches, five for a
+// cycle otherwise.  300 iterations of two systems of 8x8x8: 17.8 ms with eager passes, 15.4
+// replayed from a graph, 11.4 now; of 5x1x7 18.1, 13.6 and 10.6.
+template <bool SINGLE>
 __global__ void __launch_bounds__(kPcLdsThr)
-k_pw_coarse(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0, int lc, int conj) {
+k_pw_coarse(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g0, int lc, int which, int conj) {
   constexpr int KC = kPcLdsCells / kPcLdsThr;   // cells per thread
   extern __shared__ double2 pc_lds[];
   const int k = g0 + blockIdx.x;
@@ -1056,7 +1051,10 @@ k_pw_coarse(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g
 #pragma unroll
     for (int i = 0; i < KC; ++i) d[i] = diag_mb(S, L.h2inv, mv[i], bv[i], conj);
   };
-  for (int c = tid; c < S.lev[lc].n; c += kPcLdsThr) pl[c] = S.lev[lc].f[c];
+  for (int c = tid; c < S.lev[lc].n; c += kPcLdsThr) {
+    if constexpr (SINGLE) pl[c] = which ? S.s[c] : pc_pupd(S, stv[k].beta, c);
+    else pl[c] = S.lev[lc].f[c];
+  }
   for (int l = lc; l < last; ++l) {
     const PcLevel& L = S.lev[l];
     const PcLevel& C = S.lev[l + 1];
@@ -1142,6 +1140,28 @@ k_pw_coarse(const PcSys* __restrict__ sy, const PcState* __restrict__ stv, int g
       __syncthreads();
     }
     static_assert(kCoarseSweeps % 2 == 0, "the coarsest result is in y");
+    if constexpr (SINGLE) {
+      float2* out = which ? S.z : S.q;
+      double* red = reinterpret_cast<double*>(ya + L.n);   // a sum per 64 cells, as the waves of the per-cell passes have it
+#pragma unroll
+      for (int i = 0; i < KC; ++i) {
+        const int c = tid + i * kPcLdsThr;
+        if (c < L.n) out[c] = ya[c];
+        double v = c < L.n ? nrm(ya[c]) : 0.0;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if ((tid & 63) == 0) red[c >> 6] = v;
+      }
+      __syncthreads();
+      static_assert(kPcLdsCells <= kParts * kThr && kParts <= kPcLdsThr, "");
+      if (which && tid < kParts) {
+        double tot = 0.0;
+        if (tid * kThr < L.n)
+          for (int i = 0; i < kThr / 64; ++i) tot += red[tid * (kThr / 64) + i];
+        S.part[tid] = tot;
+      }
+      return;
+    }
     if (last == lc) {
       for (int c = tid; c < L.n; c += kPcLdsThr) L.y[c] = ya[c];   // coarse_out() of the coarsest level
       return;
@@ -1593,9 +1613,10 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     const std::vector<LevelDims> lv = levels_of(grids[G.grid]);
     const int nl = (int)lv.size();
     auto sweeps = [&]() {
-      for (int j = 0; j < kCoarseSweeps; ++j)
-        hipLaunchKernelGGL(k_pc_vcoarse, dim3(blocks_for(cells_of(lv[nl - 1])), G.cnt), dim3(kThr), 0, st, dsys, dst,
-                           G.p0, which, conj, j);
+      for (int j = 0; j < kCoarseSweeps; ++j) {
+        const int nbk = nl == 1 && j == kCoarseSweeps - 1 ? kParts : blocks_for(cells_of(lv[nl - 1]));
+        hipLaunchKernelGGL(k_pc_vcoarse, dim3(nbk, G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, which, conj, j);
+      }
     };
     if (pc_tiled(lv)) {
       // levels of one workgroup: from lc on (nl: none fits, the coarsest by separate sweeps)
@@ -1611,7 +1632,7 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       if (lc < nl) {
         size_t lds = sizeof(double2) * (size_t)cells_of(lv[lc]);
         for (int l = lc; l < nl; ++l) lds += 2 * sizeof(float2) * (size_t)cells_of(lv[l]);
-        hipLaunchKernelGGL(k_pw_coarse, dim3(G.cnt), dim3(kPcLdsThr), (unsigned)lds, st, dsys, dst, G.p0, lc, conj);
+        hipLaunchKernelGGL(k_pw_coarse<false>, dim3(G.cnt), dim3(kPcLdsThr), (unsigned)lds, st, dsys, dst, G.p0, lc, which, conj);
       } else {
         sweeps();
       }
@@ -1620,7 +1641,15 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
       PC_HIP(hipGetLastError());
       return WRI_OK;
     }
-    if (which == 0) hipLaunchKernelGGL(k_pc_pupd, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0);
+    if (which == 0 && nl > 1) hipLaunchKernelGGL(k_pc_pupd, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0);
+    if (nl == 1 && cells_of(lv[0]) <= kPcLdsCells) {
+      // w D^-1 f, f and y of the level, and the sums
+      const size_t lds = (sizeof(double2) + 2 * sizeof(float2)) * (size_t)cells_of(lv[0]) + sizeof(double) * kPcLdsCells / 64;
+      hipLaunchKernelGGL(k_pw_coarse<true>, dim3(G.cnt), dim3(kPcLdsThr), (unsigned)lds, st, dsys, dst, G.p0, 0, which,
+                         conj);
+      PC_HIP(hipGetLastError());
+      return WRI_OK;
+    }
     for (int l = 0; l + 1 < nl; ++l) {
       hipLaunchKernelGGL(k_pc_vdown, dim3(blocks_for(cells_of(lv[l])), G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0,
                          l, which, conj);
@@ -1628,15 +1657,11 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
                          G.p0, l);
     }
     sweeps();
-    if (nl == 1) {
-      hipLaunchKernelGGL(k_pc_vsingle_out, dim3(kParts, G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, which);
-    } else {
-      for (int l = nl - 2; l >= 0; --l) {
-        const int nbk = (l == 0) ? kParts : blocks_for(cells_of(lv[l]));
-        hipLaunchKernelGGL(k_pc_vprolong, dim3(blocks_for(cells_of(lv[l])), G.cnt), dim3(kThr), 0, st, dsys, dst,
-                           G.p0, l, which, conj);
-        hipLaunchKernelGGL(k_pc_vsmooth, dim3(nbk, G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, l, which, conj);
-      }
+    for (int l = nl - 2; l >= 0; --l) {
+      const int nbk = (l == 0) ? kParts : blocks_for(cells_of(lv[l]));
+      hipLaunchKernelGGL(k_pc_vprolong, dim3(blocks_for(cells_of(lv[l])), G.cnt), dim3(kThr), 0, st, dsys, dst,
+                         G.p0, l, which, conj);
+      hipLaunchKernelGGL(k_pc_vsmooth, dim3(nbk, G.cnt), dim3(kThr), 0, st, dsys, dst, G.p0, l, which, conj);
     }
     PC_HIP(hipGetLastError());
     return WRI_OK;
