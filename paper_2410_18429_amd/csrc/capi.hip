@@ -594,7 +594,7 @@ bool tiles_fit(const Ctx& C, const TileCfg& t) {
 
 // The tile of grids in batches that are not tuned (too small for the timing to tell, or
 // WRI_FLAG_NO_AUTOTUNE): the window march with the shortest chain of work per
-// workgroup, 13.8 us per iteration on 4 systems of 70x37x19 cells against 164 us
+// workgroup, 13.2 us per iteration on 4 systems of 70x37x19 cells against 164 us
 // with the slab tile 4,4,32,0,0, which grids that it does not fit keep.  It depends on
 // the system's own grid only, so a system gives the same bits alone and in a batch;
 // where both kinds of grid are in the batch each kind has launches of its own.

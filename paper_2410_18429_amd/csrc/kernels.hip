@@ -1738,15 +1738,16 @@ k_adj_rc(const SysDev* __restrict__ sysv, SysState* __restrict__ stv, const doub
 // All loads of the TZ + 2 planes are issued at once, one barrier separates them
 // from the stencils, and nothing is serial in z.  The price is (TZ + 2) / TZ of
 // the own cells and 2 nx / B of halo re-read, which the L2s serve (8 systems of
-// 64^3: 38 MB fetched past L2 per launch, 34.6 MB of inputs).  t is stored:
+// 64^3: 39 MB fetched past L2 per launch, 34.6 MB of inputs).  t is stored:
 // recomputing it would double the halo.
 //
 // Measured, us per iteration (both launches), best slab tile -> best window:
-// 4 systems of 70x37x19 42.2 -> 13.8 (164 with the untuned default 4,4,32,0,0),
-// 48 of 32^3 71.2 -> 32.2, 8 of 64^3 70.7 -> 37.8, 8 each of 48^3, 64^3 and 96^3
+// 4 systems of 70x37x19 42.2 -> 13.2 (164 with the untuned default 4,4,32,0,0),
+// 48 of 32^3 71.2 -> 31.3, 8 of 64^3 70.7 -> 36.7, 8 each of 48^3, 64^3 and 96^3
 // 231 -> 184.  The smallest is bound by the chain launch - tables - loads -
-// stores (7 us per launch), the others by the 72 MB per launch between the L2s
-// and memory (5.5 TB/s for 8 systems of 64^3).
+// stores (7 us per launch), the others by that and by the traffic past the L2s: 8
+// systems of 64^3 move 73 MB a launch in 15.3 and 17.0 us (4.7 and 4.3 TB/s) and
+// 127 MB with the x update in 22.2 (5.7 TB/s), 82 bytes a cell and iteration.
 //
 // Same stencil routine, same operands in the same order and the same rounding
 // points as the slab marches: iterates differ only through the summation order

@@ -337,7 +337,7 @@ __global__ void __launch_bounds__(kThreads) k_og_adj(const OgSys* __restrict__ s
 // columns and a load latency and two barriers per plane: what bounded it on batches
 // that fit the caches.  Every stored value is rounded where it was; only the order of
 // the float64 sums differs.  Per iteration (four launches): 8 systems of 64^3 78 us before
-// and 44 now, 2 of 24x20x18 35 and 23, 48 of 128^3 2.07 ms and 1.74 (88 bytes a cell at
+// and 45 now, 2 of 24x20x18 35 and 19, 48 of 128^3 2.07 ms and 1.75 (88 bytes a cell at
 // 5.1 TB/s: memory).
 // ---------------------------------------------------------------------------
 constexpr int kOwW = 4, kOwZ = 4;

@@ -67,9 +67,9 @@ __device__ __forceinline__ float block_max(float v, float* red) {
 // pass that stored the three q in float64 and one that read them back moved 60.
 // Bound by the float64 square root and divisions (one and three per cell, nx / kTvB
 // more for the rows before the tile).  Rows too wide for the LDS (ROWS = false)
-// form q of the cell c - nx again instead.  Value and gradient, whole call
-// (25 us of it the launches and the copy of the value): 128^3 70 -> 43 us,
-// 256x256x192 299 -> 107 us.
+// form q of the cell c - nx again instead.  Value and gradient, whole call from
+// Python: 128^3 74 -> 46 us (the pass 18, the rest launches and the copy of the
+// value), 256x256x192 304 -> 110 us.
 constexpr int kTvB = 1024, kTvZ = 2;
 constexpr int kTvMaxRow = 1024;    // (kTvB + row) * kTvZ * 16 B of LDS: 64 KB
 
@@ -227,8 +227,8 @@ __global__ void k_scale_sc(float* __restrict__ y, int64_t n, const double* __res
 // arithmetic, and dir = -(H0 (g - sum alpha_j y_j) + sum c_j s_j) is one pass.  Two
 // passes over the 2 M + 1 vectors and one small launch replace 3 M + 2 dot
 // products and 2 M + 3 updates, each a launch with dir read and written (M = 5,
-// 128^3: 36 launches and 219 us -> 3 launches and 47 us; 256x256x192 847 -> 215
-// us, 290 -> 92 bytes per cell at 5.4 TB/s).  Inner products and
+// 128^3: 36 launches and 240 us a call from Python -> 3 launches and 56 us;
+// 256x256x192 875 -> 234 us, 290 -> 92 bytes per cell).  Inner products and
 // coefficients are float64; dir is rounded once instead of after every update.
 // Up to kLbFused pairs (the accumulators live in registers: 88 for 8 pairs); longer
 // memories, and workspaces without room for the partials of all inner products, take the

@@ -579,8 +579,8 @@ __global__ void __launch_bounds__(kThr) k_pc_vsmooth(const PcSys* __restrict__ s
 // through the order of the float64 sums; r and p are written to their other
 // buffer because neighbouring tiles still read the old one.
 //
-// Per iteration (eager launches): 8 systems of 64^3 401 us before and 195 now,
-// 48 of 128^3 11.7 ms and 5.04, 2 of 24x20x18 178 us and 77.
+// Per iteration (eager launches): 8 systems of 64^3 401 us before and 194 now,
+// 48 of 128^3 11.7 ms and 5.07, 2 of 24x20x18 178 us and 75.
 // ---------------------------------------------------------------------------
 
 constexpr int kPcW = 4, kPcZ = 4;
@@ -1711,10 +1711,10 @@ int pc_run(const wri_grid* grids, int n_grids, const float* const* m, const wri_
     PC_HIP(hipStreamSynchronize(st));
     return WRI_OK;
   };
-  // Eager launches: a pass takes longer than the host needs to enqueue the next, and
-  // building a graph of a chunk cost more than a solve of a few iterations (1.9 ms
-  // for 624 nodes).  Every system has stopped after max_iter iterations, so the
-  // statuses are looked at between chunks only.
+  // Eager launches: building a graph of a chunk cost more than a solve of a few
+  // iterations (1.9 ms for 624 nodes), and on all but the smallest grids a pass takes
+  // longer than the host needs to enqueue the next.  Every system has stopped after
+  // max_iter iterations, so the statuses are looked at between chunks only.
   for (int64_t done = 0; done < max_iter;) {
     const int chunk = (int)std::min<int64_t>(kCheck, max_iter - done);
     for (int i = 0; i < chunk; ++i)
