@@ -61,14 +61,14 @@ def kernel_label(dominant, pf):
 # tile shape in the key;
 # summary and commands: profiles/fused_cgls_kernels_128cube_48sys_hbm_traffic.md
 TRAFFIC = {
-    "sources_sha256": "938bdc87f537aeb7",
+    "sources_sha256": "96222e25b2f1c38e",
     "tiles": {
-        "8,4,64,2,4": {"fwd_x": {"fetch_kib": 1801633.9, "write_kib": 1573199.9},
-                       "fwd": {"fetch_kib": 976798.7, "write_kib": 786608.1},
-                       "adj": {"fetch_kib": 925137.8, "write_kib": 1573035.8}},
-        "8,4,64,2,2": {"fwd_x": {"fetch_kib": 1816373.8, "write_kib": 1573199.3},
-                       "fwd": {"fetch_kib": 1031479.1, "write_kib": 786611.2},
-                       "adj": {"fetch_kib": 976953.5, "write_kib": 1573040.3}},
+        "8,4,64,2,4": {"fwd_x": {"fetch_kib": 1799691.7, "write_kib": 1573198.4},
+                       "fwd": {"fetch_kib": 977702.2, "write_kib": 786607.1},
+                       "adj": {"fetch_kib": 925378.5, "write_kib": 1573033.4}},
+        "8,4,64,2,2": {"fwd_x": {"fetch_kib": 1815281.9, "write_kib": 1573202.6},
+                       "fwd": {"fetch_kib": 1034531.4, "write_kib": 786609.3},
+                       "adj": {"fetch_kib": 975541.8, "write_kib": 1573039.5}},
     },
     "fetch_scale": 2.000, "write_scale": 1.000,
 }
